@@ -310,7 +310,7 @@ void launch_raster_backward(hipStream_t s, const FrameDev& f, const WsDev& ws, b
 
 // ---------------------------------------------------------------------------
 // The training variant's backward pass.  Its forward pass is the dual-pixel
-// rasterizer with culled lists over the plain records (k_raster_fast with
+// rasterizer with culled lists over the plain records (k_raster with
 // EXP_HW2 and TRAIN).  Here the tile's list is replayed back to front in the
 // forward's layout: two waves, wave w owning rows 8w .. 8w+7, each lane the
 // dual pixel (x, y), (x, y+1).  Each batch is staged, folded and culled per

@@ -1,53 +1,70 @@
 // Tile rasterizers (Sec. III-D, Sec. IV-B).
 //
-// One workgroup blends one 16x16 tile front to back over the tile's sorted
-// list, staging the Gaussian records of each batch in LDS; every thread owns
-// fixed pixels and keeps its transmittance T and colour in registers.  A pair
-// is skipped when its opacity is below 1/255, blending of a pixel stops at the
-// first pair that would take T below 1e-4, and alpha is clamped at 0.99
-// (Eq. opacity_clamped).  The workgroup leaves as soon as all its pixels have
+// A tile (16x16 pixels) is blended front to back over its sorted list, the
+// Gaussian records of each batch staged in LDS; every thread owns fixed pixels
+// and keeps their transmittance T and colour in registers.  A pair is skipped
+// when its opacity is below 1/255, blending of a pixel stops at the first pair
+// that would take T below 1e-4, and alpha is clamped at 0.99
+// (Eq. opacity_clamped).  A workgroup leaves as soon as all its pixels have
 // stopped (checked at every batch).
 //
-// `raster_plain` is the 3DGS baseline: 256 threads, one pixel each, the exponent
-// of Eq. power from (x - u, y - v) and the accurate expf.
-//
-// `raster_fast` applies Sec. IV-B:
-//   * coefficient folding (Eqs. expand, c0, coeff, dot): while a batch is staged
-//     the conic, mean and ln o are folded into C1..C6 so that the folded
-//     exponent P = p + ln o (Eq. folded_exponent) is
-//     C1 x^2 + C2 xy + C3 y^2 + C4 x + C5 y + C6, five FMAs per pixel with x^2,
-//     xy, y^2, x, y hoisted.  The paper's b is the doubled off-diagonal of the
-//     conic, so C2 = -B and the 0.5 b terms become B.  Coordinates are taken
-//     relative to the tile centre, which keeps |x|, |y| <= 7.5 and the folded
-//     terms small enough for float32 at any image size;
-//   * dual-pixel evaluation (Eq. dual_pixel): each thread owns (x, y) and
-//     (x, y+1); the second exponent is P(x,y) + C2 x + C3 (2y + 1) + C5, and
-//     both pixels reuse one LDS read of the coefficients; 128 threads per tile;
-//   * the range-aware bit-level exponential (Eq. fma_exp): for P in
-//     [-ln 255, 0] the bits of exp(P) are built as the integer
+// `k_raster` serves every path: a workgroup is one wave and blends one
+// half-tile, a dual pixel (x, y), (x, y + 1) per lane, each of the half-tile's
+// eight 4x4 regions walking a list of its own.  What a pair's alpha is
+// computed from is its template argument:
+//   * EXP_PLAIN, the 3DGS baseline: the exponent of Eq. power from (x - u,
+//     y - v) and the accurate expf;
+//   * EXP_BITS, the paper's Sec. IV-B: coefficient folding (Eqs. expand, c0,
+//     coeff, dot): while a batch is staged the conic, mean and ln o are folded
+//     into C1..C6 so that the folded exponent P = p + ln o (Eq.
+//     folded_exponent) is C1 x^2 + C2 xy + C3 y^2 + C4 x + C5 y + C6, five FMAs
+//     per pixel with x^2, xy, y^2, x, y hoisted.  The paper's b is the doubled
+//     off-diagonal of the conic, so C2 = -B and the 0.5 b terms become B.
+//     Coordinates are taken relative to the tile centre, which keeps |x|, |y|
+//     <= 7.5 and the folded terms small enough for float32 at any image size;
+//     dual-pixel evaluation (Eq. dual_pixel): the second exponent is P(x,y) +
+//     C2 x + C3 (2y + 1) + C5, and both pixels reuse one LDS read of the
+//     coefficients; the range-aware bit-level exponential (Eq. fma_exp): for P
+//     in [-ln 255, 0] the bits of exp(P) are built as the integer
 //     floor(P 2^23 log2 e + 2^23 (127 - sigma)), sigma = 0.045677, one FMA and
 //     one float-to-int conversion.  The skip test is made on P itself;
-//   * per-wave culled lists: while a batch is staged, each Gaussian is tested
-//     against the two 16x8 half-tiles of the two waves, first with the box of
-//     its alpha >= 1/255 ellipse, then with the ellipse itself (the least value
-//     of its quadratic form over the half-tile), both widened far beyond the
-//     float32 error of P; each wave blends only its survivors, in depth order.
-//     A culled pair would have failed the skip test, so no result changes.
+//   * EXP_HW2: the same with log2 e folded into C1..C6 and alpha = min(0.99,
+//     exp2(P)) from the hardware exp2, over the fast path's records or, as the
+//     training variant of the plain path, over the plain path's float32 records
+//     (which then carry ln o and the box); EXP_LIBM: an ablation.
+// With TRAIN it also leaves each pixel's final T and visited-pair count; the
+// backward pass recomputes every alpha from them bit for bit.
 //
-// `raster_train` is the training variant of the plain path: the dual-pixel
-// rasterizer with the culled lists over the plain path's float32 records
-// (which then carry ln o and the box), with log2 e folded into C1..C6 and
-// alpha = min(0.99, exp2(P)) from the hardware exp2.  It also leaves each
-// pixel's final T and visited-pair count; the backward pass replays the same
-// lists with the same folding, so it recomputes every alpha bit for bit.
+// The lists.  A lane costs the same whether its pair passes the skip test or
+// not, so what bounds the kernel (VALU issue: 0.36 wave instructions per SIMD
+// and cycle while its CUs are busy, where eight independent FMA chains reach
+// 0.39) is how many pairs it evaluates for each one it blends: at 1M / 1080p
+// 5.1 with one list per 16x8 half-tile, 3.4 with one per 8x8, 2.4 with one per
+// 4x4 (eight lists walked side by side, to the length of the longest of each
+// batch), 2.1 with one per 4x2, whose lists would cost twice the staging.
+// While a batch is staged, one entry per lane, each entry finds the columns
+// that its alpha >= 1/255 ellipse covers in each band of four rows (RegionSpans
+// in rgs_fold.h), and the eight lists take its index in depth order from eight
+// ballots.  A culled pair would have failed the skip test, so no result
+// changes.  The stop test is made once per group of four entries: T never
+// grows, so a pixel stops inside a group iff it is below the limit at its end,
+// and such a group is blended again entry by entry.
+// Measured, kernel alone (1M / 1080p orbit frame, 3M / 4K orbit frame): fast
+// 115 -> 87 and 322 -> 242 us, plain 612 -> 172 us at 1080p, against one list
+// per half-tile (plain: none) and two waves per workgroup.  Batches of 64, 128
+// and 192 entries differ by less than 3 % at 1080p (192: less occupancy, +7 % at
+// 4K); two waves per workgroup with barriers 96 and 285 us; a whole tile per
+// wave with four pixels per lane 103 and 264 us; the exponents and colours on
+// v_mfma_f32_4x4x1 (bit for bit the same FMAs) 129 us against 115: a float32
+// matrix instruction occupies the vector ALUs (16 of them and 64 FMAs take 530
+// cycles, 165 and 166 alone).
 //
-// Workgroup b renders tile ws.order[b] (longest lists first, so that the grid
-// does not end on a few long tiles; see the tile-order kernel) in frames that
-// take the schedule, else tile b in row-major order.  Workgroups are
-// dispatched to the 8 XCDs round-robin, so the tiles' uneven work spreads
-// evenly over the XCDs.  Giving each XCD one contiguous band of tile rows
-// (for its L2) was 4 % slower than row-major at 1M / 1080p, and bands of two
-// rows dealt out round-robin 8 % slower.
+// Workgroups b and b + 8 blend the two halves of tile ws.order[..] (longest
+// lists first, so that the grid does not end on a few long tiles; see the
+// tile-order kernel) in frames that take the schedule, else of tiles in
+// row-major order.  Workgroups are dispatched to the 8 XCDs round-robin, so
+// both halves of a tile share an L2, and the tiles' uneven work spreads evenly
+// over the XCDs.
 #include "rgs_fold.h"
 
 namespace rgs {
@@ -59,278 +76,298 @@ constexpr float FEXP_B = 1064970048.0f;
 
 // ---------------------------------------------------------------------------
 
-template <bool COUNT>
-__global__ __launch_bounds__(256) void k_raster_plain(FrameDev f, WsDev ws,
-                                                      const uint32_t* __restrict__ vals) {
-    __shared__ float4 s_a[256];   // u, v (tile-local), A, B
-    __shared__ float4 s_b[256];   // C, opacity, r, g
-    __shared__ float s_c[256];    // b
-    if (blockIdx.x >= (uint32_t)f.n_tiles) return;
-    const uint32_t tile = f.ordered ? ws.order[blockIdx.x] : blockIdx.x;
-    const uint32_t tx = tile % (uint32_t)f.tiles_x, ty = tile / (uint32_t)f.tiles_x;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t lx = tid % TILE, ly = tid / TILE;
-    const uint32_t px = tx * TILE + lx, py = ty * TILE + ly;
-    const bool inside = px < (uint32_t)f.width && py < (uint32_t)f.height;
-    const uint32_t start = ws.ranges[2 * tile], end = ws.ranges[2 * tile + 1];
-    const float ox = (float)(tx * TILE), oy = (float)(ty * TILE);
-    const float x = (float)lx, y = (float)ly;
-
-    float T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
-    bool done = !inside;
-    uint32_t stop_at = 0xffffffffu;
-    uint32_t n_blend = 0;
-    for (uint32_t b0 = start; b0 < end; b0 += 256) {
-        if (__syncthreads_count(!done) == 0) break;
-        const uint32_t idx = b0 + tid;
-        if (idx < end) {
-            const uint32_t g = vals[idx];
-            const Record rec = ws.records[g < f.n_gaussians ? g : 0u];
-            s_a[tid] = make_float4((rec.u_hi - ox) + rec.u_lo, (rec.v_hi - oy) + rec.v_lo, rec.A, rec.B);
-            s_b[tid] = make_float4(rec.C, rec.opa, rec.r, rec.g);
-            s_c[tid] = rec.b;
-        }
-        __syncthreads();
-        const uint32_t cnt = min(256u, end - b0);
-        if (!done) {
-            for (uint32_t j = 0; j < cnt; ++j) {
-                const float4 a = s_a[j];
-                const float4 m = s_b[j];
-                const float dx = x - a.x, dy = y - a.y;
-                const float p = fmaf(-0.5f, fmaf(a.z * dx, dx, m.x * dy * dy), -a.w * dx * dy);
-                const float e = expf(p);
-                const float alpha = fminf(ALPHA_MAX, m.y * e);
-                if (alpha < ALPHA_MIN) continue;
-                const float Tn = T * (1.0f - alpha);
-                if (Tn < T_MIN) {
-                    done = true;
-                    stop_at = b0 + j;
-                    break;
-                }
-                const float w = alpha * T;
-                cr = fmaf(w, m.z, cr);
-                cg = fmaf(w, m.w, cg);
-                cb = fmaf(w, s_c[j], cb);
-                T = Tn;
-                if (COUNT) ++n_blend;
-            }
-        }
-        __syncthreads();
-    }
-    if (inside) {
-        const uint64_t plane = (uint64_t)f.width * f.height;
-        const uint64_t o = (uint64_t)py * f.width + px;
-        float* __restrict__ out = ws.params->out;
-        const float bg0 = ws.params->cam.bg[0], bg1 = ws.params->cam.bg[1], bg2 = ws.params->cam.bg[2];
-        out[o] = fmaf(T, bg0, cr);
-        out[plane + o] = fmaf(T, bg1, cg);
-        out[2 * plane + o] = fmaf(T, bg2, cb);
-        ws.t_final[o] = T;
-        ws.n_proc[o] = stop_at != 0xffffffffu ? (stop_at - start + 1) | N_PROC_STOPPED : end - start;
-        if (COUNT) ws.n_blend[o] = n_blend;
-    }
-}
-
-void launch_raster_plain(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b, bool count) {
-    const uint32_t* vals = result_in_b ? ws.vals_b : ws.vals_a;
-    const dim3 grid((uint32_t)f.n_tiles), block(256);
-    if (count) hipLaunchKernelGGL(k_raster_plain<true>, grid, block, 0, s, f, ws, vals);
-    else hipLaunchKernelGGL(k_raster_plain<false>, grid, block, 0, s, f, ws, vals);
-}
-
-// ---------------------------------------------------------------------------
-
-constexpr int FAST_THREADS = 128;    // 2 waves: wave w owns tile rows 8w .. 8w+7
-constexpr int FAST_BATCH = FAST_THREADS;
 constexpr int LIST_UNROLL = 4;
-constexpr int LIST_CAP = FAST_BATCH + LIST_UNROLL;
-// How the fast rasterizer takes alpha from the folded exponent P.
+// What a pair's alpha is computed from.  The first three take it from the
+// folded exponent P = p + ln o; EXP_PLAIN is the 3DGS baseline.
 enum ExpMode : int {
     EXP_BITS = 0,   // Eq. fma_exp: the bit-level exponential (the paper's fast path)
     EXP_LIBM = 1,   // min(0.99, expf(P)): the exponential's ablation
     EXP_HW2 = 2,    // min(0.99, v_exp_f32(P log2 e)) with log2 e folded into C1..C6
+    EXP_PLAIN = 3,  // min(0.99, o expf(p)), p by Eq. power from (x - u, y - v)
 };
 
-// TRAIN: the training variant of the plain path (EXP_HW2 over the plain
-// path's records, which then hold ln o and the alpha-ellipse box): every
-// render also leaves each pixel's final T and visited-pair count for the
-// backward pass.
-template <bool COUNT, int EXPM, bool TRAIN = false>
-__global__ __launch_bounds__(FAST_THREADS) void k_raster_fast(FrameDev f, WsDev ws,
-                                                              const uint32_t* __restrict__ vals) {
-    constexpr bool EXACT = EXPM == EXP_LIBM;
-    // per-wave lists of folded Gaussians, in depth order
-    __shared__ float4 s_a[2][LIST_CAP];   // C1, C2, C3, C4
-    __shared__ float2 s_b[2][LIST_CAP];   // C5, C6
-    __shared__ float4 s_c[2][LIST_CAP];   // r, g, b, list position (as float bits)
-    __shared__ uint32_t s_cnt[2][2];      // [wave of the staging thread][list]
-    if (blockIdx.x >= (uint32_t)f.n_tiles) return;
-    const uint32_t tile = f.ordered ? ws.order[blockIdx.x] : blockIdx.x;
+// Alpha of a pair from its folded exponent P, 0 when P is below the threshold
+// thr (the skip threshold, or NaN for a pixel that has stopped or lies outside
+// the image: no P passes).
+template <int EXPM>
+__device__ inline float alpha_of(float P, float thr) {
+    float al;
+    if (EXPM == EXP_LIBM) {             // the exponential's ablation: alpha = min(0.99, exp(P))
+        al = fminf(ALPHA_MAX, expf(P));
+    } else if (EXPM == EXP_HW2) {
+        al = fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(P));
+    } else {
+        // alpha = min(0.99, exp_hat(P)) without the minimum, which cannot bind here:
+        // P = ln o - q/2 with ln o <= 0 and q >= 0, and for a kept pair every term of
+        // its float32 evaluation is below ~1600 in magnitude (conic entries <= 1/0.3,
+        // coordinates within a tile), so P < 1e-3 and exp_hat(P) < 0.978
+        al = __int_as_float((int)fmaf(P, FEXP_A, FEXP_B));
+    }
+    return P >= thr ? al : 0.0f;
+}
+
+// A lane's dual pixel (x, y), (x, y + 1): in tile-centre coordinates with the
+// monomials of Eq. dot, or for EXP_PLAIN relative to the tile's corner.
+struct DualPixel {
+    float x, y, x2, xy, y2, y21;
+};
+
+// Both pixels' alphas of a staged entry; thr0 and thr1 are the thresholds of
+// alpha_of, for EXP_PLAIN on alpha itself.
+template <int EXPM>
+__device__ inline void pair_alphas(const float4& a, const float2& c, const DualPixel& d, float thr0, float thr1,
+                                   float& al0, float& al1) {
+    if (EXPM == EXP_PLAIN) {
+        // a = (u, v, A, B), c = (C, o)
+        const float dx = d.x - a.x, dy0 = d.y - a.y, dy1 = (d.y + 1.0f) - a.y;
+        const float p0 = fmaf(-0.5f, fmaf(a.z * dx, dx, c.x * dy0 * dy0), -a.w * dx * dy0);
+        const float p1 = fmaf(-0.5f, fmaf(a.z * dx, dx, c.x * dy1 * dy1), -a.w * dx * dy1);
+        al0 = fminf(ALPHA_MAX, c.y * expf(p0));
+        al1 = fminf(ALPHA_MAX, c.y * expf(p1));
+        al0 = al0 >= thr0 ? al0 : 0.0f;
+        al1 = al1 >= thr1 ? al1 : 0.0f;
+    } else {
+        float P0, P1;
+        folded_exponents(a, c.x, c.y, d.x, d.y, d.x2, d.xy, d.y2, d.y21, P0, P1);
+        al0 = alpha_of<EXPM>(P0, thr0);
+        al1 = alpha_of<EXPM>(P1, thr1);
+    }
+}
+
+// T behind a pair of opacity al and weight w = al T.
+template <int EXPM>
+__device__ inline float behind(float T, float al, float w) {
+    return EXPM == EXP_PLAIN ? T * (1.0f - al) : T - w;
+}
+
+// A workgroup is one wave and blends one half-tile (16x8 pixels), a dual pixel
+// per lane, in eight regions of 4x4 pixels: the eight lanes of a region walk the
+// region's own list.
+constexpr int REGION = 4;
+constexpr int REGIONS = 8;                        // of a half-tile: two bands of four
+constexpr int FAST_BATCH = 64;                    // entries staged at once, one per lane
+constexpr int FAST_LIST = FAST_BATCH + LIST_UNROLL;
+constexpr uint32_t XCDS = 8;                      // workgroups go to the XCDs round-robin
+
+// TRAIN: a path with a backward pass (EXP_PLAIN, and its training variant:
+// EXP_HW2 over the plain path's records, which then hold ln o and the
+// alpha-ellipse box): every render also leaves each pixel's final T and
+// visited-pair count for it.
+template <bool COUNT, int EXPM, bool TRAIN>
+__global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint32_t* __restrict__ vals) {
+    // the batch's folded entries, and at FAST_BATCH an inert one (P = -1e30, or o = 0: always
+    // skipped), in three arrays of 16 bytes an entry, so that one address serves all three:
+    // (C1, C2, C3, C4), (C5, C6, r, g), b; EXP_PLAIN: (u, v, A, B), (C, o, r, g), b
+    constexpr uint32_t PART = (FAST_BATCH + 1) * 16;
+    __shared__ __align__(16) char s_ent[3 * PART];
+    auto coef = [&](uint32_t at) { return *reinterpret_cast<const float4*>(s_ent + at); };
+    auto tail = [&](uint32_t at) { return *reinterpret_cast<const float2*>(s_ent + at + PART); };
+    auto red_green = [&](uint32_t at) { return *reinterpret_cast<const float2*>(s_ent + at + PART + 8); };
+    auto blue = [&](uint32_t at) { return *reinterpret_cast<const float*>(s_ent + at + 2 * PART); };
+    auto put_entry = [&](uint32_t e, const float4& a, const float4& b, float c) {
+        *reinterpret_cast<float4*>(s_ent + e * 16) = a;
+        *reinterpret_cast<float4*>(s_ent + e * 16 + PART) = b;
+        *reinterpret_cast<float*>(s_ent + e * 16 + 2 * PART) = c;
+    };
+    // per region, the batch's entries that can reach it, in depth order
+    __shared__ uint32_t s_list4[REGIONS * FAST_LIST / 4];
+    uint8_t* s_list = reinterpret_cast<uint8_t*>(s_list4);
+    // both halves of a tile on one XCD, whose L2 then serves the records to both
+    const uint32_t slot_t = blockIdx.x / (2 * XCDS) * XCDS + blockIdx.x % XCDS, half = blockIdx.x / XCDS % 2;
+    if (slot_t >= (uint32_t)f.n_tiles) return;
+    const uint32_t tile = f.ordered ? ws.order[slot_t] : slot_t;
     const uint32_t tx = tile % (uint32_t)f.tiles_x, ty = tile / (uint32_t)f.tiles_x;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t wave = tid / 64, lane = tid % 64;
-    const uint32_t lx = tid % TILE, ly = 2 * (tid / TILE);
+    const uint32_t lane = threadIdx.x;
+    const uint32_t region = lane / 8;
+    const uint32_t lx = (region % 4) * REGION + lane % REGION;
+    const uint32_t ly = half * 8 + (region / 4) * REGION + (lane / REGION % 2) * 2;
     const uint32_t px = tx * TILE + lx, py = ty * TILE + ly;
     const bool in0 = px < (uint32_t)f.width && py < (uint32_t)f.height;
     const bool in1 = px < (uint32_t)f.width && py + 1 < (uint32_t)f.height;
     const uint32_t start = ws.ranges[2 * tile], end = ws.ranges[2 * tile + 1];
-    // tile-centre coordinates
-    const float ox = (float)(tx * TILE) + 7.5f, oy = (float)(ty * TILE) + 7.5f;
-    const float x = (float)lx - 7.5f, y = (float)ly - 7.5f;
-    const float x2 = x * x, xy = x * y, y2 = y * y, y21 = fmaf(2.0f, y, 1.0f);
+    // tile-centre coordinates (EXP_PLAIN: relative to the tile's corner)
+    constexpr float CENTRE = EXPM == EXP_PLAIN ? 0.0f : 7.5f;
+    const float ox = (float)(tx * TILE) + CENTRE, oy = (float)(ty * TILE) + CENTRE;
+    DualPixel dp;
+    dp.x = (float)lx - CENTRE;
+    dp.y = (float)ly - CENTRE;
+    dp.x2 = dp.x * dp.x;
+    dp.xy = dp.x * dp.y;
+    dp.y2 = dp.y * dp.y;
+    dp.y21 = fmaf(2.0f, dp.y, 1.0f);
+    const float top = (float)(half * 8) - 7.5f;        // the half-tile's first row
 
+    constexpr float SKIP = EXPM == EXP_PLAIN ? ALPHA_MIN : EXPM == EXP_HW2 ? -LOG2_255F : -LN255F;
+    const float NEVER = __uint_as_float(0x7fc00000u);
     float T0 = 1.0f, r0 = 0.0f, g0 = 0.0f, b0 = 0.0f;
     float T1 = 1.0f, r1 = 0.0f, g1 = 0.0f, b1 = 0.0f;
-    bool live0 = in0, live1 = in1;
+    // the exponents (EXP_PLAIN: alphas) that pass at each pixel: >= thr, none once it has stopped
+    float thr0 = in0 ? SKIP : NEVER, thr1 = in1 ? SKIP : NEVER;
     uint32_t stop0 = 0xffffffffu, stop1 = 0xffffffffu;
     uint32_t nbl0 = 0, nbl1 = 0;
     uint32_t steps = 0;         // counting renders: list entries this wave evaluated
+    if (lane == 0)
+        put_entry(FAST_BATCH, make_float4(0.f, 0.f, 0.f, 0.f),
+                  make_float4(0.f, EXPM == EXP_PLAIN ? 0.f : -1.0e30f, 0.f, 0.f), 0.f);
 
+    uint32_t ahead = start + lane < end ? vals[start + lane] : 0u;      // this lane's Gaussian of the next batch
     for (uint32_t base = start; base < end; base += FAST_BATCH) {
-        if (__syncthreads_count(live0 || live1) == 0) break;
-        // ---- stage: fold, cull against both half-tiles, compact per wave ----
-        const uint32_t idx = base + tid;
-        bool hit0 = false, hit1 = false;
-        float4 ca = make_float4(0.f, 0.f, 0.f, 0.f), cbv = make_float4(0.f, 0.f, 0.f, 0.f);
-        float cb = 0.f;
-        if (idx < end) {
-            const uint32_t g = vals[idx];
-            const Record rec = ws.records[g < f.n_gaussians ? g : 0u];
+        if (__ballot(thr0 == thr0 || thr1 == thr1) == 0) break;      // every pixel has stopped
+        // ---- stage: fold, and list each entry in the regions it can reach ----
+        __syncthreads();                 // (one wave: orders its LDS accesses for the compiler)
+#pragma unroll
+        for (uint32_t i = 0; i < REGIONS * FAST_LIST / 4; i += 64)
+            if (i + 64 <= REGIONS * FAST_LIST / 4 || i + lane < REGIONS * FAST_LIST / 4)
+                s_list4[i + lane] = FAST_BATCH * 0x01010101u;
+        __syncthreads();
+        // EXP_PLAIN leaves a skipped pair out altogether: with a colour that is
+        // not finite, a blend by zero would not, and the batch goes entry by entry
+        bool careful = false;
+        RegionSpans sp;
+        sp.none();
+        if (base + lane < end) {
+            const Record rec = ws.records[ahead < f.n_gaussians ? ahead : 0u];
             float u, v;
-            fold_record<EXPM == EXP_HW2>(rec, ox, oy, u, v, ca, cbv);
-            cb = rec.b;
-            cull_half_tiles(rec, u, v, hit0, hit1);
-        }
-        const uint64_t m0 = __ballot(hit0), m1 = __ballot(hit1);
-        const uint64_t lt = lanemask_lt();
-        if (lane == 0) {
-            s_cnt[wave][0] = (uint32_t)__popcll(m0);
-            s_cnt[wave][1] = (uint32_t)__popcll(m1);
-        }
-        __syncthreads();
-        const uint32_t off0 = wave ? s_cnt[0][0] : 0u, off1 = wave ? s_cnt[0][1] : 0u;
-        const float posf = __uint_as_float(idx);
-        if (hit0) {
-            const uint32_t p = off0 + (uint32_t)__popcll(m0 & lt);
-            s_a[0][p] = ca;
-            s_b[0][p] = make_float2(cbv.x, cbv.y);
-            s_c[0][p] = make_float4(cbv.z, cbv.w, cb, posf);
-        }
-        if (hit1) {
-            const uint32_t p = off1 + (uint32_t)__popcll(m1 & lt);
-            s_a[1][p] = ca;
-            s_b[1][p] = make_float2(cbv.x, cbv.y);
-            s_c[1][p] = make_float4(cbv.z, cbv.w, cb, posf);
-        }
-        const uint32_t n0 = s_cnt[0][0] + s_cnt[1][0], n1 = s_cnt[0][1] + s_cnt[1][1];
-        // inert padding up to a multiple of the unroll: P = -1e30 is always skipped
-        if (tid < 2 * LIST_UNROLL) {
-            const uint32_t w = tid / LIST_UNROLL, k = tid % LIST_UNROLL;
-            const uint32_t p = (w ? n1 : n0) + k;
-            s_a[w][p] = make_float4(0.f, 0.f, 0.f, 0.f);
-            s_b[w][p] = make_float2(0.f, -1.0e30f);
-            s_c[w][p] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        __syncthreads();
-
-        // ---- blend this wave's list ----
-        // (the list length is the same for the whole wave: keep it scalar)
-        const uint32_t n = __builtin_amdgcn_readfirstlane(wave ? n1 : n0);
-        const float4* __restrict__ la = s_a[wave];
-        const float2* __restrict__ lb = s_b[wave];
-        const float4* __restrict__ lc = s_c[wave];
-        if (__ballot(live0 || live1) != 0) {
-            bool wave_done = false;     // every pixel of the wave has stopped
-            for (uint32_t k0 = 0; k0 < n && !wave_done; k0 += LIST_UNROLL) {
-                if (COUNT) steps += LIST_UNROLL;
-                float P0s[LIST_UNROLL], P1s[LIST_UNROLL];
-#pragma unroll
-                for (int u = 0; u < LIST_UNROLL; ++u) {
-                    const float4 a = la[k0 + u];
-                    const float2 e = lb[k0 + u];
-                    folded_exponents(a, e.x, e.y, x, y, x2, xy, y2, y21, P0s[u], P1s[u]);
-                }
-#pragma unroll
-                for (int u = 0; u < LIST_UNROLL; ++u) {
-                    const float4 c = lc[k0 + u];
-                    const float P0 = P0s[u];
-                    const float P1 = P1s[u];
-                    constexpr float SKIP = EXPM == EXP_HW2 ? -LOG2_255F : -LN255F;
-                    const bool pass0 = live0 && P0 >= SKIP;
-                    const bool pass1 = live1 && P1 >= SKIP;
-                    float al0, al1;
-                    if (EXACT) {          // the exponential's ablation: alpha = min(0.99, exp(P))
-                        al0 = pass0 ? fminf(ALPHA_MAX, expf(P0)) : 0.0f;
-                        al1 = pass1 ? fminf(ALPHA_MAX, expf(P1)) : 0.0f;
-                    } else if (EXPM == EXP_HW2) {
-                        al0 = pass0 ? fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(P0)) : 0.0f;
-                        al1 = pass1 ? fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(P1)) : 0.0f;
-                    } else {
-                        // alpha = min(0.99, exp_hat(P)) without the minimum, which cannot bind here:
-                        // P = ln o - q/2 with ln o <= 0 and q >= 0, and for a kept pair every term of
-                        // its float32 evaluation is below ~1600 in magnitude (conic entries <= 1/0.3,
-                        // coordinates within a tile), so P < 1e-3 and exp_hat(P) < 0.978
-                        al0 = pass0 ? __int_as_float((int)fmaf(P0, FEXP_A, FEXP_B)) : 0.0f;
-                        al1 = pass1 ? __int_as_float((int)fmaf(P1, FEXP_A, FEXP_B)) : 0.0f;
-                    }
-                    const float w0 = al0 * T0, w1 = al1 * T1;
-                    float Tn0 = T0 - w0, Tn1 = T1 - w1;
-                    float nr0 = fmaf(w0, c.x, r0), ng0 = fmaf(w0, c.y, g0), nb0 = fmaf(w0, c.z, b0);
-                    float nr1 = fmaf(w1, c.x, r1), ng1 = fmaf(w1, c.y, g1), nb1 = fmaf(w1, c.z, b1);
-                    const bool s0 = Tn0 < T_MIN, s1 = Tn1 < T_MIN;
-                    if (COUNT) {
-                        nbl0 += (al0 > 0.0f && !s0) ? 1u : 0u;
-                        nbl1 += (al1 > 0.0f && !s1) ? 1u : 0u;
-                    }
-                    if (__ballot(s0 || s1) != 0) {
-                        // a pixel reached the stop: that pair is not blended
-                        const uint32_t at = __float_as_uint(c.w);
-                        if (s0) {
-                            live0 = false;
-                            stop0 = at;
-                            Tn0 = T0; nr0 = r0; ng0 = g0; nb0 = b0;
-                        }
-                        if (s1) {
-                            live1 = false;
-                            stop1 = at;
-                            Tn1 = T1; nr1 = r1; ng1 = g1; nb1 = b1;
-                        }
-                        wave_done = __ballot(live0 || live1) == 0;
-                    }
-                    T0 = Tn0; r0 = nr0; g0 = ng0; b0 = nb0;
-                    T1 = Tn1; r1 = nr1; g1 = ng1; b1 = nb1;
-                }
+            if (EXPM == EXP_PLAIN) {
+                u = (rec.u_hi - ox) + rec.u_lo;
+                v = (rec.v_hi - oy) + rec.v_lo;
+                put_entry(lane, make_float4(u, v, rec.A, rec.B), make_float4(rec.C, rec.opa, rec.r, rec.g), rec.b);
+                careful = !(fabsf(rec.r) + fabsf(rec.g) + fabsf(rec.b) < 1.0e30f);
+                // o e^p >= 1/255 iff q <= 2 ln(255 o); the record stores no box
+                sp.reach(rec.A, rec.B, rec.C, 2.0f * logf(255.0f * rec.opa), 1.0e30f, 1.0e30f, u - 7.5f, v - 7.5f, top);
+            } else {
+                float4 ca, cbv;
+                fold_record<EXPM == EXP_HW2>(rec, ox, oy, u, v, ca, cbv);
+                put_entry(lane, ca, cbv, rec.b);
+                sp.reach(rec.A, rec.B, rec.C, 2.0f * (LN255F + rec.opa), half_lo(rec.extra), half_hi(rec.extra), u, v,
+                         top);
             }
         }
+        uint32_t n = 0;                  // the longest list
+#pragma unroll
+        for (int k = 0; k < REGIONS; ++k) {
+            const bool hit = sp.hits(k);
+            const uint64_t m = __ballot(hit);
+            const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (hit) s_list[k * FAST_LIST + p] = (uint8_t)lane;
+            n = max(n, (uint32_t)__popcll(m));
+        }
+        n = __builtin_amdgcn_readfirstlane(n);
+        const bool one_by_one = EXPM == EXP_PLAIN && __ballot(careful) != 0;
+        const uint32_t next = base + FAST_BATCH + lane;
+        ahead = next < end ? vals[next] : 0u;
         __syncthreads();
+
+        // ---- blend: every region's lanes walk the region's list ----
+        const uint8_t* list = s_list + region * FAST_LIST;
+        uint32_t k0 = 0;
+        while (true) {
+            // whole groups, until one in which some pixel stops
+            for (; k0 < n; k0 += LIST_UNROLL) {
+                const uint32_t word = *reinterpret_cast<const uint32_t*>(list + k0);
+                float al0[LIST_UNROLL], al1[LIST_UNROLL], w0[LIST_UNROLL], w1[LIST_UNROLL];
+                uint32_t at[LIST_UNROLL];
+                float4 a[LIST_UNROLL];
+                float2 c[LIST_UNROLL];
+#pragma unroll
+                for (int u = 0; u < LIST_UNROLL; ++u) {
+                    at[u] = ((word >> (8 * u)) & 0xffu) * 16;
+                    a[u] = coef(at[u]);
+                    c[u] = tail(at[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < LIST_UNROLL; ++u) pair_alphas<EXPM>(a[u], c[u], dp, thr0, thr1, al0[u], al1[u]);
+                float Tn0 = T0, Tn1 = T1;
+                uint32_t pass0 = 0, pass1 = 0;
+                float2 rg[LIST_UNROLL];
+                float b[LIST_UNROLL];
+#pragma unroll
+                for (int u = 0; u < LIST_UNROLL; ++u) {
+                    rg[u] = red_green(at[u]);
+                    b[u] = blue(at[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < LIST_UNROLL; ++u) {
+                    w0[u] = al0[u] * Tn0;
+                    w1[u] = al1[u] * Tn1;
+                    Tn0 = behind<EXPM>(Tn0, al0[u], w0[u]);
+                    Tn1 = behind<EXPM>(Tn1, al1[u], w1[u]);
+                    if (COUNT) {
+                        pass0 += al0[u] > 0.0f ? 1u : 0u;
+                        pass1 += al1[u] > 0.0f ? 1u : 0u;
+                    }
+                }
+                // T never grows: a pixel stops in this group iff T falls below the limit at its end
+                if (one_by_one || (__ballot(Tn0 < T_MIN) | __ballot(Tn1 < T_MIN)) != 0) break;
+                T0 = Tn0;
+                T1 = Tn1;
+#pragma unroll
+                for (int u = 0; u < LIST_UNROLL; ++u) {
+                    r0 = fmaf(w0[u], rg[u].x, r0);
+                    g0 = fmaf(w0[u], rg[u].y, g0);
+                    b0 = fmaf(w0[u], b[u], b0);
+                    r1 = fmaf(w1[u], rg[u].x, r1);
+                    g1 = fmaf(w1[u], rg[u].y, g1);
+                    b1 = fmaf(w1[u], b[u], b1);
+                }
+                if (COUNT) {
+                    nbl0 += pass0;
+                    nbl1 += pass1;
+                    steps += LIST_UNROLL;
+                }
+            }
+            if (k0 >= n) break;
+            // that group entry by entry: the pair that would take a pixel below the limit
+            // is not blended
+#pragma unroll 1
+            for (uint32_t u = k0; u < k0 + LIST_UNROLL; ++u) {
+                const uint32_t e = list[u];
+                float al0, al1;
+                pair_alphas<EXPM>(coef(e * 16), tail(e * 16), dp, thr0, thr1, al0, al1);
+                const float2 col = red_green(e * 16);
+                const float bl = blue(e * 16);
+                auto blend = [&](float al, float& T, float& r, float& g, float& b, float& thr, uint32_t& stop,
+                                 uint32_t& nbl) {
+                    if (EXPM == EXP_PLAIN && al == 0.0f) return;
+                    const float w = al * T;
+                    const float Tn = behind<EXPM>(T, al, w);
+                    if (Tn < T_MIN) {
+                        thr = NEVER;
+                        stop = base + e;
+                    } else {
+                        T = Tn;
+                        r = fmaf(w, col.x, r);
+                        g = fmaf(w, col.y, g);
+                        b = fmaf(w, bl, b);
+                        if (COUNT) nbl += al > 0.0f ? 1u : 0u;
+                    }
+                };
+                blend(al0, T0, r0, g0, b0, thr0, stop0, nbl0);
+                blend(al1, T1, r1, g1, b1, thr1, stop1, nbl1);
+            }
+            if (COUNT) steps += LIST_UNROLL;
+            if (__ballot(thr0 == thr0 || thr1 == thr1) == 0) break;
+            k0 += LIST_UNROLL;
+        }
     }
-    if (COUNT && lane == 0 && steps) atomicAdd(reinterpret_cast<unsigned long long*>(&ws.header->list_steps),
-                                               (unsigned long long)steps);
+    if (COUNT && EXPM != EXP_PLAIN && lane == 0 && steps)
+        atomicAdd(reinterpret_cast<unsigned long long*>(&ws.header->list_steps), (unsigned long long)steps);
     const uint64_t plane = (uint64_t)f.width * f.height;
     float* __restrict__ out = ws.params->out;
     const float bg0 = ws.params->cam.bg[0], bg1 = ws.params->cam.bg[1], bg2 = ws.params->cam.bg[2];
-    if (in0) {
-        const uint64_t o = (uint64_t)py * f.width + px;
-        out[o] = fmaf(T0, bg0, r0);
-        out[plane + o] = fmaf(T0, bg1, g0);
-        out[2 * plane + o] = fmaf(T0, bg2, b0);
+    auto put_pixel = [&](uint32_t row, float T, float r, float g, float b, uint32_t stop, uint32_t nbl) {
+        const uint64_t o = (uint64_t)row * f.width + px;
+        out[o] = fmaf(T, bg0, r);
+        out[plane + o] = fmaf(T, bg1, g);
+        out[2 * plane + o] = fmaf(T, bg2, b);
         if (COUNT || TRAIN) {       // the debug render's and the training variant's per-pixel outputs
-            ws.t_final[o] = T0;
-            ws.n_proc[o] = stop0 != 0xffffffffu ? (stop0 - start + 1) | N_PROC_STOPPED : end - start;
+            ws.t_final[o] = T;
+            ws.n_proc[o] = stop != 0xffffffffu ? (stop - start + 1) | N_PROC_STOPPED : end - start;
         }
-        if (COUNT) ws.n_blend[o] = nbl0;
-    }
-    if (in1) {
-        const uint64_t o = (uint64_t)(py + 1) * f.width + px;
-        out[o] = fmaf(T1, bg0, r1);
-        out[plane + o] = fmaf(T1, bg1, g1);
-        out[2 * plane + o] = fmaf(T1, bg2, b1);
-        if (COUNT || TRAIN) {       // the debug render's and the training variant's per-pixel outputs
-            ws.t_final[o] = T1;
-            ws.n_proc[o] = stop1 != 0xffffffffu ? (stop1 - start + 1) | N_PROC_STOPPED : end - start;
-        }
-        if (COUNT) ws.n_blend[o] = nbl1;
-    }
+        if (COUNT) ws.n_blend[o] = nbl;
+    };
+    if (in0) put_pixel(py, T0, r0, g0, b0, stop0, nbl0);
+    if (in1) put_pixel(py + 1, T1, r1, g1, b1, stop1, nbl1);
 }
 
 // One, or four, pixels per lane: the dual-pixel ablation (one pixel per
@@ -575,13 +612,10 @@ __global__ __launch_bounds__(FastShape<PIX>::THREADS) void k_raster_fast_px(Fram
 }
 
 template <int EXPM, bool TRAIN = false>
-static void launch_fast_dual(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count) {
-    if (count)
-        hipLaunchKernelGGL((k_raster_fast<true, EXPM, TRAIN>), dim3((uint32_t)f.n_tiles), dim3(FAST_THREADS), 0, s,
-                           f, ws, vals);
-    else
-        hipLaunchKernelGGL((k_raster_fast<false, EXPM, TRAIN>), dim3((uint32_t)f.n_tiles), dim3(FAST_THREADS), 0, s,
-                           f, ws, vals);
+static void launch_dual(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count) {
+    const dim3 grid(((uint32_t)f.n_tiles + XCDS - 1) / XCDS * 2 * XCDS), block(64);
+    if (count) hipLaunchKernelGGL((k_raster<true, EXPM, TRAIN>), grid, block, 0, s, f, ws, vals);
+    else hipLaunchKernelGGL((k_raster<false, EXPM, TRAIN>), grid, block, 0, s, f, ws, vals);
 }
 
 template <int EXPM, int PIX>
@@ -598,15 +632,19 @@ void launch_raster_fast(hipStream_t s, const FrameDev& f, const WsDev& ws, bool 
     const uint32_t* vals = result_in_b ? ws.vals_b : ws.vals_a;
     const bool exact = (opts & OPT_FASTEXP) != 0, single = (opts & OPT_DUALPIXEL) != 0;
     if (opts & OPT_QUAD) launch_fast_px<EXP_BITS, 4>(s, f, ws, vals, count);        // not with the two below
-    else if (opts & OPT_HW_EXP2) launch_fast_dual<EXP_HW2>(s, f, ws, vals, count);  // not with the two below
-    else if (!exact && !single) launch_fast_dual<EXP_BITS>(s, f, ws, vals, count);
-    else if (exact && !single) launch_fast_dual<EXP_LIBM>(s, f, ws, vals, count);
+    else if (opts & OPT_HW_EXP2) launch_dual<EXP_HW2>(s, f, ws, vals, count);  // not with the two below
+    else if (!exact && !single) launch_dual<EXP_BITS>(s, f, ws, vals, count);
+    else if (exact && !single) launch_dual<EXP_LIBM>(s, f, ws, vals, count);
     else if (!exact && single) launch_fast_px<EXP_BITS, 1>(s, f, ws, vals, count);
     else launch_fast_px<EXP_LIBM, 1>(s, f, ws, vals, count);
 }
 
+void launch_raster_plain(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b, bool count) {
+    launch_dual<EXP_PLAIN, true>(s, f, ws, result_in_b ? ws.vals_b : ws.vals_a, count);
+}
+
 void launch_raster_train(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b, bool count) {
-    launch_fast_dual<EXP_HW2, true>(s, f, ws, result_in_b ? ws.vals_b : ws.vals_a, count);
+    launch_dual<EXP_HW2, true>(s, f, ws, result_in_b ? ws.vals_b : ws.vals_a, count);
 }
 
 }  // namespace rgs

@@ -88,6 +88,75 @@ __device__ inline void cull_half_tiles(const Record& rec, float u, float v, bool
     if (hit1) hit1 = !(conic_rect_min(u, v, A, B, C, iA, iC, 0.5f, 7.5f) > qlim);
 }
 
+// Which of the eight 4x4 regions of a half-tile (rows top .. top + 7) a record
+// can reach with P >= -ln 255: for each of its two bands of four rows, the span of columns that its ellipse q <= tau (up
+// to the margin above) covers inside the band.  The ellipse is convex, so it
+// meets the 4x4 region of columns x0 .. x0 + 3 iff its span in the band meets
+// [x0, x0 + 3].  At the height dy the ellipse covers -B/A dy +- sqrt(A tau -
+// det dy^2) / A; the right end is a concave function of dy with its peak at dy =
+// -B/C hx (hx the ellipse's half-width) and the left end its mirror image, so
+// each takes its extreme over the band at that height clamped to the band.
+// The spans are widened by 0.05 pixel, far beyond the rounding of this
+// evaluation.  det = AC - B^2 loses relative accuracy as AC / det grows; an
+// error of det by a factor 1 + e moves the boundary as one of tau by the same
+// factor, so up to AC = 2048 det (e below 4e-4) it stays inside the margin's
+// 1e-3.  Narrower ellipses, and conics or opacities that are not finite, take the
+// box of the alpha >= 1/255 ellipse (the fast path's records hold it, FP16
+// rounded up; the plain path's take every region).  Comparisons are phrased so
+// that a NaN keeps the Gaussian.
+struct RegionSpans {
+    float left[2], right[2];
+
+    __device__ inline void none() {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            left[b] = 1.0f;
+            right[b] = -1.0e30f;
+        }
+    }
+
+    // A Gaussian at (u, v) with conic (A, B, C) whose pairs pass up to q = tau;
+    // box_x, box_y: half-extents of its box (infinite if none is known).
+    __device__ inline void reach(float A, float B, float C, float tau, float box_x, float box_y, float u, float v,
+                                 float top) {
+        const float qlim = fmaf(tau, 1.0f + Q_MARGIN_REL, Q_MARGIN_ABS);
+        if (qlim < 0.0f) return;                        // below the threshold everywhere
+        const float AC = A * C, det = fmaf(-B, B, AC);
+        const float iA = __builtin_amdgcn_rcpf(A), iC = __builtin_amdgcn_rcpf(C), iD = __builtin_amdgcn_rcpf(det);
+        const float hx = __builtin_amdgcn_sqrtf(qlim * C * iD), hy = __builtin_amdgcn_sqrtf(qlim * A * iD);
+        const float slope = -B * iA, peak = -B * iC * hx, qA = qlim * A;
+        if (det * 2048.0f > AC && hx < 1.0e4f && hy < 1.0e4f) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const float y0 = top + (float)(4 * b) - v;
+                const float lo = fmaxf(y0, -hy), hi = fminf(y0 + 3.0f, hy);
+                const float dr = fminf(fmaxf(peak, lo), hi), dl = fminf(fmaxf(-peak, lo), hi);
+                const float sr = __builtin_amdgcn_sqrtf(fmaxf(fmaf(-det * dr, dr, qA), 0.0f));
+                const float sl = __builtin_amdgcn_sqrtf(fmaxf(fmaf(-det * dl, dl, qA), 0.0f));
+                const bool out = lo > hi + BOX_MARGIN_ABS;
+                right[b] = out ? -1.0e30f : fmaf(sr, iA, fmaf(slope, dr, u)) + BOX_MARGIN_ABS;
+                left[b] = fmaf(-sl, iA, fmaf(slope, dl, u)) - BOX_MARGIN_ABS;
+            }
+        } else {
+            const float bx = fmaf(box_x, 1.0f + BOX_MARGIN_REL, BOX_MARGIN_ABS);
+            const float by = fmaf(box_y, 1.0f + BOX_MARGIN_REL, BOX_MARGIN_ABS);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const float y0 = top + (float)(4 * b);
+                const bool out = v - by > y0 + 3.0f || v + by < y0;
+                right[b] = out ? -1.0e30f : u + bx;
+                left[b] = u - bx;
+            }
+        }
+    }
+
+    // region k: rows 4 (k / 4) .. + 3, columns 4 (k % 4) .. + 3 of the half-tile
+    __device__ inline bool hits(int k) const {
+        const float x0 = (float)(4 * (k % 4)) - 7.5f;
+        return !(left[k / 4] > x0 + 3.0f) && !(right[k / 4] < x0);
+    }
+};
+
 // The folded exponents of a dual pixel: P0 at (x, y) by Eq. dot (x2 = x^2,
 // xy = x y, y2 = y^2 precomputed), and P1 at (x, y + 1) by Eq. dual_pixel's
 // step, P0 + C2 x + C3 (2y + 1) + C5 (y21 = 2y + 1).
