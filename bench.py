@@ -216,17 +216,17 @@ def frame_counts(R, ds, cam, path):
     return c
 
 
-def bucket_sorted(path, n_tiles):
-    """Whether the library sorts this frame's keys with the bucket sort (the top-digit radix
-    pass, then the other three digits per bucket in LDS, which also writes the tile ranges):
-    the fast path's 32-bit keys with 2^8 .. 2^14 tiles."""
-    b_t = max(1, int(np.ceil(np.log2(n_tiles))))
-    return path.split("/")[0] == "fast" and "no-key32" not in path.split("/") and 8 <= b_t <= 14
+def bucket_sorted(n_tiles):
+    """Whether the library sorts this frame's keys with the split sort (one radix pass on the
+    tile index's top bits, then the rest of the key per bucket in LDS, which also writes the tile
+    ranges): frames of at least 2^8 tiles whose depth interval fits the local key, which those
+    of every workload here do."""
+    return max(1, int(np.ceil(np.log2(n_tiles)))) >= 8
 
 
 def rooflines(path, counts, stage_ms, n, n_tiles):
     by = stage_bytes(path, n, counts["n_visible"], counts["n_entries"], n_tiles, counts["passes"])
-    bucket = bucket_sorted(path, n_tiles)
+    bucket = bucket_sorted(n_tiles)
     if bucket:
         # the ranges stage holds only the rasterizers' schedule (read 8 B, write 4 B per tile)
         by["ranges"] = 12 * n_tiles
@@ -238,8 +238,8 @@ def rooflines(path, counts, stage_ms, n, n_tiles):
             out[s] = dict(bound="hbm", achieved=round(gbs, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                           frac=round(gbs / HBM_PEAK_GBS, 4), bytes=int(b), ms=round(ms, 4))
     if "sort" in out:
-        # Eq. sort_memory counts every pass; the bucket sort moves keys and values through
-        # HBM twice (the top-digit pass, then each bucket once) for the same four digits
+        # Eq. sort_memory counts every pass; the split sort moves keys and values through
+        # HBM twice (the split pass, then each bucket once) for the same digits
         out["sort"]["hbm_passes"] = 2 if bucket else counts["passes"]
     ms = stage_ms["raster"]
     ops = ops_per_pair(path)
@@ -688,7 +688,7 @@ def main():
     m = res1[main_path]
     stages = {k: v for k, v in m["roofline"].items()}
     dom = max(stages, key=lambda s: stages[s]["ms"])
-    kernel = {"raster": "k_raster_fast" if main_path == "fast" else "k_raster_plain",
+    kernel = {"raster": "k_raster",
               "frontend": "k_frontend_fast" if main_path == "fast" else "k_preprocess_plain",
               "duplicate": "k_duplicate", "sort": "k_radix_pass", "ranges": "k_ranges"}[dom]
     src = {"raster": "k_raster.hip", "frontend": "k_frontend.hip", "duplicate": "k_frontend.hip",

@@ -301,9 +301,8 @@ __global__ __launch_bounds__(BWD_LANES) void k_raster_backward(FrameDev f, WsDev
     }
 }
 
-void launch_raster_backward(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b,
+void launch_raster_backward(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals,
                             const float* dimg, float4* partial, FrameKey key) {
-    const uint32_t* vals = result_in_b ? ws.vals_b : ws.vals_a;
     hipLaunchKernelGGL(k_raster_backward, dim3((uint32_t)f.n_tiles), dim3(BWD_LANES), 0, s, f, ws, vals, dimg,
                        partial, key);
 }
@@ -546,9 +545,8 @@ __global__ __launch_bounds__(TB_THREADS) void k_raster_backward_train(FrameDev f
     }
 }
 
-void launch_raster_backward_train(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b,
+void launch_raster_backward_train(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals,
                                   const float* dimg, float4* partial, FrameKey key) {
-    const uint32_t* vals = result_in_b ? ws.vals_b : ws.vals_a;
     hipLaunchKernelGGL(k_raster_backward_train, dim3((uint32_t)f.n_tiles), dim3(TB_THREADS), 0, s, f, ws, vals,
                        dimg, partial, key);
 }

@@ -322,12 +322,19 @@ __device__ inline uint32_t nth_set_bit(uint64_t m, uint32_t k) {
     return pos;
 }
 
+// Which digits of its keys a frame's front end counts.
+struct DigitPlan {
+    uint32_t split_digits, split_shift;      // the split sort's digit (0 digits: the LSD passes)
+    uint32_t p_first, passes;                // LSD: passes counted per entry (those below, per Gaussian)
+};
+
 // Entry e of the block belongs to the Gaussian j with s_incl[j-1] <= e < s_incl[j]
 // and is the (e - s_incl[j-1])-th tile of j's rectangle in row-major order, or
 // of its kept tiles when s_mask holds them (rectangles of at most
 // EXACT_TILE_MAX_AREA tiles).
-// Each stored key also counts its digits of radix passes p_first..passes-1
-// into the block's LDS histogram s_h[pass][digit] (the passes before p_first
+// Each stored key also counts its digits into the block's LDS histogram: for the
+// split sort its one digit, s_h[digit]; else those of the radix passes
+// p_first..passes-1, s_h[pass][digit] (the passes before p_first
 // read only the depth bits, which all entries of a Gaussian share: those are
 // counted once per Gaussian by count_depth_digits).  A wave whose stored keys
 // all share a digit adds it once (the high digits of neighbouring entries are
@@ -342,7 +349,7 @@ template <typename KeyT, typename KeyFn>
 __device__ inline void emit_entries(uint32_t total, uint64_t base, const uint32_t* s_incl,
                                     const uint64_t* s_rect, uint32_t first_gauss, int tiles_x,
                                     uint32_t capacity, KeyT* keys, uint32_t* vals, KeyFn key_of,
-                                    uint32_t* s_h, uint32_t p_first, uint32_t passes, const uint64_t* s_mask) {
+                                    uint32_t* s_h, const DigitPlan& plan, const uint64_t* s_mask) {
     for (uint32_t e0 = threadIdx.x; e0 < total; e0 += EMIT_ILP * FE_THREADS) {
         // j = #{i : s_incl[i] <= e}, the first Gaussian whose inclusive count
         // exceeds e, by binary lifting: after the steps of 2^k and above, j
@@ -392,16 +399,19 @@ __device__ inline void emit_entries(uint32_t total, uint64_t base, const uint32_
             }
             const uint64_t active = __ballot(true);
             const bool all_stored = __ballot(stored) == active;
-            for (uint32_t p = p_first; p < passes; ++p) {
-                const uint32_t dg = (uint32_t)(key >> (RADIX_BITS * p)) & (RADIX - 1);
+            auto tally = [&](uint32_t* h, uint32_t dg) {
                 const uint32_t d0 = __builtin_amdgcn_readfirstlane(dg);
                 if (all_stored && __ballot(dg == d0) == active) {
                     if (lane_id() == (uint32_t)__builtin_ctzll(active))
-                        atomicAdd(&s_h[p * RADIX + d0], (uint32_t)__popcll(active));
+                        atomicAdd(&h[d0], (uint32_t)__popcll(active));
                 } else if (stored) {
-                    atomicAdd(&s_h[p * RADIX + dg], 1u);
+                    atomicAdd(&h[dg], 1u);
                 }
-            }
+            };
+            if (plan.split_digits) tally(s_h, (uint32_t)(key >> plan.split_shift));
+            else
+                for (uint32_t p = plan.p_first; p < plan.passes; ++p)
+                    tally(s_h + p * RADIX, (uint32_t)(key >> (RADIX_BITS * p)) & (RADIX - 1));
         }
     }
 }
@@ -412,23 +422,25 @@ __device__ inline void emit_entries(uint32_t total, uint64_t base, const uint32_
 // radix tile that starts inside this block's entries.  Call after the emission
 // and a barrier.
 template <typename KeyT>
-__device__ inline void prepare_sort(WsDev& ws, const uint32_t* s_h, uint32_t passes, uint32_t vb, uint64_t base,
+__device__ inline void prepare_sort(WsDev& ws, const uint32_t* s_h, const DigitPlan& plan, uint32_t vb, uint64_t base,
                                     uint32_t total) {
     uint32_t* copy = ws.hist + (uint64_t)(vb % HIST_COPIES) * MAX_PASSES * RADIX;
-    for (uint32_t i = threadIdx.x; i < passes * RADIX; i += FE_THREADS) {
+    const uint32_t counts = plan.split_digits ? plan.split_digits : plan.passes * RADIX;
+    for (uint32_t i = threadIdx.x; i < counts; i += FE_THREADS) {
         const uint32_t c = s_h[i];
         if (c) atomicAdd(&copy[i], c);
     }
-    constexpr uint64_t SIZE = SortTile<KeyT>::SIZE;
+    const uint64_t SIZE = plan.split_digits ? SPLIT_SIZE : SortTile<KeyT>::SIZE;
+    const uint32_t width = plan.split_digits ? plan.split_digits : RADIX;
     const uint64_t t0 = (base + SIZE - 1) / SIZE;
     uint64_t t1 = (base + total + SIZE - 1) / SIZE;
     if (t1 > ws.sort_rows) t1 = ws.sort_rows;
-    uint32_t* tiles = sort_state_tiles(ws, 0);
-    uint32_t* groups = sort_state_groups(ws, 0);
+    uint32_t* tiles = ws.sort_state;
+    uint32_t* groups = ws.sort_state + (uint64_t)ws.sort_rows * width;
     for (uint64_t t = t0; t < t1; ++t) {
-        for (uint32_t i = threadIdx.x; i < RADIX; i += FE_THREADS) {
-            st_state(&tiles[t * RADIX + i], 0u);
-            if (t % SORT_GROUP == 0) st_state(&groups[(t / SORT_GROUP) * RADIX + i], 0u);
+        for (uint32_t i = threadIdx.x; i < width; i += FE_THREADS) {
+            st_state(&tiles[t * width + i], 0u);
+            if (t % SORT_GROUP == 0) st_state(&groups[(t / SORT_GROUP) * width + i], 0u);
         }
     }
 }
@@ -439,9 +451,9 @@ __device__ inline void zero_hist(uint32_t* s_h) {
 
 // Radix passes whose digit lies wholly below bit `shift` of the key (the depth
 // bits) come first; their digits are the same for all entries of a Gaussian.
-__device__ inline uint32_t depth_only_passes(uint32_t shift, uint32_t passes) {
-    const uint32_t p = shift / RADIX_BITS;
-    return p < passes ? p : passes;
+__device__ inline DigitPlan digit_plan(const FrameDev& f, uint32_t shift) {
+    const uint32_t passes = (uint32_t)f.passes, p = shift / RADIX_BITS;
+    return DigitPlan{f.split_bits ? 1u << f.split_bits : 0u, f.split_shift, p < passes ? p : passes, passes};
 }
 
 // The entries of a block's Gaussian j share its depth bits low[j]: add the
@@ -450,8 +462,9 @@ __device__ inline uint32_t depth_only_passes(uint32_t shift, uint32_t passes) {
 // stored, and the sort counts only stored keys).
 __device__ inline void count_depth_digits(uint32_t* s_h, const uint32_t (&count)[FE_ITEMS], const uint32_t* low,
                                           const uint32_t* s_incl, uint64_t base, uint32_t capacity,
-                                          uint32_t p_depth) {
-    if (p_depth == 0) return;
+                                          const DigitPlan& plan) {
+    const uint32_t p_depth = plan.p_first;
+    if (plan.split_digits || p_depth == 0) return;
 #pragma unroll
     for (int k = 0; k < FE_ITEMS; ++k) {
         const uint32_t j = k * FE_THREADS + threadIdx.x;
@@ -563,7 +576,7 @@ __global__ __launch_bounds__(FE_THREADS) void k_duplicate(int64_t n, FrameDev f,
     zero_hist(s_h);
     __syncthreads();
     const uint32_t vb = s_vb;
-    const uint32_t p_depth = depth_only_passes(shift, (uint32_t)f.passes);
+    const DigitPlan plan = digit_plan(f, shift);
     uint32_t count[FE_ITEMS];
     uint32_t n_vis = 0;
 #pragma unroll
@@ -593,13 +606,13 @@ __global__ __launch_bounds__(FE_THREADS) void k_duplicate(int64_t n, FrameDev f,
         const int64_t i = (int64_t)vb * per + j;
         if (j < per && i < n && count[k]) ws.offsets[i] = (uint32_t)(base + (j ? s_incl[j - 1] : 0u));
     }
-    count_depth_digits(s_h, count, s_dbits, s_incl, base, f.capacity, p_depth);
+    count_depth_digits(s_h, count, s_dbits, s_incl, base, f.capacity, plan);
     emit_entries<KeyT>(total, base, s_incl, s_rect, vb * per, f.tiles_x, f.capacity,
                        reinterpret_cast<KeyT*>(ws.keys_a), ws.vals_a,
                        [&](uint32_t tile, uint32_t j) { return ((KeyT)tile << shift) | (KeyT)s_dbits[j]; },
-                       s_h, p_depth, (uint32_t)f.passes, ws.masks ? s_mask : nullptr);
+                       s_h, plan, ws.masks ? s_mask : nullptr);
     __syncthreads();
-    prepare_sort<KeyT>(ws, s_h, (uint32_t)f.passes, vb, base, total);
+    prepare_sort<KeyT>(ws, s_h, plan, vb, base, total);
     finish_block(ws, vb, n_blocks, base, s_base_v, total, vis_total, f.capacity);
 }
 
@@ -732,7 +745,7 @@ __global__ __launch_bounds__(FE_THREADS) void k_frontend_fast(FastSceneDev sc, F
     __syncthreads();
     const uint32_t vb = s_vb;
     const uint32_t shift = sizeof(KeyT) == 8 ? 32u : (uint32_t)f.b_d;
-    const uint32_t p_depth = depth_only_passes(shift, (uint32_t)f.passes);
+    const DigitPlan plan = digit_plan(f, shift);
     uint32_t count[FE_ITEMS];
     uint32_t n_vis = 0;
 #pragma unroll
@@ -756,13 +769,13 @@ __global__ __launch_bounds__(FE_THREADS) void k_frontend_fast(FastSceneDev sc, F
     const uint32_t total = block_scan_and_chain(count, n_vis, vb, ws, s_incl, s_wtot, s_wvis, &s_base,
                                                 &s_base_v, &vis_total);
     const uint64_t base = s_base;
-    count_depth_digits(s_h, count, s_qd, s_incl, base, f.capacity, p_depth);
+    count_depth_digits(s_h, count, s_qd, s_incl, base, f.capacity, plan);
     emit_entries<KeyT>(total, base, s_incl, s_rect, vb * per, f.tiles_x, f.capacity,
                        reinterpret_cast<KeyT*>(ws.keys_a), ws.vals_a,
                        [&](uint32_t tile, uint32_t j) { return ((KeyT)tile << shift) | (KeyT)s_qd[j]; },
-                       s_h, p_depth, (uint32_t)f.passes, (opts & OPT_EXACT_TILES) ? s_mask : nullptr);
+                       s_h, plan, (opts & OPT_EXACT_TILES) ? s_mask : nullptr);
     __syncthreads();
-    prepare_sort<KeyT>(ws, s_h, (uint32_t)f.passes, vb, base, total);
+    prepare_sort<KeyT>(ws, s_h, plan, vb, base, total);
     finish_block(ws, vb, n_blocks, base, s_base_v, total, vis_total, f.capacity);
 }
 

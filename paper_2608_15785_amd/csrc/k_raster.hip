@@ -627,9 +627,8 @@ static void launch_fast_px(hipStream_t s, const FrameDev& f, const WsDev& ws, co
         hipLaunchKernelGGL((k_raster_fast_px<false, EXPM, PIX>), grid, block, 0, s, f, ws, vals);
 }
 
-void launch_raster_fast(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b, bool count,
+void launch_raster_fast(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count,
                         uint32_t opts) {
-    const uint32_t* vals = result_in_b ? ws.vals_b : ws.vals_a;
     const bool exact = (opts & OPT_FASTEXP) != 0, single = (opts & OPT_DUALPIXEL) != 0;
     if (opts & OPT_QUAD) launch_fast_px<EXP_BITS, 4>(s, f, ws, vals, count);        // not with the two below
     else if (opts & OPT_HW_EXP2) launch_dual<EXP_HW2>(s, f, ws, vals, count);  // not with the two below
@@ -639,12 +638,12 @@ void launch_raster_fast(hipStream_t s, const FrameDev& f, const WsDev& ws, bool 
     else launch_fast_px<EXP_LIBM, 1>(s, f, ws, vals, count);
 }
 
-void launch_raster_plain(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b, bool count) {
-    launch_dual<EXP_PLAIN, true>(s, f, ws, result_in_b ? ws.vals_b : ws.vals_a, count);
+void launch_raster_plain(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count) {
+    launch_dual<EXP_PLAIN, true>(s, f, ws, vals, count);
 }
 
-void launch_raster_train(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b, bool count) {
-    launch_dual<EXP_HW2, true>(s, f, ws, result_in_b ? ws.vals_b : ws.vals_a, count);
+void launch_raster_train(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count) {
+    launch_dual<EXP_HW2, true>(s, f, ws, vals, count);
 }
 
 }  // namespace rgs

@@ -35,17 +35,28 @@
 // the workspace header on the device and tiles beyond it return at once, so
 // no host round trip sits between the front end and the sort.
 //
-// The fast path's frames of 2^8 .. 2^14 tiles take the top digit first and
-// the other three per bucket in LDS (the bucket sort below), which also
-// writes the tile ranges.
+// Frames of at least 2^8 tiles take the tile index's top bits first, in one such
+// pass, and the rest per bucket in LDS (the split sort below), which also writes
+// the tile ranges.
 #include "rgs_internal.h"
 
 namespace rgs {
 
+
+// A radix pass's shape: digit width, threads and keys per thread of a tile.
+template <int BITS_, int THREADS_, int ITEMS_>
+struct PassShape {
+    static constexpr int BITS = BITS_, THREADS = THREADS_, ITEMS = ITEMS_;
+    static constexpr uint32_t DIGITS = 1u << BITS;
+    static constexpr int WAVES = THREADS / 64;
+    static constexpr uint32_t SIZE = THREADS * ITEMS;
+    static constexpr uint32_t SPLIT = THREADS / DIGITS;      // threads per digit in the look-back
+    static_assert(THREADS % DIGITS == 0 && THREADS >= (int)DIGITS, "whole digit rows per block");
+};
 template <typename KeyT>
-__device__ inline uint32_t digit_of(KeyT k, uint32_t shift) {
-    return (uint32_t)(k >> shift) & (RADIX - 1);
-}
+using LsdShape = PassShape<RADIX_BITS, SORT_THREADS, SortTile<KeyT>::ITEMS>;
+template <int BITS>
+using SplitShape = PassShape<BITS, SPLIT_THREADS, SPLIT_ITEMS>;
 
 __device__ inline uint32_t entry_count(const WsHeader* h) {
     uint64_t n = h->n_entries;
@@ -54,22 +65,20 @@ __device__ inline uint32_t entry_count(const WsHeader* h) {
 }
 
 constexpr uint32_t SORT_READY = 0x80000000u;   // look-back word: published
-constexpr int SORT_WAVES = SORT_THREADS / 64;
-constexpr uint32_t SORT_SPLIT = SORT_THREADS / RADIX;   // threads per digit in the look-back
-static_assert(SORT_THREADS % RADIX == 0 && SORT_THREADS >= RADIX, "whole digit rows per block");
 
-// Exclusive scan of one value per digit (threads 0..RADIX-1; other threads
-// pass anything and get an unspecified result).  Every thread of the block
-// must call it: it holds two barriers.
+// Exclusive scan of one value per digit (threads 0 .. DIGITS - 1; other threads
+// pass anything and get an unspecified result).  s_wtot holds DIGITS / 64 words.
+// Every thread of the block must call it: it holds two barriers.
+template <uint32_t DIGITS>
 __device__ inline uint32_t digit_exclusive_scan(uint32_t x, uint32_t* s_wtot) {
     const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
     const uint32_t incl = wave_inclusive_scan(x);
-    if (lane == 63 && wave < RADIX / 64) s_wtot[wave] = incl;
+    if (lane == 63 && wave < DIGITS / 64) s_wtot[wave] = incl;
     __syncthreads();
     uint32_t before = 0;
 #pragma unroll
-    for (int w = 0; w < RADIX / 64; ++w)
-        if ((uint32_t)w < wave) before += s_wtot[w];
+    for (uint32_t w = 0; w < DIGITS / 64; ++w)
+        if (w < wave) before += s_wtot[w];
     __syncthreads();
     return incl - x + before;
 }
@@ -85,69 +94,70 @@ constexpr uint32_t LOOKBACK_POLLS = 4096;
 
 // Shared memory of the look-back (inside the pass kernel's s_whist once the
 // tile is reordered): per-thread partial sums, a block-wide flag, and two
-// 256-digit count rows for the fallback.
+// count rows for the fallback.
 struct LookbackLds {
-    uint32_t* part;     // [SORT_SPLIT][RADIX]
+    uint32_t* part;     // [SPLIT][DIGITS]
     uint32_t* flag;     // one word
-    uint32_t* fb;       // [RADIX] digit counts of one tile
-    uint32_t* acc;      // [RADIX] digit counts of one group
+    uint32_t* fb;       // [DIGITS] digit counts of one tile
+    uint32_t* acc;      // [DIGITS] digit counts of one group
 };
 
 // Block-wide: fb[d] = keys of tile t (of the pass input) whose digit is d.
-template <typename KeyT>
+template <typename S, typename KeyT>
 __device__ inline void count_tile(const KeyT* __restrict__ kin, uint32_t t, uint32_t n, uint32_t shift,
                                   uint32_t* fb) {
-    constexpr uint32_t SIZE = SortTile<KeyT>::SIZE;
-    for (uint32_t i = threadIdx.x; i < RADIX; i += SORT_THREADS) fb[i] = 0;
+    for (uint32_t i = threadIdx.x; i < S::DIGITS; i += S::THREADS) fb[i] = 0;
     __syncthreads();
-    const uint32_t base = t * SIZE, cnt = min(SIZE, n - base);
-    for (uint32_t i = threadIdx.x; i < cnt; i += SORT_THREADS) atomicAdd(&fb[digit_of(kin[base + i], shift)], 1u);
+    const uint32_t base = t * S::SIZE, cnt = min(S::SIZE, n - base);
+    for (uint32_t i = threadIdx.x; i < cnt; i += S::THREADS)
+        atomicAdd(&fb[(uint32_t)(kin[base + i] >> shift) & (S::DIGITS - 1)], 1u);
     __syncthreads();
 }
 
 // Block-wide: out[d] = the counts of tile row t, from its published words
-// where all 256 are ready, else counted from the tile's keys.
-template <typename KeyT>
+// where all are ready, else counted from the tile's keys.
+template <typename S, typename KeyT>
 __device__ inline void tile_row(const uint32_t* tiles, const KeyT* __restrict__ kin, uint32_t t, uint32_t n,
                                 uint32_t shift, const LookbackLds& L, uint32_t* out, bool force) {
     const uint32_t tid = threadIdx.x;
     if (tid == 0) *L.flag = force ? 1u : 0u;
     __syncthreads();
     uint32_t w = SORT_READY;
-    if (tid < RADIX && !force) {
-        w = ld_state(&tiles[(uint64_t)t * RADIX + tid]);
+    if (tid < S::DIGITS && !force) {
+        w = ld_state(&tiles[(uint64_t)t * S::DIGITS + tid]);
         if (!(w & SORT_READY)) *L.flag = 1;
     }
     __syncthreads();
     if (*L.flag) {
-        count_tile(kin, t, n, shift, L.fb);
-        if (tid < RADIX) out[tid] = L.fb[tid];
-    } else if (tid < RADIX) {
+        count_tile<S>(kin, t, n, shift, L.fb);
+        if (tid < S::DIGITS) out[tid] = L.fb[tid];
+    } else if (tid < S::DIGITS) {
         out[tid] = w & ~SORT_READY;
     }
     __syncthreads();
 }
 
-// Keys of digit d = tid % RADIX in rows [r0, r1) of a look-back table (tile
+// Keys of digit d = tid % DIGITS in rows [r0, r1) of a look-back table (tile
 // rows, or group rows of SORT_GROUP tiles), this thread's share: rows
-// r0 + s, r0 + s + SORT_SPLIT, ... with s = tid / RADIX.  Each word is polled
+// r0 + s, r0 + s + SPLIT, ... with s = tid / DIGITS.  Each word is polled
 // at most LOOKBACK_POLLS times; `ok` turns false when one is still unpublished.  No
 // barrier: the block votes on `ok` later and, if any thread missed a word,
 // takes the range again with fallback_range.
+template <typename S>
 __device__ inline uint32_t poll_range(const uint32_t* tab, uint32_t r0, uint32_t r1, bool& ok) {
     constexpr int BATCH = 16;
-    const uint32_t d = threadIdx.x % RADIX, s = threadIdx.x / RADIX;
+    const uint32_t d = threadIdx.x % S::DIGITS, s = threadIdx.x / S::DIGITS;
     uint32_t sum = 0;
-    for (uint32_t r = r0 + s; r < r1; r += BATCH * SORT_SPLIT) {
+    for (uint32_t r = r0 + s; r < r1; r += BATCH * S::SPLIT) {
         uint32_t v[BATCH];
 #pragma unroll
         for (int m = 0; m < BATCH; ++m) {
-            const uint32_t rr = r + m * SORT_SPLIT;
-            v[m] = rr < r1 ? ld_state(&tab[(uint64_t)rr * RADIX + d]) : SORT_READY;
+            const uint32_t rr = r + m * S::SPLIT;
+            v[m] = rr < r1 ? ld_state(&tab[(uint64_t)rr * S::DIGITS + d]) : SORT_READY;
         }
 #pragma unroll
         for (int m = 0; m < BATCH; ++m) {
-            const uint32_t rr = r + m * SORT_SPLIT;
+            const uint32_t rr = r + m * S::SPLIT;
             uint32_t spins = 0;
             while (!(v[m] & SORT_READY)) {
                 if (++spins > LOOKBACK_POLLS) {
@@ -155,7 +165,7 @@ __device__ inline uint32_t poll_range(const uint32_t* tab, uint32_t r0, uint32_t
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
-                v[m] = ld_state(&tab[(uint64_t)rr * RADIX + d]);
+                v[m] = ld_state(&tab[(uint64_t)rr * S::DIGITS + d]);
             }
             sum += v[m] & ~SORT_READY;
         }
@@ -165,26 +175,25 @@ __device__ inline uint32_t poll_range(const uint32_t* tab, uint32_t r0, uint32_t
 
 // The same share as poll_range, taken row by row by the whole block (every
 // thread calls it with the same range): each row is read from its published
-// words where all 256 are there, else counted from the keys.  No tile ever
+// words where all are there, else counted from the keys.  No tile ever
 // waits on another without bound: the workgroups of a grid are not
 // guaranteed to run at once.
-template <typename KeyT>
-__device__ uint32_t fallback_range(const WsDev& ws, uint32_t set, bool groups, uint32_t r0, uint32_t r1,
+template <typename S, typename KeyT>
+__device__ uint32_t fallback_range(const uint32_t* tiles, bool groups, uint32_t r0, uint32_t r1,
                                    const KeyT* __restrict__ kin, uint32_t n, uint32_t shift, const LookbackLds& L,
                                    bool force) {
-    const uint32_t tid = threadIdx.x, d = tid % RADIX, s = tid / RADIX;
-    const uint32_t* tiles = sort_state_tiles(ws, set);
+    const uint32_t tid = threadIdx.x, d = tid % S::DIGITS, s = tid / S::DIGITS;
     uint32_t sum = 0;
     for (uint32_t r = r0; r < r1; ++r) {
-        const bool mine = (r - r0) % SORT_SPLIT == s;
+        const bool mine = (r - r0) % S::SPLIT == s;
         if (!groups) {
-            tile_row(tiles, kin, r, n, shift, L, L.acc, force);
+            tile_row<S>(tiles, kin, r, n, shift, L, L.acc, force);
         } else {
-            for (uint32_t i = tid; i < RADIX; i += SORT_THREADS) L.acc[i] = 0;
+            for (uint32_t i = tid; i < S::DIGITS; i += S::THREADS) L.acc[i] = 0;
             __syncthreads();
             for (uint32_t t = r * SORT_GROUP; t < (r + 1) * SORT_GROUP; ++t) {
-                tile_row(tiles, kin, t, n, shift, L, L.fb, force);
-                if (tid < RADIX) L.acc[tid] += L.fb[tid];
+                tile_row<S>(tiles, kin, t, n, shift, L, L.fb, force);
+                if (tid < S::DIGITS) L.acc[tid] += L.fb[tid];
                 __syncthreads();
             }
         }
@@ -194,45 +203,98 @@ __device__ uint32_t fallback_range(const WsDev& ws, uint32_t set, bool groups, u
     return sum;
 }
 
+// Where a pass leaves its entries: the LSD passes a key and a value array, the
+// split pass (local key, value) pairs (see the split sort below).
+template <typename KeyT>
+struct ArraysOut {
+    using Held = KeyT;                   // what the tile holds of a key in LDS
+    KeyT* keys;
+    uint32_t* vals;
+    __device__ Held hold(KeyT k) const { return k; }
+    __device__ uint32_t digit(Held h, uint32_t shift, uint32_t mask) const { return (uint32_t)(h >> shift) & mask; }
+    __device__ void put(uint32_t at, Held h, uint32_t v) const {
+        keys[at] = h;
+        vals[at] = v;
+    }
+};
+template <typename KeyT>
+struct PairsOut;
+// 32-bit keys: the local key is the key below its top digit.
+template <>
+struct PairsOut<uint32_t> {
+    using Held = uint32_t;
+    uint2* pairs;
+    LocalKey lk;
+    const FrameParams* prm;
+    __device__ Held hold(uint32_t k) const { return k; }
+    __device__ uint32_t digit(Held h, uint32_t shift, uint32_t) const { return h >> shift; }
+    __device__ void put(uint32_t at, Held h, uint32_t v) const { pairs[at] = make_uint2(h & ((1u << lk.bits) - 1u), v); }
+};
+// 64-bit keys: (tile bits below the top digit, float32 depth bits above the
+// nearest depth's).
+template <>
+struct PairsOut<uint64_t> {
+    using Held = uint64_t;
+    uint2* pairs;
+    LocalKey lk;
+    const FrameParams* prm;
+    __device__ Held hold(uint64_t k) const { return k; }
+    __device__ uint32_t digit(Held h, uint32_t shift, uint32_t) const { return (uint32_t)(h >> shift); }
+    __device__ void put(uint32_t at, Held h, uint32_t v) const {
+        const uint32_t tile = (uint32_t)(h >> 32) & ((1u << lk.tile_bits) - 1u);
+        const uint32_t depth = (uint32_t)h - depth_key_base(prm->cam);
+        pairs[at] = make_uint2((tile << (lk.bits - lk.tile_bits)) | depth, v);
+    }
+};
+
+// One stable radix pass on the digit at `shift`.  hist[c][d]: HIST_COPIES copies,
+// hist_stride words apart, of the digit counts of the whole input.  tiles,
+// groups: this pass's look-back words; next_tiles, next_groups: those of the
+// frame's next pass, cleared here (null: none).  bases: if not null, receives
+// each digit's first output place and, after the last, the entry count.
 // FORCE: take every look-back from the keys (fallback_range), for tests.
-template <typename KeyT, bool FORCE>
-__global__ __launch_bounds__(SORT_THREADS) void k_radix_pass(const KeyT* __restrict__ kin,
-                                                             const uint32_t* __restrict__ vin,
-                                                             KeyT* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                             WsDev ws, uint32_t pass, uint32_t seq) {
-    constexpr int ITEMS = SortTile<KeyT>::ITEMS;
-    constexpr int SIZE = SortTile<KeyT>::SIZE;
-    // per-wave digit counts, then each wave's offset inside the tile's digit
-    // run; reused for the look-back's partial sums once the tile is reordered
-    __shared__ uint32_t s_whist[SORT_WAVES * RADIX];
-    __shared__ uint32_t s_bstart[RADIX];   // first LDS position of digit d in the reordered tile
-    __shared__ uint32_t s_gbase[RADIX];    // bucket base of d, then output position minus s_bstart[d]
-    __shared__ uint32_t s_tot[RADIX];      // the tile's count of digit d
-    __shared__ uint32_t s_wtot[RADIX / 64];
-    __shared__ uint32_t s_missed[2];       // look-back votes: some thread found an unpublished word
-    __shared__ KeyT s_keys[SIZE];
+template <typename KeyT, typename S, typename Out, bool FORCE>
+__global__ __launch_bounds__(S::THREADS) void k_radix_pass(const KeyT* __restrict__ kin,
+                                                           const uint32_t* __restrict__ vin, Out out,
+                                                           const WsHeader* header, const uint32_t* hist,
+                                                           uint32_t hist_stride, uint32_t* tiles, uint32_t* groups,
+                                                           uint32_t* next_tiles, uint32_t* next_groups, uint32_t shift,
+                                                           uint32_t* bases) {
+    constexpr int ITEMS = S::ITEMS;
+    constexpr uint32_t SIZE = S::SIZE, DIGITS = S::DIGITS;
+    using Held = typename Out::Held;
+    // per-wave digit counts (at most 64 ITEMS each), then each wave's offset
+    // inside the tile's digit run; reused for the look-back once the tile is
+    // reordered
+    constexpr uint32_t WHIST_WORDS = S::WAVES * DIGITS / 2 > (S::SPLIT + 3) * DIGITS ? S::WAVES * DIGITS / 2
+                                                                                     : (S::SPLIT + 3) * DIGITS;
+    __shared__ uint32_t s_whist[WHIST_WORDS];
+    __shared__ uint32_t s_bstart[DIGITS];   // first LDS position of digit d in the reordered tile
+    __shared__ uint32_t s_gbase[DIGITS];    // bucket base of d, then output position minus s_bstart[d]
+    __shared__ uint32_t s_tot[DIGITS];      // the tile's count of digit d
+    __shared__ uint32_t s_wtot[DIGITS / 64];
+    __shared__ uint32_t s_missed[2];        // look-back votes: some thread found an unpublished word
+    __shared__ Held s_keys[SIZE];
     __shared__ uint32_t s_vals[SIZE];
 
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / 64;
-    const uint32_t n = entry_count(ws.header);
+    const uint32_t n = entry_count(header);
     const uint32_t vb = blockIdx.x;      // the radix tile: keys [vb * SIZE, (vb + 1) * SIZE)
     const uint32_t tile_base = vb * SIZE;
-    if (tile_base >= n) return;
-    for (uint32_t i = tid; i < SORT_WAVES * RADIX; i += SORT_THREADS) s_whist[i] = 0;
+    if (tile_base >= n) {
+        if (bases && n == 0 && vb == 0)
+            for (uint32_t i = tid; i <= DIGITS; i += S::THREADS) bases[i] = 0;
+        return;
+    }
+    for (uint32_t i = tid; i < WHIST_WORDS; i += S::THREADS) s_whist[i] = 0;
     if (tid < 2) s_missed[tid] = 0;
     __syncthreads();
-    const uint32_t shift = 8 * pass;
-    const uint32_t n_valid = min((uint32_t)SIZE, n - tile_base);
-    // look-back words: set seq & 1 (launch seq of the frame's sort), the next
-    // launch's set cleared below
-    const uint32_t set = seq & 1;
-    uint32_t* cur_tiles = sort_state_tiles(ws, set);
-    uint32_t* cur_groups = sort_state_groups(ws, set);
+    const uint32_t n_valid = min(SIZE, n - tile_base);
     // the bucket sizes do not depend on this tile: start the loads first
     uint32_t bucket = 0;
-    if (tid < RADIX) {
+    if (tid < DIGITS) {
 #pragma unroll
-        for (int c = 0; c < HIST_COPIES; ++c) bucket += ws.hist[((uint64_t)c * MAX_PASSES + pass) * RADIX + tid];
+        for (int c = 0; c < HIST_COPIES; ++c) bucket += hist[(uint64_t)c * hist_stride + tid];
     }
 
     // wave w owns entries [tile_base + w*ITEMS*64, +ITEMS*64); round r, lane l
@@ -250,25 +312,23 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_pass(const KeyT* __restr
     }
     // the next pass's look-back words of this tile (its set was last read by
     // the previous pass, which has finished)
-    if (tid < RADIX) {
-        st_state(&sort_state_tiles(ws, set ^ 1u)[(uint64_t)vb * RADIX + tid], 0u);
-        if (vb % SORT_GROUP == 0)
-            st_state(&sort_state_groups(ws, set ^ 1u)[(uint64_t)(vb / SORT_GROUP) * RADIX + tid], 0u);
+    if (next_tiles && tid < DIGITS) {
+        st_state(&next_tiles[(uint64_t)vb * DIGITS + tid], 0u);
+        if (vb % SORT_GROUP == 0) st_state(&next_groups[(uint64_t)(vb / SORT_GROUP) * DIGITS + tid], 0u);
     }
-    const uint64_t lt = lanemask_lt();
     // Lanes of a wave read counters that other lanes of the same wave wrote in
     // the previous round.  The LDS unit executes one wave's accesses in issue
     // order; the empty asm with a memory clobber keeps the compiler from
     // moving or reusing accesses across rounds.  (A volatile pointer would do
     // the same but loses the LDS address space: every access becomes a flat
     // access that waits on all outstanding global memory operations.)
-    uint32_t* my_hist = s_whist + wave * RADIX;
+    uint16_t* my_hist = reinterpret_cast<uint16_t*>(s_whist) + wave * DIGITS;
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         asm volatile("" ::: "memory");
         const uint32_t idx = wbase + r * 64 + lane;
         const bool valid = idx < n;
-        const uint32_t d = digit_of(k[r], shift);
+        const uint32_t d = (uint32_t)(k[r] >> shift) & (DIGITS - 1);
         // lanes whose digit differs from this lane's: for each bit b the
         // ballot M_b of lanes holding a 1, XOR-ed with this lane's bit spread
         // to a whole word (0 or all ones), marks the lanes that disagree on b.
@@ -276,7 +336,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_pass(const KeyT* __restr
         // the running OR (truth table 0xBE: S2 | (S0 ^ S1)).
         uint32_t diff_lo = 0, diff_hi = 0;
 #pragma unroll
-        for (int b = 0; b < RADIX_BITS; ++b) {
+        for (int b = 0; b < S::BITS; ++b) {
             const uint32_t spread = (uint32_t)((int32_t)(d << (31 - b)) >> 31);
             const uint64_t m = __ballot(spread != 0);
             diff_lo = __builtin_amdgcn_bitop3_b32((uint32_t)m, spread, diff_lo, 0xBE);
@@ -287,27 +347,32 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_pass(const KeyT* __restr
         const uint32_t below = __builtin_amdgcn_mbcnt_hi(peers_hi, __builtin_amdgcn_mbcnt_lo(peers_lo, 0u));
         const uint32_t prev = valid ? my_hist[d] : 0u;
         rank[r] = prev + below;
-        if (valid && below == 0) my_hist[d] = prev + (uint32_t)(__popc(peers_lo) + __popc(peers_hi));
+        if (valid && below == 0) my_hist[d] = (uint16_t)(prev + (uint32_t)(__popc(peers_lo) + __popc(peers_hi)));
     }
     __syncthreads();
 
     // digit d = tid: wave offsets and the tile's count, published at once
     uint32_t tot = 0;
-    if (tid < RADIX) {
+    if (tid < DIGITS) {
+        uint16_t* h = reinterpret_cast<uint16_t*>(s_whist) + tid;
 #pragma unroll
-        for (int w = 0; w < SORT_WAVES; ++w) {
-            const uint32_t c = s_whist[w * RADIX + tid];
-            s_whist[w * RADIX + tid] = tot;
+        for (int w = 0; w < S::WAVES; ++w) {
+            const uint32_t c = h[w * DIGITS];
+            h[w * DIGITS] = (uint16_t)tot;
             tot += c;
         }
-        st_state(&cur_tiles[(uint64_t)vb * RADIX + tid], SORT_READY | tot);
+        st_state(&tiles[(uint64_t)vb * DIGITS + tid], SORT_READY | tot);
         s_tot[tid] = tot;
     }
-    const uint32_t bstart = digit_exclusive_scan(tot, s_wtot);
-    const uint32_t bbase = digit_exclusive_scan(bucket, s_wtot);
-    if (tid < RADIX) {
+    const uint32_t bstart = digit_exclusive_scan<DIGITS>(tot, s_wtot);
+    const uint32_t bbase = digit_exclusive_scan<DIGITS>(bucket, s_wtot);
+    if (tid < DIGITS) {
         s_bstart[tid] = bstart;
         s_gbase[tid] = bbase;
+        if (bases && vb == 0) {
+            bases[tid] = min(bbase, n);
+            if (tid == 0) bases[DIGITS] = n;
+        }
     }
     __syncthreads();
 
@@ -316,179 +381,177 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_pass(const KeyT* __restr
     for (int r = 0; r < ITEMS; ++r) {
         const uint32_t idx = wbase + r * 64 + lane;
         if (idx < n) {
-            const uint32_t d = digit_of(k[r], shift);
-            const uint32_t pos = s_bstart[d] + s_whist[wave * RADIX + d] + rank[r];
-            s_keys[pos] = k[r];
+            const uint32_t d = (uint32_t)(k[r] >> shift) & (DIGITS - 1);
+            const uint32_t pos = s_bstart[d] + my_hist[d] + rank[r];
+            s_keys[pos] = out.hold(k[r]);
             s_vals[pos] = v[r];
         }
     }
     __syncthreads();
 
-    // keys of digit d in earlier tiles: SORT_SPLIT threads per digit share the rows
-    const uint32_t d = tid % RADIX, s = tid / RADIX;
+    // keys of digit d in earlier tiles: SPLIT threads per digit share the rows
+    const uint32_t d = tid % DIGITS, s = tid / DIGITS;
     const uint32_t g = vb / SORT_GROUP, g0 = g * SORT_GROUP;
-    uint32_t* s_part = s_whist;    // [SORT_SPLIT][RADIX]
-    const LookbackLds L{s_whist, s_whist + SORT_SPLIT * RADIX, s_whist + (SORT_SPLIT + 1) * RADIX,
-                        s_whist + (SORT_SPLIT + 2) * RADIX};
+    uint32_t* s_part = s_whist;    // [SPLIT][DIGITS]
+    const LookbackLds L{s_whist, s_whist + S::SPLIT * DIGITS, s_whist + (S::SPLIT + 1) * DIGITS,
+                        s_whist + (S::SPLIT + 2) * DIGITS};
     constexpr bool force = FORCE;
     bool ok = !force;
-    uint32_t part = force ? 0u : poll_range(cur_tiles, g0, vb, ok);
+    uint32_t part = force ? 0u : poll_range<S>(tiles, g0, vb, ok);
     if (vb % SORT_GROUP == SORT_GROUP - 1) {
         // last tile of its group: publish the group's counts before reading
         // the earlier groups, so that later groups wait as little as possible
-        s_part[s * RADIX + d] = part;
+        s_part[s * DIGITS + d] = part;
         if (__ballot(!ok) != 0 && lane == 0) s_missed[0] = 1;
         __syncthreads();
         if (s_missed[0]) {
-            part = fallback_range(ws, set, false, g0, vb, kin, n, shift, L, force);
-            s_part[s * RADIX + d] = part;
+            part = fallback_range<S>(tiles, false, g0, vb, kin, n, shift, L, force);
+            s_part[s * DIGITS + d] = part;
             __syncthreads();
             ok = !force;
         }
-        if (tid < RADIX) {
+        if (tid < DIGITS) {
             uint32_t gsum = s_tot[tid];
 #pragma unroll
-            for (uint32_t q = 0; q < SORT_SPLIT; ++q) gsum += s_part[q * RADIX + tid];
-            st_state(&cur_groups[(uint64_t)g * RADIX + tid], SORT_READY | gsum);
+            for (uint32_t q = 0; q < S::SPLIT; ++q) gsum += s_part[q * DIGITS + tid];
+            st_state(&groups[(uint64_t)g * DIGITS + tid], SORT_READY | gsum);
         }
         __syncthreads();
     }
-    if (!force) part += poll_range(cur_groups, 0, g, ok);
-    s_part[s * RADIX + d] = part;
+    if (!force) part += poll_range<S>(groups, 0, g, ok);
+    s_part[s * DIGITS + d] = part;
     if (__ballot(!ok) != 0 && lane == 0) s_missed[1] = 1;
     __syncthreads();
     if (s_missed[1]) {
         // a predecessor's counts were not published in time: take both ranges again
-        part = fallback_range(ws, set, false, g0, vb, kin, n, shift, L, force) +
-               fallback_range(ws, set, true, 0, g, kin, n, shift, L, force);
-        s_part[s * RADIX + d] = part;
+        part = fallback_range<S>(tiles, false, g0, vb, kin, n, shift, L, force) +
+               fallback_range<S>(tiles, true, 0, g, kin, n, shift, L, force);
+        s_part[s * DIGITS + d] = part;
         __syncthreads();
     }
-    if (tid < RADIX) {
+    if (tid < DIGITS) {
         uint32_t before = 0;
 #pragma unroll
-        for (uint32_t q = 0; q < SORT_SPLIT; ++q) before += s_part[q * RADIX + tid];
+        for (uint32_t q = 0; q < S::SPLIT; ++q) before += s_part[q * DIGITS + tid];
         s_gbase[tid] = s_gbase[tid] + before - s_bstart[tid];
     }
     __syncthreads();
 
-    for (uint32_t p = tid; p < n_valid; p += SORT_THREADS) {
-        const KeyT kk = s_keys[p];
-        const uint32_t dst = s_gbase[digit_of(kk, shift)] + p;
-        if (dst < n) {        // always true for consistent counts; guards the bounds regardless
-            kout[dst] = kk;
-            vout[dst] = s_vals[p];
-        }
+    for (uint32_t p = tid; p < n_valid; p += S::THREADS) {
+        const Held h = s_keys[p];
+        const uint32_t dst = s_gbase[out.digit(h, shift, DIGITS - 1)] + p;
+        if (dst < n)          // always true for consistent counts; guards the bounds regardless
+            out.put(dst, h, s_vals[p]);
     }
 }
 
 template <typename KeyT>
-static void sort_typed(hipStream_t s, const WsDev& ws, uint32_t passes, bool* result_in_b, bool force) {
+static void sort_typed(hipStream_t s, const WsDev& ws, uint32_t passes, bool force) {
+    using S = LsdShape<KeyT>;
     KeyT* ka = reinterpret_cast<KeyT*>(ws.keys_a);
     KeyT* kb = reinterpret_cast<KeyT*>(ws.keys_b);
-    const dim3 grid(ws.sort_rows), block(SORT_THREADS);
+    const dim3 grid(ws.sort_rows), block(S::THREADS);
     for (uint32_t p = 0; p < passes; ++p) {
         const bool from_a = (p % 2) == 0;
-        if (force)
-            hipLaunchKernelGGL((k_radix_pass<KeyT, true>), grid, block, 0, s, from_a ? ka : kb,
-                               from_a ? ws.vals_a : ws.vals_b, from_a ? kb : ka, from_a ? ws.vals_b : ws.vals_a,
-                               ws, p, p);
-        else
-            hipLaunchKernelGGL((k_radix_pass<KeyT, false>), grid, block, 0, s, from_a ? ka : kb,
-                               from_a ? ws.vals_a : ws.vals_b, from_a ? kb : ka, from_a ? ws.vals_b : ws.vals_a,
-                               ws, p, p);
+        const ArraysOut<KeyT> out{from_a ? kb : ka, from_a ? ws.vals_b : ws.vals_a};
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, s, from_a ? ka : kb, from_a ? ws.vals_a : ws.vals_b, out,
+                               ws.header, ws.hist + p * RADIX, (uint32_t)(MAX_PASSES * RADIX),
+                               sort_state_tiles(ws, p & 1), sort_state_groups(ws, p & 1),
+                               sort_state_tiles(ws, (p + 1) & 1), sort_state_groups(ws, (p + 1) & 1),
+                               (uint32_t)(RADIX_BITS * p), (uint32_t*)nullptr);
+        };
+        if (force) launch(k_radix_pass<KeyT, S, ArraysOut<KeyT>, true>);
+        else launch(k_radix_pass<KeyT, S, ArraysOut<KeyT>, false>);
     }
-    *result_in_b = (passes % 2) == 1;
 }
 
-void launch_sort(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32_t key_bytes, uint32_t passes,
-                 bool force, bool* result_in_b) {
-    (void)f;
+void launch_sort(hipStream_t s, const WsDev& ws, uint32_t key_bytes, uint32_t passes, bool force) {
     // force (a context's RGS_DEBUG_SORT_FALLBACK, for tests): every look-back
     // counts its rows from the keys instead of reading the published words
-    if (key_bytes == 8) sort_typed<uint64_t>(s, ws, passes, result_in_b, force);
-    else sort_typed<uint32_t>(s, ws, passes, result_in_b, force);
+    if (key_bytes == 8) sort_typed<uint64_t>(s, ws, passes, force);
+    else sort_typed<uint32_t>(s, ws, passes, force);
 }
 
 // ---------------------------------------------------------------------------
-// Bucket sort of the fast path's 32-bit keys, for frames of 2^8 .. 2^BUCKET_MAX_BT
-// tile bits (FrameDev b_t).  The same stable LSD radix sort, reorganised:
-//   * one radix pass as above on the top digit (key bits 24..31) moves every
-//     entry to its digit's bucket, in input order.  With b_t >= 8 the top digit
-//     is tile >> (b_t - 8), so a bucket holds 2^(b_t - 8) whole tiles;
-//   * one workgroup per bucket then takes the bucket's three remaining digits
-//     (bits 0..23), least significant first, each a stable counting pass
-//     ranked through per-wave LDS digit masks (bucket_rank).  A bucket of at
-//     most BK_CAP entries stays in LDS for all three; one of at most 2 BK_CAP
-//     is sorted as two runs in LDS, each written back in place, and the two
-//     merged; a larger one streams through global memory in chunks of BK_CAP,
-//     one stable pass at a time;
+// The split sort, for frames of at least 2^SPLIT_MIN_BT tiles.  The same stable
+// sort, reorganised:
+//   * one radix pass as above on the tile index's top D bits moves every entry
+//     to its digit's bucket, in input order: a bucket holds 2^(b_t - D) whole
+//     tiles.  It leaves (local key, value) pairs, the local key being what is
+//     left to sort: the remaining tile bits, then the depth (32-bit keys: the
+//     quantised depth; 64-bit keys: the float32 depth's bits above those of
+//     z_near, which no depth is below);
+//   * one workgroup per bucket then takes the bucket's local key, least
+//     significant digit first, each a stable counting pass in LDS
+//     (bucket_rank).  A bucket of at most CAP entries stays in LDS for all of
+//     them; one of at most 2 CAP is sorted as two runs in LDS, each written back
+//     in place, and the two merged; a larger one streams through global memory
+//     in chunks of CAP, one stable pass at a time;
 //   * the same workgroup, holding its bucket sorted, writes its tiles' ranges.
-// Every pass is stable and the top digit is taken first, then bits 0..23
-// least significant first; as a stable sort on the top digit followed by a
-// stable sort on the rest leaves the keys ordered by (top digit, rest) with
-// ties in input order, the result is the LSD sort's, bit for bit.  The frame
-// then needs two sort kernels instead of four passes and the ranges kernel.
+// Every pass is stable and the top digit is taken first, then the rest least
+// significant first; as a stable sort on the top digit followed by a stable
+// sort on the rest leaves the keys ordered by (top digit, rest) with ties in
+// input order, the result is the LSD sort's, bit for bit.  The frame then needs
+// two sort kernels instead of four (32-bit keys) or six (64-bit keys, 1080p and
+// 4K) passes and the ranges kernel.
 
-constexpr int BK_THREADS = 1024;
-constexpr int BK_WAVES = BK_THREADS / 64;
-constexpr int BK_ITEMS = 16;
-constexpr uint32_t BK_CAP = BK_THREADS * BK_ITEMS;     // 16384 entries: 128 KB of keys and values
-constexpr int BK_DIGITS = 3;                             // bits 0..23 after the top digit
+constexpr uint32_t BK_LOAD_BATCH = 8;       // loads of a thread in flight where a loop stages or merges
 
-// Block-wide: bucket blockIdx.x is [b0, b0 + cnt) of the top-digit pass's
-// output, from the front end's counts of the top digit (as that pass placed
-// it), clipped to the entries the workspace holds.
-__device__ inline void bucket_span(const WsDev& ws, uint32_t n, uint32_t* s_span, uint32_t* s_wtot, uint32_t& b0,
-                                   uint32_t& cnt) {
-    const uint32_t tid = threadIdx.x;
-    uint32_t c = 0;
-    if (tid < RADIX) {
-#pragma unroll
-        for (int h = 0; h < HIST_COPIES; ++h) c += ws.hist[((uint64_t)h * MAX_PASSES + 3) * RADIX + tid];
-    }
-    const uint32_t excl = digit_exclusive_scan(c, s_wtot);
-    if (tid == blockIdx.x) {
-        s_span[0] = excl;
-        s_span[1] = c;
-    }
-    __syncthreads();
-    b0 = s_span[0];
-    cnt = b0 < n ? min(s_span[1], n - b0) : 0u;
+// A bucket's workgroup: threads, and entries each holds.
+template <int THREADS_, int ITEMS_>
+struct BucketShape {
+    static constexpr int THREADS = THREADS_, ITEMS = ITEMS_;
+    static constexpr int WAVES = THREADS / 64;
+    static constexpr uint32_t CAP = THREADS * ITEMS;
+};
+
+// Shared memory of the bucket sort.
+template <typename B>
+struct BucketLds {
+    uint2 pair[B::CAP];                        // (local key, value)
+    uint16_t whist[B::WAVES * RADIX];          // per-wave digit counts, then places (below CAP)
+    uint32_t tot[RADIX], bs[RADIX], base[RADIX];
+    uint32_t wtot[RADIX / 64];
+};
+
+// The digit of a local key at `shift` (0 past its end).
+__device__ inline uint32_t digit_at(uint32_t k, uint32_t shift) {
+    return shift < 32 ? (k >> shift) & (RADIX - 1) : 0u;
 }
 
-// Block-wide stable ranking of up to BK_CAP keys.  Wave w holds entries
+// Block-wide stable ranking of up to CAP keys.  Wave w holds entries
 // [w R 64, (w + 1) R 64) of the chunk, round r and lane l holding entry
-// (w R + r) 64 + l, with R = ceil(cnt / BK_THREADS) <= BK_ITEMS rounds, so
-// that all sixteen waves share the work.  pos[r] is the key's place when the
-// chunk is ordered by the digit at `shift` (ties in entry order), s_tot[d] the
-// chunk's count of digit d and s_bs[d] its first place.  s_match, 4096 words
-// of 64 bits, is scratch: the caller's LDS copy of the keys, which every
-// thread has read into k before the call.  Every thread calls it (barriers).
+// (w R + r) 64 + l, with R = ceil(cnt / THREADS) <= ITEMS rounds, so that
+// all waves share the work.  pos[r] is the key's place when the chunk is
+// ordered by the RADIX_BITS-bit digit at `shift` (ties in entry order), tot[d]
+// the chunk's count of digit d and bs[d] its first place.  lds.pair is scratch:
+// every entry has been read from it before the call, and it may be overwritten
+// on return.  Every thread calls it (barriers).
 //
-// The lanes of a round that share a digit are found through LDS rather than
-// with ballots: each lane ORs its bit into its digit's 64-bit mask in the
-// wave's row of s_match, reads the mask back (a wave's LDS accesses execute
-// in issue order), and the lowest lane of the digit clears it again.  Eight
-// ballots and their bit operations cost about 40 VALU instructions per
-// round, this a few VALU and five LDS accesses (the OR, the mask read, the
-// count's read and write, the clear): the bucket kernel went from 41.9 to
-// 40.2 us at 1M / 1080p.  At random digit addresses the rounds are bound by
-// the LDS's bank conflicts, about half of its busy cycles.
-__device__ inline void bucket_rank(const uint32_t (&k)[BK_ITEMS], uint32_t cnt, uint32_t R, uint32_t shift,
-                                   uint32_t (&pos)[BK_ITEMS], uint32_t* s_whist, uint32_t* s_tot, uint32_t* s_bs,
-                                   uint32_t* s_wtot, uint64_t* s_match) {
+// The lanes of a round that share a digit are found through LDS: each lane ORs
+// its bit into its digit's 64-bit mask in the wave's row, reads the mask back (a
+// wave's LDS accesses execute in issue order), and the lowest lane of the digit
+// clears it again.  Eight ballots and their bit operations, as in the radix
+// pass, cost twice the VALU instructions of the whole kernel.
+template <typename B>
+__device__ inline void bucket_rank(const uint32_t (&k)[B::ITEMS], uint32_t cnt, uint32_t R, uint32_t shift,
+                                   uint32_t (&pos)[B::ITEMS], BucketLds<B>& lds) {
+    constexpr int WAVES = B::WAVES, THREADS = B::THREADS, BK_ITEMS = B::ITEMS;
+    static_assert(sizeof(lds.pair) >= WAVES * RADIX * 8, "the masks fit the entries' LDS");
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / 64;
     // entries of this wave that exist: round r, lane l holds one when r < R and r * 64 + l < lim
     const int lim = __builtin_amdgcn_readfirstlane((int)cnt - (int)(wave * R * 64));
-    __syncthreads();            // every key read: s_match may be overwritten
-    for (uint32_t i = tid; i < BK_WAVES * RADIX; i += BK_THREADS) {
-        s_whist[i] = 0;
-        s_match[i] = 0ull;
-    }
+    uint64_t* match = reinterpret_cast<uint64_t*>(lds.pair);
+    __syncthreads();            // every entry has been read
+    uint32_t* zero = reinterpret_cast<uint32_t*>(lds.whist);
+    for (uint32_t i = tid; i < WAVES * RADIX / 2; i += THREADS) zero[i] = 0;
+    for (uint32_t i = tid; i < WAVES * RADIX / 2; i += THREADS)
+        reinterpret_cast<uint4*>(match)[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    uint32_t* my_hist = s_whist + wave * RADIX;
-    uint64_t* my_match = s_match + wave * RADIX;
+    uint16_t* my_hist = lds.whist + wave * RADIX;
+    uint64_t* my_match = match + wave * RADIX;
+    const uint64_t my_bit = 1ull << lane;
 #pragma unroll
     for (int r = 0; r < BK_ITEMS; ++r) {
         if ((uint32_t)r >= R) break;
@@ -496,199 +559,211 @@ __device__ inline void bucket_rank(const uint32_t (&k)[BK_ITEMS], uint32_t cnt, 
         // pos[r] holds the rank among the wave's keys of the same digit until
         // the scan below
         asm volatile("" ::: "memory");
-        const bool valid = (int)lane < lim - r * 64;
-        const uint32_t d = (k[r] >> shift) & (RADIX - 1);
-        if (valid) atomicOr(&my_match[d], 1ull << lane);
-        const uint64_t peers = valid ? my_match[d] : 0ull;
-        const uint32_t below =
-            __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
-        const uint32_t prev = valid ? my_hist[d] : 0u;
-        pos[r] = prev + below;
-        if (valid && below == 0) {
-            my_hist[d] = prev + (uint32_t)__popcll(peers);
-            my_match[d] = 0ull;
+        pos[r] = 0;
+        if ((int)lane < lim - r * 64) {
+            const uint32_t d = digit_at(k[r], shift);
+            atomicOr(reinterpret_cast<unsigned long long*>(&my_match[d]), (unsigned long long)my_bit);
+            const uint64_t peers = my_match[d];
+            const uint32_t prev = my_hist[d];
+            const uint32_t below =
+                __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+            pos[r] = prev + below;
+            if (below == 0) {
+                my_hist[d] = (uint16_t)(prev + (uint32_t)__popcll(peers));
+                my_match[d] = 0ull;
+            }
         }
     }
     __syncthreads();
-    // digit d = tid: each wave's offset inside the chunk's digit run (all
-    // sixteen counts loaded before any is rewritten)
-    uint32_t tot = 0;
+    // digit d = tid: each wave's first place in the chunk
+    uint32_t tot = 0, off = 0;
+    uint32_t c[WAVES];
     if (tid < RADIX) {
-        uint32_t c[BK_WAVES];
 #pragma unroll
-        for (int w = 0; w < BK_WAVES; ++w) c[w] = s_whist[w * RADIX + tid];
-#pragma unroll
-        for (int w = 0; w < BK_WAVES; ++w) {
-            s_whist[w * RADIX + tid] = tot;
+        for (int w = 0; w < WAVES; ++w) {
+            c[w] = lds.whist[w * RADIX + tid];
             tot += c[w];
         }
-        s_tot[tid] = tot;
+        lds.tot[tid] = tot;
     }
-    const uint32_t bs = digit_exclusive_scan(tot, s_wtot);
-    if (tid < RADIX) s_bs[tid] = bs;
+    const uint32_t bs = digit_exclusive_scan<RADIX>(tot, lds.wtot);
+    if (tid < RADIX) {
+        lds.bs[tid] = bs;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            lds.whist[w * RADIX + tid] = (uint16_t)(bs + off);
+            off += c[w];
+        }
+    }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < BK_ITEMS; ++r) {
         if ((uint32_t)r >= R) break;
-        const uint32_t d = (k[r] >> shift) & (RADIX - 1);
-        pos[r] += s_bs[d] + my_hist[d];
+        pos[r] += my_hist[digit_at(k[r], shift)];
     }
 }
 
-// Sorts m <= BK_CAP entries (keys ks, values vs) by key bits 0..23 in LDS,
-// three stable passes, and writes them to kd / vd.  The source may be the
-// destination (everything is in LDS before the first store).  With `runs`,
-// the keys are a whole bucket starting at entry b0 of the frame, and the
-// tiles' runs go to ws.ranges as they are written.  Every thread calls it
-// (barriers).
-__device__ inline void bucket_lds_sort(const uint32_t* ks, const uint32_t* vs, uint32_t* kd, uint32_t* vd,
-                                       uint32_t m, uint32_t* s_keys, uint32_t* s_vals, uint32_t* s_whist,
-                                       uint32_t* s_tot, uint32_t* s_bs, uint32_t* s_wtot, uint64_t* s_match,
-                                       bool runs, const WsDev& ws, uint32_t b0, uint32_t b_d, uint32_t n_tiles) {
-    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / 64;
+// Digits of a local key of `bits` bits.
+__device__ inline uint32_t digit_passes(uint32_t bits) { return bits ? (bits + RADIX_BITS - 1) / RADIX_BITS : 1u; }
+
+// Where the sorted entries of a bucket go: the values, the tiles' ranges, and
+// (debug renders) the full keys.
+struct BucketOut {
+    uint32_t* vals;
+    uint32_t* ranges;
+    uint32_t* keys32;       // 32-bit keys, or null
+    uint64_t* keys64;       // 64-bit keys, or null
+    uint32_t* error;
+    const FrameParams* prm;
+    LocalKey lk;
+    uint32_t n_tiles;
+
+    __device__ uint32_t tile_of(uint32_t local) const {
+        const uint32_t depth_bits = lk.bits - lk.tile_bits;
+        return (blockIdx.x << lk.tile_bits) | (lk.tile_bits ? local >> depth_bits : 0u);
+    }
+    // The tile's run starts at entry `at` of the frame / ended before it.
+    __device__ void start(uint32_t at, uint32_t local) const {
+        const uint32_t t = tile_of(local);
+        if (t < n_tiles) ranges[2 * t] = at;
+        else atomicOr(error, 4u);       // only after a failed front end
+    }
+    __device__ void end(uint32_t at, uint32_t local) const {
+        const uint32_t t = tile_of(local);
+        if (t < n_tiles) ranges[2 * t + 1] = at;
+        else atomicOr(error, 4u);
+    }
+    // Entry `at` and the one before it have these local keys.
+    __device__ void boundary(uint32_t at, uint32_t before, uint32_t local) const {
+        if (lk.tile_bits && (before ^ local) >> (lk.bits - lk.tile_bits)) {
+            end(at, before);
+            start(at, local);
+        }
+    }
+    __device__ bool want_keys() const { return keys32 || keys64; }
+    __device__ void put_key(uint32_t at, uint32_t local) const {
+        const uint32_t depth_bits = lk.bits - lk.tile_bits;
+        const uint32_t depth = lk.tile_bits ? local & ((1u << depth_bits) - 1u) : local, t = tile_of(local);
+        if (keys32) keys32[at] = (t << depth_bits) | depth;
+        if (keys64) keys64[at] = ((uint64_t)t << 32) | (depth_key_base(prm->cam) + depth);
+    }
+};
+
+// Sorts m <= CAP pairs of src by their local key in LDS, all digits, leaving
+// them in lds.pair.  Every thread calls it (barriers).
+template <typename B>
+__device__ inline void bucket_lds_sort(const uint2* src, uint32_t m, uint32_t bits, BucketLds<B>& lds) {
+    constexpr int THREADS = B::THREADS, BK_ITEMS = B::ITEMS;
+    const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
     // Entry e is held in round r < R by (wave, lane) with e = (wave R + r) 64
-    // + lane, the layout of bucket_rank; the values are read after the
-    // ranking, which needs only the keys.  The bounds are wave-uniform counts
-    // against the lane index, so that no per-entry index stays live across
-    // the passes.
+    // + lane, the layout of bucket_rank.  The bounds are wave-uniform counts
+    // against the lane index, so that no per-entry index stays live across the
+    // passes.  The first pass takes its pairs straight from global memory in
+    // that layout, every load of a thread in flight at once.
     uint32_t k[BK_ITEMS], v[BK_ITEMS], pos[BK_ITEMS];
-    const uint32_t R = (m + BK_THREADS - 1) / BK_THREADS;
-    const uint32_t* wkeys = s_keys + wave * R * 64 + lane;
-    const uint32_t* wvals = s_vals + wave * R * 64 + lane;
+    const uint32_t R = (m + THREADS - 1) / THREADS;
     const int lim = __builtin_amdgcn_readfirstlane((int)m - (int)(wave * R * 64));
-    // The first pass takes its keys and values straight from global memory in
-    // that layout, every load of a thread in flight at once (a load loop
-    // through LDS waits for each round trip in turn).
+    const uint2* mine = src + wave * R * 64 + lane;
+    const uint2* held = lds.pair + wave * R * 64 + lane;
 #pragma unroll
-    for (int r = 0; r < BK_ITEMS; ++r)
-        k[r] = (uint32_t)r < R && (int)lane < lim - r * 64 ? ks[(wave * R + r) * 64 + lane] : 0u;
-    for (int q = 0; q < BK_DIGITS; ++q) {
+    for (int r = 0; r < BK_ITEMS; ++r) {
+        const uint2 p = (uint32_t)r < R && (int)lane < lim - r * 64 ? mine[r * 64] : make_uint2(0u, 0u);
+        k[r] = p.x;
+        v[r] = p.y;
+    }
+    const uint32_t passes = digit_passes(bits);
+    for (uint32_t q = 0; q < passes; ++q) {
         if (q > 0) {
 #pragma unroll
-            for (int r = 0; r < BK_ITEMS; ++r)
-                k[r] = (uint32_t)r < R && (int)lane < lim - r * 64 ? wkeys[r * 64] : 0u;
+            for (int r = 0; r < BK_ITEMS; ++r) {
+                const uint2 p = (uint32_t)r < R && (int)lane < lim - r * 64 ? held[r * 64] : make_uint2(0u, 0u);
+                k[r] = p.x;
+                v[r] = p.y;
+            }
         }
-        bucket_rank(k, m, R, 8 * q, pos, s_whist, s_tot, s_bs, s_wtot, s_match);
-        if (q == 0) {
-#pragma unroll
-            for (int r = 0; r < BK_ITEMS; ++r)
-                v[r] = (uint32_t)r < R && (int)lane < lim - r * 64 ? vs[(wave * R + r) * 64 + lane] : 0u;
-        } else {
-#pragma unroll
-            for (int r = 0; r < BK_ITEMS; ++r)
-                v[r] = (uint32_t)r < R && (int)lane < lim - r * 64 ? wvals[r * 64] : 0u;
-        }
-        __syncthreads();        // every entry read before any is moved
+        bucket_rank<B>(k, m, R, RADIX_BITS * q, pos, lds);
+        __syncthreads();        // the masks are done with
 #pragma unroll
         for (int r = 0; r < BK_ITEMS; ++r)
-            if ((uint32_t)r < R && (int)lane < lim - r * 64) {
-                s_keys[pos[r]] = k[r];
-                s_vals[pos[r]] = v[r];
-            }
+            if ((uint32_t)r < R && (int)lane < lim - r * 64) lds.pair[pos[r]] = make_uint2(k[r], v[r]);
         __syncthreads();
     }
-    for (uint32_t e = tid; e < m; e += BK_THREADS) {
-        const uint32_t key = s_keys[e];
-        kd[e] = key;
-        vd[e] = s_vals[e];
-        if (!runs) continue;
-        const uint32_t t = key >> b_d;
-        if (t >= n_tiles) {          // only after a failed front end
-            atomicOr(&ws.header->error, 4u);
-            continue;
-        }
-        if (e == 0 || (s_keys[e - 1] >> b_d) != t) ws.ranges[2 * t] = b0 + e;
-        if (e + 1 == m || (s_keys[e + 1] >> b_d) != t) ws.ranges[2 * t + 1] = b0 + e + 1;
-    }
 }
 
-// The runs of the tiles in the sorted bucket [b0, b0 + cnt) of kout, read
-// back past the CU's vector cache.
-__device__ inline void bucket_ranges_global(const uint32_t* kout, uint32_t b0, uint32_t cnt, const WsDev& ws,
-                                            uint32_t b_d, uint32_t n_tiles) {
-    for (uint32_t e = threadIdx.x; e < cnt; e += BK_THREADS) {
-        const uint32_t t = ld_state(&kout[b0 + e]) >> b_d;
-        if (t >= n_tiles) {
-            atomicOr(&ws.header->error, 4u);
-            continue;
-        }
-        if (e == 0 || (ld_state(&kout[b0 + e - 1]) >> b_d) != t) ws.ranges[2 * t] = b0 + e;
-        if (e + 1 == cnt || (ld_state(&kout[b0 + e + 1]) >> b_d) != t) ws.ranges[2 * t + 1] = b0 + e + 1;
-    }
-}
-
-// dst[e] = src[e] for e < cnt, src read past the CU's vector cache, into LDS:
-// BK_LOAD_BATCH loads of a thread in flight before its LDS stores.  Every
-// thread calls it.
-constexpr uint32_t BK_LOAD_BATCH = 8;
-__device__ inline void bucket_stage(const uint32_t* src, uint32_t cnt, uint32_t* dst) {
-    for (uint32_t e0 = threadIdx.x; e0 < cnt; e0 += BK_LOAD_BATCH * BK_THREADS) {
-        uint32_t t[BK_LOAD_BATCH];
-#pragma unroll
-        for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
-            const uint32_t e = e0 + j * BK_THREADS;
-            t[j] = e < cnt ? ld_state(&src[e]) : 0u;
-        }
-#pragma unroll
-        for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
-            const uint32_t e = e0 + j * BK_THREADS;
-            if (e < cnt) dst[e] = t[j];
-        }
-    }
+__device__ inline uint2 ld_pair(const uint2* p) {
+    const uint64_t w = ld_state(reinterpret_cast<const uint64_t*>(p));
+    return make_uint2((uint32_t)w, (uint32_t)(w >> 32));
 }
 
 // FORCE: every bucket through the global-memory path (for tests).
-template <bool FORCE>
-__global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const uint32_t* kin, const uint32_t* vin,
-                                                            uint32_t* kout, uint32_t* vout, WsDev ws, uint32_t b_d,
-                                                            uint32_t n_tiles) {
-    // keys and values of up to BK_CAP entries; for a two-run merge, the keys
-    // of up to 2 BK_CAP entries across both arrays
-    __shared__ __align__(16) uint32_t s_lds[2 * BK_CAP];
-    uint32_t* s_keys = s_lds;
-    uint32_t* s_vals = s_lds + BK_CAP;
-    __shared__ uint32_t s_whist[BK_WAVES * RADIX];
-    // the ranking's digit masks live in the keys' LDS while the keys are in registers
-    uint64_t* s_match = reinterpret_cast<uint64_t*>(s_keys);
-    static_assert(BK_WAVES * RADIX * 2 <= BK_CAP, "the masks fit the keys' LDS");
-    __shared__ uint32_t s_tot[RADIX];
-    __shared__ uint32_t s_bs[RADIX];
-    __shared__ uint32_t s_base[RADIX];
-    __shared__ uint32_t s_wtot[RADIX / 64];
-    __shared__ uint32_t s_span[2];
+// pairs: the split pass's output; tmp_keys, out.vals: a second buffer for that
+// path (this bucket's own entries of both).
+template <typename B, bool FORCE>
+__global__ __launch_bounds__(B::THREADS) void k_bucket_sort(uint2* pairs, uint32_t* tmp_keys, const uint32_t* bases,
+                                                         BucketOut out) {
+    constexpr int THREADS = B::THREADS, BK_ITEMS = B::ITEMS;
+    constexpr uint32_t CAP = B::CAP;
+    __shared__ __align__(16) BucketLds<B> lds;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / 64;
-    const uint32_t n = entry_count(ws.header);
-    uint32_t b0, cnt;
-    bucket_span(ws, n, s_span, s_wtot, b0, cnt);
-    if (cnt == 0) return;
+    const uint32_t b0 = bases[blockIdx.x];
+    const uint32_t b1 = bases[blockIdx.x + 1];
+    if (b1 <= b0) return;
+    const uint32_t cnt = b1 - b0, bits = out.lk.bits;
+    uint2* src = pairs + b0;
 
-    if (!FORCE && cnt <= 2 * BK_CAP) {
+    uint32_t* akeys = tmp_keys + b0;
+    uint32_t* avals = out.vals + b0;
+    // a debug render's keys, from the bucket's sorted local keys in akeys
+    auto put_keys = [&]() {
+        if (!out.want_keys()) return;
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        for (uint32_t e = tid; e < cnt; e += THREADS) out.put_key(b0 + e, ld_state(&akeys[e]));
+    };
+    if (!FORCE && cnt <= 2 * CAP) {
         // ---- the bucket in LDS, or in two runs: each half sorted in LDS and
         // written back in place, then the two merged ----
-        const uint32_t runs = cnt <= BK_CAP ? 1u : 2u;
+        const uint32_t runs = cnt <= CAP ? 1u : 2u;
         const uint32_t cA = runs == 1 ? cnt : (cnt + 1) / 2, cB = cnt - cA;
         for (uint32_t h = 0; h < runs; ++h) {
             const uint32_t o = h ? cA : 0u, m = h ? cB : cA;
-            uint32_t* kd = runs == 1 ? kout : const_cast<uint32_t*>(kin);
-            uint32_t* vd = runs == 1 ? vout : const_cast<uint32_t*>(vin);
-            bucket_lds_sort(kin + b0 + o, vin + b0 + o, kd + b0 + o, vd + b0 + o, m, s_keys, s_vals, s_whist,
-                            s_tot, s_bs, s_wtot, s_match, runs == 1, ws, b0, b_d, n_tiles);
-            if (h + 1 < runs) __syncthreads();     // the first run's LDS before the second's loads
+            bucket_lds_sort<B>(src + o, m, bits, lds);
+            if (runs == 1) {
+                for (uint32_t e = tid; e < cnt; e += THREADS) {
+                    const uint2 p = lds.pair[e];
+                    out.vals[b0 + e] = p.y;
+                    if (e == 0) out.start(b0, p.x);
+                    else out.boundary(b0 + e, lds.pair[e - 1].x, p.x);
+                    if (e + 1 == cnt) out.end(b0 + cnt, p.x);
+                    if (out.want_keys()) out.put_key(b0 + e, p.x);
+                }
+                return;
+            }
+            for (uint32_t e = tid; e < m; e += THREADS) src[o + e] = lds.pair[e];
+            __syncthreads();     // the first run's LDS before the second's loads
         }
-        if (runs == 1) return;
         // both runs' keys into LDS, read past the CU's vector cache (it may
         // hold the first run's lines from before they were sorted)
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        bucket_stage(kin + b0, cnt, s_lds);
+        uint32_t* keys = reinterpret_cast<uint32_t*>(lds.pair);
+        for (uint32_t e0 = tid; e0 < cnt; e0 += BK_LOAD_BATCH * THREADS) {
+            uint32_t t[BK_LOAD_BATCH];
+#pragma unroll
+            for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j)
+                t[j] = e0 + j * THREADS < cnt ? ld_state(&src[e0 + j * THREADS].x) : 0u;
+#pragma unroll
+            for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j)
+                if (e0 + j * THREADS < cnt) keys[e0 + j * THREADS] = t[j];
+        }
         __syncthreads();
         // Merge path: thread t writes outputs [t S, (t + 1) S).  Its first
         // output takes i entries from A and o - i from B, i the least index
         // with A[i] > B[o - i - 1]; then the two are merged sequentially, A
         // first on equal keys (A holds the earlier entries: stable).
-        const uint32_t* A = s_lds;
-        const uint32_t* Bk = s_lds + cA;
-        const uint32_t S = (cnt + BK_THREADS - 1) / BK_THREADS;
+        const uint32_t* A = keys;
+        const uint32_t* Bk = keys + cA;
+        const uint32_t S = (cnt + THREADS - 1) / THREADS;
         const uint32_t o0 = tid * S, o1 = min(o0 + S, cnt);
         if (o0 < cnt) {
             uint32_t lo = o0 > cB ? o0 - cB : 0u, hi = min(o0, cA);
@@ -698,6 +773,8 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const uint32_t* kin,
                 else hi = mid;
             }
             uint32_t ia = lo, ib = o0 - lo;
+            // the key before this thread's first output, for the tile runs
+            uint32_t before = max(ia > 0 ? A[ia - 1] : 0u, ib > 0 ? Bk[ib - 1] : 0u);
             // BK_LOAD_BATCH outputs at a time: their value loads in flight together
             for (uint32_t ob = o0; ob < o1; ob += BK_LOAD_BATCH) {
                 uint32_t key[BK_LOAD_BATCH], val[BK_LOAD_BATCH];
@@ -705,117 +782,172 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const uint32_t* kin,
                 for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
                     if (ob + j >= o1) break;
                     const bool take_a = ib >= cB || (ia < cA && A[ia] <= Bk[ib]);
-                    const uint32_t src = take_a ? ia : cA + ib;
+                    const uint32_t at = take_a ? ia : cA + ib;
                     key[j] = take_a ? A[ia] : Bk[ib];
-                    val[j] = ld_state(&vin[b0 + src]);
+                    val[j] = ld_state(&src[at].y);
                     if (take_a) ++ia;
                     else ++ib;
                 }
 #pragma unroll
                 for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
                     if (ob + j >= o1) break;
-                    kout[b0 + ob + j] = key[j];
-                    vout[b0 + ob + j] = val[j];
+                    const uint32_t o = ob + j;
+                    out.vals[b0 + o] = val[j];
+                    if (o == 0) out.start(b0, key[j]);
+                    else out.boundary(b0 + o, before, key[j]);
+                    if (o + 1 == cnt) out.end(b0 + cnt, key[j]);
+                    if (out.want_keys()) akeys[o] = key[j];
+                    before = key[j];
                 }
             }
         }
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        bucket_ranges_global(kout, b0, cnt, ws, b_d, n_tiles);
+        put_keys();
         return;
     }
 
-    uint32_t k[BK_ITEMS], v[BK_ITEMS], pos[BK_ITEMS];
     // ---- a bucket larger than the LDS ----
-    // Each of the three passes streams it through global memory in chunks of
-    // BK_CAP: a histogram sweep, then the chunks in order, each ranked in LDS
-    // and scattered after the chunks before it.  Pass q reads src and writes
-    // dst, alternating kout and the input buffer, so that the third pass ends
-    // in kout.  Reads of what this workgroup wrote in the previous pass bypass
-    // the CU's vector cache.
-    for (int q = 0; q < BK_DIGITS; ++q) {
-        const uint32_t shift = 8 * q;
-        const uint32_t* ks = q == 1 ? kout : kin;
-        const uint32_t* vs = q == 1 ? vout : vin;
-        uint32_t* kd = q == 1 ? const_cast<uint32_t*>(kin) : kout;
-        uint32_t* vd = q == 1 ? const_cast<uint32_t*>(vin) : vout;
-        if (tid < RADIX) s_tot[tid] = 0;
+    // Each pass streams it through global memory in chunks of CAP: a
+    // histogram sweep, then the chunks in order, each ranked in LDS and
+    // scattered after the chunks before it.  Passes alternate between the pairs
+    // and the second buffer's arrays and their number is odd, so that the last
+    // ends in the arrays.  Reads of what this workgroup wrote in the previous
+    // pass bypass the CU's vector cache.
+    uint32_t k[BK_ITEMS], v[BK_ITEMS], pos[BK_ITEMS];
+    const uint32_t passes = digit_passes(bits) | 1u;
+    for (uint32_t q = 0; q < passes; ++q) {
+        const uint32_t shift = RADIX_BITS * q;
+        const bool from_pairs = q % 2 == 0;
+        if (tid < RADIX) lds.tot[tid] = 0;
         __syncthreads();
-        for (uint32_t i0 = tid; i0 < cnt; i0 += BK_LOAD_BATCH * BK_THREADS) {
+        for (uint32_t i0 = tid; i0 < cnt; i0 += BK_LOAD_BATCH * THREADS) {
             uint32_t t[BK_LOAD_BATCH];
 #pragma unroll
             for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
-                const uint32_t i = i0 + j * BK_THREADS;
-                t[j] = i < cnt ? ld_state(&ks[b0 + i]) : 0u;
+                const uint32_t i = i0 + j * THREADS;
+                t[j] = i < cnt ? ld_state(from_pairs ? &src[i].x : &akeys[i]) : 0u;
             }
 #pragma unroll
             for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j)
-                if (i0 + j * BK_THREADS < cnt) atomicAdd(&s_tot[(t[j] >> shift) & (RADIX - 1)], 1u);
+                if (i0 + j * THREADS < cnt) atomicAdd(&lds.tot[digit_at(t[j], shift)], 1u);
         }
         __syncthreads();
-        const uint32_t base = digit_exclusive_scan(tid < RADIX ? s_tot[tid] : 0u, s_wtot);
-        if (tid < RADIX) s_base[tid] = base;
+        const uint32_t base = digit_exclusive_scan<RADIX>(tid < RADIX ? lds.tot[tid] : 0u, lds.wtot);
+        if (tid < RADIX) lds.base[tid] = base;
         __syncthreads();
-        for (uint32_t c0 = 0; c0 < cnt; c0 += BK_CAP) {
-            const uint32_t ccnt = min(BK_CAP, cnt - c0);
-            bucket_stage(ks + b0 + c0, ccnt, s_keys);
-            bucket_stage(vs + b0 + c0, ccnt, s_vals);
-            __syncthreads();
-            const uint32_t R = (ccnt + BK_THREADS - 1) / BK_THREADS;
-            const uint32_t* wkeys = s_keys + wave * R * 64 + lane;
-            const uint32_t* wvals = s_vals + wave * R * 64 + lane;
+        for (uint32_t c0 = 0; c0 < cnt; c0 += CAP) {
+            const uint32_t ccnt = min(CAP, cnt - c0);
+            const uint32_t R = (ccnt + THREADS - 1) / THREADS;
             const int lim = __builtin_amdgcn_readfirstlane((int)ccnt - (int)(wave * R * 64));
 #pragma unroll
-            for (int r = 0; r < BK_ITEMS; ++r)
-                k[r] = (uint32_t)r < R && (int)lane < lim - r * 64 ? wkeys[r * 64] : 0u;
-            bucket_rank(k, ccnt, R, shift, pos, s_whist, s_tot, s_bs, s_wtot, s_match);
-#pragma unroll
-            for (int r = 0; r < BK_ITEMS; ++r)
-                v[r] = (uint32_t)r < R && (int)lane < lim - r * 64 ? wvals[r * 64] : 0u;
+            for (int r = 0; r < BK_ITEMS; ++r) {
+                k[r] = v[r] = 0u;
+                if ((uint32_t)r < R && (int)lane < lim - r * 64) {
+                    const uint32_t e = c0 + (wave * R + r) * 64 + lane;
+                    if (from_pairs) {
+                        const uint2 p = ld_pair(&src[e]);
+                        k[r] = p.x;
+                        v[r] = p.y;
+                    } else {
+                        k[r] = ld_state(&akeys[e]);
+                        v[r] = ld_state(&avals[e]);
+                    }
+                }
+            }
+            bucket_rank<B>(k, ccnt, R, shift, pos, lds);
 #pragma unroll
             for (int r = 0; r < BK_ITEMS; ++r) {
                 if ((uint32_t)r < R && (int)lane < lim - r * 64) {
-                    const uint32_t d = (k[r] >> shift) & (RADIX - 1);
-                    const uint32_t dst = b0 + s_base[d] + pos[r] - s_bs[d];
-                    if (dst < n) {      // always true for consistent counts
-                        kd[dst] = k[r];
-                        vd[dst] = v[r];
+                    const uint32_t d = digit_at(k[r], shift);
+                    const uint32_t dst = lds.base[d] + pos[r] - lds.bs[d];
+                    if (dst < cnt) {      // always true for consistent counts
+                        if (from_pairs) {
+                            akeys[dst] = k[r];
+                            avals[dst] = v[r];
+                        } else {
+                            src[dst] = make_uint2(k[r], v[r]);
+                        }
                     }
                 }
             }
             // the stores reach the L2 before any thread of the workgroup reads
-            // them back (the next chunk's LDS staging, the next pass, the ranges)
+            // them back (the next pass, the ranges)
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
-            if (tid < RADIX) s_base[tid] += s_tot[tid];
+            if (tid < RADIX) lds.base[tid] += lds.tot[tid];
             __syncthreads();
         }
     }
-    bucket_ranges_global(kout, b0, cnt, ws, b_d, n_tiles);
+    // the arrays hold the bucket sorted
+    for (uint32_t e = tid; e < cnt; e += THREADS) {
+        const uint32_t key = ld_state(&akeys[e]);
+        if (e == 0) out.start(b0, key);
+        else out.boundary(b0 + e, ld_state(&akeys[e - 1]), key);
+        if (e + 1 == cnt) out.end(b0 + cnt, key);
+    }
+    put_keys();
 }
 
-bool bucket_sort_applies(const FrameDev& f, uint32_t key_bytes) {
-    return key_bytes == 4 && f.b_t >= 8 && f.b_t <= BUCKET_MAX_BT;
+template <typename B>
+static void launch_bucket(hipStream_t s, uint2* pairs, uint32_t* tmp_keys, const WsDev& ws, uint32_t buckets,
+                          const BucketOut& out, bool force) {
+    if (force)
+        hipLaunchKernelGGL((k_bucket_sort<B, true>), dim3(buckets), dim3(B::THREADS), 0, s, pairs, tmp_keys,
+                           ws.bases, out);
+    else
+        hipLaunchKernelGGL((k_bucket_sort<B, false>), dim3(buckets), dim3(B::THREADS), 0, s, pairs, tmp_keys,
+                           ws.bases, out);
 }
 
-void launch_sort_bucket(hipStream_t s, const FrameDev& f, const WsDev& ws, bool force, bool* result_in_b) {
-    uint32_t* ka = reinterpret_cast<uint32_t*>(ws.keys_a);
-    uint32_t* kb = reinterpret_cast<uint32_t*>(ws.keys_b);
-    // the top digit: keys_a -> keys_b, look-back set 0 (cleared by the front end)
-    if (force)
-        hipLaunchKernelGGL((k_radix_pass<uint32_t, true>), dim3(ws.sort_rows), dim3(SORT_THREADS), 0, s, ka,
-                           ws.vals_a, kb, ws.vals_b, ws, 3u, 0u);
-    else
-        hipLaunchKernelGGL((k_radix_pass<uint32_t, false>), dim3(ws.sort_rows), dim3(SORT_THREADS), 0, s, ka,
-                           ws.vals_a, kb, ws.vals_b, ws, 3u, 0u);
-    // each bucket: keys_b -> keys_a, with its tiles' ranges
-    if (force)
-        hipLaunchKernelGGL(k_bucket_sort<true>, dim3(RADIX), dim3(BK_THREADS), 0, s, kb, ws.vals_b, ka, ws.vals_a,
-                           ws, (uint32_t)f.b_d, (uint32_t)f.n_tiles);
-    else
-        hipLaunchKernelGGL(k_bucket_sort<false>, dim3(RADIX), dim3(BK_THREADS), 0, s, kb, ws.vals_b, ka, ws.vals_a,
-                           ws, (uint32_t)f.b_d, (uint32_t)f.n_tiles);
-    *result_in_b = false;
+template <typename KeyT, int BITS>
+static void launch_split_pass(hipStream_t s, const FrameDev& f, const WsDev& ws, uint2* pairs, bool force) {
+    using S = SplitShape<BITS>;
+    const PairsOut<KeyT> out{pairs, f.lk, ws.params};
+    uint32_t* tiles = ws.sort_state;
+    uint32_t* groups = ws.sort_state + (uint64_t)ws.sort_rows * S::DIGITS;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(ws.sort_rows), dim3(S::THREADS), 0, s,
+                           reinterpret_cast<const KeyT*>(ws.keys_a), ws.vals_a, out, ws.header, ws.hist,
+                           (uint32_t)(MAX_PASSES * RADIX), tiles, groups, (uint32_t*)nullptr, (uint32_t*)nullptr,
+                           f.split_shift, ws.bases);
+    };
+    if (force) launch(k_radix_pass<KeyT, S, PairsOut<KeyT>, true>);
+    else launch(k_radix_pass<KeyT, S, PairsOut<KeyT>, false>);
+}
+
+void launch_sort_split(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32_t key_bytes, bool force,
+                       bool want_keys) {
+    // pairs in the second key and value arrays (32-bit keys: the two are
+    // adjacent); sorted values in the first value array
+    uint2* pairs = reinterpret_cast<uint2*>(ws.keys_b);
+    if (key_bytes == 8) {
+        if (f.split_bits == 10) launch_split_pass<uint64_t, 10>(s, f, ws, pairs, force);
+        else launch_split_pass<uint64_t, 8>(s, f, ws, pairs, force);
+    } else {
+        if (f.split_bits == 10) launch_split_pass<uint32_t, 10>(s, f, ws, pairs, force);
+        else launch_split_pass<uint32_t, 8>(s, f, ws, pairs, force);
+    }
+    const uint32_t buckets = 1u << f.split_bits;
+    BucketOut out{};
+    out.vals = ws.vals_a;
+    out.ranges = ws.ranges;
+    // 32-bit keys replace the emitted ones; 64-bit keys take the place of their own pairs
+    out.keys32 = want_keys && key_bytes == 4 ? reinterpret_cast<uint32_t*>(ws.keys_a) : nullptr;
+    out.keys64 = want_keys && key_bytes == 8 ? reinterpret_cast<uint64_t*>(ws.keys_b) : nullptr;
+    out.error = &ws.header->error;
+    out.prm = ws.params;
+    out.lk = f.lk;
+    out.n_tiles = (uint32_t)f.n_tiles;
+    uint32_t* tmp_keys = reinterpret_cast<uint32_t*>(ws.keys_a);
+    // The workgroup by the entries a bucket may hold on average (what the
+    // workspace holds, usually 1.25 to 2 times the frame's): the busiest bucket
+    // has about twice the frame's average, and should still be one run in LDS,
+    // while smaller workgroups start together and share a CU better.  Kernel
+    // times in us with 512 x 9, 512 x 16 and 1024 x 16 entries:
+    // 1280x720 28, 35, 56; 1080p (1M) 33, 42, 68 (plain 65, 63, 94); 4K (3M) 94, 73, 104.
+    const uint32_t room = f.capacity >> f.split_bits;
+    if (room <= 4608) launch_bucket<BucketShape<512, 9>>(s, pairs, tmp_keys, ws, buckets, out, force);
+    else if (room <= 12288) launch_bucket<BucketShape<512, 16>>(s, pairs, tmp_keys, ws, buckets, out, force);
+    else launch_bucket<BucketShape<1024, 16>>(s, pairs, tmp_keys, ws, buckets, out, force);
 }
 
 // ---------------------------------------------------------------------------

@@ -537,7 +537,8 @@ static void make_layout(int64_t n, const rgs_plan& p, int32_t path, uint64_t cap
     L.passes = L.key_bytes == 8 ? (uint32_t)p.plain_passes : (uint32_t)p.fast_passes;
     fe_block_shape(n, L.fe_blocks, L.fe_per);
     const uint64_t st = sort_tile_size(L.key_bytes);
-    L.sort_blocks_max = (uint32_t)((capacity + st - 1) / st);
+    L.lsd_rows = (uint32_t)((capacity + st - 1) / st);
+    L.split_rows = (uint32_t)((capacity + SPLIT_SIZE - 1) / SPLIT_SIZE);
     uint64_t off = 0;
     L.header = off;
     off = align256(off + sizeof(WsHeader));
@@ -571,17 +572,21 @@ static void make_layout(int64_t n, const rgs_plan& p, int32_t path, uint64_t cap
     }
     L.keys_a = off;
     off = align256(off + capacity * L.key_bytes);
-    L.keys_b = off;
-    off = align256(off + capacity * L.key_bytes);
     L.vals_a = off;
     off = align256(off + capacity * 4);
+    L.keys_b = off;                  // with vals_b, room for the split sort's (key, value) pairs
+    off = align256(off + capacity * L.key_bytes);
     L.vals_b = off;
     off = align256(off + capacity * 4);
     L.sort_state = off;
     {
-        const uint64_t groups = (L.sort_blocks_max + SORT_GROUP - 1) / SORT_GROUP;
-        off = align256(off + 2 * ((uint64_t)L.sort_blocks_max + groups) * RADIX * 4);
+        const uint64_t lsd = 2 * ((uint64_t)L.lsd_rows + (L.lsd_rows + SORT_GROUP - 1) / SORT_GROUP) * RADIX;
+        const uint64_t split = p.b_t < SPLIT_MIN_BT ? 0
+            : ((uint64_t)L.split_rows + (L.split_rows + SORT_GROUP - 1) / SORT_GROUP) << (p.b_t < SPLIT_WIDE_BT ? 8 : 10);
+        off = align256(off + std::max(lsd, split) * 4);
     }
+    L.bases = off;
+    off = align256(off + (uint64_t)(SPLIT_DIGITS_MAX + 1) * 4);
     L.t_final = off;
     off = align256(off + (uint64_t)p.width * p.height * 4);
     L.n_proc = off;
@@ -681,8 +686,9 @@ static WsDev ws_pointers(void* base, const WsLayout& L) {
     w.vals_b = reinterpret_cast<uint32_t*>(b + L.vals_b);
     w.hist = reinterpret_cast<uint32_t*>(b + L.hist);
     w.sort_state = reinterpret_cast<uint32_t*>(b + L.sort_state);
-    w.sort_rows = L.sort_blocks_max;
-    w.sort_groups = (L.sort_blocks_max + SORT_GROUP - 1) / SORT_GROUP;
+    w.bases = reinterpret_cast<uint32_t*>(b + L.bases);
+    w.sort_rows = L.lsd_rows;
+    w.sort_groups = (L.lsd_rows + SORT_GROUP - 1) / SORT_GROUP;
     w.t_final = reinterpret_cast<float*>(b + L.t_final);
     w.n_proc = reinterpret_cast<uint32_t*>(b + L.n_proc);
     w.n_blend = reinterpret_cast<uint32_t*>(b + L.n_blend);
@@ -895,14 +901,51 @@ rgs_status rgs::prepare_frame(const rgs_scene* sc, int32_t W, int32_t H, int32_t
     f.capacity = (uint32_t)cap;
     f.n_gaussians = (uint32_t)sc->n;
     f.ordered = (base == RGS_PATH_PLAIN || p.n_tiles <= ORDER_MAX_TILES) ? 1u : 0u;
+    f.split_bits = 0;                // choose_sort decides
+    f.split_shift = 0;
+    f.lk = LocalKey{};
     fl->plain = PlainSceneDev{sc->plain, sc->n_pad, sc->n};
     fl->fast = FastSceneDev{sc->fast, sc->n_pad, sc->n, sc->plain};
     return RGS_OK;
 }
 
+bool rgs::choose_sort(FrameLaunch& fl, const CamDev& cam) {
+    FrameDev& f = fl.f;
+    const bool wide = f.b_t >= SPLIT_WIDE_BT && (fl.L.key_bytes == 8 || f.capacity >= SPLIT_WIDE_CAPACITY);
+    const int32_t digit = f.b_t < SPLIT_MIN_BT ? 0 : wide ? SPLIT_WIDE_BT : SPLIT_MIN_BT;
+    LocalKey lk{};
+    lk.tile_bits = (uint32_t)(f.b_t - digit);
+    bool split = digit > 0;
+    if (fl.L.key_bytes == 4) {
+        lk.bits = 32 - (uint32_t)digit;
+        f.split_shift = lk.bits;
+    } else {
+        // A visible Gaussian's depth d lies in (z_near, z_far], so its float32
+        // bits lie between theirs (positive floats order as their bits), and
+        // the local key holds them if their distance fits beside the tile bits:
+        // z_far / z_near below about 2^(2^(9 - tile_bits)), at 4K 2^16.  A subnormal
+        // z_near is left to the LSD passes.
+        lk.bits = 32;
+        f.split_shift = 32 + lk.tile_bits;
+        const uint32_t near = depth_key_base(cam), far = __builtin_bit_cast(uint32_t, (float)cam.zf);
+        split = split && near >= 0x00800000u && far >= near && lk.tile_bits < 32 &&
+                ((uint64_t)(far - near) >> (32 - lk.tile_bits)) == 0;
+    }
+    f.split_bits = split ? digit : 0;
+    f.lk = split ? lk : LocalKey{};
+    const uint32_t rows = split ? fl.L.split_rows : fl.L.lsd_rows;
+    fl.w.sort_rows = rows;
+    fl.w.sort_groups = (rows + SORT_GROUP - 1) / SORT_GROUP;
+    return split;
+}
+
+const uint32_t* rgs::sorted_vals(const FrameLaunch& fl) {
+    return !fl.f.split_bits && fl.L.passes % 2 == 1 ? fl.w.vals_b : fl.w.vals_a;
+}
+
 rgs_status rgs::enqueue_frame(hipStream_t st, const FrameLaunch& fl, const FrameParams& prm,
                               const DebugDev* dbg, bool count, FrameStatus* status,
-                              const FrameHooks* hooks, bool* result_in_b) {
+                              const FrameHooks* hooks) {
     auto mark = [&](int k) {
         if (hooks && hooks->mark) hooks->mark(hooks->user, k);
     };
@@ -928,23 +971,22 @@ rgs_status rgs::enqueue_frame(hipStream_t st, const FrameLaunch& fl, const Frame
         rgs_status s = hooks->after_front(hooks->user);
         if (s != RGS_OK) return s;
     }
-    bool in_b = false;
-    if (bucket_sort_applies(fl.f, fl.L.key_bytes)) {
-        launch_sort_bucket(st, fl.f, w, fl.sort_fallback, &in_b);     // the ranges come with it
+    if (fl.f.split_bits) {
+        launch_sort_split(st, fl.f, w, fl.L.key_bytes, fl.sort_fallback, count);     // the ranges come with it
         mark(3);
     } else {
-        launch_sort(st, fl.f, w, fl.L.key_bytes, fl.L.passes, fl.sort_fallback, &in_b);
+        launch_sort(st, w, fl.L.key_bytes, fl.L.passes, fl.sort_fallback);
         mark(3);
-        launch_ranges(st, fl.f, w, fl.L.key_bytes, in_b);
+        launch_ranges(st, fl.f, w, fl.L.key_bytes, fl.L.passes % 2 == 1);
     }
     launch_tile_order(st, fl.f, w);
     mark(4);
-    if (fl.path == RGS_PATH_PLAIN && (fl.opts & OPT_HW_EXP2)) launch_raster_train(st, fl.f, w, in_b, count);
-    else if (fl.path == RGS_PATH_PLAIN) launch_raster_plain(st, fl.f, w, in_b, count);
-    else launch_raster_fast(st, fl.f, w, in_b, count, fl.opts);
+    const uint32_t* vals = sorted_vals(fl);
+    if (fl.path == RGS_PATH_PLAIN && (fl.opts & OPT_HW_EXP2)) launch_raster_train(st, fl.f, w, vals, count);
+    else if (fl.path == RGS_PATH_PLAIN) launch_raster_plain(st, fl.f, w, vals, count);
+    else launch_raster_fast(st, fl.f, w, vals, count, fl.opts);
     mark(5);
     if (status) launch_export_status(st, w, status);
-    if (result_in_b) *result_in_b = in_b;
     HIP_TRY(hipGetLastError());
     return RGS_OK;
 }
@@ -1027,10 +1069,9 @@ static rgs_status render_impl(rgs_ctx* ctx, const rgs_scene* sc, const rgs_camer
         if (s != RGS_OK) return s;
     }
     FrameHooks hooks{hook_mark, hook_after_front, &rh};
-    bool in_b = false;
     const FrameParams prm = frame_params(cam, out, sc, W, H);
-    s = enqueue_frame(st, fl, prm, dbg ? &dd : nullptr, dbg != nullptr, nullptr, (rh.fe || dbg) ? &hooks : nullptr,
-                      &in_b);
+    choose_sort(fl, prm.cam);
+    s = enqueue_frame(st, fl, prm, dbg ? &dd : nullptr, dbg != nullptr, nullptr, (rh.fe || dbg) ? &hooks : nullptr);
     if (s != RGS_OK) return s;
     s = note_frame(ctx, fl, ws, ws_bytes, sc, prm, W, H, path);
     if (s != RGS_OK) return s;
@@ -1038,8 +1079,9 @@ static rgs_status render_impl(rgs_ctx* ctx, const rgs_scene* sc, const rgs_camer
     if (dbg) {
         const WsDev& w = fl.w;
         const uint64_t n_entries = rh.n_entries;
+        const bool in_b = fl.f.split_bits ? fl.L.key_bytes == 8 : fl.L.passes % 2 == 1;
         const void* ks = in_b ? w.keys_b : w.keys_a;
-        const uint32_t* vs = in_b ? w.vals_b : w.vals_a;
+        const uint32_t* vs = sorted_vals(fl);
         if (dbg->keys_sorted && n_entries) {
             if (fl.L.key_bytes == 8)
                 HIP_TRY(hipMemcpyAsync(dbg->keys_sorted, ks, n_entries * 8, hipMemcpyDeviceToDevice, st));
@@ -1211,14 +1253,16 @@ extern "C" rgs_status rgs_render_backward(rgs_ctx* ctx, const rgs_scene* scene, 
     }
     if (path_word != (uint32_t)RGS_PATH_PLAIN && path_word != (uint32_t)(RGS_PATH_PLAIN | RGS_HW_EXP2))
         return fail(RGS_E_INVALID, "the workspace does not hold a plain render of this size");
-    const bool in_b = (fl.L.passes % 2) == 1;
+    const CamDev cd = cam_dev(cam);
+    choose_sort(fl, cd);             // as the frame was sorted
+    const uint32_t* vals = sorted_vals(fl);
     float4* partial = static_cast<float4*>(grads->scratch);
     const bool train = (path_word & RGS_HW_EXP2) != 0;
     const FrameKey key{scene->tag, hash};
-    if (train) launch_raster_backward_train(ctx->stream, fl.f, fl.w, in_b, dL_dimg, partial, key);
-    else launch_raster_backward(ctx->stream, fl.f, fl.w, in_b, dL_dimg, partial, key);
+    if (train) launch_raster_backward_train(ctx->stream, fl.f, fl.w, vals, dL_dimg, partial, key);
+    else launch_raster_backward(ctx->stream, fl.f, fl.w, vals, dL_dimg, partial, key);
     GradOut go{grads->d_means, grads->d_scales, grads->d_quats, grads->d_opacity, grads->d_sh, grads->d_screen};
-    launch_grad_gaussian(ctx->stream, fl.plain, cam_dev(cam), fl.w, partial, go, train, key);
+    launch_grad_gaussian(ctx->stream, fl.plain, cd, fl.w, partial, go, train, key);
     HIP_TRY(hipGetLastError());
     return ok();
 }

@@ -59,11 +59,18 @@ struct FrameHooks {
     void* user;
 };
 
-// Enqueues reset, front end, sort, ranges and raster of one frame on st.  With
-// status set, a last kernel copies the header's outcome to that host-visible
-// address.  *result_in_b tells which key/value buffer holds the sorted result.
+// How a frame of fl seen by cam is sorted, set in fl.f and fl.w: by the split sort
+// (at least 2^SPLIT_MIN_BT tiles, and what its buckets sort fits 32 bits; for
+// 64-bit keys that depends on the camera's depth interval) or by the LSD
+// passes.  Returns whether the split sort applies.
+bool choose_sort(FrameLaunch& fl, const CamDev& cam);
+// The sorted values of such a frame.
+const uint32_t* sorted_vals(const FrameLaunch& fl);
+
+// Enqueues reset, front end, sort, ranges and raster of one frame on st
+// (choose_sort has been called with its camera).  With status set, a last
+// kernel copies the header's outcome to that host-visible address.
 rgs_status enqueue_frame(hipStream_t st, const FrameLaunch& fl, const FrameParams& prm,
-                         const DebugDev* dbg, bool count, FrameStatus* status, const FrameHooks* hooks,
-                         bool* result_in_b);
+                         const DebugDev* dbg, bool count, FrameStatus* status, const FrameHooks* hooks);
 
 }  // namespace rgs

@@ -72,6 +72,21 @@ struct SortTile {
 inline uint32_t sort_tile_size(uint32_t key_bytes) {
     return key_bytes == 8 ? (uint32_t)SortTile<uint64_t>::SIZE : (uint32_t)SortTile<uint32_t>::SIZE;
 }
+// The split pass (frames of at least 2^SPLIT_MIN_BT tiles): radix tiles of 9216
+// keys, ranked by the tile index's top 10 bits where it has them, else 8.  1024
+// buckets spread the 2.2M entries of a 1M / 1080p frame over four times the
+// workgroups that 256 do, and its busiest bucket (about twice the average) is one
+// run in LDS: at 256 buckets it has up to 16300 entries, at or past what LDS
+// holds (sort of a 20-degree orbit frame 100 us, with 1024 buckets 56 us).  A
+// frame of few entries takes 8 bits: the 1024-digit rows then cost more than
+// the buckets save (32-bit keys only; what is left of a 64-bit key is to fit 32
+// bits).
+constexpr int SPLIT_THREADS = 1024;
+constexpr int SPLIT_ITEMS = 9;
+constexpr uint32_t SPLIT_SIZE = SPLIT_THREADS * SPLIT_ITEMS;
+constexpr int32_t SPLIT_MIN_BT = 8, SPLIT_WIDE_BT = 10;
+constexpr uint32_t SPLIT_DIGITS_MAX = 1024;
+constexpr uint32_t SPLIT_WIDE_CAPACITY = 1u << 18;
 // Radix tiles per look-back group: the last tile of each group publishes the
 // group's digit counts, so a tile reads at most SORT_GROUP - 1 tile states plus
 // one state per earlier group.  32 balances the two (1M / 1080p fast sort:
@@ -131,6 +146,12 @@ struct FrameParams {
 };
 static_assert(sizeof(FrameParams) <= 256, "frame parameters fit one 256-byte slot");
 
+// What the split sort leaves to sort inside a bucket: tile_bits tile bits, then
+// the depth, bits in all.
+struct LocalKey {
+    uint32_t bits, tile_bits;
+};
+
 struct FrameDev {
     int32_t width, height;
     int32_t tiles_x, tiles_y, n_tiles;
@@ -139,6 +160,9 @@ struct FrameDev {
     uint32_t capacity;
     uint32_t n_gaussians;
     uint32_t ordered;         // 1: rasterizer workgroup b takes tile ws.order[b], else tile b
+    int32_t split_bits;       // the split sort's digit width, 0: the frame takes the LSD passes
+    uint32_t split_shift;     // ... and its place in the key
+    LocalKey lk;
 };
 
 // Frames whose rasterizers take their tiles longest list first (ws.order):
@@ -195,11 +219,12 @@ struct WsLayout {
     uint64_t order;
     uint64_t records, counts, rects, depths, offsets, masks;
     uint64_t keys_a, keys_b, vals_a, vals_b;
-    uint64_t hist, sort_state;
+    uint64_t hist, sort_state, bases;
     uint64_t t_final, n_proc, n_blend;
     uint64_t total;
     uint64_t capacity;
-    uint32_t key_bytes, passes, fe_blocks, sort_blocks_max;   // sort_blocks_max: radix tiles at capacity
+    uint32_t key_bytes, passes, fe_blocks;
+    uint32_t lsd_rows, split_rows;   // radix tiles at capacity, of the LSD passes and of the split pass
     uint32_t fe_per;          // Gaussians per front-end / duplication workgroup (<= FE_TILE)
 };
 
@@ -222,8 +247,10 @@ struct WsDev {
     uint32_t* vals_a;
     uint32_t* vals_b;
     uint32_t* hist;           // [HIST_COPIES][MAX_PASSES][RADIX] digit counts of every radix pass
-    uint32_t* sort_state;     // 2 x [sort_rows + sort_groups][RADIX] look-back words, one set per
-                              // pass parity: ready flag (bit 31) | digit count
+    uint32_t* sort_state;     // look-back words: ready flag (bit 31) | digit count.  LSD passes: 2 x
+                              // [sort_rows + sort_groups][RADIX], one set per pass parity; split pass:
+                              // one set of rows of its digits
+    uint32_t* bases;          // split pass: first entry of each bucket, and the entry count
     uint32_t sort_rows;       // radix tiles at capacity
     uint32_t sort_groups;     // ceil(sort_rows / SORT_GROUP)
     float* t_final;           // [H][W]
@@ -401,6 +428,11 @@ __host__ __device__ inline uint32_t quantize_depth(double d, double zn, double z
     return (uint32_t)q;
 }
 
+// Local keys hold a float32 depth as its bits above those of z_near.
+__host__ __device__ inline uint32_t depth_key_base(const CamDev& cam) {
+    return __builtin_bit_cast(uint32_t, (float)cam.zn);
+}
+
 // ---------------------------------------------------------------------------
 // Wave64 helpers.
 
@@ -446,13 +478,13 @@ __device__ inline void st_state(uint32_t* p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Look-back word sets of the sort: set 0 serves even passes, set 1 odd passes.
-// Each set holds sort_rows tile rows, then sort_groups group rows, of RADIX
-// words.
-__device__ inline uint32_t* sort_state_tiles(const WsDev& ws, uint32_t set) {
+// Look-back word sets of the LSD passes: set 0 serves even passes, set 1 odd
+// passes.  Each set holds sort_rows tile rows, then sort_groups group rows, of
+// RADIX words.
+__host__ __device__ inline uint32_t* sort_state_tiles(const WsDev& ws, uint32_t set) {
     return ws.sort_state + (uint64_t)set * ((uint64_t)ws.sort_rows + ws.sort_groups) * RADIX;
 }
-__device__ inline uint32_t* sort_state_groups(const WsDev& ws, uint32_t set) {
+__host__ __device__ inline uint32_t* sort_state_groups(const WsDev& ws, uint32_t set) {
     return sort_state_tiles(ws, set) + (uint64_t)ws.sort_rows * RADIX;
 }
 
@@ -521,21 +553,20 @@ void launch_frontend_fast(hipStream_t s, const FastSceneDev& sc, const FrameDev&
                           uint32_t fe_blocks, uint32_t fe_per, const DebugDev* dbg, uint32_t opts);
 void launch_preprocess_fast(hipStream_t s, const FastSceneDev& sc, const FrameDev& f, const WsDev& ws,
                             const DebugDev* dbg, uint32_t opts);
-void launch_sort(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32_t key_bytes, uint32_t passes,
-                 bool force_fallback, bool* result_in_b);
+// The LSD passes end in keys_a / vals_a, or the b arrays after an odd number.
+void launch_sort(hipStream_t s, const WsDev& ws, uint32_t key_bytes, uint32_t passes, bool force_fallback);
 void launch_ranges(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32_t key_bytes,
                    bool result_in_b);
+// The split sort (f.split_bits): sorted values end in vals_a, and the tile
+// ranges are written too (no launch_ranges); with want_keys also the sorted
+// keys, 32-bit ones in keys_a and 64-bit ones in keys_b.
+void launch_sort_split(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32_t key_bytes, bool force_fallback,
+                       bool want_keys);
 // The rasterizers' schedule: ws.order from the tile ranges.
 void launch_tile_order(hipStream_t s, const FrameDev& f, const WsDev& ws);
-// The fast path's bucket sort (frames of 8 .. BUCKET_MAX_BT tile bits, 32-bit
-// keys): sorted keys and values end in keys_a / vals_a, and the tile ranges
-// are written too (no launch_ranges).
-constexpr int32_t BUCKET_MAX_BT = 14;
-bool bucket_sort_applies(const FrameDev& f, uint32_t key_bytes);
-void launch_sort_bucket(hipStream_t s, const FrameDev& f, const WsDev& ws, bool force, bool* result_in_b);
-void launch_raster_plain(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b, bool count);
-void launch_raster_train(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b, bool count);
-void launch_raster_fast(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b, bool count,
+void launch_raster_plain(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count);
+void launch_raster_train(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count);
+void launch_raster_fast(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count,
                         uint32_t opts);
 void launch_widen_keys(hipStream_t s, const uint32_t* in, uint64_t* out, uint64_t n);
 void launch_probe_valu(hipStream_t s, float* out, uint32_t blocks, uint32_t iters);
@@ -563,9 +594,9 @@ void launch_update_plain(hipStream_t s, float* planes, uint64_t n_pad, int64_t n
 struct FrameKey {
     uint64_t scene_tag, cam_hash;
 };
-void launch_raster_backward(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b,
+void launch_raster_backward(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals,
                             const float* dimg, float4* partial, FrameKey key);
-void launch_raster_backward_train(hipStream_t s, const FrameDev& f, const WsDev& ws, bool result_in_b,
+void launch_raster_backward_train(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals,
                                   const float* dimg, float4* partial, FrameKey key);
 // lno_opacity: the partials' opacity slot holds dL/d(ln o) (the training
 // variant's), converted to dL/do here.

@@ -47,6 +47,8 @@ struct Workspace {
     hipGraphExec_t exec = nullptr;
     hipGraphNode_t reset_node = nullptr;
     hipKernelNodeParams reset_params{};
+    bool graph_split = false;                // the captured frame's sort (choose_sort)
+    bool replayed = false;                   // the last frame was a graph replay
     bool busy = false;
     uint64_t last_used = 0;
 };
@@ -121,7 +123,8 @@ void release(rgs_server* s, Workspace* w) {
 // that its baked arguments name real buffers.
 rgs_status capture(rgs_server* s, Workspace* w, const FrameParams& first, hipStream_t st) {
     HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-    rgs_status es = enqueue_frame(st, w->fl, first, nullptr, false, w->status, nullptr, nullptr);
+    w->graph_split = choose_sort(w->fl, first.cam);
+    rgs_status es = enqueue_frame(st, w->fl, first, nullptr, false, w->status, nullptr);
     hipGraph_t g = nullptr;
     hipError_t ce = hipStreamEndCapture(st, &g);
     if (es != RGS_OK) {
@@ -217,7 +220,10 @@ rgs_status acquire(rgs_server* s, const ClassKey& k, const FrameParams& first, h
 rgs_status launch(rgs_server* s, Slot& slot, Workspace* w, const rgs_request& r) {
     w->status->done = 0;
     const FrameParams prm = frame_params(&r.camera, r.out_chw, r.scene, r.width, r.height);
-    if (w->exec) {
+    // the graph's sort is the captured camera's: one that sorts otherwise (64-bit
+    // keys with a depth interval that does not fit) is launched kernel by kernel
+    w->replayed = choose_sort(w->fl, prm.cam) == w->graph_split && w->exec;
+    if (w->replayed) {
         ResetArgs ra = reset_args(w->fl.w, w->fl.L.zero_end, w->fl.f, w->fl.path_word, prm);
         void* args[] = {&ra};
         hipKernelNodeParams np = w->reset_params;
@@ -226,7 +232,7 @@ rgs_status launch(rgs_server* s, Slot& slot, Workspace* w, const rgs_request& r)
         HIP_TRY(hipGraphExecKernelNodeSetParams(w->exec, w->reset_node, &np));
         HIP_TRY(hipGraphLaunch(w->exec, slot.stream));
     } else {
-        rgs_status e = enqueue_frame(slot.stream, w->fl, prm, nullptr, false, w->status, nullptr, nullptr);
+        rgs_status e = enqueue_frame(slot.stream, w->fl, prm, nullptr, false, w->status, nullptr);
         if (e != RGS_OK) return e;
     }
     HIP_TRY(hipEventRecord(slot.done, slot.stream));
@@ -421,8 +427,8 @@ extern "C" rgs_status rgs_serve(rgs_server* s, const rgs_request* reqs, int64_t 
             if (!w) break;                 // wait for memory
             resp[i].t_admit = seconds_since(t0);
             resp[i].slot = slot_id;
-            resp[i].graph = w->exec != nullptr;
             e = launch(s, *free_slot, w, r);
+            resp[i].graph = w->replayed;
             if (e != RGS_OK) {
                 fatal = e;
                 break;
