@@ -2,20 +2,20 @@
 // image definition with its discrete decisions held fixed), and the device
 // update of plain attributes that a training step needs.
 //
-// raster_backward: one wave per 16x16 tile, four pixels per lane, the tile's
-// sorted list walked back to front in batches staged in LDS.  A pixel
-// starts after its last blended pair (the forward pass left its final T, the
-// number of pairs it visited and whether it stopped); T before each blended
-// pair is recovered as T_after / (1 - alpha), and the colour accumulated behind
-// the pair plus the background's share, S' = S + T_final bg, is carried along
-// (it starts at T_final bg), so that
-//   dC/dc_j = alpha_j T_j,   dC/dalpha_j = c_j T_j - S'_j / (1 - alpha_j).
-// The nine image-space derivatives of a pair (u, v, A, B, C, o, r, g, b) are
-// summed over a lane's four pixels, then over the wave with DPP adds, and each
-// entry receives one 48-byte partial at its position in emission order: no
-// atomics.  Ordered allocation emitted a Gaussian's entries contiguously,
-// one per tile of its rectangle in row-major order, from the offset the
-// duplication kernel recorded, so that position is known from the tile.
+// raster_backward: two waves per 16x16 tile, the tile's sorted list walked back
+// to front in batches staged in LDS.  A pixel starts after its last blended
+// pair (the forward pass left its final T, the number of pairs it visited and
+// whether it stopped); T before each blended pair is recovered as T_after /
+// (1 - alpha).  With S' the colour accumulated behind the pair plus the
+// background's share (it starts at T_final bg),
+//   dC/dc_j = alpha_j T_j,   dC/dalpha_j = c_j T_j - S'_j / (1 - alpha_j),
+// and of S' only its product with dL/dC is carried along.  The nine image-space
+// derivatives of a pair (u, v, A, B, C, o, r, g, b) are summed over 4x4-pixel
+// regions, then over the tile, and each entry receives one 48-byte partial at
+// its position in emission order: no atomics.  Ordered allocation emitted a
+// Gaussian's entries contiguously, one per tile of its rectangle in row-major
+// order, from the offset the duplication kernel recorded, so that position is
+// known from the tile.
 //
 // grad_gaussian: one thread per Gaussian sums its contiguous partials and
 // applies the chain rule through the EWA projection and the SH colour in
@@ -89,26 +89,40 @@ void launch_update_plain(hipStream_t s, float* planes, uint64_t n_pad, int64_t n
 }
 
 // ---------------------------------------------------------------------------
-// Row sums of N values at once: after two quad permutations and two row
-// shifts (each a DPP-modified add) lane 16 r + 15 holds the sum over row r of
-// the wave.  The N chains are independent, so the DPP instructions of one
-// value are spaced by those of the others and need no wait states.
-
-template <int CTRL>
-__device__ inline float dpp_moved(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-
-template <int N>
-__device__ inline void row_sums(float (&g)[N]) {
-#pragma unroll
-    for (int c = 0; c < N; ++c) g[c] += dpp_moved<0xb1>(g[c]);     // quad_perm [1,0,3,2]
-#pragma unroll
-    for (int c = 0; c < N; ++c) g[c] += dpp_moved<0x4e>(g[c]);     // quad_perm [2,3,0,1]
-#pragma unroll
-    for (int c = 0; c < N; ++c) g[c] += dpp_moved<0x114>(g[c]);    // row_shr:4
-#pragma unroll
-    for (int c = 0; c < N; ++c) g[c] += dpp_moved<0x118>(g[c]);    // row_shr:8
+// Sums over the eight lanes of each group of the wave, nine values at once:
+// lane 8 q + i (i < 4) receives the sums of g[0..3] of group q in o[0..3], lane
+// 8 q + 4 + i those of g[4..7], and every lane that of g[8] in o[4].  A mirror
+// within the group adds lane i to lane 7 - i; the masked second half of it
+// (bank_mask 0xa: lanes 4..7 of each group) puts g[4..7] into the same registers,
+// so the two additions within the quad are shared: 19 instructions for 27
+// additions.  One block, since the compiler does not know DPP operands inside
+// it: the leading s_nop covers the wait states of a DPP read after the last
+// write of g or of EXEC, and every DPP operand written inside is written at
+// least three instructions before it is read.  EXEC must be full.
+__device__ inline void group_sums(const float (&g)[9], float (&o)[5]) {
+    asm volatile(
+        "s_nop 4\n\t"
+        "v_add_f32_dpp %4, %13, %13 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %6, %6 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %8, %8 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %9, %9 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %1, %10, %10 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %2, %11, %11 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %3, %12, %12 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %3, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %3, %3 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4])
+        : "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "v"(g[4]), "v"(g[5]), "v"(g[6]), "v"(g[7]), "v"(g[8]));
 }
 
 // Position, in emission order, of Gaussian g's entry for tile (tx, ty).
@@ -116,32 +130,6 @@ __device__ inline uint64_t emission_pos(const WsDev& ws, uint32_t g, uint32_t tx
     const uint64_t rc = ws.rects[g];
     const uint32_t x0 = rc & 0xffff, x1 = (rc >> 16) & 0xffff, y0 = (rc >> 32) & 0xffff;
     return (uint64_t)ws.offsets[g] + (uint64_t)(ty - y0) * (x1 - x0 + 1) + (tx - x0);
-}
-
-// One wave per tile; lane l owns the pixels (l % 16, l / 16 + 4 k), k = 0..3,
-// and adds its four pixels' terms before the wave reduction of an entry.
-constexpr int BWD_LANES = 64;
-constexpr int BWD_PIX = 4;
-constexpr int BWD_BATCH = 32;
-constexpr int BWD_ROWS = BWD_LANES / 16;     // DPP rows of the wave
-
-// Row bands k (tile rows 4k .. 4k+3) that can hold a pixel with alpha >= 1/255
-// for a Gaussian at tile-local (u, v) with conic (A, B, C) and opacity o: the
-// ellipse A dx^2 + 2 B dx dy + C dy^2 <= 2 ln(255 o) spans |dy| <= sqrt(tau A / det).
-// The half-height is widened by 1e-3 of itself plus 0.05 pixel, far beyond the
-// float32 rounding of the exponent, so no blended pair falls outside.
-__device__ inline uint32_t band_mask(float v, float A, float B, float C, float o) {
-    const float tau = 2.0f * logf(255.0f * o);
-    if (!(tau > 0.0f)) return 0u;                      // alpha < 1/255 everywhere
-    const float det = A * C - B * B;
-    if (!(det > 0.0f)) return 0xfu;
-    const float hy = sqrtf(tau * A / det) * 1.001f + 0.05f;
-    if (!(hy < 1e30f)) return 0xfu;
-    uint32_t m = 0;
-#pragma unroll
-    for (int k = 0; k < BWD_PIX; ++k)
-        if (v - hy <= (float)(4 * k + 3) && v + hy >= (float)(4 * k)) m |= 1u << k;
-    return m;
 }
 
 // Whether the workspace still holds the frame the caller asked for; if not,
@@ -153,194 +141,40 @@ __device__ inline bool frame_matches(const WsDev& ws, FrameKey key) {
     return false;
 }
 
-__global__ __launch_bounds__(BWD_LANES) void k_raster_backward(FrameDev f, WsDev ws,
-                                                               const uint32_t* __restrict__ vals,
-                                                               const float* __restrict__ dimg,
-                                                               float4* __restrict__ partial, FrameKey key) {
-    if (!frame_matches(ws, key)) return;
-    __shared__ float4 s_a[BWD_BATCH];          // u, v (tile-local), A, B
-    __shared__ float4 s_b[BWD_BATCH];          // C, o, r, g
-    __shared__ float s_c[BWD_BATCH];           // b
-    __shared__ uint32_t s_band[BWD_BATCH];     // row bands the entry can reach
-    __shared__ float4 s_acc4[9 * BWD_ROWS * BWD_BATCH / 4];   // per-row entry sums of the batch
-    float* s_acc = reinterpret_cast<float*>(s_acc4);              // [9][BWD_ROWS][BWD_BATCH]
-    if (blockIdx.x >= (uint32_t)f.n_tiles) return;
-    const uint32_t tile = f.ordered ? ws.order[blockIdx.x] : blockIdx.x;   // the rasterizers' schedule
-    const uint32_t tx = tile % (uint32_t)f.tiles_x, ty = tile / (uint32_t)f.tiles_x;
-    const uint32_t lane = threadIdx.x;
-    const uint32_t lx = lane % TILE, ly0 = lane / TILE;
-    const uint32_t px = tx * TILE + lx;
-    const uint32_t start = ws.ranges[2 * tile], end = ws.ranges[2 * tile + 1];
-    const float ox = (float)(tx * TILE), oy = (float)(ty * TILE);
-    const float x = (float)lx;
-    const uint64_t plane = (uint64_t)f.width * f.height;
-    const float bg0 = ws.params->cam.bg[0], bg1 = ws.params->cam.bg[1], bg2 = ws.params->cam.bg[2];
-
-    float T[BWD_PIX], d[BWD_PIX][3], S[BWD_PIX][3];   // S: colour behind the pair + T_final bg
-    uint32_t last[BWD_PIX];                    // pairs [start, last) may have been blended
-    uint32_t lane_last = start;
-#pragma unroll
-    for (int k = 0; k < BWD_PIX; ++k) {
-        const uint32_t py = ty * TILE + ly0 + 4 * k;
-        T[k] = 1.0f;
-        last[k] = start;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) d[k][c] = 0.0f;
-        if (px < (uint32_t)f.width && py < (uint32_t)f.height) {
-            const uint64_t o = (uint64_t)py * f.width + px;
-            T[k] = ws.t_final[o];
-            const uint32_t word = ws.n_proc[o];
-            last[k] = start + (word & ~N_PROC_STOPPED) - ((word & N_PROC_STOPPED) ? 1u : 0u);
-            d[k][0] = dimg[o];
-            d[k][1] = dimg[plane + o];
-            d[k][2] = dimg[2 * plane + o];
-        }
-        S[k][0] = T[k] * bg0;
-        S[k][1] = T[k] * bg1;
-        S[k][2] = T[k] * bg2;
-        lane_last = max(lane_last, last[k]);
-    }
-    uint32_t wave_last = lane_last;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) wave_last = max(wave_last, (uint32_t)__shfl_xor((int)wave_last, off));
-
-    for (uint32_t b_end = wave_last; b_end > start;) {
-        const uint32_t b0 = b_end - start > (uint32_t)BWD_BATCH ? b_end - BWD_BATCH : start;
-        const uint32_t cnt = b_end - b0;
-        __syncthreads();                         // the previous batch is fully read
-        uint64_t my_pos = 0;
-        if (lane < cnt) {
-            const uint32_t g0 = vals[b0 + lane];
-            const uint32_t g = g0 < f.n_gaussians ? g0 : 0u;
-            const Record rec = ws.records[g];
-            s_a[lane] = make_float4((rec.u_hi - ox) + rec.u_lo, (rec.v_hi - oy) + rec.v_lo, rec.A, rec.B);
-            s_b[lane] = make_float4(rec.C, rec.opa, rec.r, rec.g);
-            s_c[lane] = rec.b;
-            s_band[lane] = band_mask((rec.v_hi - oy) + rec.v_lo, rec.A, rec.B, rec.C, rec.opa);
-            my_pos = emission_pos(ws, g, tx, ty);
-        }
-        for (uint32_t q = lane; q < 9 * BWD_ROWS * BWD_BATCH / 4; q += BWD_LANES)
-            s_acc4[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        __syncthreads();
-        for (int j = (int)cnt - 1; j >= 0; --j) {
-            const uint32_t idx = b0 + (uint32_t)j;
-            if (__ballot(idx < lane_last) == 0) continue;
-            const float4 a = s_a[j];
-            const float4 m = s_b[j];
-            const float cb = s_c[j];
-            const uint32_t band = s_band[j];
-            float g[9];
-#pragma unroll
-            for (int c = 0; c < 9; ++c) g[c] = 0.0f;
-            bool any = false;
-#pragma unroll
-            for (int k = 0; k < BWD_PIX; ++k) {
-                if (((band >> k) & 1u) && idx < last[k]) {
-                    const float dx = x - a.x, dy = (float)(ly0 + 4 * k) - a.y;
-                    const float p = fmaf(-0.5f, fmaf(a.z * dx, dx, m.x * dy * dy), -a.w * dx * dy);
-                    const float e = expf(p);
-                    const float raw = m.y * e;
-                    const float alpha = fminf(ALPHA_MAX, raw);
-                    if (alpha >= ALPHA_MIN) {
-                        any = true;
-                        const float inv = __builtin_amdgcn_rcpf(1.0f - alpha);
-                        const float Tb = T[k] * inv;
-                        const float w = alpha * Tb;
-                        g[6] = fmaf(w, d[k][0], g[6]);
-                        g[7] = fmaf(w, d[k][1], g[7]);
-                        g[8] = fmaf(w, d[k][2], g[8]);
-                        const float dA = d[k][0] * (m.z * Tb - S[k][0] * inv) +
-                                         d[k][1] * (m.w * Tb - S[k][1] * inv) +
-                                         d[k][2] * (cb * Tb - S[k][2] * inv);
-                        S[k][0] = fmaf(m.z, w, S[k][0]);
-                        S[k][1] = fmaf(m.w, w, S[k][1]);
-                        S[k][2] = fmaf(cb, w, S[k][2]);
-                        T[k] = Tb;
-                        const float dRaw = raw <= ALPHA_MAX ? dA : 0.0f;   // a clamped alpha is constant
-                        g[5] = fmaf(dRaw, e, g[5]);
-                        const float dP = dRaw * raw;
-                        g[0] = fmaf(dP, fmaf(a.z, dx, a.w * dy), g[0]);    // dp/du = A dx + B dy
-                        g[1] = fmaf(dP, fmaf(m.x, dy, a.w * dx), g[1]);    // dp/dv = C dy + B dx
-                        g[2] = fmaf(-0.5f * dP, dx * dx, g[2]);
-                        g[3] = fmaf(-dP, dx * dy, g[3]);
-                        g[4] = fmaf(-0.5f * dP, dy * dy, g[4]);
-                    }
-                }
-            }
-            if (__ballot(any) != 0) {
-                row_sums(g);
-                if ((lane & 15) == 15) {
-                    const uint32_t r = lane >> 4;
-#pragma unroll
-                    for (int c = 0; c < 9; ++c) s_acc[(c * BWD_ROWS + r) * BWD_BATCH + j] = g[c];
-                }
-            }
-        }
-        __syncthreads();
-        if (lane < cnt) {
-            float4* dst = partial + 3ull * my_pos;
-            float sum[9];
-#pragma unroll
-            for (int c = 0; c < 9; ++c) {
-                const float* row = s_acc + c * BWD_ROWS * BWD_BATCH + lane;
-                sum[c] = (row[0] + row[BWD_BATCH]) + (row[2 * BWD_BATCH] + row[3 * BWD_BATCH]);
-            }
-            dst[0] = make_float4(sum[0], sum[1], sum[2], sum[3]);
-            dst[1] = make_float4(sum[4], sum[5], sum[6], sum[7]);
-            dst[2] = make_float4(sum[8], 0.0f, 0.0f, 0.0f);
-        }
-        b_end = b0;
-    }
-    // entries no pixel of the tile reached
-    for (uint32_t idx = wave_last + lane; idx < end; idx += BWD_LANES) {
-        const uint32_t g = vals[idx];
-        float4* dst = partial + 3ull * emission_pos(ws, g < f.n_gaussians ? g : 0u, tx, ty);
-        dst[0] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        dst[1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        dst[2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
-}
-
-void launch_raster_backward(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals,
-                            const float* dimg, float4* partial, FrameKey key) {
-    hipLaunchKernelGGL(k_raster_backward, dim3((uint32_t)f.n_tiles), dim3(BWD_LANES), 0, s, f, ws, vals, dimg,
-                       partial, key);
-}
-
-// ---------------------------------------------------------------------------
-// The training variant's backward pass.  Its forward pass is the dual-pixel
-// rasterizer with culled lists over the plain records (k_raster with
-// EXP_HW2 and TRAIN).  Here the tile's list is replayed back to front in the
-// forward's layout: two waves, wave w owning rows 8w .. 8w+7, each lane the
-// dual pixel (x, y), (x, y+1).  Each batch is staged, folded and culled per
-// wave by the forward's own functions (rgs_fold.h), so every exponent, alpha
-// and skip decision is the forward's, bit for bit, and T before a pair is
-// recovered from the forward's final T as in the plain backward.  A pair's
-// exponent P = ln o + p in natural units gives dalpha/dP = alpha, and
-// dP/d(ln o) = 1: the opacity slot of the partials carries dL/d(ln o), which
-// the per-Gaussian pass divides by o.  Per entry, each lane's nine terms (its
-// two pixels added) are summed over each half-wave with DPP row operations and
-// the two half-wave sums kept in LDS; at the end of a batch each entry adds its
-// four half-wave sums and writes them to its emission position.  Measured at
-// 1M / 1080p (the training step's backward call): 1.02 ms with a full-wave DPP
-// reduction per entry and per-channel colour sums, 0.88 ms with the sums below;
-// four row sums kept instead of two, or batches of 32, made no difference;
-// reading the next entry's coefficients one step ahead and keeping the
-// half-wave broadcast out of the store's lane mask took it to 0.77 ms.
-
-constexpr int TB_THREADS = 128;
-constexpr int TB_BATCH = 64;
-
 // Adds one blended pair's terms at one pixel to g[9] and steps the pixel's
-// state back over the pair.  dx, dy: pixel minus mean; col: the pair's colour;
-// d: dL/dC at the pixel; DS = d . S, S the colour behind the pair plus the
-// background's share, so that dL/dalpha = Tb (d . col) - DS / (1 - alpha).
-// The conic terms are left as moments of dL/dP: g[0] += dP dx, g[1] += dP dy,
-// g[2] += dP dx^2, g[3] += dP dx dy, g[4] += dP dy^2; the wave's sums of them
-// are turned into dL/d(u, v, A, B, C) once per entry (the conic is constant
-// over the entry's pixels).
-__device__ inline void pair_adjoint(float P, float dx, float dy, const float4& col, const float (&d)[3], float& T,
-                                    float& DS, float (&g)[9]) {
+// state back over the pair.  dx, dy: pixel minus mean; a = (u, v, A, B), m = (C,
+// o, r, g), cb: b; d: dL/dC at the pixel; DS = d . S, S the colour behind the
+// pair plus the background's share, so that dL/dalpha = Tb (d . col) -
+// DS / (1 - alpha); raw = o e.
+__device__ inline void pair_adjoint_plain(float e, float raw, float dx, float dy, const float4& a, const float4& m,
+                                          float cb, const float (&d)[3], float& T, float& DS, float (&g)[9]) {
+    const float alpha = fminf(ALPHA_MAX, raw);
+    const float inv = __builtin_amdgcn_rcpf(1.0f - alpha);
+    const float Tb = T * inv;
+    const float w = alpha * Tb;
+    g[6] = fmaf(w, d[0], g[6]);
+    g[7] = fmaf(w, d[1], g[7]);
+    g[8] = fmaf(w, d[2], g[8]);
+    const float dcol = fmaf(d[0], m.z, fmaf(d[1], m.w, d[2] * cb));
+    const float dA = fmaf(Tb, dcol, -(DS * inv));
+    DS = fmaf(w, dcol, DS);
+    T = Tb;
+    const float dRaw = raw <= ALPHA_MAX ? dA : 0.0f;   // a clamped alpha is constant
+    g[5] = fmaf(dRaw, e, g[5]);
+    const float dP = dRaw * raw;
+    g[0] = fmaf(dP, fmaf(a.z, dx, a.w * dy), g[0]);    // dp/du = A dx + B dy
+    g[1] = fmaf(dP, fmaf(m.x, dy, a.w * dx), g[1]);    // dp/dv = C dy + B dx
+    g[2] = fmaf(-0.5f * dP, dx * dx, g[2]);
+    g[3] = fmaf(-dP, dx * dy, g[3]);
+    g[4] = fmaf(-0.5f * dP, dy * dy, g[4]);
+}
+
+// The same for the training variant, P the pair's exponent in log2 units.  The conic
+// terms are left as moments of dL/dP: g[0] += dP dx, g[1] += dP dy, g[2] += dP
+// dx^2, g[3] += dP dx dy, g[4] += dP dy^2; an entry's sums of them are turned
+// into dL/d(u, v, A, B, C) once (the conic is constant over its pixels).
+__device__ inline void pair_adjoint(float P, float dx, float dy, float cr, float cg, float cb, const float (&d)[3],
+                                    float& T, float& DS, float (&g)[9]) {
     const float raw = __builtin_amdgcn_exp2f(P);
     const float alpha = fminf(ALPHA_MAX, raw);
     const float inv = __builtin_amdgcn_rcpf(1.0f - alpha);
@@ -349,7 +183,7 @@ __device__ inline void pair_adjoint(float P, float dx, float dy, const float4& c
     g[6] = fmaf(w, d[0], g[6]);
     g[7] = fmaf(w, d[1], g[7]);
     g[8] = fmaf(w, d[2], g[8]);
-    const float dcol = fmaf(d[0], col.x, fmaf(d[1], col.y, d[2] * col.z));
+    const float dcol = fmaf(d[0], cr, fmaf(d[1], cg, d[2] * cb));
     const float dA = fmaf(Tb, dcol, -(DS * inv));
     DS = fmaf(w, dcol, DS);
     T = Tb;
@@ -363,39 +197,74 @@ __device__ inline void pair_adjoint(float P, float dx, float dy, const float4& c
     g[4] = fmaf(ey, dy, g[4]);
 }
 
-__global__ __launch_bounds__(TB_THREADS) void k_raster_backward_train(FrameDev f, WsDev ws,
-                                                                      const uint32_t* __restrict__ vals,
-                                                                      const float* __restrict__ dimg,
-                                                                      float4* __restrict__ partial, FrameKey key) {
-    // per-wave lists of the batch's folded entries, in depth order
-    __shared__ float4 s_a[2][TB_BATCH];      // C1, C2, C3, C4 (log2 units)
-    __shared__ float4 s_b[2][TB_BATCH];      // C5, C6, entry index, slot in the batch (bits)
-    __shared__ float4 s_m[2][TB_BATCH];      // r, g, b, v (tile-centre)
-    __shared__ float4 s_q[2][TB_BATCH];      // A, B, C, u (tile-centre)
-    __shared__ uint32_t s_cnt[2];
-    __shared__ uint32_t s_wlast[2];
-    // [wave][term][half][slot]: an entry's sums over each 32-lane half of a wave
-    __shared__ float4 s_acc4[2 * 9 * 2 * TB_BATCH / 4];
-    float (*s_acc)[9][2][TB_BATCH] = reinterpret_cast<float (*)[9][2][TB_BATCH]>(s_acc4);
+// The backward pass in the forward pass's layout: wave w owns the half-tile of
+// rows 8 w .. 8 w + 7, the eight lanes of a group own a 4x4 region, a dual pixel
+// each, and walk the region's own list, so that up to eight entries are
+// evaluated at once and about 2.3 pixels per blended one (a wave per tile with
+// four pixels per lane and skipped bands of four rows: about 3.5; half-tile
+// lists: 4.8).  Staging, folding and culling are the forward's (rgs_fold.h), and
+// every exponent, alpha and skip decision is the forward's, bit for bit.
+//
+// An entry's nine sums over a region take 19 DPP additions for eight regions at
+// a time and go to a row of LDS of their own; the staging lane of an entry
+// adds its rows and writes the partial, so the result does not depend on the
+// order in which waves run.  The rows of a batch are those of its lists, one
+// list after the other, so no row is written for a region that an entry does
+// not reach.  A batch whose rows do not fit BWD_ROWS keeps the entries that do
+// (304 rows are a batch of the usual four to five regions an entry, and leave
+// LDS for ten workgroups a CU).  The two waves take turns: one adds the rows of a
+// batch while the other stages the next.
+//
+// Bound by VALU issue, about 0.31 instructions per SIMD and cycle with four
+// transcendentals in each 150, and at a tile a CU or two by the latency of the
+// entry loop; two entries in flight (BWD_UNROLL) shorten it, four take
+// registers that cost a wave per SIMD.  Measured, plain at 1M / 1080p, 401x267
+// with 20K Gaussians, and the training variant at 1M / 1080p (us): 689, 349, 520
+// with the layouts named above; 379, 129, 301 with lists of regions in
+// two passes over the ballots; 318, 112, 267 as it stands (one entry at a
+// time: 335, 119, 265; four: 348, 108, 291; the next batch's records loaded
+// ahead: no change).
+constexpr int BWD_THREADS = 128;           // wave w: the half-tile of rows 8 w .. 8 w + 7
+constexpr int BWD_BATCH = 64;              // entries staged at once, one per lane of the staging wave
+constexpr int BWD_UNROLL = 2;              // entries of a list taken at once; divides 4
+constexpr int BWD_REGIONS = 16;            // 4x4 pixels each
+constexpr uint32_t BWD_ROWS = 304;         // (entry, region) sums of a batch; at least 16, one entry's
+
+template <bool TRAIN>
+__global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, WsDev ws,
+                                                                 const uint32_t* __restrict__ vals,
+                                                                 const float* __restrict__ dimg,
+                                                                 float4* __restrict__ partial, FrameKey key) {
+    // the batch's entries: (u, v, A, B), (C, o, r, g), (b); TRAIN: (C1, C2, C3, C4), (C5, C6, r, g), (b, u, v)
+    __shared__ float4 s_a[BWD_BATCH], s_b[BWD_BATCH], s_c[BWD_BATCH];
+    // per region, the slots of the entries that reach it, back to front, and the rows of their sums
+    __shared__ uint32_t s_list4[BWD_REGIONS][BWD_BATCH / 4];
+    __shared__ uint32_t s_count[BWD_REGIONS], s_base[2][BWD_REGIONS];     // (s_base: by staging wave)
+    __shared__ uint32_t s_last[BWD_REGIONS];     // end of the entries that a pixel of the region may have blended
+    __shared__ uint32_t s_kept, s_longest[2];
+    __shared__ float4 s_row[BWD_ROWS][2];        // sums of one entry over one region
+    __shared__ float s_row8[BWD_ROWS];
     if (!frame_matches(ws, key)) return;
     if (blockIdx.x >= (uint32_t)f.n_tiles) return;
     const uint32_t tile = f.ordered ? ws.order[blockIdx.x] : blockIdx.x;   // the rasterizers' schedule
     const uint32_t tx = tile % (uint32_t)f.tiles_x, ty = tile / (uint32_t)f.tiles_x;
     const uint32_t tid = threadIdx.x;
-    const uint32_t wave = tid / 64, lane = tid % 64;
-    const uint32_t lx = tid % TILE, ly = 2 * (tid / TILE);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
+    const uint32_t region = tid / 8;
+    const uint32_t lx = (region % 4) * 4 + lane % 4;
+    const uint32_t ly = (region / 4) * 4 + (lane / 4 % 2) * 2;
     const uint32_t px = tx * TILE + lx, py = ty * TILE + ly;
     const uint32_t start = ws.ranges[2 * tile], end = ws.ranges[2 * tile + 1];
-    // tile-centre coordinates, as the forward pass
-    const float ox = (float)(tx * TILE) + 7.5f, oy = (float)(ty * TILE) + 7.5f;
-    const float x = (float)lx - 7.5f, y = (float)ly - 7.5f;
+    // as the forward pass: tile-centre coordinates, or relative to the tile's corner
+    constexpr float CENTRE = TRAIN ? 7.5f : 0.0f;
+    const float ox = (float)(tx * TILE) + CENTRE, oy = (float)(ty * TILE) + CENTRE;
+    const float x = (float)lx - CENTRE, y = (float)ly - CENTRE, y1 = y + 1.0f;
     const float x2 = x * x, xy = x * y, y2 = y * y, y21 = fmaf(2.0f, y, 1.0f);
-    const float y1 = y + 1.0f;
     const uint64_t plane = (uint64_t)f.width * f.height;
     const float bg0 = ws.params->cam.bg[0], bg1 = ws.params->cam.bg[1], bg2 = ws.params->cam.bg[2];
 
-    // per pixel: T after the pairs behind, dL/dC, DS = dL/dC . (colour behind +
-    // T_final bg), and the end of the pairs [start, last) that may have been blended
+    // per pixel: T after the pairs behind, dL/dC, DS = dL/dC . (colour behind + T_final
+    // bg), and the end of the pairs [start, last) that may have been blended
     float T[2], d[2][3], DS[2];
     uint32_t last[2];
 #pragma unroll
@@ -414,129 +283,194 @@ __global__ __launch_bounds__(TB_THREADS) void k_raster_backward_train(FrameDev f
         }
         DS[k] = T[k] * fmaf(d[k][0], bg0, fmaf(d[k][1], bg1, d[k][2] * bg2));
     }
-    uint32_t wlast = max(last[0], last[1]);
+    uint32_t rlast = max(last[0], last[1]);
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) wlast = max(wlast, (uint32_t)__shfl_xor((int)wlast, off));
-    if (lane == 0) s_wlast[wave] = wlast;
+    for (int off = 1; off < 8; off <<= 1) rlast = max(rlast, (uint32_t)__shfl_xor((int)rlast, off));
+    if (lane % 8 == 0) s_last[region] = rlast;
     __syncthreads();
-    const uint32_t tile_last = max(s_wlast[0], s_wlast[1]);
+    uint32_t tile_last = start;
+#pragma unroll
+    for (int r = 0; r < BWD_REGIONS; ++r) tile_last = max(tile_last, s_last[r]);
+    tile_last = __builtin_amdgcn_readfirstlane(tile_last);
 
-    for (uint32_t b_end = tile_last; b_end > start;) {
-        const uint32_t b0 = b_end - start > (uint32_t)TB_BATCH ? b_end - TB_BATCH : start;
-        const uint32_t cnt = b_end - b0;
-        __syncthreads();                         // the previous batch is fully read
-        for (uint32_t q = tid; q < 2 * 9 * 2 * TB_BATCH / 4; q += TB_THREADS) s_acc4[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        // ---- stage (wave 0, one entry per lane): fold, cull, compact per wave ----
-        uint64_t my_pos = 0;
-        float eA = 0.0f, eB = 0.0f, eC = 0.0f;     // the staged entry's conic
-        if (wave == 0) {
-            bool hit0 = false, hit1 = false;
-            float4 ca = make_float4(0.f, 0.f, 0.f, 0.f), cbv = ca, q4 = ca;
-            float u = 0.0f, v = 0.0f, cb = 0.0f;
-            const uint32_t idx = b0 + lane;
-            if (lane < cnt) {
-                const uint32_t g0 = vals[idx];
-                const uint32_t g = g0 < f.n_gaussians ? g0 : 0u;
-                const Record rec = ws.records[g];
-                fold_record<true>(rec, ox, oy, u, v, ca, cbv);
-                cb = rec.b;
-                q4 = make_float4(rec.A, rec.B, rec.C, u);
+    // the staging wave's lane: its entry's position in emission order, the regions it is listed
+    // in and its place in each of their lists (a byte each)
+    uint64_t my_pos = 0;
+    uint32_t my_mask = 0, my_place[4] = {0, 0, 0, 0};
+    float eA = 0.0f, eB = 0.0f, eC = 0.0f;     // TRAIN: its conic
+
+    auto list_of = [&](int r) { return reinterpret_cast<uint8_t*>(s_list4[r]); };
+    // One wave stages the entries before b_end, lane l the l-th from the back,
+    // and lists them in the regions whose pixels they can reach; the last ones,
+    // from the first whose rows of sums do not fit, are left to the next batch.
+    auto stage = [&](uint32_t b_end) {
+        const uint32_t cnt = min(b_end - start, (uint32_t)BWD_BATCH);
+        RegionSpans lo, hi;
+        lo.none();
+        hi.none();
+        uint32_t idx = 0xffffffffu;
+        if (lane < cnt) {
+            idx = b_end - 1 - lane;
+            const uint32_t g0 = vals[idx];
+            const uint32_t g = g0 < f.n_gaussians ? g0 : 0u;
+            const Record rec = ws.records[g];
+            my_pos = emission_pos(ws, g, tx, ty);
+            float u, v, tau, bx = 1.0e30f, by = 1.0e30f;
+            if (TRAIN) {
+                float4 ca, cb;
+                fold_record<true>(rec, ox, oy, u, v, ca, cb);
+                s_a[lane] = ca;
+                s_b[lane] = cb;
+                s_c[lane] = make_float4(rec.b, u, v, 0.0f);
                 eA = rec.A;
                 eB = rec.B;
                 eC = rec.C;
-                cull_half_tiles(rec, u, v, hit0, hit1);
-                my_pos = emission_pos(ws, g, tx, ty);
+                tau = 2.0f * (LN255F + rec.opa);
+                bx = half_lo(rec.extra);
+                by = half_hi(rec.extra);
+            } else {
+                u = (rec.u_hi - ox) + rec.u_lo;
+                v = (rec.v_hi - oy) + rec.v_lo;
+                s_a[lane] = make_float4(u, v, rec.A, rec.B);
+                s_b[lane] = make_float4(rec.C, rec.opa, rec.r, rec.g);
+                s_c[lane].x = rec.b;
+                u -= 7.5f;
+                v -= 7.5f;
+                tau = 2.0f * logf(255.0f * rec.opa);
             }
-            const uint64_t m0 = __ballot(hit0), m1 = __ballot(hit1);
-            const uint64_t lt = lanemask_lt();
-            const float4 b4 = make_float4(cbv.x, cbv.y, __uint_as_float(idx), __uint_as_float(lane));
-            const float4 m4 = make_float4(cbv.z, cbv.w, cb, v);
-            if (hit0) {
-                const uint32_t p = (uint32_t)__popcll(m0 & lt);
-                s_a[0][p] = ca;
-                s_b[0][p] = b4;
-                s_m[0][p] = m4;
-                s_q[0][p] = q4;
-            }
-            if (hit1) {
-                const uint32_t p = (uint32_t)__popcll(m1 & lt);
-                s_a[1][p] = ca;
-                s_b[1][p] = b4;
-                s_m[1][p] = m4;
-                s_q[1][p] = q4;
-            }
+            lo.reach(rec.A, rec.B, rec.C, tau, bx, by, u, v, -7.5f);
+            hi.reach(rec.A, rec.B, rec.C, tau, bx, by, u, v, 0.5f);
+        }
+        uint32_t mask = 0, below = 0;
+        uint64_t m[BWD_REGIONS];
+#pragma unroll
+        for (int r = 0; r < BWD_REGIONS; ++r) {
+            const bool hit = (r < 8 ? lo.hits(r % 8) : hi.hits(r % 8)) && idx < s_last[r];
+            m[r] = __ballot(hit);
+            const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[r], 0u));
+            if (hit) list_of(r)[p] = (uint8_t)lane;
+            mask |= hit ? 1u << r : 0u;
+            my_place[r / 4] = r % 4 ? my_place[r / 4] | p << (8 * (r % 4)) : p;
+            below += p;
+        }
+        my_mask = mask;
+        const uint64_t kept = __ballot(below + (uint32_t)__popc(mask) <= BWD_ROWS);
+        uint32_t base = 0, longest0 = 0, longest1 = 0;
+#pragma unroll
+        for (int r = 0; r < BWD_REGIONS; ++r) {
+            const uint32_t n = (uint32_t)__popcll(m[r] & kept);
             if (lane == 0) {
-                s_cnt[0] = (uint32_t)__popcll(m0);
-                s_cnt[1] = (uint32_t)__popcll(m1);
+                s_count[r] = n;
+                s_base[wave][r] = base;
+            }
+            base += n;
+            if (r < 8) longest0 = max(longest0, n);
+            else longest1 = max(longest1, n);
+        }
+        if (lane == 0) {
+            s_kept = min(cnt, (uint32_t)__popcll(kept));
+            s_longest[0] = longest0;
+            s_longest[1] = longest1;
+        }
+    };
+
+    uint32_t stager = 0;
+    if (tile_last > start && wave == 0) stage(tile_last);
+    for (uint32_t b_end = tile_last; b_end > start;) {
+        __syncthreads();                         // the batch is staged, and the last one's rows are read
+        const uint32_t kept = __builtin_amdgcn_readfirstlane(s_kept);
+        const uint32_t longest = __builtin_amdgcn_readfirstlane(s_longest[wave]);
+        const uint32_t n = s_count[region], row0 = s_base[stager][region];
+        // slots from which each pixel may have blended
+        const int lim0 = (int)(b_end - last[0]), lim1 = (int)(b_end - last[1]);
+        for (uint32_t k0 = 0; k0 < longest; k0 += BWD_UNROLL) {
+            const uint32_t word = s_list4[region][k0 / 4] >> (8 * (k0 % 4));
+            uint32_t slot[BWD_UNROLL];
+            float4 a[BWD_UNROLL], m[BWD_UNROLL];
+            float P0[BWD_UNROLL], P1[BWD_UNROLL];      // exponents; plain: e^p
+            bool pass0[BWD_UNROLL], pass1[BWD_UNROLL];
+#pragma unroll
+            for (int u = 0; u < BWD_UNROLL; ++u) {
+                slot[u] = (word >> (8 * u)) % BWD_BATCH;
+                a[u] = s_a[slot[u]];
+                m[u] = s_b[slot[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < BWD_UNROLL; ++u) {
+                const int at = k0 + u < n ? (int)slot[u] : -0x7fffffff;
+                if (TRAIN) {
+                    folded_exponents(a[u], m[u].x, m[u].y, x, y, x2, xy, y2, y21, P0[u], P1[u]);
+                    pass0[u] = at >= lim0 && P0[u] >= -LOG2_255F;
+                    pass1[u] = at >= lim1 && P1[u] >= -LOG2_255F;
+                } else {
+                    const float dx = x - a[u].x, dy0 = y - a[u].y, dy1 = y1 - a[u].y;
+                    P0[u] = expf(fmaf(-0.5f, fmaf(a[u].z * dx, dx, m[u].x * dy0 * dy0), -a[u].w * dx * dy0));
+                    P1[u] = expf(fmaf(-0.5f, fmaf(a[u].z * dx, dx, m[u].x * dy1 * dy1), -a[u].w * dx * dy1));
+                    pass0[u] = at >= lim0 && fminf(ALPHA_MAX, m[u].y * P0[u]) >= ALPHA_MIN;
+                    pass1[u] = at >= lim1 && fminf(ALPHA_MAX, m[u].y * P1[u]) >= ALPHA_MIN;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < BWD_UNROLL; ++u) {
+                float g[9];
+#pragma unroll
+                for (int c = 0; c < 9; ++c) g[c] = 0.0f;
+                if (TRAIN) {
+                    const float4 c = s_c[slot[u]];
+                    const float dx = x - c.y;
+                    if (pass0[u]) pair_adjoint(P0[u], dx, y - c.z, m[u].z, m[u].w, c.x, d[0], T[0], DS[0], g);
+                    if (pass1[u]) pair_adjoint(P1[u], dx, y1 - c.z, m[u].z, m[u].w, c.x, d[1], T[1], DS[1], g);
+                } else {
+                    const float cb = s_c[slot[u]].x;
+                    const float dx = x - a[u].x;
+                    if (pass0[u])
+                        pair_adjoint_plain(P0[u], m[u].y * P0[u], dx, y - a[u].y, a[u], m[u], cb, d[0], T[0], DS[0], g);
+                    if (pass1[u])
+                        pair_adjoint_plain(P1[u], m[u].y * P1[u], dx, y1 - a[u].y, a[u], m[u], cb, d[1], T[1], DS[1], g);
+                }
+                float o[5];
+                group_sums(g, o);
+                if (k0 + u < n && lane % 4 == 0) {
+                    const uint32_t row = row0 + k0 + u;
+                    s_row[row][lane / 4 % 2] = make_float4(o[0], o[1], o[2], o[3]);
+                    if (lane % 8 == 0) s_row8[row] = o[4];
+                }
             }
         }
-        __syncthreads();
-        // ---- this wave's list, back to front ----
-        const uint32_t n = __builtin_amdgcn_readfirstlane(s_cnt[wave]);
-        // each step reads the next (closer) entry's exponent coefficients ahead,
-        // so that their LDS latency overlaps this step's work
-        float4 b4n = make_float4(0.f, 0.f, 0.f, 0.f), an = b4n;
-        if (n) {
-            b4n = s_b[wave][n - 1];
-            an = s_a[wave][n - 1];
-        }
-        for (int k = (int)n - 1; k >= 0; --k) {
-            const float4 b4 = b4n, a = an;
-            if (k > 0) {
-                b4n = s_b[wave][k - 1];
-                an = s_a[wave][k - 1];
-            }
-            const uint32_t idx = __float_as_uint(b4.z);
-            if (idx >= wlast) continue;          // no pixel of the wave got this far
-            float P0, P1;
-            folded_exponents(a, b4.x, b4.y, x, y, x2, xy, y2, y21, P0, P1);
-            const bool pass0 = idx < last[0] && P0 >= -LOG2_255F;
-            const bool pass1 = idx < last[1] && P1 >= -LOG2_255F;
-            if (__ballot(pass0 || pass1) == 0) continue;
-            const float4 mg = s_m[wave][k];
-            const float4 abc = s_q[wave][k];
-            const float dx = x - abc.w;
-            float g[9];
-#pragma unroll
-            for (int c = 0; c < 9; ++c) g[c] = 0.0f;
-            if (pass0) pair_adjoint(P0, dx, y - mg.w, mg, d[0], T[0], DS[0], g);
-            if (pass1) pair_adjoint(P1, dx, y1 - mg.w, mg, d[1], T[1], DS[1], g);
-            row_sums(g);
-            // row_bcast:15, taken by every lane (the compiler would otherwise move
-            // the add under the store's lane mask and broadcast through extra moves)
-#pragma unroll
-            for (int c = 0; c < 9; ++c) {
-                g[c] += dpp_moved<0x142>(g[c]);
-                asm volatile("" : "+v"(g[c]));
-            }
-            if ((lane & 31) == 31) {
-                const uint32_t slot = __float_as_uint(b4.w), half = lane >> 5;
-#pragma unroll
-                for (int c = 0; c < 9; ++c) s_acc[wave][c][half][slot] = g[c];
-            }
-        }
-        __syncthreads();
-        if (tid < cnt) {
-            float4* dst = partial + 3ull * my_pos;
+        __syncthreads();                         // the rows are complete, and the batch's lists are read
+        if (wave == stager && lane < kept) {
             float sum[9];
 #pragma unroll
-            for (int c = 0; c < 9; ++c)
-                sum[c] = (s_acc[0][c][0][tid] + s_acc[0][c][1][tid]) + (s_acc[1][c][0][tid] + s_acc[1][c][1][tid]);
-            // moments of dL/dP -> dL/d(u, v, A, B, C) with the entry's conic
-            const float m1 = sum[0], m2 = sum[1];
-            sum[0] = fmaf(eA, m1, eB * m2);      // dp/du = A dx + B dy
-            sum[1] = fmaf(eC, m2, eB * m1);      // dp/dv = C dy + B dx
-            sum[2] *= -0.5f;
-            sum[3] = -sum[3];
-            sum[4] *= -0.5f;
+            for (int c = 0; c < 9; ++c) sum[c] = 0.0f;
+#pragma unroll
+            for (int r = 0; r < BWD_REGIONS; ++r) {
+                if (!((my_mask >> r) & 1u)) continue;
+                const uint32_t q = s_base[wave][r] + ((my_place[r / 4] >> (8 * (r % 4))) & 0xffu);
+                const float4 s0 = s_row[q][0], s1 = s_row[q][1];
+                sum[0] += s0.x; sum[1] += s0.y; sum[2] += s0.z; sum[3] += s0.w;
+                sum[4] += s1.x; sum[5] += s1.y; sum[6] += s1.z; sum[7] += s1.w;
+                sum[8] += s_row8[q];
+            }
+            if (TRAIN) {
+                // moments of dL/dP -> dL/d(u, v, A, B, C) with the entry's conic
+                const float m1 = sum[0], m2 = sum[1];
+                sum[0] = fmaf(eA, m1, eB * m2);      // dp/du = A dx + B dy
+                sum[1] = fmaf(eC, m2, eB * m1);      // dp/dv = C dy + B dx
+                sum[2] *= -0.5f;
+                sum[3] = -sum[3];
+                sum[4] *= -0.5f;
+            }
+            float4* dst = partial + 3ull * my_pos;
             dst[0] = make_float4(sum[0], sum[1], sum[2], sum[3]);
             dst[1] = make_float4(sum[4], sum[5], sum[6], sum[7]);
             dst[2] = make_float4(sum[8], 0.0f, 0.0f, 0.0f);
         }
-        b_end = b0;
+        b_end -= kept;
+        stager ^= 1u;
+        if (wave == stager && b_end > start) stage(b_end);
     }
     // entries no pixel of the tile reached
-    for (uint32_t idx = tile_last + tid; idx < end; idx += TB_THREADS) {
+    for (uint32_t idx = tile_last + tid; idx < end; idx += BWD_THREADS) {
         const uint32_t g = vals[idx];
         float4* dst = partial + 3ull * emission_pos(ws, g < f.n_gaussians ? g : 0u, tx, ty);
         dst[0] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -545,10 +479,11 @@ __global__ __launch_bounds__(TB_THREADS) void k_raster_backward_train(FrameDev f
     }
 }
 
-void launch_raster_backward_train(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals,
-                                  const float* dimg, float4* partial, FrameKey key) {
-    hipLaunchKernelGGL(k_raster_backward_train, dim3((uint32_t)f.n_tiles), dim3(TB_THREADS), 0, s, f, ws, vals,
-                       dimg, partial, key);
+void launch_raster_backward(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals,
+                            const float* dimg, float4* partial, FrameKey key, bool train) {
+    const dim3 grid((uint32_t)f.n_tiles), block(BWD_THREADS);
+    if (train) hipLaunchKernelGGL(k_raster_backward<true>, grid, block, 0, s, f, ws, vals, dimg, partial, key);
+    else hipLaunchKernelGGL(k_raster_backward<false>, grid, block, 0, s, f, ws, vals, dimg, partial, key);
 }
 
 // ---------------------------------------------------------------------------

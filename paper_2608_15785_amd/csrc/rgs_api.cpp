@@ -1259,8 +1259,7 @@ extern "C" rgs_status rgs_render_backward(rgs_ctx* ctx, const rgs_scene* scene, 
     float4* partial = static_cast<float4*>(grads->scratch);
     const bool train = (path_word & RGS_HW_EXP2) != 0;
     const FrameKey key{scene->tag, hash};
-    if (train) launch_raster_backward_train(ctx->stream, fl.f, fl.w, vals, dL_dimg, partial, key);
-    else launch_raster_backward(ctx->stream, fl.f, fl.w, vals, dL_dimg, partial, key);
+    launch_raster_backward(ctx->stream, fl.f, fl.w, vals, dL_dimg, partial, key, train);
     GradOut go{grads->d_means, grads->d_scales, grads->d_quats, grads->d_opacity, grads->d_sh, grads->d_screen};
     launch_grad_gaussian(ctx->stream, fl.plain, cd, fl.w, partial, go, train, key);
     HIP_TRY(hipGetLastError());

@@ -1,11 +1,11 @@
-// Coefficient folding and per-half-tile culling of one staged list entry
+// Coefficient folding and per-region culling of one staged list entry
 // (Sec. IV-B: Eqs. expand, c0, coeff, dot, dual_pixel), shared by the
-// dual-pixel rasterizer and the backward pass of the training variant, so that
-// both evaluate every folded exponent with the same instructions.
+// dual-pixel rasterizer and the backward pass, so that both evaluate every
+// folded exponent with the same instructions.
 //
 // Coordinates are relative to the centre of the 16x16 tile: pixel (lx, ly)
-// sits at (lx - 7.5, ly - 7.5), and the two half-tiles of the two waves of a
-// dual-pixel workgroup are the rows [-7.5, -0.5] and [0.5, 7.5].
+// sits at (lx - 7.5, ly - 7.5), and its two half-tiles are the rows [-7.5, -0.5]
+// and [0.5, 7.5].
 #pragma once
 
 #include "rgs_internal.h"
@@ -66,31 +66,10 @@ __device__ inline void fold_record(const Record& rec, float ox, float oy, float&
     }
 }
 
-// Whether the record (mean u, v in tile-centre coordinates) can reach a pixel
-// of each half-tile with P >= -ln 255.  First the box |x - u| <= hx,
-// |y - v| <= hy of its alpha >= 1/255 ellipse (half-extents stored by the front
-// end as FP16, rounded up, then widened); then the ellipse itself: the
-// half-tile must hold a point with q <= tau = 2 (ln 255 + ln o), up to the
-// margin.  Comparisons are phrased so that a NaN keeps the Gaussian.  A culled
-// pair would have failed the skip test, so culling changes no result.
-__device__ inline void cull_half_tiles(const Record& rec, float u, float v, bool& hit0, bool& hit1) {
-    const float A = rec.A, B = rec.B, C = rec.C;
-    const float hx = fmaf(half_lo(rec.extra), 1.0f + BOX_MARGIN_REL, BOX_MARGIN_ABS);
-    const float hy = fmaf(half_hi(rec.extra), 1.0f + BOX_MARGIN_REL, BOX_MARGIN_ABS);
-    const bool x_out = u - hx > 7.5f || u + hx < -7.5f;
-    hit0 = !(x_out || v - hy > -0.5f || v + hy < -7.5f);
-    hit1 = !(x_out || v - hy > 7.5f || v + hy < 0.5f);
-    const float qlim = fmaf(2.0f * (LN255F + rec.opa), 1.0f + Q_MARGIN_REL, Q_MARGIN_ABS);
-    // the reciprocals only place the nearest point of an edge, where q is
-    // then evaluated exactly; an error of an ulp moves q by ~C (1e-6 px)^2
-    const float iA = __builtin_amdgcn_rcpf(A), iC = __builtin_amdgcn_rcpf(C);
-    if (hit0) hit0 = !(conic_rect_min(u, v, A, B, C, iA, iC, -7.5f, -0.5f) > qlim);
-    if (hit1) hit1 = !(conic_rect_min(u, v, A, B, C, iA, iC, 0.5f, 7.5f) > qlim);
-}
-
 // Which of the eight 4x4 regions of a half-tile (rows top .. top + 7) a record
-// can reach with P >= -ln 255: for each of its two bands of four rows, the span of columns that its ellipse q <= tau (up
-// to the margin above) covers inside the band.  The ellipse is convex, so it
+// can reach with P >= -ln 255: for each of its two bands of four rows, the span
+// of columns that its ellipse q <= tau (up to the margin above) covers inside
+// the band.  The ellipse is convex, so it
 // meets the 4x4 region of columns x0 .. x0 + 3 iff its span in the band meets
 // [x0, x0 + 3].  At the height dy the ellipse covers -B/A dy +- sqrt(A tau -
 // det dy^2) / A; the right end is a concave function of dy with its peak at dy =

@@ -595,9 +595,7 @@ struct FrameKey {
     uint64_t scene_tag, cam_hash;
 };
 void launch_raster_backward(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals,
-                            const float* dimg, float4* partial, FrameKey key);
-void launch_raster_backward_train(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals,
-                                  const float* dimg, float4* partial, FrameKey key);
+                            const float* dimg, float4* partial, FrameKey key, bool train);
 // lno_opacity: the partials' opacity slot holds dL/d(ln o) (the training
 // variant's), converted to dL/do here.
 void launch_grad_gaussian(hipStream_t s, const PlainSceneDev& sc, const CamDev& cam, const WsDev& ws,
