@@ -345,7 +345,7 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, 
         uint64_t m[BWD_REGIONS];
 #pragma unroll
         for (int r = 0; r < BWD_REGIONS; ++r) {
-            const bool hit = (r < 8 ? lo.hits(r % 8) : hi.hits(r % 8)) && idx < s_last[r];
+            const bool hit = (r < 8 ? lo : hi).hits(r / 4 % 2, (float)(r % 4 * 4)) && idx < s_last[r];
             m[r] = __ballot(hit);
             const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[r], 0u));
             if (hit) list_of(r)[p] = (uint8_t)lane;

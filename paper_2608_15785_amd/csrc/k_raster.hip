@@ -10,7 +10,8 @@
 //
 // `k_raster` serves every path: a workgroup is one wave and blends one
 // half-tile, a dual pixel (x, y), (x, y + 1) per lane, each of the half-tile's
-// eight 4x4 regions walking a list of its own.  What a pair's alpha is
+// eight 4x4 regions walking a list of its own (in frames of few tiles a quarter
+// of a tile, a pixel per lane, in four regions).  What a pair's alpha is
 // computed from is its template argument:
 //   * EXP_PLAIN, the 3DGS baseline: the exponent of Eq. power from (x - u,
 //     y - v) and the accurate expf;
@@ -59,11 +60,11 @@
 // matrix instruction occupies the vector ALUs (16 of them and 64 FMAs take 530
 // cycles, 165 and 166 alone).
 //
-// Workgroups b and b + 8 blend the two halves of tile ws.order[..] (longest
+// Workgroups b, b + 8, .. blend the parts of tile ws.order[..] (longest
 // lists first, so that the grid does not end on a few long tiles; see the
 // tile-order kernel) in frames that take the schedule, else of tiles in
 // row-major order.  Workgroups are dispatched to the 8 XCDs round-robin, so
-// both halves of a tile share an L2, and the tiles' uneven work spreads evenly
+// all parts of a tile share an L2, and the tiles' uneven work spreads evenly
 // over the XCDs.
 #include "rgs_fold.h"
 
@@ -106,31 +107,40 @@ __device__ inline float alpha_of(float P, float thr) {
     return P >= thr ? al : 0.0f;
 }
 
-// A lane's dual pixel (x, y), (x, y + 1): in tile-centre coordinates with the
-// monomials of Eq. dot, or for EXP_PLAIN relative to the tile's corner.
-struct DualPixel {
+// A lane's pixels: a dual pixel (x, y), (x, y + 1), or with PIX = 1 one of the two
+// (odd: the second); in tile-centre coordinates with the monomials of Eq. dot,
+// or for EXP_PLAIN relative to the tile's corner.
+struct LanePixels {
     float x, y, x2, xy, y2, y21;
+    bool odd;
 };
 
-// Both pixels' alphas of a staged entry; thr0 and thr1 are the thresholds of
-// alpha_of, for EXP_PLAIN on alpha itself.
-template <int EXPM>
-__device__ inline void pair_alphas(const float4& a, const float2& c, const DualPixel& d, float thr0, float thr1,
-                                   float& al0, float& al1) {
+// The pixels' alphas of a staged entry; thr: the thresholds of alpha_of, for
+// EXP_PLAIN on alpha itself.  A single pixel's alpha is that of the dual pixel, bit
+// for bit.
+template <int EXPM, int PIX>
+__device__ inline void pair_alphas(const float4& a, const float2& c, const LanePixels& d, const float (&thr)[PIX],
+                                   float (&al)[PIX]) {
     if (EXPM == EXP_PLAIN) {
         // a = (u, v, A, B), c = (C, o)
-        const float dx = d.x - a.x, dy0 = d.y - a.y, dy1 = (d.y + 1.0f) - a.y;
-        const float p0 = fmaf(-0.5f, fmaf(a.z * dx, dx, c.x * dy0 * dy0), -a.w * dx * dy0);
-        const float p1 = fmaf(-0.5f, fmaf(a.z * dx, dx, c.x * dy1 * dy1), -a.w * dx * dy1);
-        al0 = fminf(ALPHA_MAX, c.y * expf(p0));
-        al1 = fminf(ALPHA_MAX, c.y * expf(p1));
-        al0 = al0 >= thr0 ? al0 : 0.0f;
-        al1 = al1 >= thr1 ? al1 : 0.0f;
+        const float dx = d.x - a.x;
+#pragma unroll
+        for (int i = 0; i < PIX; ++i) {
+            const float row = PIX == 1 ? d.y + (d.odd ? 1.0f : 0.0f) : d.y + (float)i;
+            const float dy = row - a.y;
+            const float p = fmaf(-0.5f, fmaf(a.z * dx, dx, c.x * dy * dy), -a.w * dx * dy);
+            al[i] = fminf(ALPHA_MAX, c.y * expf(p));
+            al[i] = al[i] >= thr[i] ? al[i] : 0.0f;
+        }
     } else {
         float P0, P1;
         folded_exponents(a, c.x, c.y, d.x, d.y, d.x2, d.xy, d.y2, d.y21, P0, P1);
-        al0 = alpha_of<EXPM>(P0, thr0);
-        al1 = alpha_of<EXPM>(P1, thr1);
+        if (PIX == 1) {
+            al[0] = alpha_of<EXPM>(d.odd ? P1 : P0, thr[0]);
+        } else {
+            al[0] = alpha_of<EXPM>(P0, thr[0]);
+            al[PIX - 1] = alpha_of<EXPM>(P1, thr[PIX - 1]);
+        }
     }
 }
 
@@ -141,10 +151,9 @@ __device__ inline float behind(float T, float al, float w) {
 }
 
 // A workgroup is one wave and blends one half-tile (16x8 pixels), a dual pixel
-// per lane, in eight regions of 4x4 pixels: the eight lanes of a region walk the
-// region's own list.
+// per lane, in eight regions of 4x4 pixels, or with PIX = 1 a quarter (8x8), a
+// pixel per lane, in four: the lanes of a region walk the region's own list.
 constexpr int REGION = 4;
-constexpr int REGIONS = 8;                        // of a half-tile: two bands of four
 constexpr int FAST_BATCH = 64;                    // entries staged at once, one per lane
 constexpr int FAST_LIST = FAST_BATCH + LIST_UNROLL;
 constexpr uint32_t XCDS = 8;                      // workgroups go to the XCDs round-robin
@@ -153,8 +162,11 @@ constexpr uint32_t XCDS = 8;                      // workgroups go to the XCDs r
 // EXP_HW2 over the plain path's records, which then hold ln o and the
 // alpha-ellipse box): every render also leaves each pixel's final T and
 // visited-pair count for it.
-template <bool COUNT, int EXPM, bool TRAIN>
+template <bool COUNT, int EXPM, bool TRAIN, int PIX>
 __global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint32_t* __restrict__ vals) {
+    constexpr uint32_t PARTS = 4 / PIX;               // of a tile
+    constexpr int REGIONS = 4 * PIX;                  // of a part
+    constexpr uint32_t REGION_LANES = 16 / PIX;
     // the batch's folded entries, and at FAST_BATCH an inert one (P = -1e30, or o = 0: always
     // skipped), in three arrays of 16 bytes an entry, so that one address serves all three:
     // (C1, C2, C3, C4), (C5, C6, r, g), b; EXP_PLAIN: (u, v, A, B), (C, o, r, g), b
@@ -172,39 +184,56 @@ __global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint3
     // per region, the batch's entries that can reach it, in depth order
     __shared__ uint32_t s_list4[REGIONS * FAST_LIST / 4];
     uint8_t* s_list = reinterpret_cast<uint8_t*>(s_list4);
-    // both halves of a tile on one XCD, whose L2 then serves the records to both
-    const uint32_t slot_t = blockIdx.x / (2 * XCDS) * XCDS + blockIdx.x % XCDS, half = blockIdx.x / XCDS % 2;
+    // all parts of a tile on one XCD, whose L2 then serves the records to all
+    const uint32_t slot_t = blockIdx.x / (PARTS * XCDS) * XCDS + blockIdx.x % XCDS, part = blockIdx.x / XCDS % PARTS;
     if (slot_t >= (uint32_t)f.n_tiles) return;
     const uint32_t tile = f.ordered ? ws.order[slot_t] : slot_t;
     const uint32_t tx = tile % (uint32_t)f.tiles_x, ty = tile / (uint32_t)f.tiles_x;
     const uint32_t lane = threadIdx.x;
-    const uint32_t region = lane / 8;
-    const uint32_t lx = (region % 4) * REGION + lane % REGION;
-    const uint32_t ly = half * 8 + (region / 4) * REGION + (lane / REGION % 2) * 2;
+    const uint32_t region = lane / REGION_LANES;
+    // the part's first column and row of the tile, and the lane's first row
+    const uint32_t left = PIX == 1 ? part % 2 * 8 : 0, top_row = PIX == 1 ? part / 2 * 8 : part * 8;
+    constexpr uint32_t ACROSS = 2 * PIX;              // regions of a band of four rows
+    const uint32_t lx = left + (region % ACROSS) * REGION + lane % REGION;
+    const uint32_t band_row = PIX == 1 ? lane / REGION % REGION : lane / REGION % 2 * 2;
+    const uint32_t ly = top_row + (region / ACROSS) * REGION + band_row;
     const uint32_t px = tx * TILE + lx, py = ty * TILE + ly;
-    const bool in0 = px < (uint32_t)f.width && py < (uint32_t)f.height;
-    const bool in1 = px < (uint32_t)f.width && py + 1 < (uint32_t)f.height;
+    bool in[PIX];
+#pragma unroll
+    for (int i = 0; i < PIX; ++i) in[i] = px < (uint32_t)f.width && py + i < (uint32_t)f.height;
     const uint32_t start = ws.ranges[2 * tile], end = ws.ranges[2 * tile + 1];
     // tile-centre coordinates (EXP_PLAIN: relative to the tile's corner)
     constexpr float CENTRE = EXPM == EXP_PLAIN ? 0.0f : 7.5f;
     const float ox = (float)(tx * TILE) + CENTRE, oy = (float)(ty * TILE) + CENTRE;
-    DualPixel dp;
+    LanePixels dp;
+    dp.odd = ly % 2 != 0;
     dp.x = (float)lx - CENTRE;
-    dp.y = (float)ly - CENTRE;
+    dp.y = (float)(ly / 2 * 2) - CENTRE;
     dp.x2 = dp.x * dp.x;
     dp.xy = dp.x * dp.y;
     dp.y2 = dp.y * dp.y;
     dp.y21 = fmaf(2.0f, dp.y, 1.0f);
-    const float top = (float)(half * 8) - 7.5f;        // the half-tile's first row
+    const float top = (float)top_row - 7.5f;
 
     constexpr float SKIP = EXPM == EXP_PLAIN ? ALPHA_MIN : EXPM == EXP_HW2 ? -LOG2_255F : -LN255F;
     const float NEVER = __uint_as_float(0x7fc00000u);
-    float T0 = 1.0f, r0 = 0.0f, g0 = 0.0f, b0 = 0.0f;
-    float T1 = 1.0f, r1 = 0.0f, g1 = 0.0f, b1 = 0.0f;
     // the exponents (EXP_PLAIN: alphas) that pass at each pixel: >= thr, none once it has stopped
-    float thr0 = in0 ? SKIP : NEVER, thr1 = in1 ? SKIP : NEVER;
-    uint32_t stop0 = 0xffffffffu, stop1 = 0xffffffffu;
-    uint32_t nbl0 = 0, nbl1 = 0;
+    float T[PIX], r[PIX], g[PIX], b[PIX], thr[PIX];
+    uint32_t stop[PIX], nbl[PIX];
+#pragma unroll
+    for (int i = 0; i < PIX; ++i) {
+        T[i] = 1.0f;
+        r[i] = g[i] = b[i] = 0.0f;
+        thr[i] = in[i] ? SKIP : NEVER;
+        stop[i] = 0xffffffffu;
+        nbl[i] = 0;
+    }
+    auto all_stopped = [&] {
+        bool live = false;
+#pragma unroll
+        for (int i = 0; i < PIX; ++i) live = live || thr[i] == thr[i];
+        return __ballot(live) == 0;
+    };
     uint32_t steps = 0;         // counting renders: list entries this wave evaluated
     if (lane == 0)
         put_entry(FAST_BATCH, make_float4(0.f, 0.f, 0.f, 0.f),
@@ -212,7 +241,7 @@ __global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint3
 
     uint32_t ahead = start + lane < end ? vals[start + lane] : 0u;      // this lane's Gaussian of the next batch
     for (uint32_t base = start; base < end; base += FAST_BATCH) {
-        if (__ballot(thr0 == thr0 || thr1 == thr1) == 0) break;      // every pixel has stopped
+        if (all_stopped()) break;
         // ---- stage: fold, and list each entry in the regions it can reach ----
         __syncthreads();                 // (one wave: orders its LDS accesses for the compiler)
 #pragma unroll
@@ -246,7 +275,7 @@ __global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint3
         uint32_t n = 0;                  // the longest list
 #pragma unroll
         for (int k = 0; k < REGIONS; ++k) {
-            const bool hit = sp.hits(k);
+            const bool hit = sp.hits(k / (int)ACROSS, (float)left + (float)(k % (int)ACROSS * REGION));
             const uint64_t m = __ballot(hit);
             const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
             if (hit) s_list[k * FAST_LIST + p] = (uint8_t)lane;
@@ -265,7 +294,7 @@ __global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint3
             // whole groups, until one in which some pixel stops
             for (; k0 < n; k0 += LIST_UNROLL) {
                 const uint32_t word = *reinterpret_cast<const uint32_t*>(list + k0);
-                float al0[LIST_UNROLL], al1[LIST_UNROLL], w0[LIST_UNROLL], w1[LIST_UNROLL];
+                float al[LIST_UNROLL][PIX], w[LIST_UNROLL][PIX];
                 uint32_t at[LIST_UNROLL];
                 float4 a[LIST_UNROLL];
                 float2 c[LIST_UNROLL];
@@ -276,45 +305,47 @@ __global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint3
                     c[u] = tail(at[u]);
                 }
 #pragma unroll
-                for (int u = 0; u < LIST_UNROLL; ++u) pair_alphas<EXPM>(a[u], c[u], dp, thr0, thr1, al0[u], al1[u]);
-                float Tn0 = T0, Tn1 = T1;
-                uint32_t pass0 = 0, pass1 = 0;
+                for (int u = 0; u < LIST_UNROLL; ++u) pair_alphas<EXPM, PIX>(a[u], c[u], dp, thr, al[u]);
+                float Tn[PIX];
+                uint32_t pass[PIX];
+#pragma unroll
+                for (int i = 0; i < PIX; ++i) {
+                    Tn[i] = T[i];
+                    pass[i] = 0;
+                }
                 float2 rg[LIST_UNROLL];
-                float b[LIST_UNROLL];
+                float bl[LIST_UNROLL];
 #pragma unroll
                 for (int u = 0; u < LIST_UNROLL; ++u) {
                     rg[u] = red_green(at[u]);
-                    b[u] = blue(at[u]);
+                    bl[u] = blue(at[u]);
                 }
 #pragma unroll
                 for (int u = 0; u < LIST_UNROLL; ++u) {
-                    w0[u] = al0[u] * Tn0;
-                    w1[u] = al1[u] * Tn1;
-                    Tn0 = behind<EXPM>(Tn0, al0[u], w0[u]);
-                    Tn1 = behind<EXPM>(Tn1, al1[u], w1[u]);
-                    if (COUNT) {
-                        pass0 += al0[u] > 0.0f ? 1u : 0u;
-                        pass1 += al1[u] > 0.0f ? 1u : 0u;
+#pragma unroll
+                    for (int i = 0; i < PIX; ++i) {
+                        w[u][i] = al[u][i] * Tn[i];
+                        Tn[i] = behind<EXPM>(Tn[i], al[u][i], w[u][i]);
+                        if (COUNT) pass[i] += al[u][i] > 0.0f ? 1u : 0u;
                     }
                 }
                 // T never grows: a pixel stops in this group iff T falls below the limit at its end
-                if (one_by_one || (__ballot(Tn0 < T_MIN) | __ballot(Tn1 < T_MIN)) != 0) break;
-                T0 = Tn0;
-                T1 = Tn1;
+                bool stops = false;
 #pragma unroll
-                for (int u = 0; u < LIST_UNROLL; ++u) {
-                    r0 = fmaf(w0[u], rg[u].x, r0);
-                    g0 = fmaf(w0[u], rg[u].y, g0);
-                    b0 = fmaf(w0[u], b[u], b0);
-                    r1 = fmaf(w1[u], rg[u].x, r1);
-                    g1 = fmaf(w1[u], rg[u].y, g1);
-                    b1 = fmaf(w1[u], b[u], b1);
+                for (int i = 0; i < PIX; ++i) stops = stops || Tn[i] < T_MIN;
+                if (one_by_one || __ballot(stops) != 0) break;
+#pragma unroll
+                for (int i = 0; i < PIX; ++i) {
+                    T[i] = Tn[i];
+#pragma unroll
+                    for (int u = 0; u < LIST_UNROLL; ++u) {
+                        r[i] = fmaf(w[u][i], rg[u].x, r[i]);
+                        g[i] = fmaf(w[u][i], rg[u].y, g[i]);
+                        b[i] = fmaf(w[u][i], bl[u], b[i]);
+                    }
+                    if (COUNT) nbl[i] += pass[i];
                 }
-                if (COUNT) {
-                    nbl0 += pass0;
-                    nbl1 += pass1;
-                    steps += LIST_UNROLL;
-                }
+                if (COUNT) steps += LIST_UNROLL;
             }
             if (k0 >= n) break;
             // that group entry by entry: the pair that would take a pixel below the limit
@@ -322,31 +353,29 @@ __global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint3
 #pragma unroll 1
             for (uint32_t u = k0; u < k0 + LIST_UNROLL; ++u) {
                 const uint32_t e = list[u];
-                float al0, al1;
-                pair_alphas<EXPM>(coef(e * 16), tail(e * 16), dp, thr0, thr1, al0, al1);
+                float al[PIX];
+                pair_alphas<EXPM, PIX>(coef(e * 16), tail(e * 16), dp, thr, al);
                 const float2 col = red_green(e * 16);
                 const float bl = blue(e * 16);
-                auto blend = [&](float al, float& T, float& r, float& g, float& b, float& thr, uint32_t& stop,
-                                 uint32_t& nbl) {
-                    if (EXPM == EXP_PLAIN && al == 0.0f) return;
-                    const float w = al * T;
-                    const float Tn = behind<EXPM>(T, al, w);
+#pragma unroll
+                for (int i = 0; i < PIX; ++i) {
+                    if (EXPM == EXP_PLAIN && al[i] == 0.0f) continue;
+                    const float w = al[i] * T[i];
+                    const float Tn = behind<EXPM>(T[i], al[i], w);
                     if (Tn < T_MIN) {
-                        thr = NEVER;
-                        stop = base + e;
+                        thr[i] = NEVER;
+                        stop[i] = base + e;
                     } else {
-                        T = Tn;
-                        r = fmaf(w, col.x, r);
-                        g = fmaf(w, col.y, g);
-                        b = fmaf(w, bl, b);
-                        if (COUNT) nbl += al > 0.0f ? 1u : 0u;
+                        T[i] = Tn;
+                        r[i] = fmaf(w, col.x, r[i]);
+                        g[i] = fmaf(w, col.y, g[i]);
+                        b[i] = fmaf(w, bl, b[i]);
+                        if (COUNT) nbl[i] += al[i] > 0.0f ? 1u : 0u;
                     }
-                };
-                blend(al0, T0, r0, g0, b0, thr0, stop0, nbl0);
-                blend(al1, T1, r1, g1, b1, thr1, stop1, nbl1);
+                }
             }
             if (COUNT) steps += LIST_UNROLL;
-            if (__ballot(thr0 == thr0 || thr1 == thr1) == 0) break;
+            if (all_stopped()) break;
             k0 += LIST_UNROLL;
         }
     }
@@ -355,19 +384,19 @@ __global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint3
     const uint64_t plane = (uint64_t)f.width * f.height;
     float* __restrict__ out = ws.params->out;
     const float bg0 = ws.params->cam.bg[0], bg1 = ws.params->cam.bg[1], bg2 = ws.params->cam.bg[2];
-    auto put_pixel = [&](uint32_t row, float T, float r, float g, float b, uint32_t stop, uint32_t nbl) {
-        const uint64_t o = (uint64_t)row * f.width + px;
-        out[o] = fmaf(T, bg0, r);
-        out[plane + o] = fmaf(T, bg1, g);
-        out[2 * plane + o] = fmaf(T, bg2, b);
+#pragma unroll
+    for (int i = 0; i < PIX; ++i) {
+        if (!in[i]) continue;
+        const uint64_t o = (uint64_t)(py + i) * f.width + px;
+        out[o] = fmaf(T[i], bg0, r[i]);
+        out[plane + o] = fmaf(T[i], bg1, g[i]);
+        out[2 * plane + o] = fmaf(T[i], bg2, b[i]);
         if (COUNT || TRAIN) {       // the debug render's and the training variant's per-pixel outputs
-            ws.t_final[o] = T;
-            ws.n_proc[o] = stop != 0xffffffffu ? (stop - start + 1) | N_PROC_STOPPED : end - start;
+            ws.t_final[o] = T[i];
+            ws.n_proc[o] = stop[i] != 0xffffffffu ? (stop[i] - start + 1) | N_PROC_STOPPED : end - start;
         }
-        if (COUNT) ws.n_blend[o] = nbl;
-    };
-    if (in0) put_pixel(py, T0, r0, g0, b0, stop0, nbl0);
-    if (in1) put_pixel(py + 1, T1, r1, g1, b1, stop1, nbl1);
+        if (COUNT) ws.n_blend[o] = nbl[i];
+    }
 }
 
 // One, or four, pixels per lane: the dual-pixel ablation (one pixel per
@@ -611,11 +640,25 @@ __global__ __launch_bounds__(FastShape<PIX>::THREADS) void k_raster_fast_px(Fram
     }
 }
 
+// A frame of few tiles leaves most SIMDs with a wave or two, and its time is the
+// chain of instructions of the wave with the longest lists: a pixel per lane in
+// a quarter of a tile nearly halves that chain, for more instructions in all.
+// Frame times with dual and with single pixels (us): 256 tiles, 10K Gaussians
+// fast 97 and 83, plain 140 and 106; 1M Gaussians, fast and plain, 300 tiles
+// 400, 602 and 340, 463; 1200 tiles 270, 431 and 226, 337; 2040 tiles 205, 333 and
+// 182, 280; 3072 tiles 216, 351 and 206, 320; the kernel alone, fast, at 3600 tiles
+// 79 and 89, at 4056 60 and 70, at 8160 88 and 124 us.  Counting renders keep the
+// dual pixel (the counts are in its units); both give the same bits.
+constexpr int32_t SINGLE_MAX_TILES = 3072;
+
 template <int EXPM, bool TRAIN = false>
-static void launch_dual(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count) {
-    const dim3 grid(((uint32_t)f.n_tiles + XCDS - 1) / XCDS * 2 * XCDS), block(64);
-    if (count) hipLaunchKernelGGL((k_raster<true, EXPM, TRAIN>), grid, block, 0, s, f, ws, vals);
-    else hipLaunchKernelGGL((k_raster<false, EXPM, TRAIN>), grid, block, 0, s, f, ws, vals);
+static void launch_raster(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count) {
+    const uint32_t groups = ((uint32_t)f.n_tiles + XCDS - 1) / XCDS * XCDS;
+    const dim3 block(64);
+    if (count) hipLaunchKernelGGL((k_raster<true, EXPM, TRAIN, 2>), dim3(2 * groups), block, 0, s, f, ws, vals);
+    else if (f.n_tiles > SINGLE_MAX_TILES)
+        hipLaunchKernelGGL((k_raster<false, EXPM, TRAIN, 2>), dim3(2 * groups), block, 0, s, f, ws, vals);
+    else hipLaunchKernelGGL((k_raster<false, EXPM, TRAIN, 1>), dim3(4 * groups), block, 0, s, f, ws, vals);
 }
 
 template <int EXPM, int PIX>
@@ -631,19 +674,19 @@ void launch_raster_fast(hipStream_t s, const FrameDev& f, const WsDev& ws, const
                         uint32_t opts) {
     const bool exact = (opts & OPT_FASTEXP) != 0, single = (opts & OPT_DUALPIXEL) != 0;
     if (opts & OPT_QUAD) launch_fast_px<EXP_BITS, 4>(s, f, ws, vals, count);        // not with the two below
-    else if (opts & OPT_HW_EXP2) launch_dual<EXP_HW2>(s, f, ws, vals, count);  // not with the two below
-    else if (!exact && !single) launch_dual<EXP_BITS>(s, f, ws, vals, count);
-    else if (exact && !single) launch_dual<EXP_LIBM>(s, f, ws, vals, count);
+    else if (opts & OPT_HW_EXP2) launch_raster<EXP_HW2>(s, f, ws, vals, count);  // not with the two below
+    else if (!exact && !single) launch_raster<EXP_BITS>(s, f, ws, vals, count);
+    else if (exact && !single) launch_raster<EXP_LIBM>(s, f, ws, vals, count);
     else if (!exact && single) launch_fast_px<EXP_BITS, 1>(s, f, ws, vals, count);
     else launch_fast_px<EXP_LIBM, 1>(s, f, ws, vals, count);
 }
 
 void launch_raster_plain(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count) {
-    launch_dual<EXP_PLAIN, true>(s, f, ws, vals, count);
+    launch_raster<EXP_PLAIN, true>(s, f, ws, vals, count);
 }
 
 void launch_raster_train(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals, bool count) {
-    launch_dual<EXP_HW2, true>(s, f, ws, vals, count);
+    launch_raster<EXP_HW2, true>(s, f, ws, vals, count);
 }
 
 }  // namespace rgs

@@ -129,10 +129,10 @@ struct RegionSpans {
         }
     }
 
-    // region k: rows 4 (k / 4) .. + 3, columns 4 (k % 4) .. + 3 of the half-tile
-    __device__ inline bool hits(int k) const {
-        const float x0 = (float)(4 * (k % 4)) - 7.5f;
-        return !(left[k / 4] > x0 + 3.0f) && !(right[k / 4] < x0);
+    // the region of band b whose first column is the tile's x
+    __device__ inline bool hits(int b, float x) const {
+        const float x0 = x - 7.5f;
+        return !(left[b] > x0 + 3.0f) && !(right[b] < x0);
     }
 };
 
