@@ -551,7 +551,7 @@ static void make_layout(int64_t n, const rgs_plan& p, int32_t path, uint64_t cap
     L.zero_end = off;
     L.params = off;                  // written by the reset kernel, outside the zeroed span
     off = align256(off + sizeof(FrameParams));
-    L.order = off;                   // written whole by the tile-order kernel
+    L.order = off;                   // written whole by the tile-order kernel or the bucket sort
     off = align256(off + (uint64_t)p.n_tiles * 4);
     L.records = off;
     off = align256(off + (uint64_t)n * sizeof(Record));
@@ -900,8 +900,8 @@ rgs_status rgs::prepare_frame(const rgs_scene* sc, int32_t W, int32_t H, int32_t
     f.passes = (int32_t)fl->L.passes;
     f.capacity = (uint32_t)cap;
     f.n_gaussians = (uint32_t)sc->n;
-    f.ordered = (base == RGS_PATH_PLAIN || p.n_tiles <= ORDER_MAX_TILES) ? 1u : 0u;
-    f.split_bits = 0;                // choose_sort decides
+    f.ordered = ORDER_NONE;          // choose_sort decides
+    f.split_bits = 0;
     f.split_shift = 0;
     f.lk = LocalKey{};
     fl->plain = PlainSceneDev{sc->plain, sc->n_pad, sc->n};
@@ -909,7 +909,7 @@ rgs_status rgs::prepare_frame(const rgs_scene* sc, int32_t W, int32_t H, int32_t
     return RGS_OK;
 }
 
-bool rgs::choose_sort(FrameLaunch& fl, const CamDev& cam) {
+bool rgs::choose_sort(FrameLaunch& fl, const CamDev& cam, bool debug) {
     FrameDev& f = fl.f;
     const bool wide = f.b_t >= SPLIT_WIDE_BT && (fl.L.key_bytes == 8 || f.capacity >= SPLIT_WIDE_CAPACITY);
     const int32_t digit = f.b_t < SPLIT_MIN_BT ? 0 : wide ? SPLIT_WIDE_BT : SPLIT_MIN_BT;
@@ -933,6 +933,12 @@ bool rgs::choose_sort(FrameLaunch& fl, const CamDev& cam) {
     }
     f.split_bits = split ? digit : 0;
     f.lk = split ? lk : LocalKey{};
+    f.ordered = ORDER_NONE;
+    if (debug || (f.n_tiles > ORDER_MIN_TILES && !split)) {
+        if (fl.path == RGS_PATH_PLAIN || f.n_tiles <= ORDER_MAX_TILES) f.ordered = ORDER_TILES;
+    } else if (f.n_tiles > ORDER_MIN_TILES) {
+        f.ordered = ORDER_BUCKETS;
+    }
     const uint32_t rows = split ? fl.L.split_rows : fl.L.lsd_rows;
     fl.w.sort_rows = rows;
     fl.w.sort_groups = (rows + SORT_GROUP - 1) / SORT_GROUP;
@@ -979,7 +985,7 @@ rgs_status rgs::enqueue_frame(hipStream_t st, const FrameLaunch& fl, const Frame
         mark(3);
         launch_ranges(st, fl.f, w, fl.L.key_bytes, fl.L.passes % 2 == 1);
     }
-    launch_tile_order(st, fl.f, w);
+    if (fl.f.ordered == ORDER_TILES) launch_tile_order(st, fl.f, w);
     mark(4);
     const uint32_t* vals = sorted_vals(fl);
     if (fl.path == RGS_PATH_PLAIN && (fl.opts & OPT_HW_EXP2)) launch_raster_train(st, fl.f, w, vals, count);
@@ -1070,7 +1076,7 @@ static rgs_status render_impl(rgs_ctx* ctx, const rgs_scene* sc, const rgs_camer
     }
     FrameHooks hooks{hook_mark, hook_after_front, &rh};
     const FrameParams prm = frame_params(cam, out, sc, W, H);
-    choose_sort(fl, prm.cam);
+    choose_sort(fl, prm.cam, dbg != nullptr);
     s = enqueue_frame(st, fl, prm, dbg ? &dd : nullptr, dbg != nullptr, nullptr, (rh.fe || dbg) ? &hooks : nullptr);
     if (s != RGS_OK) return s;
     s = note_frame(ctx, fl, ws, ws_bytes, sc, prm, W, H, path);
@@ -1254,7 +1260,7 @@ extern "C" rgs_status rgs_render_backward(rgs_ctx* ctx, const rgs_scene* scene, 
     if (path_word != (uint32_t)RGS_PATH_PLAIN && path_word != (uint32_t)(RGS_PATH_PLAIN | RGS_HW_EXP2))
         return fail(RGS_E_INVALID, "the workspace does not hold a plain render of this size");
     const CamDev cd = cam_dev(cam);
-    choose_sort(fl, cd);             // as the frame was sorted
+    choose_sort(fl, cd, false);      // as the frame was sorted
     const uint32_t* vals = sorted_vals(fl);
     float4* partial = static_cast<float4*>(grads->scratch);
     const bool train = (path_word & RGS_HW_EXP2) != 0;

@@ -62,8 +62,9 @@ struct FrameHooks {
 // How a frame of fl seen by cam is sorted, set in fl.f and fl.w: by the split sort
 // (at least 2^SPLIT_MIN_BT tiles, and what its buckets sort fits 32 bits; for
 // 64-bit keys that depends on the camera's depth interval) or by the LSD
-// passes.  Returns whether the split sort applies.
-bool choose_sort(FrameLaunch& fl, const CamDev& cam);
+// passes; and where its tile schedule comes from (debug: a debug render).
+// Returns whether the split sort applies.
+bool choose_sort(FrameLaunch& fl, const CamDev& cam, bool debug);
 // The sorted values of such a frame.
 const uint32_t* sorted_vals(const FrameLaunch& fl);
 

@@ -159,22 +159,27 @@ struct FrameDev {
     int32_t passes;
     uint32_t capacity;
     uint32_t n_gaussians;
-    uint32_t ordered;         // 1: rasterizer workgroup b takes tile ws.order[b], else tile b
+    uint32_t ordered;         // rasterizer workgroup b takes tile b (ORDER_NONE) or ws.order[b]
     int32_t split_bits;       // the split sort's digit width, 0: the frame takes the LSD passes
     uint32_t split_shift;     // ... and its place in the key
     LocalKey lk;
 };
 
-// Frames whose rasterizers take their tiles longest list first (ws.order):
-// every frame of the plain path and its training variant, and fast-path
-// frames of at most ORDER_MAX_TILES tiles.  The schedule costs a kernel of
-// about 10 us; it pays where the grid's last round of workgroups is a large
-// share of the rasterizer's time: at 1M / 1080p (8160 tiles, about three
-// rounds of the fast rasterizer's workgroups on 256 CUs) it saved 17 us of
-// 123, at 3M / 4K (32400 tiles, about thirteen rounds) 4 us of 279.  The
-// plain rasterizers' tiles take several times longer, so a round always
-// outweighs the kernel there.
-constexpr int32_t ORDER_MAX_TILES = 16384;
+// The rasterizers' schedule (FrameDev::ordered): tiles with long lists first,
+// which pays where the grid's last workgroups are a large share of the
+// rasterizer's time.  Frames that take the split sort get it from the bucket
+// sort, the tiles of the busiest buckets first (ORDER_BUCKETS).  Frames that take the
+// LSD passes, and debug renders, get it by tile from a kernel of its own
+// (ORDER_TILES, up to 10 us): every frame of the plain path and its training
+// variant, and fast-path frames of at most ORDER_MAX_TILES tiles (at 3M / 4K,
+// 32400 tiles, the order was worth 4 us of 279).  Frames of at most
+// ORDER_MIN_TILES tiles have every wave resident at once and take the tiles
+// as they come.  Frame times in us with none, by tile and by bucket: 1M
+// Gaussians at 480x360 (690 tiles) 234, 236, 232, at 960x540 189, 184, 178, at
+// 1024x768 243, 207, 204; 1280x720 197, 187, 181; 1080p 209, 214, 213 fast, 402,
+// 383, 382 plain; training steps at 1080p, kernels only, 892, 858, 855.
+constexpr uint32_t ORDER_NONE = 0, ORDER_TILES = 1, ORDER_BUCKETS = 2;
+constexpr int32_t ORDER_MIN_TILES = 512, ORDER_MAX_TILES = 16384;
 
 // Per visible Gaussian record read by the rasterizer (48 bytes).  The
 // projected mean is split into float hi + lo parts so that tile-local

@@ -123,7 +123,7 @@ void release(rgs_server* s, Workspace* w) {
 // that its baked arguments name real buffers.
 rgs_status capture(rgs_server* s, Workspace* w, const FrameParams& first, hipStream_t st) {
     HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-    w->graph_split = choose_sort(w->fl, first.cam);
+    w->graph_split = choose_sort(w->fl, first.cam, false);
     rgs_status es = enqueue_frame(st, w->fl, first, nullptr, false, w->status, nullptr);
     hipGraph_t g = nullptr;
     hipError_t ce = hipStreamEndCapture(st, &g);
@@ -222,7 +222,7 @@ rgs_status launch(rgs_server* s, Slot& slot, Workspace* w, const rgs_request& r)
     const FrameParams prm = frame_params(&r.camera, r.out_chw, r.scene, r.width, r.height);
     // the graph's sort is the captured camera's: one that sorts otherwise (64-bit
     // keys with a depth interval that does not fit) is launched kernel by kernel
-    w->replayed = choose_sort(w->fl, prm.cam) == w->graph_split && w->exec;
+    w->replayed = choose_sort(w->fl, prm.cam, false) == w->graph_split && w->exec;
     if (w->replayed) {
         ResetArgs ra = reset_args(w->fl.w, w->fl.L.zero_end, w->fl.f, w->fl.path_word, prm);
         void* args[] = {&ra};

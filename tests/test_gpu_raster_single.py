@@ -1,7 +1,7 @@
-"""The rasterizer with a pixel per lane (frames of up to 3072 tiles) against the dual pixel (needs
-an MI355X): a render takes the one, a counting render of the same frame the other, and images,
-and gradients computed from the final T and pair counts that the render left, are the same bit
-for bit."""
+"""The rasterizer with a pixel per lane (frames of up to 3072 tiles) against the dual pixel, and the
+schedules without, and by, buckets against that by tile (needs an MI355X): a render takes the
+first of each, a counting render of the same frame the other, and images, and gradients computed
+from the final T and pair counts that the render left, are the same bit for bit."""
 from __future__ import annotations
 
 import numpy as np
@@ -23,7 +23,7 @@ def R():
 
 @pytest.mark.parametrize("path", ["fast", "fast/hw-exp2", "fast/no-fastexp", "plain", "plain/hw-exp2"])
 @pytest.mark.parametrize("W,H,n", [(16, 16, 257), (21, 30, 1), (37, 61, 3000), (401, 267, 20000), (1024, 768, 60000),
-                                   (1025, 768, 60000)])
+                                   (1025, 768, 60000), (1300, 900, 3000), (1300, 900, 60000), (2064, 2048, 5000)])
 def test_single_pixel_is_the_dual_pixel(R, path, W, H, n):
     import torch
     import paper_2608_15785_amd as rgs
@@ -43,7 +43,8 @@ def test_single_pixel_is_the_dual_pixel(R, path, W, H, n):
         return {k: v.cpu().numpy() for k, v in g.items()}
 
     want = grads() if train else {}
-    img, _ = R.render(ds, cam, path)
+    img = torch.full((3, H, W), float("nan"), device="cuda")
+    R.render(ds, cam, path, out=img)
     torch.cuda.synchronize()
     assert np.array_equal(img.cpu().numpy().view(np.uint32), dual["image"].view(np.uint32))
     got = grads() if train else {}
