@@ -343,6 +343,14 @@ rgs_status rgs_render_static(rgs_ctx* ctx, const rgs_scene* scene, const rgs_cam
 rgs_status rgs_workspace_check(rgs_ctx* ctx, const void* workspace, rgs_frame_stats* stats,
                                int64_t n_gaussians);
 
+/* The same report on the plain frame that this context rendered last into the
+ * workspace, without waiting for the whole frame: its outcome is decided when its
+ * entries are sorted, and the call returns then, while the image is still being
+ * blended on the context's stream.  Errors: as rgs_workspace_check; INVALID when
+ * the context's last frame there was not a plain render, or is not among its last 8
+ * workspaces. */
+rgs_status rgs_frame_outcome(rgs_ctx* ctx, const void* workspace, rgs_frame_stats* stats, int64_t n_gaussians);
+
 /* ---------------------------------------------------------------------------
  * Parity access: render as rgs_render, then copy the frame's intermediates
  * into caller-owned device buffers (any pointer may be NULL).  Synchronous.
@@ -541,9 +549,10 @@ rgs_status rgs_backward_scratch_size(int64_t n, int32_t width, int32_t height, u
  * chain rule through projection and SH in double precision.  Enqueued on the
  * context's stream.  The checks below need the frame's outcome: when the
  * workspace's last frame is the one this context rendered last into it (the
- * usual training loop), the outcome comes from a stamp the frame's last kernel
- * wrote to host-visible memory, and the call only waits for that frame to
- * finish (not for later work on the stream); otherwise it reads the workspace
+ * usual training loop), the outcome comes from a stamp the frame's rasterizer
+ * writes to host-visible memory, and the call only waits for that frame's
+ * entries to be sorted (if the context has changed its stream since, for the
+ * frame's stream); otherwise it reads the workspace
  * header and frame parameters synchronously.  In the first case the kernels
  * still compare the workspace's frame with the caller's: if another context
  * has rendered into the workspace since, they write zero gradients and set bit

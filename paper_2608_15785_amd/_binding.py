@@ -175,6 +175,7 @@ SIGNATURES = [
     ("rgs_render", C.c_int32, [C.c_void_p, C.c_void_p, C.POINTER(CameraC), C.c_int32, C.c_int32,
                                C.c_int32, C.c_void_p, C.c_uint64, C.c_void_p, C.POINTER(FrameStats)]),
     ("rgs_workspace_check", C.c_int32, [C.c_void_p, C.c_void_p, C.POINTER(FrameStats), C.c_int64]),
+    ("rgs_frame_outcome", C.c_int32, [C.c_void_p, C.c_void_p, C.POINTER(FrameStats), C.c_int64]),
     ("rgs_render_debug", C.c_int32, [C.c_void_p, C.c_void_p, C.POINTER(CameraC), C.c_int32, C.c_int32,
                                      C.c_int32, C.c_void_p, C.c_uint64, C.c_void_p, C.POINTER(DebugOut),
                                      C.POINTER(FrameStats)]),
@@ -318,9 +319,11 @@ class Context:
             stream = _torch().cuda.current_stream(device).cuda_stream
         _check(lib.rgs_ctx_create(device, stream, C.byref(h)), "rgs_ctx_create")
         self.handle = h.value
+        self.stream = stream or 0
 
     def set_stream(self, stream: int):
         _check(lib.rgs_ctx_set_stream(self.handle, stream), "rgs_ctx_set_stream")
+        self.stream = stream or 0
 
     def set_debug(self, flags: int):
         """RGS_DEBUG_* flags for this context's renders (DEBUG_SORT_FALLBACK)."""
@@ -481,6 +484,14 @@ def workspace_stats(ctx: Context, workspace, n: int = 0) -> dict:
 def workspace_check(ctx: Context, workspace, n: int = 0) -> dict:
     st = FrameStats()
     _check(lib.rgs_workspace_check(ctx.handle, workspace.data_ptr(), C.byref(st), n), "rgs_workspace_check")
+    return st.as_dict()
+
+
+def frame_outcome(ctx: Context, workspace, n: int = 0) -> dict:
+    """Statistics of the plain frame ``ctx`` rendered last into ``workspace``, as soon as its
+    entries are sorted (the image may still be being blended)."""
+    st = FrameStats()
+    _check(lib.rgs_frame_outcome(ctx.handle, workspace.data_ptr(), C.byref(st), n), "rgs_frame_outcome")
     return st.as_dict()
 
 

@@ -73,9 +73,15 @@ class GaussianRasterizer:
         B.scene_update_plain(self.R.ctx, scene, *(p.detach().float().contiguous() for p in params))
         self._gen += 1
         ws = self.workspace(cam)
+        # On the context's own stream, whose later work waits for the image anyway, the call
+        # returns once the frame's outcome is known; for another stream it waits for the image.
+        ctx = self.R.ctx
+        own = torch.cuda.current_stream(ctx.device).cuda_stream == ctx.stream
         for _ in range(4):
             try:
-                img, _ = B.render(self.R.ctx, scene, cam, self.path, ws, stats=True)
+                img, _ = B.render(ctx, scene, cam, self.path, ws, stats=not own)
+                if own:
+                    B.frame_outcome(ctx, ws, self.n)
                 break
             except B.RGSError as e:
                 if e.status != B.RGS_E_CAPACITY:

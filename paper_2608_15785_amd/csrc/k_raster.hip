@@ -158,6 +158,29 @@ constexpr int FAST_BATCH = 64;                    // entries staged at once, one
 constexpr int FAST_LIST = FAST_BATCH + LIST_UNROLL;
 constexpr uint32_t XCDS = 8;                      // workgroups go to the XCDs round-robin
 
+// The outcome of the frame, decided by now, to the host (FrameStamp).
+__device__ void export_stamp(const WsDev& ws) {
+    const FrameParams* prm = ws.params;
+    FrameStamp* dst = prm->stamp;
+    if (!dst) return;
+    const WsHeader* h = ws.header;
+    dst->n_entries = h->n_entries;
+    dst->n_visible = h->n_visible;
+    dst->capacity = h->capacity;
+    dst->path = h->path;
+    dst->passes = h->passes;
+    dst->overflow = h->overflow;
+    dst->error = h->error;
+    dst->scene_tag = prm->scene_tag;
+    dst->cam_hash = prm->cam_hash;
+    __threadfence_system();
+    __hip_atomic_store(&dst->seq, prm->stamp_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The workgroup that exports the stamp: among the first that the grid starts (256
+// CUs hold 8192), but not one of the longest tiles'.
+constexpr uint32_t STAMP_BLOCK = 4096;
+
 // TRAIN: a path with a backward pass (EXP_PLAIN, and its training variant:
 // EXP_HW2 over the plain path's records, which then hold ln o and the
 // alpha-ellipse box): every render also leaves each pixel's final T and
@@ -184,6 +207,7 @@ __global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint3
     // per region, the batch's entries that can reach it, in depth order
     __shared__ uint32_t s_list4[REGIONS * FAST_LIST / 4];
     uint8_t* s_list = reinterpret_cast<uint8_t*>(s_list4);
+    if (TRAIN && blockIdx.x == min(gridDim.x - 1, STAMP_BLOCK) && threadIdx.x == 0) export_stamp(ws);
     // all parts of a tile on one XCD, whose L2 then serves the records to all
     const uint32_t slot_t = blockIdx.x / (PARTS * XCDS) * XCDS + blockIdx.x % XCDS, part = blockIdx.x / XCDS % PARTS;
     if (slot_t >= (uint32_t)f.n_tiles) return;

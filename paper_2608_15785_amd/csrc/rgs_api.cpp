@@ -211,7 +211,7 @@ struct FrameEvents {
 
 // The last plain frame a context rendered into a workspace.  Its outcome and
 // stamp arrive in stamps[slot] (host-visible memory written by the frame's
-// last kernel), so that the backward pass needs no device read when it
+// rasterizer as it starts), so that the backward pass needs no device read when it
 // differentiates a frame its own context rendered.
 struct FrameRecord {
     const void* ws = nullptr;     // nullptr: slot unused
@@ -779,12 +779,11 @@ static uint64_t camera_hash(const rgs_camera* c, int32_t width, int32_t height) 
     return h;
 }
 
-// Notes the frame just enqueued on ctx's stream into ws.  A plain frame gets
-// a record and a stamp export after its last kernel; any other frame only
-// retires the workspace's record.
-static rgs_status note_frame(rgs_ctx* ctx, const FrameLaunch& fl, const void* ws, uint64_t ws_bytes,
-                             const rgs_scene* sc, const FrameParams& prm, int32_t width, int32_t height,
-                             int32_t path) {
+// Before a frame is enqueued on ctx's stream into ws: retires the workspace's
+// record, and gives a plain frame a record's slot (else *out = -1) and a stamp to
+// export to it.
+static rgs_status reserve_record(rgs_ctx* ctx, const FrameLaunch& fl, const void* ws, FrameParams* prm, int* out) {
+    *out = -1;
     int slot = -1;
     for (int i = 0; i < N_FRAME_RECORDS; ++i)
         if (ctx->records[i].ws == ws) slot = i;
@@ -805,6 +804,17 @@ static rgs_status note_frame(rgs_ctx* ctx, const FrameLaunch& fl, const void* ws
     FrameRecord& r = ctx->records[slot];
     // a stamp export still queued on another stream must not land after this one
     if (r.ws && r.stream != ctx->stream) HIP_TRY(hipStreamSynchronize(r.stream));
+    r = FrameRecord{};
+    prm->stamp = &ctx->stamps[slot];
+    prm->stamp_seq = ++ctx->seq;
+    *out = slot;
+    return RGS_OK;
+}
+
+// Notes the plain frame just enqueued in its slot.
+static void note_frame(rgs_ctx* ctx, int slot, const void* ws, uint64_t ws_bytes, const rgs_scene* sc,
+                       const FrameParams& prm, int32_t width, int32_t height, int32_t path) {
+    FrameRecord& r = ctx->records[slot];
     r.ws = ws;
     r.ws_bytes = ws_bytes;
     r.scene = sc;
@@ -814,15 +824,12 @@ static rgs_status note_frame(rgs_ctx* ctx, const FrameLaunch& fl, const void* ws
     r.height = height;
     r.path = path;
     r.stream = ctx->stream;
-    r.seq = ++ctx->seq;
+    r.seq = prm.stamp_seq;
     r.last_use = ++ctx->uses;
-    launch_export_stamp(ctx->stream, fl.w, &ctx->stamps[slot], r.seq);
-    HIP_TRY(hipGetLastError());
-    return RGS_OK;
 }
 
 // Waits, spinning on host-visible memory, until the stamp of record `slot`
-// has arrived, i.e. its frame has finished on the GPU, and copies it.
+// has arrived, i.e. its frame's entries are sorted, and copies it.
 static rgs_status wait_stamp(rgs_ctx* ctx, int slot, FrameStamp* out) {
     const FrameRecord& r = ctx->records[slot];
     FrameStamp* p = &ctx->stamps[slot];
@@ -840,18 +847,26 @@ static rgs_status wait_stamp(rgs_ctx* ctx, int slot, FrameStamp* out) {
         __builtin_ia32_pause();
 #endif
     }
-    out->n_entries = p->n_entries;
-    out->overflow = p->overflow;
-    out->error = p->error;
-    out->scene_tag = p->scene_tag;
-    out->cam_hash = p->cam_hash;
-    out->seq = r.seq;
+    *out = *p;
     return RGS_OK;
+}
+
+// The header fields that a stamp holds.
+static WsHeader stamp_header(const FrameStamp& st) {
+    WsHeader h{};
+    h.n_entries = st.n_entries;
+    h.n_visible = st.n_visible;
+    h.capacity = st.capacity;
+    h.path = st.path;
+    h.passes = st.passes;
+    h.overflow = st.overflow;
+    h.error = st.error;
+    return h;
 }
 
 FrameParams rgs::frame_params(const rgs_camera* c, float* out, const rgs_scene* sc, int32_t width,
                               int32_t height) {
-    FrameParams p;
+    FrameParams p{};
     p.cam = cam_dev(c);
     p.out = out;
     p.scene_tag = sc ? sc->tag : 0;
@@ -1075,12 +1090,14 @@ static rgs_status render_impl(rgs_ctx* ctx, const rgs_scene* sc, const rgs_camer
         if (s != RGS_OK) return s;
     }
     FrameHooks hooks{hook_mark, hook_after_front, &rh};
-    const FrameParams prm = frame_params(cam, out, sc, W, H);
+    FrameParams prm = frame_params(cam, out, sc, W, H);
+    int slot;
+    s = reserve_record(ctx, fl, ws, &prm, &slot);
+    if (s != RGS_OK) return s;
     choose_sort(fl, prm.cam, dbg != nullptr);
     s = enqueue_frame(st, fl, prm, dbg ? &dd : nullptr, dbg != nullptr, nullptr, (rh.fe || dbg) ? &hooks : nullptr);
     if (s != RGS_OK) return s;
-    s = note_frame(ctx, fl, ws, ws_bytes, sc, prm, W, H, path);
-    if (s != RGS_OK) return s;
+    if (slot >= 0) note_frame(ctx, slot, ws, ws_bytes, sc, prm, W, H, path);
 
     if (dbg) {
         const WsDev& w = fl.w;
@@ -1167,6 +1184,20 @@ extern "C" rgs_status rgs_workspace_check(rgs_ctx* ctx, const void* workspace, r
     return s == RGS_OK ? ok() : s;
 }
 
+extern "C" rgs_status rgs_frame_outcome(rgs_ctx* ctx, const void* workspace, rgs_frame_stats* stats,
+                                        int64_t n_gaussians) {
+    if (!ctx || !workspace) return fail(RGS_E_INVALID, "ctx or workspace is NULL");
+    for (int i = 0; i < N_FRAME_RECORDS; ++i) {
+        if (ctx->records[i].ws != workspace) continue;
+        FrameStamp st;
+        rgs_status s = wait_stamp(ctx, i, &st);
+        if (s != RGS_OK) return s;
+        s = header_status(stamp_header(st), stats, n_gaussians);
+        return s == RGS_OK ? ok() : s;
+    }
+    return fail(RGS_E_INVALID, "the context's last frames into the workspace were not plain renders");
+}
+
 extern "C" rgs_status rgs_scene_update_plain(rgs_ctx* ctx, rgs_scene* sc, const rgs_device_params* p) {
     if (!ctx || !sc || !p) return fail(RGS_E_INVALID, "rgs_scene_update_plain: NULL argument");
     if (!(sc->formats & RGS_FMT_PLAIN)) return fail(RGS_E_INVALID, "scene has no plain format");
@@ -1232,13 +1263,10 @@ extern "C" rgs_status rgs_render_backward(rgs_ctx* ctx, const rgs_scene* scene, 
         FrameStamp st;
         s = wait_stamp(ctx, slot, &st);
         if (s != RGS_OK) return s;
-        WsHeader h{};
-        h.n_entries = st.n_entries;
-        h.overflow = st.overflow;
-        h.error = st.error;
-        h.capacity = fl.f.capacity;
-        s = header_status(h, nullptr, scene->n);
+        s = header_status(stamp_header(st), nullptr, scene->n);
         if (s != RGS_OK) return s;
+        // on another stream than the frame's nothing orders the kernels after it
+        if (r->stream != ctx->stream) HIP_TRY(hipStreamSynchronize(r->stream));
         path_word = (uint32_t)r->path;
     } else {                        // otherwise the workspace itself is asked
         WsHeader h;

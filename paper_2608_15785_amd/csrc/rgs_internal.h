@@ -143,6 +143,9 @@ struct FrameParams {
     // of the camera and the image size.
     uint64_t scene_tag;
     uint64_t cam_hash;
+    // A plain frame's stamp in host-visible memory, or null, and its sequence number.
+    struct FrameStamp* stamp;
+    uint64_t stamp_seq;
 };
 static_assert(sizeof(FrameParams) <= 256, "frame parameters fit one 256-byte slot");
 
@@ -533,12 +536,17 @@ struct FrameStatus {
     uint64_t out;        // output address the frame used (checks replayed parameters)
 };
 
-// A plain render's outcome and stamp, copied by the frame's last kernel into
-// host-visible memory of the rendering context: the backward pass learns
-// whether its frame overflowed, and that the frame is the one it expects,
-// without reading the device.  seq is written last, after a system fence.
+// A plain render's outcome and stamp, copied by its rasterizer into host-visible
+// memory of the rendering context: the backward pass learns whether its frame
+// overflowed, and that the frame is the one it expects, without reading the
+// device.  Nothing after the sort changes the outcome, so one workgroup of the
+// rasterizer's first writes it as it starts, and the host goes on while
+// the frame is blended (a kernel of its own after the frame took 5 us, and the
+// host work between a forward and a backward call the GPU's time).  seq is
+// written last, after a system fence.
 struct FrameStamp {
     uint64_t n_entries;
+    uint32_t n_visible, capacity, path, passes;
     uint32_t overflow, error;
     uint64_t scene_tag, cam_hash;
     uint64_t seq;
@@ -549,7 +557,6 @@ ResetArgs reset_args(const WsDev& ws, uint64_t zero_bytes, const FrameDev& f, ui
 void launch_reset(hipStream_t s, const ResetArgs& a);
 const void* reset_kernel();          // host handle of the reset kernel (graph node lookup)
 void launch_export_status(hipStream_t s, const WsDev& ws, FrameStatus* dst);
-void launch_export_stamp(hipStream_t s, const WsDev& ws, FrameStamp* dst, uint64_t seq);
 void launch_preprocess_plain(hipStream_t s, const PlainSceneDev& sc, const FrameDev& f,
                              const WsDev& ws, const DebugDev* dbg, bool train);
 void launch_duplicate(hipStream_t s, int64_t n, const FrameDev& f, const WsDev& ws, uint32_t fe_blocks, uint32_t fe_per,
