@@ -539,29 +539,16 @@ __device__ inline void sh_basis_double(double x, double y, double z, double* Y) 
     Y[15] = -c3a * x * (xx - 3.0 * yy);
 }
 
-constexpr int GRAD_THREADS = 128;
+constexpr int GRAD_THREADS = 64;
 
-// Gradients of Gaussian i: sum of its partials, then the chain rule.  The SH
-// gradients go to dsh (48 floats, LDS), the rest straight to global memory.
-// refused: the workspace holds another frame than the caller's; all gradients are zero.
-__device__ inline void grad_one(const PlainSceneDev& sc, const CamDev& cam, const WsDev& ws,
-                                const float4* __restrict__ partial, const GradOut& go, int64_t i,
-                                float* dsh, bool lno_opacity, bool refused) {
-    const uint32_t count = refused ? 0u : ws.counts[i];
+// Gradients of Gaussian i from the sum of its count partials by the chain rule.
+// The SH gradients go to dsh (48 floats, LDS), the rest straight to global memory.
+__device__ inline void grad_one(const PlainSceneDev& sc, const CamDev& cam, const WsDev& ws, const float (&acc)[9],
+                                uint32_t count, const GradOut& go, int64_t i, float4* dsh, bool lno_opacity) {
     double gs[9];
 #pragma unroll
     for (int c = 0; c < 9; ++c) gs[c] = 0.0;
     if (count) {
-        const float4* pp = partial + 3ull * ws.offsets[i];
-        float acc[9];
-#pragma unroll
-        for (int c = 0; c < 9; ++c) acc[c] = 0.0f;
-        for (uint32_t q = 0; q < count; ++q, pp += 3) {
-            const float4 p0 = pp[0], p1 = pp[1], p2 = pp[2];
-            acc[0] += p0.x; acc[1] += p0.y; acc[2] += p0.z; acc[3] += p0.w;
-            acc[4] += p1.x; acc[5] += p1.y; acc[6] += p1.z; acc[7] += p1.w;
-            acc[8] += p2.x;
-        }
 #pragma unroll
         for (int c = 0; c < 9; ++c) gs[c] = acc[c];
         if (lno_opacity) {      // dL/do = dL/d(ln o) / o
@@ -582,7 +569,7 @@ __device__ inline void grad_one(const PlainSceneDev& sc, const CamDev& cam, cons
 #pragma unroll
         for (int k = 0; k < 4; ++k) dq[k] = 0.0f;
         go.opacity[i] = 0.0f;
-        for (int k = 0; k < 48; ++k) dsh[k] = 0.0f;
+        for (int k = 0; k < 12; ++k) dsh[k] = make_float4(0.f, 0.f, 0.f, 0.f);
         return;
     }
     const float* P = sc.base;
@@ -702,14 +689,18 @@ __device__ inline void grad_one(const PlainSceneDev& sc, const CamDev& cam, cons
     const double ux = vx / vlen, uy = vy / vlen, uz = vz / vlen;
     double Y[16], gY[16];
     sh_basis_double(ux, uy, uz, Y);
+#pragma unroll
     for (int k = 0; k < 16; ++k) {
-        double acc = 0.0;
-        for (int c = 0; c < 3; ++c) {
-            dsh[3 * k + c] = (float)(Y[k] * ga[c]);
-            acc += (double)P[(P_SH0 + 3 * k + c) * np + i] * ga[c];
-        }
-        gY[k] = acc;
+        double dot = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) dot += (double)P[(P_SH0 + 3 * k + c) * np + i] * ga[c];
+        gY[k] = dot;
     }
+#pragma unroll
+    for (int q = 0; q < 12; ++q)
+        dsh[q] = make_float4((float)(Y[4 * q / 3] * ga[4 * q % 3]), (float)(Y[(4 * q + 1) / 3] * ga[(4 * q + 1) % 3]),
+                             (float)(Y[(4 * q + 2) / 3] * ga[(4 * q + 2) % 3]),
+                             (float)(Y[(4 * q + 3) / 3] * ga[(4 * q + 3) % 3]));
     double gdx, gdy, gdz;
     sh_basis_backward(ux, uy, uz, gY, gdx, gdy, gdz);
     const double dot = ux * gdx + uy * gdy + uz * gdz;
@@ -719,19 +710,106 @@ __device__ inline void grad_one(const PlainSceneDev& sc, const CamDev& cam, cons
     for (int k = 0; k < 3; ++k) dm[k] = (float)gmu[k];
 }
 
+// The partials of a workgroup's Gaussians follow one another in emission order.
+// They pass through LDS in spans of GRAD_STAGE, read as one run of 16-byte loads
+// while the span before is added, and each thread adds its Gaussian's in order,
+// four rows' LDS reads in flight.  Bound by HBM at 1M Gaussians (planes, records,
+// partials and gradients: 620 MB, 120 us as a copy) and on small scenes by the
+// latency of the partials.  Measured, 1M / 1080p and 20K at 401x267 (us): each
+// thread reading its own rows from global memory, and SH rows of 48 floats in LDS
+// (16-way bank conflicts), 165 and 47; through LDS 138 and 44; four rows at a
+// time 135 and 33; the next span's loads ahead 123 and 24; workgroups of 64
+// threads instead of 128 124 and 22.
+constexpr int GRAD_ROW4 = 13;                  // a Gaussian's SH gradients in LDS: 48 floats and a pad of 4
+constexpr uint32_t GRAD_STAGE = GRAD_THREADS * GRAD_ROW4 / 3;
+
 template <bool LNO>
 __global__ __launch_bounds__(GRAD_THREADS) void k_grad_gaussian(PlainSceneDev sc, CamDev cam, WsDev ws,
                                                                 const float4* __restrict__ partial,
                                                                 GradOut go, FrameKey key) {
-    __shared__ float s_sh[GRAD_THREADS * 48];
+    __shared__ float4 s_buf[GRAD_THREADS * GRAD_ROW4];
+    __shared__ uint32_t s_lo[GRAD_THREADS / 64], s_hi[GRAD_THREADS / 64];
     const int64_t first = (int64_t)blockIdx.x * GRAD_THREADS;
     const int64_t i = first + threadIdx.x;
+    // the workspace holds another frame than the caller's: all gradients are zero
     const bool refused = ws.params->scene_tag != key.scene_tag || ws.params->cam_hash != key.cam_hash;
-    if (i < sc.n) grad_one(sc, cam, ws, partial, go, i, s_sh + 48 * threadIdx.x, LNO, refused);
+    const uint32_t count = i < sc.n && !refused ? ws.counts[i] : 0u;
+    const uint32_t begin = count ? ws.offsets[i] : 0u, end = begin + count;
+    uint32_t lo = count ? begin : 0xffffffffu, hi = end;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
+    }
+    if (lane_id() == 0) {
+        s_lo[threadIdx.x / 64] = lo;
+        s_hi[threadIdx.x / 64] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < GRAD_THREADS / 64; ++w) {
+        lo = min(lo, s_lo[w]);
+        hi = max(hi, s_hi[w]);
+    }
+    float acc[9];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) acc[c] = 0.0f;
+    // the next span's loads are in flight while this one is added
+    float4 next[GRAD_ROW4];
+    auto fetch = [&](uint32_t c0) {
+        const uint32_t words = c0 < hi ? 3 * min(GRAD_STAGE, hi - c0) : 0;
+        const float4* src = partial + 3ull * c0;
+#pragma unroll
+        for (uint32_t k = 0; k < GRAD_ROW4; ++k) {
+            const uint32_t q = k * GRAD_THREADS + threadIdx.x;
+            next[k] = q < words ? src[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    fetch(lo);
+    for (uint32_t c0 = lo; c0 < hi; c0 += GRAD_STAGE) {
+#pragma unroll
+        for (uint32_t k = 0; k < GRAD_ROW4; ++k) s_buf[k * GRAD_THREADS + threadIdx.x] = next[k];
+        __syncthreads();
+        if (c0 + GRAD_STAGE < hi) fetch(c0 + GRAD_STAGE);
+        const uint32_t e1 = min(end, c0 + GRAD_STAGE);
+        uint32_t e = max(begin, c0);
+        for (; e + 4 <= e1; e += 4) {
+            const float4* p = s_buf + 3 * (e - c0);
+            float4 p0[4], p1[4];
+            float p2[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                p0[u] = p[3 * u];
+                p1[u] = p[3 * u + 1];
+                p2[u] = p[3 * u + 2].x;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                acc[0] += p0[u].x; acc[1] += p0[u].y; acc[2] += p0[u].z; acc[3] += p0[u].w;
+                acc[4] += p1[u].x; acc[5] += p1[u].y; acc[6] += p1[u].z; acc[7] += p1[u].w;
+                acc[8] += p2[u];
+            }
+        }
+        for (; e < e1; ++e) {
+            const float4* p = s_buf + 3 * (e - c0);
+            const float4 p0 = p[0], p1 = p[1];
+            acc[0] += p0.x; acc[1] += p0.y; acc[2] += p0.z; acc[3] += p0.w;
+            acc[4] += p1.x; acc[5] += p1.y; acc[6] += p1.z; acc[7] += p1.w;
+            acc[8] += p[2].x;
+        }
+        __syncthreads();
+    }
+    if (i < sc.n) grad_one(sc, cam, ws, acc, count, go, i, s_buf + GRAD_ROW4 * threadIdx.x, LNO);
     __syncthreads();
     const int64_t rows = sc.n - first < GRAD_THREADS ? sc.n - first : GRAD_THREADS;
     float* dst = go.sh + 48 * first;
-    for (int64_t k = threadIdx.x; k < rows * 48; k += GRAD_THREADS) dst[k] = s_sh[k];
+    if (reinterpret_cast<uintptr_t>(dst) % 16 == 0) {
+        float4* dst4 = reinterpret_cast<float4*>(dst);
+        for (int k = threadIdx.x; k < (int)rows * 12; k += GRAD_THREADS) dst4[k] = s_buf[k / 12 * GRAD_ROW4 + k % 12];
+    } else {
+        const float* buf = reinterpret_cast<const float*>(s_buf);
+        for (int k = threadIdx.x; k < (int)rows * 48; k += GRAD_THREADS) dst[k] = buf[k / 48 * 4 * GRAD_ROW4 + k % 48];
+    }
 }
 
 void launch_grad_gaussian(hipStream_t s, const PlainSceneDev& sc, const CamDev& cam, const WsDev& ws,

@@ -1,6 +1,7 @@
-"""The backward kernel's lists and rows of sums at their edges (needs an MI355X): tiles of no, one,
-a batch's and more entries, and entries that reach all sixteen regions of a tile, so that a batch's
-rows hold fewer entries than it stages.  The image-space sums against the float64 adjoint, to 1e-3 of
+"""The backward kernels' lists and rows of sums at their edges (needs an MI355X): tiles of no, one,
+a batch's and more entries, entries that reach all sixteen regions of a tile, so that a batch's
+rows hold fewer entries than it stages, and Gaussians of more partials than a workgroup of the
+per-Gaussian pass stages.  The image-space sums against the float64 adjoint, to 1e-3 of
 the sum of their terms' magnitudes and the slack of near-threshold decisions, as in the backward
 pass's other tests; a second run is the same bit for bit."""
 from __future__ import annotations
@@ -26,9 +27,10 @@ def R():
 
 
 @pytest.mark.parametrize("path", PATHS)
-@pytest.mark.parametrize("n,log_scale", [(1, -3.0), (65, -0.5), (400, -0.7), (900, -4.5)])
-@pytest.mark.parametrize("W,H", [(16, 16), (50, 35)])
-def test_lists(R, n, log_scale, W, H, path):
+@pytest.mark.parametrize("W,H,n,log_scale", [(W, H, n, s) for W, H in ((16, 16), (50, 35))
+                                             for n, s in ((1, -3.0), (65, -0.5), (400, -0.7), (900, -4.5))]
+                         + [(401, 267, 1, 0.4), (401, 267, 65, 0.2)])
+def test_lists(R, W, H, n, log_scale, path):
     sc = wl.make_scene(n, 1.0, log_scale, 0.3, 100 + n)
     if n > 1:
         sc.opacity[:] = np.clip(sc.opacity * 0.08, 0.006, 1.0)     # few pixels stop: long lists
@@ -49,3 +51,31 @@ def test_lists(R, n, log_scale, W, H, path):
     again = gpu_backward(R, sc, cam, dimg, path)
     for k in ("means", "scales", "quats", "opacity", "sh", "screen"):
         assert np.array_equal(g[k], again[k]), k
+
+
+def test_sh_gradients_at_an_odd_address(R):
+    """The SH gradients leave in 16-byte stores where the caller's buffer allows them."""
+    import ctypes as C
+    import torch
+    import paper_2608_15785_amd as rgs
+    from paper_2608_15785_amd import _binding as B
+    sc = wl.make_scene(131, 1.0, -2.0, 0.4, 7)
+    cam = wl.config_camera("small", width=64, height=48)
+    dimg = torch.ones((3, 48, 64), device="cuda")
+    ds = R.upload(sc, ("plain",))
+    R.render(ds, cam, "plain")
+    ws = R.workspace(sc.n, 64, 48, "plain")
+    want = rgs.render_backward(R.ctx, ds, cam, ws, dimg)
+    g = {k: torch.empty_like(v) for k, v in want.items()}
+    sh = torch.full((sc.n * 48 + 2,), float("nan"), device="cuda")
+    scratch = torch.empty(rgs.backward_scratch_size(sc.n, 64, 48, ws.numel()), dtype=torch.uint8, device="cuda")
+    gr = B.Grads(d_means=g["means"].data_ptr(), d_scales=g["scales"].data_ptr(), d_quats=g["quats"].data_ptr(),
+                 d_opacity=g["opacity"].data_ptr(), d_sh=sh.data_ptr() + 4, d_screen=None, scratch=scratch.data_ptr(),
+                 scratch_bytes=scratch.numel())
+    cc = rgs.camera_struct(cam)
+    assert B.lib.rgs_render_backward(R.ctx.handle, ds.handle, C.byref(cc), 64, 48, dimg.data_ptr(), ws.data_ptr(),
+                                     ws.numel(), C.byref(gr)) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(sh[1:-1], want["sh"].reshape(-1))
+    assert torch.isnan(sh[0]) and torch.isnan(sh[-1])
+    ds.release()
