@@ -39,8 +39,14 @@ constexpr int FE_TILE = FE_THREADS * FE_ITEMS;   // most Gaussians a block takes
 // fills a CU) is spread evenly over up to that many, at least FE_MIN_PER_BLOCK
 // Gaussians each: a 1M scene becomes 253 workgroups of 3968 instead of 245 of
 // 4096, which left 11 CUs idle.  Larger scenes take FE_TILE per workgroup.
+// On small scenes the FP64 projection of a full workgroup is what takes time (16
+// waves on one CU), so they are spread down to 256 Gaussians: front end (duplication)
+// of 2.5K Gaussians at 250x170 15.6 -> 11.4 us, of 10K at 256x256 17.6 -> 12.3
+// (12.9 -> 10.6), of 20K at 401x267 (17.8 -> 13.3), against 1024; 128 the same, 64
+// 13.5 (12.2) at 10K.  More, smaller workgroups throughout add more digit
+// counts to the shared ones: 512 threads and 2048 Gaussians 61 us at 1M, against 50.
 constexpr uint32_t FE_CU_QUANTUM = 256;
-constexpr uint32_t FE_MIN_PER_BLOCK = 1024;
+constexpr uint32_t FE_MIN_PER_BLOCK = 256;
 inline void fe_block_shape(int64_t n, uint32_t& blocks, uint32_t& per) {
     const uint64_t un = n > 0 ? (uint64_t)n : 1u;
     uint64_t b = (un + FE_TILE - 1) / FE_TILE;
