@@ -583,7 +583,11 @@ static void make_layout(int64_t n, const rgs_plan& p, int32_t path, uint64_t cap
         const uint64_t lsd = 2 * ((uint64_t)L.lsd_rows + (L.lsd_rows + SORT_GROUP - 1) / SORT_GROUP) * RADIX;
         const uint64_t split = p.b_t < SPLIT_MIN_BT ? 0
             : ((uint64_t)L.split_rows + (L.split_rows + SORT_GROUP - 1) / SORT_GROUP) << (p.b_t < SPLIT_WIDE_BT ? 8 : 10);
-        off = align256(off + std::max(lsd, split) * 4);
+        // the split pass's look-back words: with 64-bit keys the second value array is
+        // free while they are in use
+        const bool in_vals = L.key_bytes == 8 && split <= capacity;
+        L.split_state = in_vals ? L.vals_b : off;
+        off = align256(off + (in_vals ? lsd : std::max(lsd, split)) * 4);
     }
     L.bases = off;
     off = align256(off + (uint64_t)(SPLIT_DIGITS_MAX + 1) * 4);
@@ -955,6 +959,8 @@ bool rgs::choose_sort(FrameLaunch& fl, const CamDev& cam, bool debug) {
         f.ordered = ORDER_BUCKETS;
     }
     const uint32_t rows = split ? fl.L.split_rows : fl.L.lsd_rows;
+    fl.w.sort_state = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(fl.w.header) - fl.L.header +
+                                                  (split ? fl.L.split_state : fl.L.sort_state));
     fl.w.sort_rows = rows;
     fl.w.sort_groups = (rows + SORT_GROUP - 1) / SORT_GROUP;
     return split;

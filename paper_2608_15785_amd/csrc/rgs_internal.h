@@ -103,8 +103,9 @@ constexpr int RADIX = 1 << RADIX_BITS;
 constexpr int MAX_PASSES = 8;
 // Copies of the digit histogram that the histogram kernel's blocks spread
 // their atomics over (block b adds into copy b % HIST_COPIES): device-scope
-// atomics on one address serialise at about 11 ns each.
-constexpr int HIST_COPIES = 16;
+// atomics on one address serialise at about 11 ns each (4 copies: the front end of
+// 3M Gaussians at 4K 1 us slower; 8, 16 and 32: the same).
+constexpr int HIST_COPIES = 8;
 
 // Plain-format planes (float32, one per scalar, each n_pad long).
 // P_LNO holds ln o rounded to float32 (computed in double on the host); only
@@ -233,7 +234,7 @@ struct WsLayout {
     uint64_t order;
     uint64_t records, counts, rects, depths, offsets, masks;
     uint64_t keys_a, keys_b, vals_a, vals_b;
-    uint64_t hist, sort_state, bases;
+    uint64_t hist, sort_state, split_state, bases;
     uint64_t t_final, n_proc, n_blend;
     uint64_t total;
     uint64_t capacity;
