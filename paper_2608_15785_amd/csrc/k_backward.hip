@@ -125,6 +125,39 @@ __device__ inline void group_sums(const float (&g)[9], float (&o)[5]) {
         : "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "v"(g[4]), "v"(g[5]), "v"(g[6]), "v"(g[7]), "v"(g[8]));
 }
 
+// The same over the sixteen lanes of each row of the wave: lanes 16 q .. 16 q + 7
+// receive the sums of g[0..3] of row q, lanes 16 q + 8 .. 16 q + 15 those of g[4..7].
+__device__ inline void row_sums(const float (&g)[9], float (&o)[5]) {
+    asm volatile(
+        "s_nop 4\n\t"
+        "v_add_f32_dpp %4, %13, %13 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %5, %5 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %6, %6 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %7, %7 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %8, %8 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %9, %9 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %10, %10 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %11, %11 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %3, %12, %12 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %4, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %3, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %3, %3 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4])
+        : "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "v"(g[4]), "v"(g[5]), "v"(g[6]), "v"(g[7]), "v"(g[8]));
+}
+
 // Position, in emission order, of Gaussian g's entry for tile (tx, ty).
 __device__ inline uint64_t emission_pos(const WsDev& ws, uint32_t g, uint32_t tx, uint32_t ty) {
     const uint64_t rc = ws.rects[g];
@@ -199,7 +232,8 @@ __device__ inline void pair_adjoint(float P, float dx, float dy, float cr, float
 
 // The backward pass in the forward pass's layout: wave w owns the half-tile of
 // rows 8 w .. 8 w + 7, the eight lanes of a group own a 4x4 region, a dual pixel
-// each, and walk the region's own list, so that up to eight entries are
+// each (with PIX = 1 four waves of four rows, sixteen lanes a region, a pixel
+// each), and walk the region's own list, so that up to eight entries are
 // evaluated at once and about 2.3 pixels per blended one (a wave per tile with
 // four pixels per lane and skipped bands of four rows: about 3.5; half-tile
 // lists: 4.8).  Staging, folding and culling are the forward's (rgs_fold.h), and
@@ -224,24 +258,25 @@ __device__ inline void pair_adjoint(float P, float dx, float dy, float cr, float
 // two passes over the ballots; 318, 112, 267 as it stands (one entry at a
 // time: 335, 119, 265; four: 348, 108, 291; the next batch's records loaded
 // ahead: no change).
-constexpr int BWD_THREADS = 128;           // wave w: the half-tile of rows 8 w .. 8 w + 7
 constexpr int BWD_BATCH = 64;              // entries staged at once, one per lane of the staging wave
 constexpr int BWD_UNROLL = 2;              // entries of a list taken at once; divides 4
 constexpr int BWD_REGIONS = 16;            // 4x4 pixels each
 constexpr uint32_t BWD_ROWS = 304;         // (entry, region) sums of a batch; at least 16, one entry's
 
-template <bool TRAIN>
-__global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, WsDev ws,
+// PIX: pixels per lane, 2 (wave w: rows 8 w .. 8 w + 7) or 1 (four waves, wave w rows 4 w .. 4 w + 3).
+template <bool TRAIN, int PIX>
+__global__ __launch_bounds__(256 / PIX, 4) void k_raster_backward(FrameDev f, WsDev ws,
                                                                  const uint32_t* __restrict__ vals,
                                                                  const float* __restrict__ dimg,
                                                                  float4* __restrict__ partial, FrameKey key) {
+    constexpr uint32_t THREADS = 256 / PIX, REGION_LANES = 16 / PIX, WAVE_REGIONS = 4 * PIX;
     // the batch's entries: (u, v, A, B), (C, o, r, g), (b); TRAIN: (C1, C2, C3, C4), (C5, C6, r, g), (b, u, v)
     __shared__ float4 s_a[BWD_BATCH], s_b[BWD_BATCH], s_c[BWD_BATCH];
     // per region, the slots of the entries that reach it, back to front, and the rows of their sums
     __shared__ uint32_t s_list4[BWD_REGIONS][BWD_BATCH / 4];
     __shared__ uint32_t s_count[BWD_REGIONS], s_base[2][BWD_REGIONS];     // (s_base: by staging wave)
     __shared__ uint32_t s_last[BWD_REGIONS];     // end of the entries that a pixel of the region may have blended
-    __shared__ uint32_t s_kept, s_longest[2];
+    __shared__ uint32_t s_kept, s_longest[THREADS / 64];
     __shared__ float4 s_row[BWD_ROWS][2];        // sums of one entry over one region
     __shared__ float s_row8[BWD_ROWS];
     if (!frame_matches(ws, key)) return;
@@ -250,25 +285,27 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, 
     const uint32_t tx = tile % (uint32_t)f.tiles_x, ty = tile / (uint32_t)f.tiles_x;
     const uint32_t tid = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
-    const uint32_t region = tid / 8;
+    const uint32_t region = tid / REGION_LANES;
     const uint32_t lx = (region % 4) * 4 + lane % 4;
-    const uint32_t ly = (region / 4) * 4 + (lane / 4 % 2) * 2;
+    const uint32_t ly = (region / 4) * 4 + (PIX == 1 ? lane / 4 % 4 : lane / 4 % 2 * 2);
     const uint32_t px = tx * TILE + lx, py = ty * TILE + ly;
     const uint32_t start = ws.ranges[2 * tile], end = ws.ranges[2 * tile + 1];
     // as the forward pass: tile-centre coordinates, or relative to the tile's corner
     constexpr float CENTRE = TRAIN ? 7.5f : 0.0f;
     const float ox = (float)(tx * TILE) + CENTRE, oy = (float)(ty * TILE) + CENTRE;
-    const float x = (float)lx - CENTRE, y = (float)ly - CENTRE, y1 = y + 1.0f;
+    // the dual pixel's rows; with one pixel per lane it is the first or (odd) the second of them
+    const bool odd = PIX == 1 && ly % 2 != 0;
+    const float x = (float)lx - CENTRE, y = (float)(ly / 2 * 2) - CENTRE, y1 = y + 1.0f;
     const float x2 = x * x, xy = x * y, y2 = y * y, y21 = fmaf(2.0f, y, 1.0f);
     const uint64_t plane = (uint64_t)f.width * f.height;
     const float bg0 = ws.params->cam.bg[0], bg1 = ws.params->cam.bg[1], bg2 = ws.params->cam.bg[2];
 
     // per pixel: T after the pairs behind, dL/dC, DS = dL/dC . (colour behind + T_final
     // bg), and the end of the pairs [start, last) that may have been blended
-    float T[2], d[2][3], DS[2];
-    uint32_t last[2];
+    float T[PIX], d[PIX][3], DS[PIX];
+    uint32_t last[PIX], rlast = start;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < PIX; ++k) {
         T[k] = 1.0f;
         last[k] = start;
         d[k][0] = d[k][1] = d[k][2] = 0.0f;
@@ -282,11 +319,11 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, 
             d[k][2] = dimg[2 * plane + o];
         }
         DS[k] = T[k] * fmaf(d[k][0], bg0, fmaf(d[k][1], bg1, d[k][2] * bg2));
+        rlast = max(rlast, last[k]);
     }
-    uint32_t rlast = max(last[0], last[1]);
 #pragma unroll
-    for (int off = 1; off < 8; off <<= 1) rlast = max(rlast, (uint32_t)__shfl_xor((int)rlast, off));
-    if (lane % 8 == 0) s_last[region] = rlast;
+    for (uint32_t off = 1; off < REGION_LANES; off <<= 1) rlast = max(rlast, (uint32_t)__shfl_xor((int)rlast, off));
+    if (lane % REGION_LANES == 0) s_last[region] = rlast;
     __syncthreads();
     uint32_t tile_last = start;
 #pragma unroll
@@ -355,7 +392,9 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, 
         }
         my_mask = mask;
         const uint64_t kept = __ballot(below + (uint32_t)__popc(mask) <= BWD_ROWS);
-        uint32_t base = 0, longest0 = 0, longest1 = 0;
+        uint32_t base = 0, longest[THREADS / 64];
+#pragma unroll
+        for (uint32_t w = 0; w < THREADS / 64; ++w) longest[w] = 0;
 #pragma unroll
         for (int r = 0; r < BWD_REGIONS; ++r) {
             const uint32_t n = (uint32_t)__popcll(m[r] & kept);
@@ -364,13 +403,12 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, 
                 s_base[wave][r] = base;
             }
             base += n;
-            if (r < 8) longest0 = max(longest0, n);
-            else longest1 = max(longest1, n);
+            longest[r / WAVE_REGIONS] = max(longest[r / WAVE_REGIONS], n);
         }
         if (lane == 0) {
             s_kept = min(cnt, (uint32_t)__popcll(kept));
-            s_longest[0] = longest0;
-            s_longest[1] = longest1;
+#pragma unroll
+            for (uint32_t w = 0; w < THREADS / 64; ++w) s_longest[w] = longest[w];
         }
     };
 
@@ -382,32 +420,40 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, 
         const uint32_t longest = __builtin_amdgcn_readfirstlane(s_longest[wave]);
         const uint32_t n = s_count[region], row0 = s_base[stager][region];
         // slots from which each pixel may have blended
-        const int lim0 = (int)(b_end - last[0]), lim1 = (int)(b_end - last[1]);
+        int lim[PIX];
+#pragma unroll
+        for (int i = 0; i < PIX; ++i) lim[i] = (int)(b_end - last[i]);
         for (uint32_t k0 = 0; k0 < longest; k0 += BWD_UNROLL) {
             const uint32_t word = s_list4[region][k0 / 4] >> (8 * (k0 % 4));
             uint32_t slot[BWD_UNROLL];
             float4 a[BWD_UNROLL], m[BWD_UNROLL];
-            float P0[BWD_UNROLL], P1[BWD_UNROLL];      // exponents; plain: e^p
-            bool pass0[BWD_UNROLL], pass1[BWD_UNROLL];
+            float P[BWD_UNROLL][PIX];          // exponents; plain: e^p
+            bool pass[BWD_UNROLL][PIX];
 #pragma unroll
             for (int u = 0; u < BWD_UNROLL; ++u) {
                 slot[u] = (word >> (8 * u)) % BWD_BATCH;
                 a[u] = s_a[slot[u]];
                 m[u] = s_b[slot[u]];
             }
+            auto row_of = [&](int i) { return i == 1 || odd ? y1 : y; };
 #pragma unroll
             for (int u = 0; u < BWD_UNROLL; ++u) {
                 const int at = k0 + u < n ? (int)slot[u] : -0x7fffffff;
                 if (TRAIN) {
-                    folded_exponents(a[u], m[u].x, m[u].y, x, y, x2, xy, y2, y21, P0[u], P1[u]);
-                    pass0[u] = at >= lim0 && P0[u] >= -LOG2_255F;
-                    pass1[u] = at >= lim1 && P1[u] >= -LOG2_255F;
+                    float P0, P1;
+                    folded_exponents(a[u], m[u].x, m[u].y, x, y, x2, xy, y2, y21, P0, P1);
+                    P[u][0] = odd ? P1 : P0;
+                    if (PIX == 2) P[u][PIX - 1] = P1;
+#pragma unroll
+                    for (int i = 0; i < PIX; ++i) pass[u][i] = at >= lim[i] && P[u][i] >= -LOG2_255F;
                 } else {
-                    const float dx = x - a[u].x, dy0 = y - a[u].y, dy1 = y1 - a[u].y;
-                    P0[u] = expf(fmaf(-0.5f, fmaf(a[u].z * dx, dx, m[u].x * dy0 * dy0), -a[u].w * dx * dy0));
-                    P1[u] = expf(fmaf(-0.5f, fmaf(a[u].z * dx, dx, m[u].x * dy1 * dy1), -a[u].w * dx * dy1));
-                    pass0[u] = at >= lim0 && fminf(ALPHA_MAX, m[u].y * P0[u]) >= ALPHA_MIN;
-                    pass1[u] = at >= lim1 && fminf(ALPHA_MAX, m[u].y * P1[u]) >= ALPHA_MIN;
+                    const float dx = x - a[u].x;
+#pragma unroll
+                    for (int i = 0; i < PIX; ++i) {
+                        const float dy = row_of(i) - a[u].y;
+                        P[u][i] = expf(fmaf(-0.5f, fmaf(a[u].z * dx, dx, m[u].x * dy * dy), -a[u].w * dx * dy));
+                        pass[u][i] = at >= lim[i] && fminf(ALPHA_MAX, m[u].y * P[u][i]) >= ALPHA_MIN;
+                    }
                 }
             }
 #pragma unroll
@@ -418,22 +464,26 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, 
                 if (TRAIN) {
                     const float4 c = s_c[slot[u]];
                     const float dx = x - c.y;
-                    if (pass0[u]) pair_adjoint(P0[u], dx, y - c.z, m[u].z, m[u].w, c.x, d[0], T[0], DS[0], g);
-                    if (pass1[u]) pair_adjoint(P1[u], dx, y1 - c.z, m[u].z, m[u].w, c.x, d[1], T[1], DS[1], g);
+#pragma unroll
+                    for (int i = 0; i < PIX; ++i)
+                        if (pass[u][i])
+                            pair_adjoint(P[u][i], dx, row_of(i) - c.z, m[u].z, m[u].w, c.x, d[i], T[i], DS[i], g);
                 } else {
                     const float cb = s_c[slot[u]].x;
                     const float dx = x - a[u].x;
-                    if (pass0[u])
-                        pair_adjoint_plain(P0[u], m[u].y * P0[u], dx, y - a[u].y, a[u], m[u], cb, d[0], T[0], DS[0], g);
-                    if (pass1[u])
-                        pair_adjoint_plain(P1[u], m[u].y * P1[u], dx, y1 - a[u].y, a[u], m[u], cb, d[1], T[1], DS[1], g);
+#pragma unroll
+                    for (int i = 0; i < PIX; ++i)
+                        if (pass[u][i])
+                            pair_adjoint_plain(P[u][i], m[u].y * P[u][i], dx, row_of(i) - a[u].y, a[u], m[u], cb, d[i],
+                                               T[i], DS[i], g);
                 }
                 float o[5];
-                group_sums(g, o);
-                if (k0 + u < n && lane % 4 == 0) {
+                if (PIX == 1) row_sums(g, o);
+                else group_sums(g, o);
+                if (k0 + u < n && lane % (REGION_LANES / 2) == 0) {
                     const uint32_t row = row0 + k0 + u;
-                    s_row[row][lane / 4 % 2] = make_float4(o[0], o[1], o[2], o[3]);
-                    if (lane % 8 == 0) s_row8[row] = o[4];
+                    s_row[row][lane / (REGION_LANES / 2) % 2] = make_float4(o[0], o[1], o[2], o[3]);
+                    if (lane % REGION_LANES == 0) s_row8[row] = o[4];
                 }
             }
         }
@@ -470,7 +520,7 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, 
         if (wave == stager && b_end > start) stage(b_end);
     }
     // entries no pixel of the tile reached
-    for (uint32_t idx = tile_last + tid; idx < end; idx += BWD_THREADS) {
+    for (uint32_t idx = tile_last + tid; idx < end; idx += THREADS) {
         const uint32_t g = vals[idx];
         float4* dst = partial + 3ull * emission_pos(ws, g < f.n_gaussians ? g : 0u, tx, ty);
         dst[0] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -479,11 +529,28 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_raster_backward(FrameDev f, 
     }
 }
 
+// With few tiles the longest tile's chain of batches and entries is what takes
+// time, and four waves of a pixel per lane shorten it for more instructions in
+// all.  Both passes of the backward call with dual and single pixels (us): 20K Gaussians at
+// 401x267 (442 tiles) 149 and 127, 640x480 166 and 151, 960x540 (2040) 252 and 245,
+// 1024x768 (3072) 301 and 314; 1M at 640x480 561 and 507, 960x540 405 and 371,
+// 1024x768 413 and 439, 1080p 468 and 527; training variant, 1M, 379 and 368 at
+// 960x540, 377 and 428 at 1024x768.
+constexpr int32_t BWD_SINGLE_MAX_TILES = 2048;
+
 void launch_raster_backward(hipStream_t s, const FrameDev& f, const WsDev& ws, const uint32_t* vals,
                             const float* dimg, float4* partial, FrameKey key, bool train) {
-    const dim3 grid((uint32_t)f.n_tiles), block(BWD_THREADS);
-    if (train) hipLaunchKernelGGL(k_raster_backward<true>, grid, block, 0, s, f, ws, vals, dimg, partial, key);
-    else hipLaunchKernelGGL(k_raster_backward<false>, grid, block, 0, s, f, ws, vals, dimg, partial, key);
+    const dim3 grid((uint32_t)f.n_tiles);
+    auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, f, ws, vals, dimg, partial, key);
+    };
+    if (f.n_tiles > BWD_SINGLE_MAX_TILES) {
+        if (train) launch(k_raster_backward<true, 2>, 128);
+        else launch(k_raster_backward<false, 2>, 128);
+    } else {
+        if (train) launch(k_raster_backward<true, 1>, 256);
+        else launch(k_raster_backward<false, 1>, 256);
+    }
 }
 
 // ---------------------------------------------------------------------------

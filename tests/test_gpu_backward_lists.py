@@ -1,6 +1,7 @@
 """The backward kernels' lists and rows of sums at their edges (needs an MI355X): tiles of no, one,
 a batch's and more entries, entries that reach all sixteen regions of a tile, so that a batch's
-rows hold fewer entries than it stages, and Gaussians of more partials than a workgroup of the
+rows hold fewer entries than it stages (on frames that take a pixel per lane and, 800x800, on
+ones that take two), and Gaussians of more partials than a workgroup of the
 per-Gaussian pass stages.  The image-space sums against the float64 adjoint, to 1e-3 of
 the sum of their terms' magnitudes and the slack of near-threshold decisions, as in the backward
 pass's other tests; a second run is the same bit for bit."""
@@ -29,7 +30,8 @@ def R():
 @pytest.mark.parametrize("path", PATHS)
 @pytest.mark.parametrize("W,H,n,log_scale", [(W, H, n, s) for W, H in ((16, 16), (50, 35))
                                              for n, s in ((1, -3.0), (65, -0.5), (400, -0.7), (900, -4.5))]
-                         + [(401, 267, 1, 0.4), (401, 267, 65, 0.2)])
+                         + [(401, 267, 1, 0.4), (401, 267, 65, 0.2), (800, 800, 1, -0.5), (800, 800, 65, 0.0),
+                            (800, 800, 300, -2.5)])
 def test_lists(R, W, H, n, log_scale, path):
     sc = wl.make_scene(n, 1.0, log_scale, 0.3, 100 + n)
     if n > 1:
