@@ -451,7 +451,7 @@ __global__ __launch_bounds__(256 / PIX, 4) void k_raster_backward(FrameDev f, Ws
 #pragma unroll
                     for (int i = 0; i < PIX; ++i) {
                         const float dy = row_of(i) - a[u].y;
-                        P[u][i] = expf(fmaf(-0.5f, fmaf(a[u].z * dx, dx, m[u].x * dy * dy), -a[u].w * dx * dy));
+                        P[u][i] = exp_pair(fmaf(-0.5f, fmaf(a[u].z * dx, dx, m[u].x * dy * dy), -a[u].w * dx * dy));
                         pass[u][i] = at >= lim[i] && fminf(ALPHA_MAX, m[u].y * P[u][i]) >= ALPHA_MIN;
                     }
                 }

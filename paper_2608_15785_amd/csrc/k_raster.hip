@@ -14,7 +14,7 @@
 // of a tile, a pixel per lane, in four regions).  What a pair's alpha is
 // computed from is its template argument:
 //   * EXP_PLAIN, the 3DGS baseline: the exponent of Eq. power from (x - u,
-//     y - v) and the accurate expf;
+//     y - v) and an accurate exponential (exp_pair);
 //   * EXP_BITS, the paper's Sec. IV-B: coefficient folding (Eqs. expand, c0,
 //     coeff, dot): while a batch is staged the conic, mean and ln o are folded
 //     into C1..C6 so that the folded exponent P = p + ln o (Eq.
@@ -129,7 +129,7 @@ __device__ inline void pair_alphas(const float4& a, const float2& c, const LaneP
             const float row = PIX == 1 ? d.y + (d.odd ? 1.0f : 0.0f) : d.y + (float)i;
             const float dy = row - a.y;
             const float p = fmaf(-0.5f, fmaf(a.z * dx, dx, c.x * dy * dy), -a.w * dx * dy);
-            al[i] = fminf(ALPHA_MAX, c.y * expf(p));
+            al[i] = fminf(ALPHA_MAX, c.y * exp_pair(p));
             al[i] = al[i] >= thr[i] ? al[i] : 0.0f;
         }
     } else {
