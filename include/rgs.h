@@ -116,7 +116,7 @@ typedef int32_t rgs_status;
 #define RGS_STAGE_FRONTEND  0 /* plain: preprocess; fast: fused front end                  */
 #define RGS_STAGE_DUPLICATE 1 /* plain: ordered duplication with keys; fast: unused (0)    */
 #define RGS_STAGE_SORT      2 /* radix passes, or split pass + bucket sort                 */
-#define RGS_STAGE_RANGES    3 /* per-tile ranges (LSD passes only) and the tile schedule   */
+#define RGS_STAGE_RANGES    3 /* per-tile ranges and schedule (split sort: part of it, 0)  */
 #define RGS_STAGE_RASTER    4 /* per-tile blending                                         */
 #define RGS_N_STAGES        5
 

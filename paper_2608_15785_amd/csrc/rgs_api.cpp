@@ -1007,7 +1007,7 @@ rgs_status rgs::enqueue_frame(hipStream_t st, const FrameLaunch& fl, const Frame
         launch_ranges(st, fl.f, w, fl.L.key_bytes, fl.L.passes % 2 == 1);
     }
     if (fl.f.ordered == ORDER_TILES) launch_tile_order(st, fl.f, w);
-    mark(4);
+    mark(fl.f.split_bits && fl.f.ordered != ORDER_TILES ? -4 : 4);      // (nothing between sort and raster)
     const uint32_t* vals = sorted_vals(fl);
     if (fl.path == RGS_PATH_PLAIN && (fl.opts & OPT_HW_EXP2)) launch_raster_train(st, fl.f, w, vals, count);
     else if (fl.path == RGS_PATH_PLAIN) launch_raster_plain(st, fl.f, w, vals, count);
