@@ -224,8 +224,8 @@ struct ArraysOut {
     using Held = KeyT;                   // what the tile holds of a key in LDS
     KeyT* keys;
     uint32_t* vals;
-    __device__ Held hold(KeyT k) const { return k; }
-    __device__ uint32_t digit(Held h, uint32_t shift, uint32_t mask) const { return (uint32_t)(h >> shift) & mask; }
+    __host__ __device__ Held hold(KeyT k) const { return k; }
+    __host__ __device__ uint32_t digit(Held h, uint32_t shift, uint32_t mask) const { return (uint32_t)(h >> shift) & mask; }
     __device__ void put(uint32_t at, Held h, uint32_t v) const {
         keys[at] = h;
         vals[at] = v;
@@ -240,20 +240,22 @@ struct PairsOut<uint32_t> {
     uint2* pairs;
     LocalKey lk;
     const FrameParams* prm;
-    __device__ Held hold(uint32_t k) const { return k; }
-    __device__ uint32_t digit(Held h, uint32_t shift, uint32_t) const { return h >> shift; }
+    __host__ __device__ Held hold(uint32_t k) const { return k; }
+    __host__ __device__ uint32_t digit(Held h, uint32_t shift, uint32_t) const { return h >> shift; }
     __device__ void put(uint32_t at, Held h, uint32_t v) const { pairs[at] = make_uint2(h & ((1u << lk.bits) - 1u), v); }
 };
 // 64-bit keys: (tile bits below the top digit, float32 depth bits above the
-// nearest depth's).
+// nearest depth's).  The digit is masked, as where the tile ranks its keys: after a
+// front end that gave up, keys are whatever memory held, and their bits above the
+// tile index must not index the digit tables.
 template <>
 struct PairsOut<uint64_t> {
     using Held = uint64_t;
     uint2* pairs;
     LocalKey lk;
     const FrameParams* prm;
-    __device__ Held hold(uint64_t k) const { return k; }
-    __device__ uint32_t digit(Held h, uint32_t shift, uint32_t) const { return (uint32_t)(h >> shift); }
+    __host__ __device__ Held hold(uint64_t k) const { return k; }
+    __host__ __device__ uint32_t digit(Held h, uint32_t shift, uint32_t mask) const { return (uint32_t)(h >> shift) & mask; }
     __device__ void put(uint32_t at, Held h, uint32_t v) const {
         const uint32_t tile = (uint32_t)(h >> 32) & ((1u << lk.tile_bits) - 1u);
         const uint32_t depth = (uint32_t)h - depth_key_base(prm->cam);
