@@ -1193,6 +1193,7 @@ extern "C" rgs_status rgs_workspace_check(rgs_ctx* ctx, const void* workspace, r
 extern "C" rgs_status rgs_frame_outcome(rgs_ctx* ctx, const void* workspace, rgs_frame_stats* stats,
                                         int64_t n_gaussians) {
     if (!ctx || !workspace) return fail(RGS_E_INVALID, "ctx or workspace is NULL");
+    HIP_TRY(hipSetDevice(ctx->device));     // the default stream is the current device's
     for (int i = 0; i < N_FRAME_RECORDS; ++i) {
         if (ctx->records[i].ws != workspace) continue;
         FrameStamp st;
