@@ -220,6 +220,7 @@ struct FrameRecord {
     uint64_t scene_tag = 0, cam_hash = 0;
     int32_t width = 0, height = 0, path = 0;
     hipStream_t stream = nullptr;
+    bool stamped = false;         // a frame on `stream` writes the slot's stamp (kept when the record retires)
     uint64_t seq = 0;             // the stamp's sequence number once written
     uint64_t last_use = 0;
 };
@@ -783,6 +784,14 @@ static uint64_t camera_hash(const rgs_camera* c, int32_t width, int32_t height) 
     return h;
 }
 
+// Frees a record's slot; the last frame that was given it may still write the stamp.
+static void retire(FrameRecord& r) {
+    FrameRecord free;
+    free.stream = r.stream;
+    free.stamped = r.stamped;
+    r = free;
+}
+
 // Before a frame is enqueued on ctx's stream into ws: retires the workspace's
 // record, and gives a plain frame a record's slot (else *out = -1) and a stamp to
 // export to it.
@@ -792,23 +801,29 @@ static rgs_status reserve_record(rgs_ctx* ctx, const FrameLaunch& fl, const void
     for (int i = 0; i < N_FRAME_RECORDS; ++i)
         if (ctx->records[i].ws == ws) slot = i;
     if (fl.path != RGS_PATH_PLAIN) {
-        if (slot >= 0) ctx->records[slot] = FrameRecord{};
+        if (slot >= 0) retire(ctx->records[slot]);
         return RGS_OK;
     }
-    if (slot < 0) {                 // an unused slot, else the least recently used
+    if (slot < 0) {                 // an unused slot, best one that needs no wait, else the least recently used
+        auto cost = [&](const FrameRecord& r) {
+            return r.ws ? 2 : r.stamped && r.stream != ctx->stream ? 1 : 0;
+        };
         slot = 0;
-        for (int i = 0; i < N_FRAME_RECORDS; ++i) {
-            if (!ctx->records[i].ws) {
-                slot = i;
-                break;
-            }
-            if (ctx->records[i].last_use < ctx->records[slot].last_use) slot = i;
+        for (int i = 1; i < N_FRAME_RECORDS; ++i) {
+            const FrameRecord &a = ctx->records[i], &b = ctx->records[slot];
+            if (cost(a) < cost(b) || (cost(a) == 2 && cost(b) == 2 && a.last_use < b.last_use)) slot = i;
         }
     }
     FrameRecord& r = ctx->records[slot];
     // a stamp export still queued on another stream must not land after this one
-    if (r.ws && r.stream != ctx->stream) HIP_TRY(hipStreamSynchronize(r.stream));
-    r = FrameRecord{};
+    // (if that stream no longer exists, its work may)
+    if (r.stamped && r.stream != ctx->stream && hipStreamSynchronize(r.stream) != hipSuccess) {
+        (void)hipGetLastError();
+        HIP_TRY(hipDeviceSynchronize());
+    }
+    retire(r);
+    r.stream = ctx->stream;
+    r.stamped = true;
     prm->stamp = &ctx->stamps[slot];
     prm->stamp_seq = ++ctx->seq;
     *out = slot;
@@ -827,7 +842,6 @@ static void note_frame(rgs_ctx* ctx, int slot, const void* ws, uint64_t ws_bytes
     r.width = width;
     r.height = height;
     r.path = path;
-    r.stream = ctx->stream;
     r.seq = prm.stamp_seq;
     r.last_use = ++ctx->uses;
 }

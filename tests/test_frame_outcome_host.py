@@ -1,6 +1,7 @@
 """Host side of a plain frame's outcome, without a GPU: the library runs over a stand-in HIP runtime
 with two devices whose kernels do nothing, and what it asks of the runtime is recorded.  A wait for a
-frame asks the frame's own device."""
+frame asks the frame's own device; and a stamp slot whose last frame may still be queued on another
+stream is not given to a frame before that stream has drained, whatever was rendered in between."""
 import subprocess
 import sys
 import tempfile
@@ -93,3 +94,39 @@ B.lib.{call}
 mark("end")
 """)
     assert asked and all("dev1" in line for line in asked)
+
+
+@pytest.mark.parametrize("between", ["", "render(ctx, ds, 'fast', ws)", "ctx.set_stream(5); render(ctx, ds, 'fast', ws)"])
+def test_a_slot_changes_streams_after_its_frame(between):
+    """A plain frame on stream 7, perhaps another path's frame into its workspace (which retires
+    the record), then a plain frame on stream 9: stream 7 drains first, or the slot is another."""
+    asked = run(f"""
+ctx = B.Context(0, 7)
+ds = B.DeviceScene(ctx, sc, ("plain", "fast"))
+spaces = [workspace("plain") for _ in range(9)]
+ws = spaces[0]
+for w in spaces[:8]:
+    render(ctx, ds, "plain", w)             # every slot in use on stream 7
+{between}
+ctx.set_stream(9)
+mark("asked")
+render(ctx, ds, "plain", spaces[8])
+mark("end")
+""")
+    assert asked[0].startswith("synchronize") and asked[0].endswith("stream7")
+    assert len(asked) > 4 and all(line == "launch dev0 stream9" for line in asked[1:])
+
+
+def test_a_free_slot_needs_no_wait():
+    asked = run("""
+ctx = B.Context(0, 7)
+ds = B.DeviceScene(ctx, sc, ("plain", "fast"))
+ws = workspace("plain")
+render(ctx, ds, "plain", ws)
+render(ctx, ds, "fast", ws)
+ctx.set_stream(9)
+mark("asked")
+render(ctx, ds, "plain", ws)
+mark("end")
+""")
+    assert len(asked) > 3 and all(line == "launch dev0 stream9" for line in asked)
