@@ -79,22 +79,34 @@ __device__ inline void lds_barrier() {
 // pass anything and get an unspecified result).  s_wtot holds DIGITS / 64 words.
 // Every thread of the block must call it: it holds two barriers.
 // LDS_ONLY: the barriers leave global loads in flight.
-template <uint32_t DIGITS, bool LDS_ONLY = false>
-__device__ inline uint32_t digit_exclusive_scan(uint32_t x, uint32_t* s_wtot) {
+// VOTE: bit 31 of the totals tells every thread (any) whether a thread below DIGITS has
+// set its flag.
+template <uint32_t DIGITS, bool LDS_ONLY, bool VOTE>
+__device__ inline uint32_t digit_exclusive_scan(uint32_t x, uint32_t* s_wtot, bool flag, bool& any) {
+    constexpr uint32_t FLAG = VOTE ? 0x80000000u : 0u;
     auto barrier = [] {
         if (LDS_ONLY) lds_barrier();
         else __syncthreads();
     };
     const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
     const uint32_t incl = wave_inclusive_scan(x);
-    if (lane == 63 && wave < DIGITS / 64) s_wtot[wave] = incl;
+    const uint32_t mark = VOTE && __ballot(flag) != 0 ? FLAG : 0u;
+    if (lane == 63 && wave < DIGITS / 64) s_wtot[wave] = incl | mark;
     barrier();
-    uint32_t before = 0;
+    uint32_t before = 0, all = 0;
 #pragma unroll
-    for (uint32_t w = 0; w < DIGITS / 64; ++w)
-        if (w < wave) before += s_wtot[w];
+    for (uint32_t w = 0; w < DIGITS / 64; ++w) {
+        if (w < wave) before += s_wtot[w] & ~FLAG;
+        all |= s_wtot[w];
+    }
     barrier();
+    any = VOTE && __builtin_amdgcn_readfirstlane(all) >= FLAG;
     return incl - x + before;
+}
+template <uint32_t DIGITS>
+__device__ inline uint32_t digit_exclusive_scan(uint32_t x, uint32_t* s_wtot) {
+    bool any;
+    return digit_exclusive_scan<DIGITS, false, false>(x, s_wtot, false, any);
 }
 
 // Polls of a not yet published look-back word (each a short sleep and a
@@ -217,10 +229,21 @@ __device__ uint32_t fallback_range(const uint32_t* tiles, bool groups, uint32_t 
     return sum;
 }
 
+// What the split pass leaves for the bucket sort beside the entries.  In a frame with a
+// bucket of more than `limit` entries, every bucket of more than `alone` is sorted by
+// several workgroups, about `part` entries each.
+struct SplitPlan {
+    uint32_t* bases;        // each bucket's first place and, after the last, the entry count
+    uint32_t* n_parts;      // parts of all such buckets together
+    uint32_t* parts;        // of the buckets up to this one (if there are any)
+    uint32_t limit, alone, part;
+};
+
 // Where a pass leaves its entries: the LSD passes a key and a value array, the
 // split pass (local key, value) pairs (see the split sort below).
 template <typename KeyT>
 struct ArraysOut {
+    static constexpr bool PAIRS = false;
     using Held = KeyT;                   // what the tile holds of a key in LDS
     KeyT* keys;
     uint32_t* vals;
@@ -236,13 +259,15 @@ struct PairsOut;
 // 32-bit keys: the local key is the key below its top digit.
 template <>
 struct PairsOut<uint32_t> {
+    static constexpr bool PAIRS = true;
     using Held = uint32_t;
     uint2* pairs;
     LocalKey lk;
     const FrameParams* prm;
     __host__ __device__ Held hold(uint32_t k) const { return k; }
     __host__ __device__ uint32_t digit(Held h, uint32_t shift, uint32_t) const { return h >> shift; }
-    __device__ void put(uint32_t at, Held h, uint32_t v) const { pairs[at] = make_uint2(h & ((1u << lk.bits) - 1u), v); }
+    __device__ uint32_t local(Held h) const { return h & ((1u << lk.bits) - 1u); }
+    __device__ void put(uint32_t at, Held h, uint32_t v) const { pairs[at] = make_uint2(local(h), v); }
 };
 // 64-bit keys: (tile bits below the top digit, float32 depth bits above the
 // nearest depth's).  The digit is masked, as where the tile ranks its keys: after a
@@ -250,24 +275,159 @@ struct PairsOut<uint32_t> {
 // tile index must not index the digit tables.
 template <>
 struct PairsOut<uint64_t> {
+    static constexpr bool PAIRS = true;
     using Held = uint64_t;
     uint2* pairs;
     LocalKey lk;
     const FrameParams* prm;
     __host__ __device__ Held hold(uint64_t k) const { return k; }
     __host__ __device__ uint32_t digit(Held h, uint32_t shift, uint32_t mask) const { return (uint32_t)(h >> shift) & mask; }
-    __device__ void put(uint32_t at, Held h, uint32_t v) const {
+    __device__ uint32_t local(Held h) const {
         const uint32_t tile = (uint32_t)(h >> 32) & ((1u << lk.tile_bits) - 1u);
         const uint32_t depth = (uint32_t)h - depth_key_base(prm->cam);
-        pairs[at] = make_uint2((tile << (lk.bits - lk.tile_bits)) | depth, v);
+        return lk.tile_bits ? (tile << (lk.bits - lk.tile_bits)) | depth : depth;
     }
+    __device__ void put(uint32_t at, Held h, uint32_t v) const { pairs[at] = make_uint2(local(h), v); }
 };
+
+// The digit of a local key at `shift` (0 past its end).
+__device__ inline uint32_t digit_at(uint32_t k, uint32_t shift) {
+    return shift < 32 ? (k >> shift) & (RADIX - 1) : 0u;
+}
+
+// Digits of a local key of `bits` bits.
+__device__ inline uint32_t digit_passes(uint32_t bits) { return bits ? (bits + RADIX_BITS - 1) / RADIX_BITS : 1u; }
+
+// Ranks the keys of one wave among those with equal digits, in entry order: round r,
+// lane l holds entry first + r * 64 + l, existing ones below n.  my_hist: the wave's
+// digit counts, from zero on.
+// Lanes of a wave read counters that other lanes of the same wave wrote in
+// the previous round.  The LDS unit executes one wave's accesses in issue
+// order; the empty asm with a memory clobber keeps the compiler from
+// moving or reusing accesses across rounds.  (A volatile pointer would do
+// the same but loses the LDS address space: every access becomes a flat
+// access that waits on all outstanding global memory operations.)
+template <int BITS, int ITEMS, typename KeyT, typename DigitFn>
+__device__ inline void rank_wave(const KeyT (&k)[ITEMS], uint32_t first, uint32_t n, DigitFn digit, uint16_t* my_hist,
+                                 uint32_t (&rank)[ITEMS]) {
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        asm volatile("" ::: "memory");
+        const bool valid = first + r * 64 + lane_id() < n;
+        const uint32_t d = digit(k[r]);
+        // lanes whose digit differs from this lane's: for each bit b the
+        // ballot M_b of lanes holding a 1, XOR-ed with this lane's bit spread
+        // to a whole word (0 or all ones), marks the lanes that disagree on b.
+        // One three-input bit operation per half-mask folds M_b ^ spread into
+        // the running OR (truth table 0xBE: S2 | (S0 ^ S1)).
+        uint32_t diff_lo = 0, diff_hi = 0;
+#pragma unroll
+        for (int b = 0; b < BITS; ++b) {
+            const uint32_t spread = (uint32_t)((int32_t)(d << (31 - b)) >> 31);
+            const uint64_t m = __ballot(spread != 0);
+            diff_lo = __builtin_amdgcn_bitop3_b32((uint32_t)m, spread, diff_lo, 0xBE);
+            diff_hi = __builtin_amdgcn_bitop3_b32((uint32_t)(m >> 32), spread, diff_hi, 0xBE);
+        }
+        const uint64_t vmask = __ballot(valid);
+        const uint32_t peers_lo = ~diff_lo & (uint32_t)vmask, peers_hi = ~diff_hi & (uint32_t)(vmask >> 32);
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi(peers_hi, __builtin_amdgcn_mbcnt_lo(peers_lo, 0u));
+        const uint32_t prev = valid ? my_hist[d] : 0u;
+        rank[r] = prev + below;
+        if (valid && below == 0) my_hist[d] = (uint16_t)(prev + (uint32_t)(__popc(peers_lo) + __popc(peers_hi)));
+    }
+}
+
+// Orders a radix tile by its entries' local keys, all digits, in LDS: the entries come
+// and leave in registers, in rank_wave's layout with wave w's first entry at w ITEMS
+// 64.  Every thread calls it (barriers); whist is scratch.
+template <typename S, typename KeyT, typename Out>
+__device__ inline void sort_tile_local(KeyT (&k)[S::ITEMS], uint32_t (&v)[S::ITEMS], uint32_t n_valid, const Out& out,
+                                       uint32_t* whist, uint32_t* wtot, KeyT* keys, uint32_t* vals) {
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / 64;
+    const uint32_t first = wave * (S::ITEMS * 64);
+    uint16_t* my_hist = reinterpret_cast<uint16_t*>(whist) + wave * RADIX;
+    uint32_t rank[S::ITEMS];
+    for (uint32_t q = 0; q < digit_passes(out.lk.bits); ++q) {
+        auto digit = [&](KeyT key) { return digit_at(out.local(key), RADIX_BITS * q); };
+        __syncthreads();
+        for (uint32_t i = tid; i < S::WAVES * RADIX / 2; i += S::THREADS) whist[i] = 0;
+        __syncthreads();
+        rank_wave<RADIX_BITS>(k, first, n_valid, digit, my_hist, rank);
+        __syncthreads();
+        uint16_t* h = reinterpret_cast<uint16_t*>(whist) + tid;
+        uint32_t tot = 0;
+        if (tid < RADIX)
+            for (int w = 0; w < S::WAVES; ++w) tot += h[w * RADIX];
+        uint32_t at = digit_exclusive_scan<RADIX>(tot, wtot);
+        if (tid < RADIX)
+            for (int w = 0; w < S::WAVES; ++w) {
+                const uint32_t c = h[w * RADIX];
+                h[w * RADIX] = (uint16_t)at;
+                at += c;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < S::ITEMS; ++r) {
+            if (first + r * 64 + lane < n_valid) {
+                const uint32_t pos = my_hist[digit(k[r])] + rank[r];
+                keys[pos] = k[r];
+                vals[pos] = v[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < S::ITEMS; ++r) {
+            const uint32_t e = first + r * 64 + lane;
+            k[r] = e < n_valid ? keys[e] : (KeyT)0;
+            v[r] = e < n_valid ? vals[e] : 0u;
+        }
+    }
+    __syncthreads();
+}
+
+// Shared memory of a radix pass.
+template <typename S, typename Held>
+struct alignas(8) TileLds {
+    // per-wave digit counts (at most 64 ITEMS each), then where each wave's run of a
+    // digit starts in the reordered tile; reused for the look-back once the tile is
+    // reordered
+    static constexpr uint32_t WHIST_WORDS = S::WAVES * S::DIGITS / 2 > (S::SPLIT + 3) * S::DIGITS
+                                                ? S::WAVES * S::DIGITS / 2
+                                                : (S::SPLIT + 3) * S::DIGITS;
+    Held keys[S::SIZE];
+    uint32_t vals[S::SIZE];
+    uint32_t whist[WHIST_WORDS];
+    uint32_t bstart[S::DIGITS];   // first LDS position of digit d in the reordered tile
+    uint32_t gbase[S::DIGITS];    // bucket base of d, then output position minus bstart[d]
+    uint32_t tot[S::DIGITS];      // the tile's count of digit d
+    uint32_t wtot[S::DIGITS / 64];
+    uint32_t missed[2];           // look-back votes: some thread found an unpublished word
+};
+
+// The split pass in a frame with a bucket for more than one workgroup, a function of its own
+// (radix_tile).  Its arguments come in LDS, as what a call cannot pass in registers
+// would make the kernel's stack larger.
+template <typename KeyT, typename Out>
+struct PassArgs {
+    const KeyT* kin;
+    const uint32_t* vin;
+    Out out;
+    const WsHeader* header;
+    const uint32_t* hist;
+    uint32_t *tiles, *groups;
+    uint32_t hist_stride, shift;
+    SplitPlan plan;
+};
+template <typename T>
+using Lds = __attribute__((address_space(3))) T;
+template <typename KeyT, typename S, typename Out, bool FORCE>
+__device__ void crowded_tile(Lds<TileLds<S, typename Out::Held>>* lds);
 
 // One stable radix pass on the digit at `shift`.  hist[c][d]: HIST_COPIES copies,
 // hist_stride words apart, of the digit counts of the whole input.  tiles,
 // groups: this pass's look-back words; next_tiles, next_groups: those of the
-// frame's next pass, cleared here (null: none).  bases: if not null, receives
-// each digit's first output place and, after the last, the entry count.
+// frame's next pass, cleared here (null: none).  The split pass also leaves the
+// bucket sort's plan (SplitPlan).
 // FORCE: take every look-back from the keys (fallback_range), for tests.
 //
 // The split pass at 1M / 1080p, 241 tiles of 9216 keys, one a CU, all running at
@@ -278,37 +438,29 @@ struct PairsOut<uint64_t> {
 // group publishes the group before it reorders: 23.3 -> 21.3 us (plain, 313
 // tiles in two rounds, 41.2 -> 40.5; 3M / 4K 63.3 -> 62.7).  Tiles of 4096, two a CU:
 // 33 and 87 us.
-template <typename KeyT, typename S, typename Out, bool FORCE>
-__global__ __launch_bounds__(S::THREADS) void k_radix_pass(const KeyT* __restrict__ kin,
-                                                           const uint32_t* __restrict__ vin, Out out,
-                                                           const WsHeader* header, const uint32_t* hist,
-                                                           uint32_t hist_stride, uint32_t* tiles, uint32_t* groups,
-                                                           uint32_t* next_tiles, uint32_t* next_groups, uint32_t shift,
-                                                           uint32_t* bases) {
+// SORTED: with the tile's entries ordered by their local keys first (sort_tile_local).
+template <typename KeyT, typename S, typename Out, bool FORCE, bool SORTED>
+__device__ inline void radix_tile(const KeyT* __restrict__ kin, const uint32_t* __restrict__ vin, const Out& out,
+                                  const WsHeader* header, const uint32_t* hist, uint32_t hist_stride, uint32_t* tiles,
+                                  uint32_t* groups, uint32_t* next_tiles, uint32_t* next_groups, uint32_t shift,
+                                  const SplitPlan& plan, TileLds<S, typename Out::Held>& lds) {
     constexpr int ITEMS = S::ITEMS;
     constexpr uint32_t SIZE = S::SIZE, DIGITS = S::DIGITS;
+    constexpr uint32_t WHIST_WORDS = TileLds<S, typename Out::Held>::WHIST_WORDS;
     using Held = typename Out::Held;
-    // per-wave digit counts (at most 64 ITEMS each), then where each wave's run of a
-    // digit starts in the reordered tile; reused for the look-back once the tile is
-    // reordered
-    constexpr uint32_t WHIST_WORDS = S::WAVES * DIGITS / 2 > (S::SPLIT + 3) * DIGITS ? S::WAVES * DIGITS / 2
-                                                                                     : (S::SPLIT + 3) * DIGITS;
-    __shared__ uint32_t s_whist[WHIST_WORDS];
-    __shared__ uint32_t s_bstart[DIGITS];   // first LDS position of digit d in the reordered tile
-    __shared__ uint32_t s_gbase[DIGITS];    // bucket base of d, then output position minus s_bstart[d]
-    __shared__ uint32_t s_tot[DIGITS];      // the tile's count of digit d
-    __shared__ uint32_t s_wtot[DIGITS / 64];
-    __shared__ uint32_t s_missed[2];        // look-back votes: some thread found an unpublished word
-    __shared__ Held s_keys[SIZE];
-    __shared__ uint32_t s_vals[SIZE];
+    uint32_t *s_whist = lds.whist, *s_bstart = lds.bstart, *s_gbase = lds.gbase, *s_tot = lds.tot;
+    uint32_t *s_wtot = lds.wtot, *s_missed = lds.missed, *s_vals = lds.vals;
+    Held* s_keys = lds.keys;
 
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / 64;
     const uint32_t n = entry_count(header);
     const uint32_t vb = blockIdx.x;      // the radix tile: keys [vb * SIZE, (vb + 1) * SIZE)
     const uint32_t tile_base = vb * SIZE;
     if (tile_base >= n) {
-        if (bases && n == 0 && vb == 0)
-            for (uint32_t i = tid; i <= DIGITS; i += S::THREADS) bases[i] = 0;
+        if (Out::PAIRS && n == 0 && vb == 0) {
+            for (uint32_t i = tid; i <= DIGITS; i += S::THREADS) plan.bases[i] = 0;
+            if (tid == 0) *plan.n_parts = 0;
+        }
         return;
     }
     const uint32_t n_valid = min(SIZE, n - tile_base);
@@ -322,7 +474,6 @@ __global__ __launch_bounds__(S::THREADS) void k_radix_pass(const KeyT* __restric
     const uint32_t wbase = tile_base + wave * (ITEMS * 64);
     KeyT k[ITEMS];
     uint32_t v[ITEMS];
-    uint32_t rank[ITEMS];
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         const uint32_t idx = wbase + r * 64 + lane;
@@ -343,40 +494,57 @@ __global__ __launch_bounds__(S::THREADS) void k_radix_pass(const KeyT* __restric
     uint32_t bucket = 0;
 #pragma unroll
     for (int c = 0; c < HIST_COPIES; ++c) bucket += copies[c];
-    const uint32_t bbase = digit_exclusive_scan<DIGITS, true>(bucket, s_wtot);
-    // Lanes of a wave read counters that other lanes of the same wave wrote in
-    // the previous round.  The LDS unit executes one wave's accesses in issue
-    // order; the empty asm with a memory clobber keeps the compiler from
-    // moving or reusing accesses across rounds.  (A volatile pointer would do
-    // the same but loses the LDS address space: every access becomes a flat
-    // access that waits on all outstanding global memory operations.)
+    bool crowded;
+    const uint32_t bbase =
+        digit_exclusive_scan<DIGITS, true, Out::PAIRS>(bucket, s_wtot, bucket > plan.limit, crowded);
     uint16_t* my_hist = reinterpret_cast<uint16_t*>(s_whist) + wave * DIGITS;
-#pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-        asm volatile("" ::: "memory");
-        const uint32_t idx = wbase + r * 64 + lane;
-        const bool valid = idx < n;
-        const uint32_t d = (uint32_t)(k[r] >> shift) & (DIGITS - 1);
-        // lanes whose digit differs from this lane's: for each bit b the
-        // ballot M_b of lanes holding a 1, XOR-ed with this lane's bit spread
-        // to a whole word (0 or all ones), marks the lanes that disagree on b.
-        // One three-input bit operation per half-mask folds M_b ^ spread into
-        // the running OR (truth table 0xBE: S2 | (S0 ^ S1)).
-        uint32_t diff_lo = 0, diff_hi = 0;
-#pragma unroll
-        for (int b = 0; b < S::BITS; ++b) {
-            const uint32_t spread = (uint32_t)((int32_t)(d << (31 - b)) >> 31);
-            const uint64_t m = __ballot(spread != 0);
-            diff_lo = __builtin_amdgcn_bitop3_b32((uint32_t)m, spread, diff_lo, 0xBE);
-            diff_hi = __builtin_amdgcn_bitop3_b32((uint32_t)(m >> 32), spread, diff_hi, 0xBE);
+    // A crowded frame starts over in code of its own, so that the pass of other frames stays
+    // as it is: as a function it takes 0 to 0.5 us from them (one copy of the rest after a
+    // branch 1 to 3 us).  Small frames of 32-bit keys and 8 bits, for which the
+    // function's stack costs 1 us, take a second copy of the rest.
+    if constexpr (Out::PAIRS && !SORTED) {
+        if (__builtin_expect(crowded, false)) {
+            __syncthreads();
+            if constexpr (sizeof(KeyT) == 4 && S::BITS == 8) {
+                radix_tile<KeyT, S, Out, FORCE, true>(kin, vin, out, header, hist, hist_stride, tiles, groups, nullptr,
+                                                      nullptr, shift, plan, lds);
+            } else {
+                using Args = PassArgs<KeyT, Out>;
+                static_assert(sizeof(Args) <= sizeof(lds.keys) && alignof(Args) <= 8, "the arguments fit");
+                if (tid == 0) {         // (field by field: a temporary would live in LDS, a copy per thread)
+                    Args* a = reinterpret_cast<Args*>(s_keys);
+                    a->kin = kin;
+                    a->vin = vin;
+                    a->out.pairs = out.pairs;
+                    a->out.lk.bits = out.lk.bits;
+                    a->out.lk.tile_bits = out.lk.tile_bits;
+                    a->out.prm = out.prm;
+                    a->header = header;
+                    a->hist = hist;
+                    a->tiles = tiles;
+                    a->groups = groups;
+                    a->hist_stride = hist_stride;
+                    a->shift = shift;
+                    a->plan.bases = plan.bases;
+                    a->plan.n_parts = plan.n_parts;
+                    a->plan.parts = plan.parts;
+                    a->plan.limit = plan.limit;
+                    a->plan.alone = plan.alone;
+                    a->plan.part = plan.part;
+                }
+                __syncthreads();
+                crowded_tile<KeyT, S, Out, FORCE>((Lds<TileLds<S, Held>>*)&lds);
+            }
+            return;
         }
-        const uint64_t vmask = __ballot(valid);
-        const uint32_t peers_lo = ~diff_lo & (uint32_t)vmask, peers_hi = ~diff_hi & (uint32_t)(vmask >> 32);
-        const uint32_t below = __builtin_amdgcn_mbcnt_hi(peers_hi, __builtin_amdgcn_mbcnt_lo(peers_lo, 0u));
-        const uint32_t prev = valid ? my_hist[d] : 0u;
-        rank[r] = prev + below;
-        if (valid && below == 0) my_hist[d] = (uint16_t)(prev + (uint32_t)(__popc(peers_lo) + __popc(peers_hi)));
     }
+    if constexpr (SORTED) {
+        sort_tile_local<S>(k, v, n_valid, out, s_whist, s_wtot, s_keys, s_vals);
+        for (uint32_t i = tid; i < WHIST_WORDS; i += S::THREADS) s_whist[i] = 0;
+        __syncthreads();
+    }
+    uint32_t rank[ITEMS];
+    rank_wave<S::BITS>(k, wbase, n, [&](KeyT key) { return (uint32_t)(key >> shift) & (DIGITS - 1); }, my_hist, rank);
     __syncthreads();
 
     // digit d = tid: the tile's count, published at once
@@ -424,12 +592,20 @@ __global__ __launch_bounds__(S::THREADS) void k_radix_pass(const KeyT* __restric
             h[w * DIGITS] = (uint16_t)at;
             at += c[w];
         }
-        if (bases && vb == 0) {
-            bases[tid] = min(bbase, n);
-            if (tid == 0) bases[DIGITS] = n;
-        }
     }
     __syncthreads();
+
+    if (Out::PAIRS && vb == 0) {
+        const uint32_t size = tid < DIGITS ? min(bbase + bucket, n) - min(bbase, n) : 0u;
+        const uint32_t parts = size > plan.alone ? (size + plan.part - 1) / plan.part : 0u;
+        const uint32_t before = SORTED ? digit_exclusive_scan<DIGITS>(parts, s_wtot) : 0u;
+        if (tid < DIGITS) {
+            plan.bases[tid] = min(bbase, n);
+            if (tid == 0) plan.bases[DIGITS] = n;
+            if (SORTED) plan.parts[tid] = before + parts;
+            if (tid == DIGITS - 1) *plan.n_parts = SORTED ? before + parts : 0u;
+        }
+    }
 
     // reorder the tile by digit in LDS
 #pragma unroll
@@ -489,6 +665,35 @@ __global__ __launch_bounds__(S::THREADS) void k_radix_pass(const KeyT* __restric
     }
 }
 
+template <typename KeyT, typename S, typename Out, bool FORCE>
+__device__ __attribute__((noinline)) void crowded_tile(Lds<TileLds<S, typename Out::Held>>* lds) {
+    auto& tile = *(TileLds<S, typename Out::Held>*)lds;
+    union Words {
+        PassArgs<KeyT, Out> args;
+        int word[sizeof(PassArgs<KeyT, Out>) / 4];
+        __device__ Words() {}
+    } a;
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(a.word) / 4; ++i)
+        a.word[i] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(tile.keys)[i]);
+    __syncthreads();
+    const PassArgs<KeyT, Out>& p = a.args;
+    radix_tile<KeyT, S, Out, FORCE, true>(p.kin, p.vin, p.out, p.header, p.hist, p.hist_stride, p.tiles, p.groups,
+                                          nullptr, nullptr, p.shift, p.plan, tile);
+}
+
+template <typename KeyT, typename S, typename Out, bool FORCE>
+__global__ __launch_bounds__(S::THREADS) void k_radix_pass(const KeyT* __restrict__ kin,
+                                                           const uint32_t* __restrict__ vin, Out out,
+                                                           const WsHeader* header, const uint32_t* hist,
+                                                           uint32_t hist_stride, uint32_t* tiles, uint32_t* groups,
+                                                           uint32_t* next_tiles, uint32_t* next_groups, uint32_t shift,
+                                                           SplitPlan plan) {
+    __shared__ TileLds<S, typename Out::Held> lds;
+    radix_tile<KeyT, S, Out, FORCE, false>(kin, vin, out, header, hist, hist_stride, tiles, groups, next_tiles,
+                                           next_groups, shift, plan, lds);
+}
+
 template <typename KeyT>
 static void sort_typed(hipStream_t s, const WsDev& ws, uint32_t passes, bool force) {
     using S = LsdShape<KeyT>;
@@ -503,7 +708,7 @@ static void sort_typed(hipStream_t s, const WsDev& ws, uint32_t passes, bool for
                                ws.header, ws.hist + p * RADIX, (uint32_t)(MAX_PASSES * RADIX),
                                sort_state_tiles(ws, p & 1), sort_state_groups(ws, p & 1),
                                sort_state_tiles(ws, (p + 1) & 1), sort_state_groups(ws, (p + 1) & 1),
-                               (uint32_t)(RADIX_BITS * p), (uint32_t*)nullptr);
+                               (uint32_t)(RADIX_BITS * p), SplitPlan{});
         };
         if (force) launch(k_radix_pass<KeyT, S, ArraysOut<KeyT>, true>);
         else launch(k_radix_pass<KeyT, S, ArraysOut<KeyT>, false>);
@@ -530,9 +735,15 @@ void launch_sort(hipStream_t s, const WsDev& ws, uint32_t key_bytes, uint32_t pa
 //     significant digit first, each a stable counting pass in LDS
 //     (bucket_rank).  A bucket of at most CAP entries stays in LDS for all of
 //     them; one of at most 2 CAP is sorted as two runs in LDS, each written back
-//     in place, and the two merged; a larger one streams through global memory
-//     in chunks of CAP, one stable pass at a time;
-//   * the same workgroup, holding its bucket sorted, writes its tiles' ranges.
+//     in place, and the two merged;
+//   * the entries of a view from afar crowd into few tiles, and then into few
+//     buckets.  A bucket of more than 2 CAP entries is divided among workgroups, CAP
+//     consecutive places of the sorted bucket each (sort_part).  The split pass, whose
+//     tiles all know the bucket sizes, then leaves its tiles sorted by the whole
+//     key, so that the bucket consists of one sorted run per radix tile, and a part
+//     finds the two cuts through the runs that hold its entries by bisection on
+//     the key, gathers them and sorts them in LDS.  No workgroup waits for another;
+//   * a workgroup, holding its entries sorted, writes its tiles' ranges.
 // Every pass is stable and the top digit is taken first, then the rest least
 // significant first; as a stable sort on the top digit followed by a stable
 // sort on the rest leaves the keys ordered by (top digit, rest) with ties in
@@ -542,12 +753,15 @@ void launch_sort(hipStream_t s, const WsDev& ws, uint32_t key_bytes, uint32_t pa
 
 constexpr uint32_t BK_LOAD_BATCH = 8;       // loads of a thread in flight where a loop stages or merges
 
-// A bucket's workgroup: threads, and entries each holds.
-template <int THREADS_, int ITEMS_>
+// A bucket's workgroup: threads, entries each holds, and the waves a SIMD that its
+// LDS allows (the registers of the parts' code must not allow fewer).
+template <int THREADS_, int ITEMS_, int WAVES_SIMD_>
 struct BucketShape {
-    static constexpr int THREADS = THREADS_, ITEMS = ITEMS_;
+    static constexpr int THREADS = THREADS_, ITEMS = ITEMS_, WAVES_SIMD = WAVES_SIMD_;
     static constexpr int WAVES = THREADS / 64;
     static constexpr uint32_t CAP = THREADS * ITEMS;
+    // a part of a divided bucket: CAP entries at most with both cuts off by the tolerance
+    static constexpr uint32_t TOLERANCE = CAP / 8, PART = CAP - 2 * TOLERANCE;
 };
 
 // Shared memory of the bucket sort.
@@ -556,14 +770,10 @@ struct BucketLds {
     static constexpr int WORDS = B::WAVES > RADIX / 64 ? B::WAVES : RADIX / 64;
     uint2 pair[B::CAP];                        // (local key, value)
     uint16_t whist[B::WAVES * RADIX];          // per-wave digit counts, then places (below CAP)
-    uint32_t tot[RADIX], bs[RADIX], base[RADIX];
+    uint32_t tot[RADIX], bs[RADIX];
     uint32_t wtot[WORDS];
+    uint32_t red[2][6][B::WAVES];              // block-wide sums and extremes
 };
-
-// The digit of a local key at `shift` (0 past its end).
-__device__ inline uint32_t digit_at(uint32_t k, uint32_t shift) {
-    return shift < 32 ? (k >> shift) & (RADIX - 1) : 0u;
-}
 
 // Block-wide stable ranking of up to CAP keys.  Wave w holds entries
 // [w R 64, (w + 1) R 64) of the chunk, round r and lane l holding entry
@@ -648,9 +858,6 @@ __device__ inline void bucket_rank(const uint32_t (&k)[B::ITEMS], uint32_t cnt, 
     }
 }
 
-// Digits of a local key of `bits` bits.
-__device__ inline uint32_t digit_passes(uint32_t bits) { return bits ? (bits + RADIX_BITS - 1) / RADIX_BITS : 1u; }
-
 // Where the sorted entries of a bucket go: the values, the tiles' ranges, and
 // (debug renders) the full keys.
 struct BucketOut {
@@ -663,10 +870,11 @@ struct BucketOut {
     const FrameParams* prm;
     LocalKey lk;
     uint32_t n_tiles;
+    uint32_t bucket;        // set by the workgroup
 
     __device__ uint32_t tile_of(uint32_t local) const {
         const uint32_t depth_bits = lk.bits - lk.tile_bits;
-        return (blockIdx.x << lk.tile_bits) | (lk.tile_bits ? local >> depth_bits : 0u);
+        return (bucket << lk.tile_bits) | (lk.tile_bits ? local >> depth_bits : 0u);
     }
     // The tile's run starts at entry `at` of the frame / ended before it.
     __device__ void start(uint32_t at, uint32_t local) const {
@@ -695,25 +903,24 @@ struct BucketOut {
     }
 };
 
-// Sorts m <= CAP pairs of src by their local key in LDS, all digits, leaving
-// them in lds.pair.  Every thread calls it (barriers).
-template <typename B>
-__device__ inline void bucket_lds_sort(const uint2* src, uint32_t m, uint32_t bits, BucketLds<B>& lds) {
+// Sorts m <= CAP pairs by their local key in LDS, all digits, leaving them in
+// lds.pair.  Entry e is held in round r < R = ceil(m / THREADS) by (wave, lane)
+// with e = (wave R + r) 64 + lane, the layout of bucket_rank; it comes from
+// load(a, b), e = a + b, every load of a thread in flight at once.  The bounds are wave-uniform counts
+// against the lane index, so that no per-entry index stays live across the
+// passes.  Every thread calls it (barriers).
+template <typename B, typename LoadFn>
+__device__ inline void bucket_lds_sort(LoadFn load, uint32_t m, uint32_t bits, BucketLds<B>& lds) {
     constexpr int THREADS = B::THREADS, BK_ITEMS = B::ITEMS;
     const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
-    // Entry e is held in round r < R by (wave, lane) with e = (wave R + r) 64
-    // + lane, the layout of bucket_rank.  The bounds are wave-uniform counts
-    // against the lane index, so that no per-entry index stays live across the
-    // passes.  The first pass takes its pairs straight from global memory in
-    // that layout, every load of a thread in flight at once.
     uint32_t k[BK_ITEMS], v[BK_ITEMS], pos[BK_ITEMS];
     const uint32_t R = (m + THREADS - 1) / THREADS;
     const int lim = __builtin_amdgcn_readfirstlane((int)m - (int)(wave * R * 64));
-    const uint2* mine = src + wave * R * 64 + lane;
-    const uint2* held = lds.pair + wave * R * 64 + lane;
+    const uint32_t first = wave * R * 64 + lane;
+    const uint2* held = lds.pair + first;
 #pragma unroll
     for (int r = 0; r < BK_ITEMS; ++r) {
-        const uint2 p = (uint32_t)r < R && (int)lane < lim - r * 64 ? mine[r * 64] : make_uint2(0u, 0u);
+        const uint2 p = (uint32_t)r < R && (int)lane < lim - r * 64 ? load(first, r * 64) : make_uint2(0u, 0u);
         k[r] = p.x;
         v[r] = p.y;
     }
@@ -733,6 +940,22 @@ __device__ inline void bucket_lds_sort(const uint2* src, uint32_t m, uint32_t bi
         for (int r = 0; r < BK_ITEMS; ++r)
             if ((uint32_t)r < R && (int)lane < lim - r * 64) lds.pair[pos[r]] = make_uint2(k[r], v[r]);
         __syncthreads();
+    }
+}
+
+// Writes the m sorted entries in lds.pair to the frame's places from `at` on.  head,
+// tail: they begin, end the bucket; if not head, `before` is the key before them.
+template <typename B>
+__device__ inline void write_sorted(const BucketLds<B>& lds, uint32_t at, uint32_t m, bool head, bool tail,
+                                    uint32_t before, const BucketOut& out) {
+    for (uint32_t e = threadIdx.x; e < m; e += B::THREADS) {
+        const uint2 p = lds.pair[e];
+        out.vals[at + e] = p.y;
+        if (e > 0) out.boundary(at + e, lds.pair[e - 1].x, p.x);
+        else if (head) out.start(at, p.x);
+        else out.boundary(at, before, p.x);
+        if (e + 1 == m && tail) out.end(at + m, p.x);
+        if (out.want_keys()) out.put_key(at + e, p.x);
     }
 }
 
@@ -770,217 +993,443 @@ __device__ inline void place_tiles(const uint32_t* __restrict__ bases, const Buc
         if (at + t < out.n_tiles) out.order[at + t] = (b << bits) + t;
 }
 
-__device__ inline uint2 ld_pair(const uint2* p) {
-    const uint64_t w = ld_state(reinterpret_cast<const uint64_t*>(p));
-    return make_uint2((uint32_t)w, (uint32_t)(w >> 32));
+// Merges the two sorted runs src[0, cA) and src[cA, cA + cB) of a bucket, which this
+// workgroup has just written.
+template <typename B>
+__device__ inline void merge_runs(const uint2* src, uint32_t cA, uint32_t cB, uint32_t b0, const BucketOut& out,
+                                  BucketLds<B>& lds) {
+    constexpr int THREADS = B::THREADS;
+    const uint32_t tid = threadIdx.x, cnt = cA + cB;
+    // both runs' keys into LDS, read past the CU's vector cache (it may
+    // hold the first run's lines from before they were sorted)
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    uint32_t* keys = reinterpret_cast<uint32_t*>(lds.pair);
+    for (uint32_t e0 = tid; e0 < cnt; e0 += BK_LOAD_BATCH * THREADS) {
+        uint32_t t[BK_LOAD_BATCH];
+#pragma unroll
+        for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j)
+            t[j] = e0 + j * THREADS < cnt ? ld_state(&src[e0 + j * THREADS].x) : 0u;
+#pragma unroll
+        for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j)
+            if (e0 + j * THREADS < cnt) keys[e0 + j * THREADS] = t[j];
+    }
+    __syncthreads();
+    // Merge path: thread t writes outputs [t S, (t + 1) S).  Its first
+    // output takes i entries from A and o - i from B, i the least index
+    // with A[i] > B[o - i - 1]; then the two are merged sequentially, A
+    // first on equal keys (A holds the earlier entries: stable).
+    const uint32_t* A = keys;
+    const uint32_t* Bk = keys + cA;
+    const uint32_t S = (cnt + THREADS - 1) / THREADS;
+    const uint32_t o0 = tid * S, o1 = min(o0 + S, cnt);
+    if (o0 >= cnt) return;
+    uint32_t lo = o0 > cB ? o0 - cB : 0u, hi = min(o0, cA);
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (A[mid] <= Bk[o0 - mid - 1]) lo = mid + 1;
+        else hi = mid;
+    }
+    uint32_t ia = lo, ib = o0 - lo;
+    // the key before this thread's first output, for the tile runs
+    uint32_t before = max(ia > 0 ? A[ia - 1] : 0u, ib > 0 ? Bk[ib - 1] : 0u);
+    // BK_LOAD_BATCH outputs at a time: their value loads in flight together
+    for (uint32_t ob = o0; ob < o1; ob += BK_LOAD_BATCH) {
+        uint32_t key[BK_LOAD_BATCH], val[BK_LOAD_BATCH];
+#pragma unroll
+        for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
+            if (ob + j >= o1) break;
+            const bool take_a = ib >= cB || (ia < cA && A[ia] <= Bk[ib]);
+            const uint32_t at = take_a ? ia : cA + ib;
+            key[j] = take_a ? A[ia] : Bk[ib];
+            val[j] = ld_state(&src[at].y);
+            if (take_a) ++ia;
+            else ++ib;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
+            if (ob + j >= o1) break;
+            const uint32_t o = ob + j;
+            out.vals[b0 + o] = val[j];
+            if (o == 0) out.start(b0, key[j]);
+            else out.boundary(b0 + o, before, key[j]);
+            if (o + 1 == cnt) out.end(b0 + cnt, key[j]);
+            if (out.want_keys()) out.put_key(b0 + o, key[j]);
+            before = key[j];
+        }
+    }
 }
 
-// FORCE: every bucket through the global-memory path (for tests).
-// pairs: the split pass's output; tmp_keys, out.vals: a second buffer for that
-// path (this bucket's own entries of both).
-template <typename B, bool FORCE>
-__global__ __launch_bounds__(B::THREADS) void k_bucket_sort(uint2* pairs, uint32_t* tmp_keys, const uint32_t* bases,
+// Block-wide exclusive scan of one value a thread, and the total.  Every thread calls
+// it (barriers).
+template <typename B>
+__device__ inline uint32_t block_scan(uint32_t x, uint32_t* wtot, uint32_t& total) {
+    const uint32_t wave = threadIdx.x / 64, incl = wave_inclusive_scan(x);
+    if (lane_id() == 63) wtot[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < B::WAVES; ++w) {
+        if (w < wave) before += wtot[w];
+        total += wtot[w];
+    }
+    __syncthreads();
+    return before + incl - x;
+}
+
+// Block-wide combination of N values a thread (value j by op(j, ..)), in place.  red: one of two sets of words
+// that successive calls alternate between, so that one barrier is enough.
+template <typename B, int N, typename Op>
+__device__ inline void block_reduce(uint32_t (&x)[N], uint32_t (*red)[B::WAVES], Op op) {
+    const uint32_t wave = threadIdx.x / 64;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) x[j] = op(j, x[j], (uint32_t)__shfl_xor((int)x[j], off, 64));
+        if (lane_id() == 0) red[j][wave] = x[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        x[j] = red[j][0];
+#pragma unroll
+        for (int w = 1; w < B::WAVES; ++w) x[j] = op(j, x[j], red[j][w]);
+    }
+}
+
+// A part's samples are every 2^SAMPLE_SKIP-th key at least: the count they give is off by
+// a third of that and the square root of the runs (a few hundred), within the tolerance.
+constexpr uint32_t SAMPLE_SKIP = 4;
+
+// One sorted run of a divided bucket: its first entry, for each of the part's two cuts the
+// places between which it lies, and those of a step's two pivots.  Then the part's
+// share of the run.
+struct PartRun {
+    uint32_t start;
+    uint16_t lo[2], hi[2], cut[2][2];
+};
+struct PartShare {
+    uint32_t at, from;               // first place among the part's entries, first entry of the bucket
+};
+
+// Sorts part q of P of a bucket that consists of n_runs sorted runs, run r of counts[r *
+// stride] entries: those from about the place size q / P of the sorted bucket to about
+// size (q + 1) / P.  A cut is a key that divides the bucket within the tolerance of
+// its place, or where equal keys leave none the exact place, and the same whichever
+// of the two parts beside it looks for it.  The key at a
+// place K is the least one that more than K entries do not exceed; of the entries
+// with just that key, the first ones in run order lie before the cut.  The key is
+// first narrowed down on the runs' samples (every 2^skip-th key, in LDS), by estimates
+// of the count; then by two pivots a step, the first of them the key so found, each step
+// a search for both in every run, a run per thread.  The searches' loads, each a cache
+// line of its own, are what costs, so there are to be few of them: one such step
+// is usually enough.  Every thread calls it (barriers).
+template <typename B>
+__device__ void sort_part(const uint2* __restrict__ src, uint32_t size, uint32_t q, uint32_t P,
+                          const uint32_t* __restrict__ counts, uint32_t stride, uint32_t n_runs, uint32_t b0,
+                          const BucketOut& out, BucketLds<B>& lds) {
+    constexpr uint32_t THREADS = B::THREADS;
+    const uint32_t tid = threadIdx.x;
+    PartRun* runs = reinterpret_cast<PartRun*>(lds.pair);
+    uint32_t* samples = reinterpret_cast<uint32_t*>(runs + n_runs);     // run r's from start >> skip on
+    uint32_t skip = SAMPLE_SKIP;
+    while (size >> skip > 2 * B::CAP - n_runs * (uint32_t)(sizeof(PartRun) / 4)) ++skip;
+    auto sum = [](int, uint32_t x, uint32_t y) { return x + y; };
+    uint32_t K[2] = {(uint32_t)((uint64_t)size * q / P), (uint32_t)((uint64_t)size * (q + 1) / P)};
+    uint32_t first = 0, total;
+    uint32_t ends[2] = {0xffffffffu, 0xffffffffu};      // least key, and the complement of the greatest
+    for (uint32_t r0 = 0; r0 < n_runs; r0 += THREADS) {
+        const uint32_t r = r0 + tid;
+        const uint32_t len = r < n_runs ? min(counts[(uint64_t)r * stride] & ~SORT_READY, SPLIT_SIZE) : 0u;
+        const uint32_t start = first + block_scan<B>(len, lds.wtot, total);
+        first += total;
+        if (r >= n_runs) continue;
+        const uint16_t l = (uint16_t)len;
+        runs[r] = PartRun{start, {0, 0}, {l, l}, {{0, 0}, {0, 0}}};
+        if (len && start + len <= size) {
+            ends[0] = min(ends[0], src[start].x);
+            ends[1] = min(ends[1], ~src[start + len - 1].x);
+        }
+    }
+    if (first != size || size == 0) {            // (uniform) only after a failed front end
+        if (tid == 0) atomicOr(out.error, 4u);
+        return;
+    }
+    block_reduce<B>(ends, lds.red[0], [](int, uint32_t x, uint32_t y) { return min(x, y); });
+    // the samples, by as many threads a run as there are; from here on run r is thread r % THREADS's alone
+    uint32_t per_run = 1;
+    while (per_run < 64 && 2 * per_run * n_runs <= THREADS) per_run *= 2;
+    for (uint32_t r = tid / per_run; r < n_runs; r += THREADS / per_run) {
+        const uint32_t start = runs[r].start, n = (uint32_t)runs[r].hi[0] >> skip;
+        const uint2* from = src + start + (1u << skip) - 1;
+#pragma unroll 4
+        for (uint32_t q = tid % per_run; q < n; q += per_run) samples[(start >> skip) + q] = from[q << skip].x;
+    }
+    __syncthreads();
+    // the keys at both cuts lie in [a, b]: lo = entries below a, hi = entries up to b, ca and cb in all
+    uint32_t a[2], b[2], ca[2], cb[2], guess[2];
+    bool found[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        found[j] = K[j] == 0 || K[j] == size;
+        a[j] = ends[0];
+        b[j] = found[j] ? a[j] : ~ends[1];
+        ca[j] = 0;
+        cb[j] = size;
+    }
+    // where the key would be if the keys in [x, y], counts cx and cy, were evenly spread, in [x, y - 1]
+    auto even = [](uint32_t x, uint32_t y, uint32_t cx, uint32_t cy, uint32_t k, float shift) {
+        const uint32_t w = y - x;
+        const float wide = fminf((float)w, 4294967040.0f);        // (a float that fits 32 bits)
+        const float share = ((float)(k - cx) + 0.5f) / (float)(cy - cx) + shift;
+        return x + min((uint32_t)(fminf(fmaxf(share, 0.0f), 1.0f) * wide), w - 1);
+    };
+    {
+        // on the samples: a run's entries up to a key are those up to its last sample up to it, and
+        // half a gap
+        uint32_t x[2] = {a[0], a[1]}, y[2] = {b[0], b[1]}, cx[2] = {0, 0}, cy[2] = {size, size};
+        auto open = [&](int j) { return x[j] < y[j] && cy[j] > cx[j]; };
+        const uint32_t half = (1u << skip) / 2;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) guess[j] = x[j];
+        for (uint32_t step = 0; open(0) || open(1); ++step) {
+            // the counts, the samples next below the key, and (complemented) next above it
+            uint32_t got[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (open(j)) guess[j] = step % 2 ? x[j] + (y[j] - x[j]) / 2 : even(x[j], y[j], cx[j], cy[j], K[j], 0.0f);
+            for (uint32_t r = tid; r < n_runs; r += THREADS) {
+                const uint32_t base = runs[r].start >> skip, n = (uint32_t)runs[r].hi[0] >> skip;
+                uint32_t s0[2] = {0, 0}, s1[2] = {n, n};
+                while (s0[0] < s1[0] || s0[1] < s1[1]) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const uint32_t m = (s0[j] + s1[j]) / 2;
+                        if (s0[j] >= s1[j]) continue;
+                        if (samples[base + m] <= guess[j]) s0[j] = m + 1;
+                        else s1[j] = m;
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    got[j] += min((s0[j] << skip) + half, (uint32_t)runs[r].hi[0]);
+                    if (s0[j] > 0) got[2 + j] = max(got[2 + j], samples[base + s0[j] - 1]);
+                    if (s0[j] < n) got[4 + j] = max(got[4 + j], ~samples[base + s0[j]]);
+                }
+            }
+            block_reduce<B>(got, lds.red[step & 1],
+                            [](int i, uint32_t p, uint32_t q) { return i < 2 ? p + q : max(p, q); });
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                if (!open(j)) continue;
+                const uint32_t upto = got[j];
+                if (max(upto, K[j]) - min(upto, K[j]) <= B::TOLERANCE / 4) {        // near enough
+                    y[j] = x[j];
+                } else if (upto > K[j]) {        // no sample between the next below and the key: neither is the cut
+                    y[j] = max(x[j], min(guess[j], got[2 + j]));
+                    cy[j] = max(upto, cx[j]);
+                    guess[j] = y[j];
+                } else {
+                    x[j] = min(y[j], max(guess[j] + 1, ~got[4 + j]));
+                    cx[j] = min(upto, cy[j]);
+                    guess[j] = x[j];
+                }
+            }
+        }
+        __syncthreads();
+    }
+    auto open = [&](int j) { return !found[j] && a[j] < b[j]; };
+    for (uint32_t step = 0; open(0) || open(1); ++step) {
+        uint32_t pivot[2][2], upto[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const uint32_t w = b[j] - a[j];
+            if (step == 0) {
+                pivot[j][0] = pivot[j][1] = open(j) ? min(guess[j], b[j] - 1) : a[j];
+            } else if (step % 3 == 0) {                  // (sure to narrow it down, whatever the keys)
+                pivot[j][0] = a[j] + w / 3;
+                pivot[j][1] = open(j) ? min(a[j] + w / 3 * 2, b[j] - 1) : a[j];
+            } else {
+                pivot[j][0] = open(j) ? even(a[j], b[j], ca[j], cb[j], K[j], -1.0f / 16.0f) : a[j];
+                pivot[j][1] = open(j) ? even(a[j], b[j], ca[j], cb[j], K[j], 1.0f / 16.0f) : a[j];
+            }
+        }
+        for (uint32_t r = tid; r < n_runs; r += THREADS) {
+            PartRun run = runs[r];
+            const uint32_t base = run.start >> skip;
+            const uint2* from = src + run.start;
+            uint32_t lo[4], hi[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = i / 2;
+                lo[i] = run.lo[j];
+                hi[i] = open(j) && (step > 0 || i % 2 == 0) ? run.hi[j] : lo[i];     // (the first step has one pivot)
+                // the sampled places between them
+                uint32_t s0 = lo[i] >> skip, s1 = hi[i] >> skip;
+                while (s0 < s1) {
+                    const uint32_t m = (s0 + s1) / 2;
+                    if (samples[base + m] <= pivot[j][i % 2]) s0 = m + 1;
+                    else s1 = m;
+                }
+                lo[i] = max(lo[i], s0 << skip);
+                hi[i] = min(hi[i], ((s0 + 1) << skip) - 1);
+            }
+            // then the others, the four searches' loads together
+            while (lo[0] < hi[0] || lo[1] < hi[1] || lo[2] < hi[2] || lo[3] < hi[3]) {
+                uint32_t key[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) key[i] = lo[i] < hi[i] ? from[(lo[i] + hi[i]) / 2].x : 0u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t m = (lo[i] + hi[i]) / 2;
+                    if (lo[i] >= hi[i]) continue;
+                    if (key[i] <= pivot[i / 2][i % 2]) lo[i] = m + 1;
+                    else hi[i] = m;
+                }
+            }
+            if (step == 0) {
+                lo[1] = lo[0];
+                lo[3] = lo[2];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                run.cut[i / 2][i % 2] = (uint16_t)lo[i];
+                upto[i] += lo[i];
+            }
+            runs[r] = run;
+        }
+        block_reduce<B>(upto, lds.red[step & 1], sum);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (!open(j)) continue;
+            const uint32_t up0 = upto[2 * j], up1 = upto[2 * j + 1];
+            const bool raise0 = up0 <= K[j], raise1 = up1 <= K[j];        // the key is above the pivot
+            const uint32_t off0 = max(up0, K[j]) - min(up0, K[j]), off1 = max(up1, K[j]) - min(up1, K[j]);
+            found[j] = min(off0, off1) <= B::TOLERANCE;
+            const int at = off0 <= off1 ? 0 : 1;
+            for (uint32_t r = tid; r < n_runs; r += THREADS) {
+                if (found[j]) {
+                    runs[r].lo[j] = runs[r].hi[j] = runs[r].cut[j][at];
+                } else {
+                    if (raise0) runs[r].lo[j] = runs[r].cut[j][raise1 ? 1 : 0];
+                    if (!raise1) runs[r].hi[j] = runs[r].cut[j][raise0 ? 1 : 0];
+                }
+            }
+            if (found[j]) {
+                K[j] = ca[j] = at ? up1 : up0;
+            } else {
+                if (raise0) {
+                    a[j] = pivot[j][raise1 ? 1 : 0] + 1;
+                    ca[j] = raise1 ? up1 : up0;
+                }
+                if (!raise1) {
+                    b[j] = pivot[j][raise0 ? 1 : 0];
+                    cb[j] = raise0 ? up1 : up0;
+                }
+            }
+        }
+    }
+    // the cuts: entries below the key, and (equal keys) the first ones of those that equal it
+    const uint32_t K0 = K[0], K1 = K[1];
+    if (K1 <= K0 || K1 - K0 > B::CAP) {             // (uniform) never, by the tolerance
+        if (tid == 0) atomicOr(out.error, 4u);
+        return;
+    }
+    uint32_t rest[2] = {K0 - ca[0], K1 - ca[1]};
+    uint32_t at = 0, before[1] = {0};
+    PartShare* shares = reinterpret_cast<PartShare*>(lds.pair);
+    for (uint32_t r0 = 0; r0 < n_runs; r0 += THREADS) {
+        const uint32_t r = r0 + tid;
+        uint32_t cut[2] = {0, 0}, start = 0;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            // (K at an end of the bucket: lo = 0, hi = all, and rest is 0 or everything)
+            const uint32_t lo = r < n_runs ? runs[r].lo[j] : 0u, equal = r < n_runs ? runs[r].hi[j] - lo : 0u;
+            const uint32_t earlier = block_scan<B>(equal, lds.wtot, total);
+            cut[j] = lo + (rest[j] > earlier ? min(rest[j] - earlier, equal) : 0u);
+            rest[j] -= min(rest[j], total);
+        }
+        if (r < n_runs) start = runs[r].start;
+        const uint32_t place = at + block_scan<B>(cut[1] - cut[0], lds.wtot, total);      // (the runs have been read)
+        at += total;
+        if (r < n_runs) {
+            if (cut[0] > 0) before[0] = max(before[0], src[start + cut[0] - 1].x);
+            shares[r] = PartShare{place, start + cut[0]};
+        }
+    }
+    block_reduce<B>(before, lds.red[0], [](int, uint32_t x, uint32_t y) { return max(x, y); });
+    // entry e of the part is in the last run whose share begins at or before it
+    auto entry = [&](uint32_t a, uint32_t b) {
+        const uint32_t e = a + b;
+        uint32_t lo = 0, hi = n_runs - 1;
+        while (lo < hi) {
+            const uint32_t m = (lo + hi + 1) / 2;
+            if (shares[m].at <= e) lo = m;
+            else hi = m - 1;
+        }
+        return src[min(shares[lo].from + (e - shares[lo].at), size - 1)];
+    };
+    bucket_lds_sort<B>(entry, K1 - K0, out.lk.bits, lds);
+    write_sorted<B>(lds, b0 + K0, K1 - K0, K0 == 0, K1 == size, before[0], out);
+}
+
+// pairs: the split pass's output; plan.limit is 2 CAP and plan.alone CAP, or both 0 to divide
+// every bucket (for tests).  counts: the split pass's tiles' digit counts.
+template <typename B>
+__global__ __launch_bounds__(B::THREADS, B::WAVES_SIMD) void k_bucket_sort(uint2* pairs, SplitPlan plan, const uint32_t* counts,
                                                          BucketOut out) {
-    constexpr int THREADS = B::THREADS, BK_ITEMS = B::ITEMS;
+    constexpr int THREADS = B::THREADS;
     constexpr uint32_t CAP = B::CAP;
     __shared__ __align__(16) BucketLds<B> lds;
-    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / 64;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t* __restrict__ bases = plan.bases;
+    const uint32_t n_parts = *plan.n_parts;
     const uint32_t b0 = bases[blockIdx.x];
     const uint32_t b1 = bases[blockIdx.x + 1];
     if (out.order) place_tiles<THREADS>(bases, out, lds.wtot);
-    if (b1 <= b0) return;
-    const uint32_t cnt = b1 - b0, bits = out.lk.bits;
+    const uint32_t cnt = b1 > b0 ? b1 - b0 : 0u, bits = out.lk.bits;
     uint2* src = pairs + b0;
-
-    uint32_t* akeys = tmp_keys + b0;
-    uint32_t* avals = out.vals + b0;
-    // a debug render's keys, from the bucket's sorted local keys in akeys
-    auto put_keys = [&]() {
-        if (!out.want_keys()) return;
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        for (uint32_t e = tid; e < cnt; e += THREADS) out.put_key(b0 + e, ld_state(&akeys[e]));
-    };
-    if (!FORCE && cnt <= 2 * CAP) {
+    out.bucket = blockIdx.x;
+    if (cnt > 0 && cnt <= (n_parts ? plan.alone : plan.limit)) {
         // ---- the bucket in LDS, or in two runs: each half sorted in LDS and
         // written back in place, then the two merged ----
         const uint32_t runs = cnt <= CAP ? 1u : 2u;
         const uint32_t cA = runs == 1 ? cnt : (cnt + 1) / 2, cB = cnt - cA;
         for (uint32_t h = 0; h < runs; ++h) {
             const uint32_t o = h ? cA : 0u, m = h ? cB : cA;
-            bucket_lds_sort<B>(src + o, m, bits, lds);
+            const uint2* from = src + o;
+            bucket_lds_sort<B>([&](uint32_t a, uint32_t b) { return (from + a)[b]; }, m, bits, lds);
             if (runs == 1) {
-                for (uint32_t e = tid; e < cnt; e += THREADS) {
-                    const uint2 p = lds.pair[e];
-                    out.vals[b0 + e] = p.y;
-                    if (e == 0) out.start(b0, p.x);
-                    else out.boundary(b0 + e, lds.pair[e - 1].x, p.x);
-                    if (e + 1 == cnt) out.end(b0 + cnt, p.x);
-                    if (out.want_keys()) out.put_key(b0 + e, p.x);
-                }
-                return;
-            }
-            for (uint32_t e = tid; e < m; e += THREADS) src[o + e] = lds.pair[e];
-            __syncthreads();     // the first run's LDS before the second's loads
-        }
-        // both runs' keys into LDS, read past the CU's vector cache (it may
-        // hold the first run's lines from before they were sorted)
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        uint32_t* keys = reinterpret_cast<uint32_t*>(lds.pair);
-        for (uint32_t e0 = tid; e0 < cnt; e0 += BK_LOAD_BATCH * THREADS) {
-            uint32_t t[BK_LOAD_BATCH];
-#pragma unroll
-            for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j)
-                t[j] = e0 + j * THREADS < cnt ? ld_state(&src[e0 + j * THREADS].x) : 0u;
-#pragma unroll
-            for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j)
-                if (e0 + j * THREADS < cnt) keys[e0 + j * THREADS] = t[j];
-        }
-        __syncthreads();
-        // Merge path: thread t writes outputs [t S, (t + 1) S).  Its first
-        // output takes i entries from A and o - i from B, i the least index
-        // with A[i] > B[o - i - 1]; then the two are merged sequentially, A
-        // first on equal keys (A holds the earlier entries: stable).
-        const uint32_t* A = keys;
-        const uint32_t* Bk = keys + cA;
-        const uint32_t S = (cnt + THREADS - 1) / THREADS;
-        const uint32_t o0 = tid * S, o1 = min(o0 + S, cnt);
-        if (o0 < cnt) {
-            uint32_t lo = o0 > cB ? o0 - cB : 0u, hi = min(o0, cA);
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) / 2;
-                if (A[mid] <= Bk[o0 - mid - 1]) lo = mid + 1;
-                else hi = mid;
-            }
-            uint32_t ia = lo, ib = o0 - lo;
-            // the key before this thread's first output, for the tile runs
-            uint32_t before = max(ia > 0 ? A[ia - 1] : 0u, ib > 0 ? Bk[ib - 1] : 0u);
-            // BK_LOAD_BATCH outputs at a time: their value loads in flight together
-            for (uint32_t ob = o0; ob < o1; ob += BK_LOAD_BATCH) {
-                uint32_t key[BK_LOAD_BATCH], val[BK_LOAD_BATCH];
-#pragma unroll
-                for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
-                    if (ob + j >= o1) break;
-                    const bool take_a = ib >= cB || (ia < cA && A[ia] <= Bk[ib]);
-                    const uint32_t at = take_a ? ia : cA + ib;
-                    key[j] = take_a ? A[ia] : Bk[ib];
-                    val[j] = ld_state(&src[at].y);
-                    if (take_a) ++ia;
-                    else ++ib;
-                }
-#pragma unroll
-                for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
-                    if (ob + j >= o1) break;
-                    const uint32_t o = ob + j;
-                    out.vals[b0 + o] = val[j];
-                    if (o == 0) out.start(b0, key[j]);
-                    else out.boundary(b0 + o, before, key[j]);
-                    if (o + 1 == cnt) out.end(b0 + cnt, key[j]);
-                    if (out.want_keys()) akeys[o] = key[j];
-                    before = key[j];
-                }
+                write_sorted<B>(lds, b0, cnt, true, true, 0u, out);
+            } else {
+                for (uint32_t e = tid; e < m; e += THREADS) src[o + e] = lds.pair[e];
+                __syncthreads();     // the first run's LDS before the second's loads
             }
         }
-        put_keys();
-        return;
+        if (__builtin_expect(runs == 2, false)) merge_runs<B>(src, cA, cB, b0, out, lds);
     }
-
-    // ---- a bucket larger than the LDS ----
-    // Each pass streams it through global memory in chunks of CAP: a
-    // histogram sweep, then the chunks in order, each ranked in LDS and
-    // scattered after the chunks before it.  Passes alternate between the pairs
-    // and the second buffer's arrays and their number is odd, so that the last
-    // ends in the arrays.  Reads of what this workgroup wrote in the previous
-    // pass bypass the CU's vector cache.
-    uint32_t k[BK_ITEMS], v[BK_ITEMS], pos[BK_ITEMS];
-    const uint32_t passes = digit_passes(bits) | 1u;
-    for (uint32_t q = 0; q < passes; ++q) {
-        const uint32_t shift = RADIX_BITS * q;
-        const bool from_pairs = q % 2 == 0;
-        if (tid < RADIX) lds.tot[tid] = 0;
-        __syncthreads();
-        for (uint32_t i0 = tid; i0 < cnt; i0 += BK_LOAD_BATCH * THREADS) {
-            uint32_t t[BK_LOAD_BATCH];
-#pragma unroll
-            for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
-                const uint32_t i = i0 + j * THREADS;
-                t[j] = i < cnt ? ld_state(from_pairs ? &src[i].x : &akeys[i]) : 0u;
-            }
-#pragma unroll
-            for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j)
-                if (i0 + j * THREADS < cnt) atomicAdd(&lds.tot[digit_at(t[j], shift)], 1u);
+    if (__builtin_expect(n_parts == 0, true)) return;
+    // ---- parts of larger buckets, a workgroup's share of them ----
+    const uint32_t n_runs = (bases[gridDim.x] + SPLIT_SIZE - 1) / SPLIT_SIZE;
+    for (uint32_t p = blockIdx.x; p < n_parts; p += gridDim.x) {
+        uint32_t lo = 0, hi = gridDim.x - 1;         // the bucket: the first that parts up to it exceed p
+        while (lo < hi) {
+            const uint32_t m = (lo + hi) / 2;
+            if (plan.parts[m] > p) hi = m;
+            else lo = m + 1;
         }
-        __syncthreads();
-        const uint32_t base = digit_exclusive_scan<RADIX>(tid < RADIX ? lds.tot[tid] : 0u, lds.wtot);
-        if (tid < RADIX) lds.base[tid] = base;
-        __syncthreads();
-        for (uint32_t c0 = 0; c0 < cnt; c0 += CAP) {
-            const uint32_t ccnt = min(CAP, cnt - c0);
-            const uint32_t R = (ccnt + THREADS - 1) / THREADS;
-            const int lim = __builtin_amdgcn_readfirstlane((int)ccnt - (int)(wave * R * 64));
-#pragma unroll
-            for (int r = 0; r < BK_ITEMS; ++r) {
-                k[r] = v[r] = 0u;
-                if ((uint32_t)r < R && (int)lane < lim - r * 64) {
-                    const uint32_t e = c0 + (wave * R + r) * 64 + lane;
-                    if (from_pairs) {
-                        const uint2 p = ld_pair(&src[e]);
-                        k[r] = p.x;
-                        v[r] = p.y;
-                    } else {
-                        k[r] = ld_state(&akeys[e]);
-                        v[r] = ld_state(&avals[e]);
-                    }
-                }
-            }
-            bucket_rank<B>(k, ccnt, R, shift, pos, lds);
-#pragma unroll
-            for (int r = 0; r < BK_ITEMS; ++r) {
-                if ((uint32_t)r < R && (int)lane < lim - r * 64) {
-                    const uint32_t d = digit_at(k[r], shift);
-                    const uint32_t dst = lds.base[d] + pos[r] - lds.bs[d];
-                    if (dst < cnt) {      // always true for consistent counts
-                        if (from_pairs) {
-                            akeys[dst] = k[r];
-                            avals[dst] = v[r];
-                        } else {
-                            src[dst] = make_uint2(k[r], v[r]);
-                        }
-                    }
-                }
-            }
-            // the stores reach the L2 before any thread of the workgroup reads
-            // them back (the next pass, the ranges)
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
-            if (tid < RADIX) lds.base[tid] += lds.tot[tid];
-            __syncthreads();
-        }
+        const uint32_t first = bases[lo], before = lo ? plan.parts[lo - 1] : 0u;
+        out.bucket = lo;
+        __syncthreads();             // the LDS of what this workgroup did before
+        sort_part<B>(pairs + first, bases[lo + 1] - first, p - before, plan.parts[lo] - before, counts + lo, gridDim.x,
+                     n_runs, first, out, lds);
     }
-    // the arrays hold the bucket sorted
-    for (uint32_t e = tid; e < cnt; e += THREADS) {
-        const uint32_t key = ld_state(&akeys[e]);
-        if (e == 0) out.start(b0, key);
-        else out.boundary(b0 + e, ld_state(&akeys[e - 1]), key);
-        if (e + 1 == cnt) out.end(b0 + cnt, key);
-    }
-    put_keys();
-}
-
-template <typename B>
-static void launch_bucket(hipStream_t s, uint2* pairs, uint32_t* tmp_keys, const WsDev& ws, uint32_t buckets,
-                          const BucketOut& out, bool force) {
-    if (force)
-        hipLaunchKernelGGL((k_bucket_sort<B, true>), dim3(buckets), dim3(B::THREADS), 0, s, pairs, tmp_keys,
-                           ws.bases, out);
-    else
-        hipLaunchKernelGGL((k_bucket_sort<B, false>), dim3(buckets), dim3(B::THREADS), 0, s, pairs, tmp_keys,
-                           ws.bases, out);
 }
 
 template <typename KeyT, int BITS>
-static void launch_split_pass(hipStream_t s, const FrameDev& f, const WsDev& ws, uint2* pairs, bool force) {
+static void launch_split_pass(hipStream_t s, const FrameDev& f, const WsDev& ws, uint2* pairs, const SplitPlan& plan,
+                              bool force) {
     using S = SplitShape<BITS>;
     const PairsOut<KeyT> out{pairs, f.lk, ws.params};
     uint32_t* tiles = ws.sort_state;
@@ -989,37 +1438,51 @@ static void launch_split_pass(hipStream_t s, const FrameDev& f, const WsDev& ws,
         hipLaunchKernelGGL(kernel, dim3(ws.sort_rows), dim3(S::THREADS), 0, s,
                            reinterpret_cast<const KeyT*>(ws.keys_a), ws.vals_a, out, ws.header, ws.hist,
                            (uint32_t)(MAX_PASSES * RADIX), tiles, groups, (uint32_t*)nullptr, (uint32_t*)nullptr,
-                           f.split_shift, ws.bases);
+                           f.split_shift, plan);
     };
     if (force) launch(k_radix_pass<KeyT, S, PairsOut<KeyT>, true>);
     else launch(k_radix_pass<KeyT, S, PairsOut<KeyT>, false>);
 }
 
+// The two kernels with bucket workgroups B, for buckets of up to ROOM entries on average.
+template <typename B, uint32_t ROOM>
+static void launch_split(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32_t key_bytes, uint2* pairs,
+                         const BucketOut& out, bool force) {
+    // the digit counts' copies are as wide as two split digits: the parts table takes
+    // the unused half of the first
+    static_assert(2 * SPLIT_DIGITS_MAX <= MAX_PASSES * RADIX, "the parts table fits");
+    // the frame's radix tiles, the runs of a divided bucket, fit the entries' LDS
+    static_assert(((uint64_t)(ROOM + 1) << SPLIT_WIDE_BT) / SPLIT_SIZE * sizeof(PartRun) < B::CAP * sizeof(uint2) / 2,
+                  "the runs, and samples of them, fit");
+    const SplitPlan plan{ws.bases, ws.bases + SPLIT_DIGITS_MAX + 1, ws.hist + SPLIT_DIGITS_MAX, force ? 0u : 2 * B::CAP,
+                         force ? 0u : B::CAP, B::PART};
+    if (key_bytes == 8) {
+        if (f.split_bits == 10) launch_split_pass<uint64_t, 10>(s, f, ws, pairs, plan, force);
+        else launch_split_pass<uint64_t, 8>(s, f, ws, pairs, plan, force);
+    } else {
+        if (f.split_bits == 10) launch_split_pass<uint32_t, 10>(s, f, ws, pairs, plan, force);
+        else launch_split_pass<uint32_t, 8>(s, f, ws, pairs, plan, force);
+    }
+    hipLaunchKernelGGL(k_bucket_sort<B>, dim3(1u << f.split_bits), dim3(B::THREADS), 0, s, pairs, plan, ws.sort_state,
+                       out);
+}
+
 void launch_sort_split(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32_t key_bytes, bool force,
                        bool want_keys) {
     // pairs in the second key and value arrays (32-bit keys: the two are
-    // adjacent); sorted values in the first value array
+    // adjacent); sorted values in the first value array, where wanted sorted keys
+    // in the first key array
     uint2* pairs = reinterpret_cast<uint2*>(ws.keys_b);
-    if (key_bytes == 8) {
-        if (f.split_bits == 10) launch_split_pass<uint64_t, 10>(s, f, ws, pairs, force);
-        else launch_split_pass<uint64_t, 8>(s, f, ws, pairs, force);
-    } else {
-        if (f.split_bits == 10) launch_split_pass<uint32_t, 10>(s, f, ws, pairs, force);
-        else launch_split_pass<uint32_t, 8>(s, f, ws, pairs, force);
-    }
-    const uint32_t buckets = 1u << f.split_bits;
     BucketOut out{};
     out.vals = ws.vals_a;
     out.ranges = ws.ranges;
-    // 32-bit keys replace the emitted ones; 64-bit keys take the place of their own pairs
     out.keys32 = want_keys && key_bytes == 4 ? reinterpret_cast<uint32_t*>(ws.keys_a) : nullptr;
-    out.keys64 = want_keys && key_bytes == 8 ? reinterpret_cast<uint64_t*>(ws.keys_b) : nullptr;
+    out.keys64 = want_keys && key_bytes == 8 ? reinterpret_cast<uint64_t*>(ws.keys_a) : nullptr;
     out.order = f.ordered == ORDER_BUCKETS ? ws.order : nullptr;
     out.error = &ws.header->error;
     out.prm = ws.params;
     out.lk = f.lk;
     out.n_tiles = (uint32_t)f.n_tiles;
-    uint32_t* tmp_keys = reinterpret_cast<uint32_t*>(ws.keys_a);
     // The workgroup by the entries a bucket may hold on average (what the
     // workspace holds, usually 1.25 to 2 times the frame's): the busiest bucket
     // has about twice the frame's average, and should still be one run in LDS,
@@ -1027,9 +1490,9 @@ void launch_sort_split(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32
     // times in us with 512 x 9, 512 x 16 and 1024 x 16 entries:
     // 1280x720 28, 35, 56; 1080p (1M) 33, 42, 68 (plain 65, 63, 94); 4K (3M) 94, 73, 104.
     const uint32_t room = f.capacity >> f.split_bits;
-    if (room <= 4608) launch_bucket<BucketShape<512, 9>>(s, pairs, tmp_keys, ws, buckets, out, force);
-    else if (room <= 12288) launch_bucket<BucketShape<512, 16>>(s, pairs, tmp_keys, ws, buckets, out, force);
-    else launch_bucket<BucketShape<1024, 16>>(s, pairs, tmp_keys, ws, buckets, out, force);
+    if (room <= 4608) launch_split<BucketShape<512, 9, 6>, 4608>(s, f, ws, key_bytes, pairs, out, force);
+    else if (room <= 12288) launch_split<BucketShape<512, 16, 4>, 12288>(s, f, ws, key_bytes, pairs, out, force);
+    else launch_split<BucketShape<1024, 16, 4>, SPLIT_MAX_ROOM>(s, f, ws, key_bytes, pairs, out, force);
 }
 
 // ---------------------------------------------------------------------------

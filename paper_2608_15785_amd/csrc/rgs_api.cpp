@@ -948,7 +948,7 @@ bool rgs::choose_sort(FrameLaunch& fl, const CamDev& cam, bool debug) {
     const int32_t digit = f.b_t < SPLIT_MIN_BT ? 0 : wide ? SPLIT_WIDE_BT : SPLIT_MIN_BT;
     LocalKey lk{};
     lk.tile_bits = (uint32_t)(f.b_t - digit);
-    bool split = digit > 0;
+    bool split = digit > 0 && f.capacity >> digit <= SPLIT_MAX_ROOM;
     if (fl.L.key_bytes == 4) {
         lk.bits = 32 - (uint32_t)digit;
         f.split_shift = lk.bits;
@@ -1122,7 +1122,7 @@ static rgs_status render_impl(rgs_ctx* ctx, const rgs_scene* sc, const rgs_camer
     if (dbg) {
         const WsDev& w = fl.w;
         const uint64_t n_entries = rh.n_entries;
-        const bool in_b = fl.f.split_bits ? fl.L.key_bytes == 8 : fl.L.passes % 2 == 1;
+        const bool in_b = !fl.f.split_bits && fl.L.passes % 2 == 1;
         const void* ks = in_b ? w.keys_b : w.keys_a;
         const uint32_t* vs = sorted_vals(fl);
         if (dbg->keys_sorted && n_entries) {

@@ -93,6 +93,7 @@ constexpr uint32_t SPLIT_SIZE = SPLIT_THREADS * SPLIT_ITEMS;
 constexpr int32_t SPLIT_MIN_BT = 8, SPLIT_WIDE_BT = 10;
 constexpr uint32_t SPLIT_DIGITS_MAX = 1024;
 constexpr uint32_t SPLIT_WIDE_CAPACITY = 1u << 18;
+constexpr uint32_t SPLIT_MAX_ROOM = 24576;       // capacity per bucket
 // Radix tiles per look-back group: the last tile of each group publishes the
 // group's digit counts, so a tile reads at most SORT_GROUP - 1 tile states plus
 // one state per earlier group.  32 balances the two (1M / 1080p fast sort:
@@ -578,7 +579,7 @@ void launch_ranges(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32_t k
                    bool result_in_b);
 // The split sort (f.split_bits): sorted values end in vals_a, and the tile
 // ranges are written too (no launch_ranges); with want_keys also the sorted
-// keys, 32-bit ones in keys_a and 64-bit ones in keys_b.
+// keys, in keys_a.
 void launch_sort_split(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32_t key_bytes, bool force_fallback,
                        bool want_keys);
 // The rasterizers' schedule: ws.order from the tile ranges.
