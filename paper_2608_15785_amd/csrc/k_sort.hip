@@ -43,10 +43,13 @@
 namespace rgs {
 
 
-// A radix pass's shape: digit width, threads and keys per thread of a tile.
-template <int BITS_, int THREADS_, int ITEMS_>
+// A radix pass's shape: digit width, threads and keys per thread of a tile, and the
+// waves a SIMD that the registers must allow, two workgroups a CU of the LSD passes
+// (64-bit keys, six passes at 1M / 1080p: 136 us, with one workgroup 177; 32-bit keys
+// with three, as their LDS allows, spill: four passes of 1M at 176x176 78 us, 65 with two).
+template <int BITS_, int THREADS_, int ITEMS_, int WAVES_SIMD_>
 struct PassShape {
-    static constexpr int BITS = BITS_, THREADS = THREADS_, ITEMS = ITEMS_;
+    static constexpr int BITS = BITS_, THREADS = THREADS_, ITEMS = ITEMS_, WAVES_SIMD = WAVES_SIMD_;
     static constexpr uint32_t DIGITS = 1u << BITS;
     static constexpr int WAVES = THREADS / 64;
     static constexpr uint32_t SIZE = THREADS * ITEMS;
@@ -54,9 +57,9 @@ struct PassShape {
     static_assert(THREADS % DIGITS == 0 && THREADS >= (int)DIGITS, "whole digit rows per block");
 };
 template <typename KeyT>
-using LsdShape = PassShape<RADIX_BITS, SORT_THREADS, SortTile<KeyT>::ITEMS>;
+using LsdShape = PassShape<RADIX_BITS, SORT_THREADS, SortTile<KeyT>::ITEMS, 4>;
 template <int BITS>
-using SplitShape = PassShape<BITS, SPLIT_THREADS, SPLIT_ITEMS>;
+using SplitShape = PassShape<BITS, SPLIT_THREADS, SPLIT_ITEMS, 4>;
 
 __device__ inline uint32_t entry_count(const WsHeader* h) {
     uint64_t n = h->n_entries;
@@ -683,7 +686,7 @@ __device__ __attribute__((noinline)) void crowded_tile(Lds<TileLds<S, typename O
 }
 
 template <typename KeyT, typename S, typename Out, bool FORCE>
-__global__ __launch_bounds__(S::THREADS) void k_radix_pass(const KeyT* __restrict__ kin,
+__global__ __launch_bounds__(S::THREADS, S::WAVES_SIMD) void k_radix_pass(const KeyT* __restrict__ kin,
                                                            const uint32_t* __restrict__ vin, Out out,
                                                            const WsHeader* header, const uint32_t* hist,
                                                            uint32_t hist_stride, uint32_t* tiles, uint32_t* groups,
