@@ -178,7 +178,9 @@ __device__ inline bool frame_matches(const WsDev& ws, FrameKey key) {
 // state back over the pair.  dx, dy: pixel minus mean; a = (u, v, A, B), m = (C,
 // o, r, g), cb: b; d: dL/dC at the pixel; DS = d . S, S the colour behind the
 // pair plus the background's share, so that dL/dalpha = Tb (d . col) -
-// DS / (1 - alpha); raw = o e.
+// DS / (1 - alpha), Tb = T / (1 - alpha) the transmittance in front of the pair; the
+// difference is taken of T (d . col) and DS, before the division, whose rounding
+// would otherwise enter both sides of it.  raw = o e.
 __device__ inline void pair_adjoint_plain(float e, float raw, float dx, float dy, const float4& a, const float4& m,
                                           float cb, const float (&d)[3], float& T, float& DS, float (&g)[9]) {
     const float alpha = fminf(ALPHA_MAX, raw);
@@ -189,7 +191,7 @@ __device__ inline void pair_adjoint_plain(float e, float raw, float dx, float dy
     g[7] = fmaf(w, d[1], g[7]);
     g[8] = fmaf(w, d[2], g[8]);
     const float dcol = fmaf(d[0], m.z, fmaf(d[1], m.w, d[2] * cb));
-    const float dA = fmaf(Tb, dcol, -(DS * inv));
+    const float dA = inv * fmaf(T, dcol, -DS);
     DS = fmaf(w, dcol, DS);
     T = Tb;
     const float dRaw = raw <= ALPHA_MAX ? dA : 0.0f;   // a clamped alpha is constant
@@ -217,7 +219,7 @@ __device__ inline void pair_adjoint(float P, float dx, float dy, float cr, float
     g[7] = fmaf(w, d[1], g[7]);
     g[8] = fmaf(w, d[2], g[8]);
     const float dcol = fmaf(d[0], cr, fmaf(d[1], cg, d[2] * cb));
-    const float dA = fmaf(Tb, dcol, -(DS * inv));
+    const float dA = inv * fmaf(T, dcol, -DS);
     DS = fmaf(w, dcol, DS);
     T = Tb;
     const float dP = raw <= ALPHA_MAX ? dA * raw : 0.0f;     // a clamped alpha is constant
@@ -489,17 +491,25 @@ __global__ __launch_bounds__(256 / PIX, 4) void k_raster_backward(FrameDev f, Ws
         }
         __syncthreads();                         // the rows are complete, and the batch's lists are read
         if (wave == stager && lane < kept) {
-            float sum[9];
+            float sum[9];            // of the upper half-tile's regions, then the lower's, then both
 #pragma unroll
             for (int c = 0; c < 9; ++c) sum[c] = 0.0f;
 #pragma unroll
-            for (int r = 0; r < BWD_REGIONS; ++r) {
-                if (!((my_mask >> r) & 1u)) continue;
-                const uint32_t q = s_base[wave][r] + ((my_place[r / 4] >> (8 * (r % 4))) & 0xffu);
-                const float4 s0 = s_row[q][0], s1 = s_row[q][1];
-                sum[0] += s0.x; sum[1] += s0.y; sum[2] += s0.z; sum[3] += s0.w;
-                sum[4] += s1.x; sum[5] += s1.y; sum[6] += s1.z; sum[7] += s1.w;
-                sum[8] += s_row8[q];
+            for (int h = 0; h < 2; ++h) {
+                float half[9];
+#pragma unroll
+                for (int c = 0; c < 9; ++c) half[c] = 0.0f;
+#pragma unroll
+                for (int r = 8 * h; r < 8 * h + 8; ++r) {
+                    if (!((my_mask >> r) & 1u)) continue;
+                    const uint32_t q = s_base[wave][r] + ((my_place[r / 4] >> (8 * (r % 4))) & 0xffu);
+                    const float4 s0 = s_row[q][0], s1 = s_row[q][1];
+                    half[0] += s0.x; half[1] += s0.y; half[2] += s0.z; half[3] += s0.w;
+                    half[4] += s1.x; half[5] += s1.y; half[6] += s1.z; half[7] += s1.w;
+                    half[8] += s_row8[q];
+                }
+#pragma unroll
+                for (int c = 0; c < 9; ++c) sum[c] += half[c];
             }
             if (TRAIN) {
                 // moments of dL/dP -> dL/d(u, v, A, B, C) with the entry's conic
