@@ -64,9 +64,16 @@ class GaussianRasterizer:
         ws = self._ws.get(key)
         want = min(min_entries if min_entries is not None else max(4 * self.n, 1 << 16), B.MAX_ENTRIES)
         if ws is None or B.workspace_capacity(self.n, key[0], key[1], "plain", ws.numel()) < want:
-            ws = B.new_workspace(self.n, key[0], key[1], "plain", want, self.R.device)
+            # memory of the context's own stream, on which every frame uses it: another stream's could
+            # go back to that stream's pool while a frame still runs
+            with torch.cuda.stream(self._stream()):
+                ws = B.new_workspace(self.n, key[0], key[1], "plain", want, self.R.device)
             self._ws[key] = ws
         return ws
+
+    def _stream(self):
+        ctx = self.R.ctx
+        return torch.cuda.ExternalStream(ctx.stream, ctx.device) if ctx.stream else torch.cuda.default_stream(ctx.device)
 
     def _render(self, params, cam):
         scene = self._scene_for(*params)
