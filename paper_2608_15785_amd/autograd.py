@@ -75,7 +75,14 @@ class GaussianRasterizer:
         ctx = self.R.ctx
         return torch.cuda.ExternalStream(ctx.stream, ctx.device) if ctx.stream else torch.cuda.default_stream(ctx.device)
 
+    def _own_stream(self):
+        ctx = self.R.ctx
+        return torch.cuda.current_stream(ctx.device).cuda_stream == ctx.stream
+
     def _render(self, params, cam):
+        own = self._own_stream()
+        if not own:                 # the parameters are the caller's stream's work
+            torch.cuda.current_stream(self.R.ctx.device).synchronize()
         scene = self._scene_for(*params)
         B.scene_update_plain(self.R.ctx, scene, *(p.detach().float().contiguous() for p in params))
         self._gen += 1
@@ -83,7 +90,6 @@ class GaussianRasterizer:
         # On the context's own stream, whose later work waits for the image anyway, the call
         # returns once the frame's outcome is known; for another stream it waits for the image.
         ctx = self.R.ctx
-        own = torch.cuda.current_stream(ctx.device).cuda_stream == ctx.stream
         for _ in range(4):
             try:
                 img, _ = B.render(ctx, scene, cam, self.path, ws, stats=not own)
@@ -121,5 +127,11 @@ class _RenderFunction(torch.autograd.Function):
         if rast._last.get((int(cam.width), int(cam.height))) != (ctx.fid, rast._gen):
             # the workspace holds a later frame, or the scene was rewritten since: render this frame again
             rast._render(params, cam)
-        g = B.render_backward(rast.R.ctx, rast.scene, cam, rast.workspace(cam), dimg.float().contiguous())
+        dimg = dimg.float().contiguous()
+        own = rast._own_stream()
+        if not own:                 # dimg is the caller's stream's work, and the gradients are for it
+            torch.cuda.current_stream(rast.R.ctx.device).synchronize()
+        g = B.render_backward(rast.R.ctx, rast.scene, cam, rast.workspace(cam), dimg)
+        if not own:
+            rast._stream().synchronize()
         return g["means"], g["scales"], g["quats"], g["opacity"], g["sh"], None, None
