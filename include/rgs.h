@@ -188,6 +188,12 @@ rgs_status rgs_ctx_collect_timing(rgs_ctx* ctx, double* stage_ms, int64_t* n_fra
  * [1, 2^20], iters < 0), HIP. */
 rgs_status rgs_probe_valu(rgs_ctx* ctx, int32_t blocks, int32_t iters, float* out);
 
+/* The plain path's exponential by itself: for each of the n exponents p, e^p as
+ * its rasterizer and backward pass take it, and by the device library's expf, so
+ * that the two and a reference can be compared.  All device, n floats,
+ * caller-owned.  Asynchronous.  Errors: INVALID (NULL, n < 0), HIP. */
+rgs_status rgs_probe_exp(rgs_ctx* ctx, const float* p, int64_t n, float* out_pair, float* out_expf);
+
 /* ---------------------------------------------------------------------------
  * Scene upload (once per scene, not per frame).
  * Inputs are the activated parameters a trained 3DGS scene holds, all host

@@ -180,6 +180,7 @@ SIGNATURES = [
                                      C.c_int32, C.c_void_p, C.c_uint64, C.c_void_p, C.POINTER(DebugOut),
                                      C.POINTER(FrameStats)]),
     ("rgs_probe_valu", C.c_int32, [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p]),
+    ("rgs_probe_exp", C.c_int32, [C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]),
     ("rgs_ctx_set_debug", C.c_int32, [C.c_void_p, C.c_uint32]),
     ("rgs_render_static", C.c_int32, [C.c_void_p, C.c_void_p, C.POINTER(CameraC), C.c_int32, C.c_int32,
                                       C.c_int32, C.c_void_p, C.POINTER(FrameStats)]),
@@ -307,6 +308,15 @@ def probe_valu(ctx: "Context", blocks: int, iters: int, out) -> None:
     if out.numel() < blocks * 256 or out.dtype != _torch().float32 or not out.is_cuda:
         raise ValueError("out must be a float32 device tensor of blocks * 256 elements")
     _check(lib.rgs_probe_valu(ctx.handle, int(blocks), int(iters), _ptr(out)), "rgs_probe_valu")
+
+
+def probe_exp(ctx: "Context", p):
+    """e^p of a float32 device tensor as the plain path takes it, and by the device's expf (rgs_probe_exp)."""
+    if p.dtype != _torch().float32 or not p.is_cuda or not p.is_contiguous():
+        raise ValueError("p must be a contiguous float32 device tensor")
+    pair, libm = _torch().empty_like(p), _torch().empty_like(p)
+    _check(lib.rgs_probe_exp(ctx.handle, _ptr(p), p.numel(), _ptr(pair), _ptr(libm)), "rgs_probe_exp")
+    return pair, libm
 
 
 class Context:

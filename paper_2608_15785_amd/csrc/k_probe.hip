@@ -7,7 +7,9 @@
 // FMAs, `iters` rounds, so each wave issues exactly 8 * iters FMA
 // instructions in its loop (plus a few dozen set-up and final instructions),
 // with enough independent work per wave to issue back to back.
-#include "rgs_internal.h"
+//
+// A second probe evaluates the plain path's exponential (exp_pair) and expf.
+#include "rgs_fold.h"
 
 namespace rgs {
 
@@ -35,6 +37,20 @@ __global__ __launch_bounds__(PROBE_THREADS) void k_probe_valu(float* __restrict_
 
 void launch_probe_valu(hipStream_t s, float* out, uint32_t blocks, uint32_t iters) {
     hipLaunchKernelGGL(k_probe_valu, dim3(blocks), dim3(PROBE_THREADS), 0, s, out, iters);
+}
+
+__global__ __launch_bounds__(PROBE_THREADS) void k_probe_exp(const float* __restrict__ p, int64_t n,
+                                                             float* __restrict__ pair, float* __restrict__ libm) {
+    for (int64_t i = (int64_t)blockIdx.x * PROBE_THREADS + threadIdx.x; i < n; i += (int64_t)gridDim.x * PROBE_THREADS) {
+        pair[i] = exp_pair(p[i]);
+        libm[i] = expf(p[i]);
+    }
+}
+
+void launch_probe_exp(hipStream_t s, const float* p, int64_t n, float* pair, float* libm) {
+    const int64_t blocks = (n + PROBE_THREADS - 1) / PROBE_THREADS;
+    hipLaunchKernelGGL(k_probe_exp, dim3((uint32_t)(blocks < 4096 ? blocks : 4096)), dim3(PROBE_THREADS), 0, s, p, n,
+                       pair, libm);
 }
 
 }  // namespace rgs

@@ -369,6 +369,16 @@ extern "C" rgs_status rgs_probe_valu(rgs_ctx* ctx, int32_t blocks, int32_t iters
     return ok();
 }
 
+extern "C" rgs_status rgs_probe_exp(rgs_ctx* ctx, const float* p, int64_t n, float* out_pair, float* out_expf) {
+    if (!ctx || !p || !out_pair || !out_expf) return fail(RGS_E_INVALID, "rgs_probe_exp: NULL argument");
+    if (n < 0) return fail(RGS_E_INVALID, "rgs_probe_exp: n = %lld", (long long)n);
+    if (n == 0) return ok();
+    HIP_TRY(hipSetDevice(ctx->device));
+    launch_probe_exp(ctx->stream, p, n, out_pair, out_expf);
+    HIP_TRY(hipGetLastError());
+    return ok();
+}
+
 // Events of the next timed frame (the pool grows on demand; full pools are
 // harvested, which synchronises the stream only every 1024 frames).
 static rgs_status next_events(rgs_ctx* ctx, FrameEvents** fe) {

@@ -590,6 +590,7 @@ void launch_raster_fast(hipStream_t s, const FrameDev& f, const WsDev& ws, const
                         uint32_t opts);
 void launch_widen_keys(hipStream_t s, const uint32_t* in, uint64_t* out, uint64_t n);
 void launch_probe_valu(hipStream_t s, float* out, uint32_t blocks, uint32_t iters);
+void launch_probe_exp(hipStream_t s, const float* p, int64_t n, float* pair, float* libm);
 
 // The n_proc word of a pixel: pairs visited, with this bit set when blending
 // stopped at the last of them (that pair was not blended).
