@@ -35,7 +35,7 @@
 // the workspace header on the device and tiles beyond it return at once, so
 // no host round trip sits between the front end and the sort.
 //
-// Frames of at least 2^8 tiles take the tile index's top bits first, in one such
+// Frames of more than 2^7 tiles (8 tile bits) take the index's top bits first, in one such
 // pass, and the rest per bucket in LDS (the split sort below), which also writes
 // the tile ranges.
 #include "rgs_internal.h"
@@ -726,8 +726,8 @@ void launch_sort(hipStream_t s, const WsDev& ws, uint32_t key_bytes, uint32_t pa
 }
 
 // ---------------------------------------------------------------------------
-// The split sort, for frames of at least 2^SPLIT_MIN_BT tiles.  The same stable
-// sort, reorganised:
+// The split sort, for frames of SPLIT_MIN_BT tile bits or more (129 tiles).  The same
+// stable sort, reorganised:
 //   * one radix pass as above on the tile index's top D bits moves every entry
 //     to its digit's bucket, in input order: a bucket holds 2^(b_t - D) whole
 //     tiles.  It leaves (local key, value) pairs, the local key being what is
@@ -739,13 +739,15 @@ void launch_sort(hipStream_t s, const WsDev& ws, uint32_t key_bytes, uint32_t pa
 //     (bucket_rank).  A bucket of at most CAP entries stays in LDS for all of
 //     them; one of at most 2 CAP is sorted as two runs in LDS, each written back
 //     in place, and the two merged;
+//   * one of more, up to the shape's LIMIT, is streamed by its workgroup through global
+//     memory, digit by digit (stream_bucket);
 //   * the entries of a view from afar crowd into few tiles, and then into few
-//     buckets.  A bucket of more than 2 CAP entries is divided among workgroups, CAP
-//     consecutive places of the sorted bucket each (sort_part).  The split pass, whose
+//     buckets.  In a crowded frame, one with a bucket beyond the LIMIT, every bucket of
+//     more than CAP entries is divided among workgroups (sort_part).  The split pass, whose
 //     tiles all know the bucket sizes, then leaves its tiles sorted by the whole
-//     key, so that the bucket consists of one sorted run per radix tile, and a part
-//     finds the two cuts through the runs that hold its entries by bisection on
-//     the key, gathers them and sorts them in LDS.  No workgroup waits for another;
+//     key, so that the bucket consists of one sorted run per radix tile; a part finds
+//     its two cuts through the runs by their keys, gathers its entries and sorts
+//     them in LDS.  No workgroup waits for another;
 //   * a workgroup, holding its entries sorted, writes its tiles' ranges.
 // Every pass is stable and the top digit is taken first, then the rest least
 // significant first; as a stable sort on the top digit followed by a stable
@@ -756,13 +758,22 @@ void launch_sort(hipStream_t s, const WsDev& ws, uint32_t key_bytes, uint32_t pa
 
 constexpr uint32_t BK_LOAD_BATCH = 8;       // loads of a thread in flight where a loop stages or merges
 
-// A bucket's workgroup: threads, entries each holds, and the waves a SIMD that its
-// LDS allows (the registers of the parts' code must not allow fewer).
-template <int THREADS_, int ITEMS_, int WAVES_SIMD_>
+// A bucket's workgroup: threads, entries each holds, the waves a SIMD that its LDS
+// allows (the registers must not allow fewer), and the limit of the buckets that one
+// workgroup sorts.
+//
+// The limit: streaming costs a time with the one bucket's entries, dividing one with all the
+// frame's, which the split pass sorts by the whole key.  Sort in us, streamed and
+// divided: 512 x 9, busiest bucket of 2 to 3 CAP (1M Gaussians / 1080p from 40) 80, 80 (plain
+// 194, 215), of 3 to 4 CAP (from 60) 156, 133 (312, 174), of more (from 200) 707, 141 (1378,
+// 184); 512 x 16 of 3 to 4 CAP (3M / 4K from 100, plain) 522, 571, of more (from 300) 1600,
+// 490; 1024 x 16 of 3 to 4 CAP (6M / 4K from 100, plain) 850, 1190.
+template <int THREADS_, int ITEMS_, int WAVES_SIMD_, uint32_t LIMIT_CAPS>
 struct BucketShape {
     static constexpr int THREADS = THREADS_, ITEMS = ITEMS_, WAVES_SIMD = WAVES_SIMD_;
     static constexpr int WAVES = THREADS / 64;
     static constexpr uint32_t CAP = THREADS * ITEMS;
+    static constexpr uint32_t LIMIT = LIMIT_CAPS * CAP;
     // a part of a divided bucket: CAP entries at most with both cuts off by the tolerance
     static constexpr uint32_t TOLERANCE = CAP / 8, PART = CAP - 2 * TOLERANCE;
 };
@@ -773,7 +784,7 @@ struct BucketLds {
     static constexpr int WORDS = B::WAVES > RADIX / 64 ? B::WAVES : RADIX / 64;
     uint2 pair[B::CAP];                        // (local key, value)
     uint16_t whist[B::WAVES * RADIX];          // per-wave digit counts, then places (below CAP)
-    uint32_t tot[RADIX], bs[RADIX];
+    uint32_t tot[RADIX], bs[RADIX], base[RADIX];
     uint32_t wtot[WORDS];
     uint32_t red[2][6][B::WAVES];              // block-wide sums and extremes
 };
@@ -1061,6 +1072,102 @@ __device__ inline void merge_runs(const uint2* src, uint32_t cA, uint32_t cB, ui
             before = key[j];
         }
     }
+}
+
+__device__ inline uint2 ld_pair(const uint2* p) {
+    const uint64_t w = ld_state(reinterpret_cast<const uint64_t*>(p));
+    return make_uint2((uint32_t)w, (uint32_t)(w >> 32));
+}
+
+// Sorts a bucket of any size by one workgroup, bound by the latency of one chunk after
+// another: each pass streams it through global memory in chunks of CAP, a histogram sweep,
+// then the chunks in order, each ranked in LDS and scattered after the chunks before it.
+// Passes alternate between the pairs and the second buffer's arrays (akeys, and the
+// bucket's output values) and their number is odd, so that the last ends in the arrays.
+// Reads of what this workgroup wrote in the previous pass bypass the CU's vector cache.
+// Every thread calls it (barriers).
+template <typename B>
+__device__ inline void stream_bucket(uint2* src, uint32_t* akeys, uint32_t cnt, uint32_t b0, const BucketOut& out,
+                                     BucketLds<B>& lds) {
+    constexpr int THREADS = B::THREADS, BK_ITEMS = B::ITEMS;
+    constexpr uint32_t CAP = B::CAP;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / 64;
+    uint32_t* avals = out.vals + b0;
+    uint32_t k[BK_ITEMS], v[BK_ITEMS], pos[BK_ITEMS];
+    const uint32_t passes = digit_passes(out.lk.bits) | 1u;
+    for (uint32_t q = 0; q < passes; ++q) {
+        const uint32_t shift = RADIX_BITS * q;
+        const bool from_pairs = q % 2 == 0;
+        if (tid < RADIX) lds.tot[tid] = 0;
+        __syncthreads();
+        for (uint32_t i0 = tid; i0 < cnt; i0 += BK_LOAD_BATCH * THREADS) {
+            uint32_t t[BK_LOAD_BATCH];
+#pragma unroll
+            for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j) {
+                const uint32_t i = i0 + j * THREADS;
+                t[j] = i < cnt ? ld_state(from_pairs ? &src[i].x : &akeys[i]) : 0u;
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < BK_LOAD_BATCH; ++j)
+                if (i0 + j * THREADS < cnt) atomicAdd(&lds.tot[digit_at(t[j], shift)], 1u);
+        }
+        __syncthreads();
+        const uint32_t base = digit_exclusive_scan<RADIX>(tid < RADIX ? lds.tot[tid] : 0u, lds.wtot);
+        if (tid < RADIX) lds.base[tid] = base;
+        __syncthreads();
+        for (uint32_t c0 = 0; c0 < cnt; c0 += CAP) {
+            const uint32_t ccnt = min(CAP, cnt - c0);
+            const uint32_t R = (ccnt + THREADS - 1) / THREADS;
+            const int lim = __builtin_amdgcn_readfirstlane((int)ccnt - (int)(wave * R * 64));
+#pragma unroll
+            for (int r = 0; r < BK_ITEMS; ++r) {
+                k[r] = v[r] = 0u;
+                if ((uint32_t)r < R && (int)lane < lim - r * 64) {
+                    const uint32_t e = c0 + (wave * R + r) * 64 + lane;
+                    if (from_pairs) {
+                        const uint2 p = ld_pair(&src[e]);
+                        k[r] = p.x;
+                        v[r] = p.y;
+                    } else {
+                        k[r] = ld_state(&akeys[e]);
+                        v[r] = ld_state(&avals[e]);
+                    }
+                }
+            }
+            bucket_rank<B>(k, ccnt, R, shift, pos, lds);
+#pragma unroll
+            for (int r = 0; r < BK_ITEMS; ++r) {
+                if ((uint32_t)r < R && (int)lane < lim - r * 64) {
+                    const uint32_t d = digit_at(k[r], shift);
+                    const uint32_t dst = lds.base[d] + pos[r] - lds.bs[d];
+                    if (dst < cnt) {      // always true for consistent counts
+                        if (from_pairs) {
+                            akeys[dst] = k[r];
+                            avals[dst] = v[r];
+                        } else {
+                            src[dst] = make_uint2(k[r], v[r]);
+                        }
+                    }
+                }
+            }
+            // the stores reach the L2 before any thread of the workgroup reads
+            // them back (the next pass, the ranges)
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            if (tid < RADIX) lds.base[tid] += lds.tot[tid];
+            __syncthreads();
+        }
+    }
+    // the arrays hold the bucket sorted
+    for (uint32_t e = tid; e < cnt; e += THREADS) {
+        const uint32_t key = ld_state(&akeys[e]);
+        if (e == 0) out.start(b0, key);
+        else out.boundary(b0 + e, ld_state(&akeys[e - 1]), key);
+        if (e + 1 == cnt) out.end(b0 + cnt, key);
+    }
+    if (!out.want_keys()) return;
+    __syncthreads();             // 32-bit keys take the place of the local ones
+    for (uint32_t e = tid; e < cnt; e += THREADS) out.put_key(b0 + e, ld_state(&akeys[e]));
 }
 
 // Block-wide exclusive scan of one value a thread, and the total.  Every thread calls
@@ -1377,11 +1484,54 @@ __device__ void sort_part(const uint2* __restrict__ src, uint32_t size, uint32_t
     write_sorted<B>(lds, b0 + K0, K1 - K0, K0 == 0, K1 == size, before[0], out);
 }
 
-// pairs: the split pass's output; plan.limit is 2 CAP and plan.alone CAP, or both 0 to divide
-// every bucket (for tests).  counts: the split pass's tiles' digit counts.
+// This workgroup's share of a crowded frame's parts.  A function of its own, its arguments in
+// LDS: with its registers in the kernel, which then spills, frames without parts take 10 to
+// 30 us more (1M / 1080p, 3M / 4K).  The call makes the parts 10 to 40 us slower.
+struct PartsArgs {
+    uint2* pairs;
+    const uint32_t* counts;
+    SplitPlan plan;
+    BucketOut out;
+};
 template <typename B>
-__global__ __launch_bounds__(B::THREADS, B::WAVES_SIMD) void k_bucket_sort(uint2* pairs, SplitPlan plan, const uint32_t* counts,
-                                                         BucketOut out) {
+__device__ __attribute__((noinline)) void bucket_parts(Lds<BucketLds<B>>* lds_) {
+    BucketLds<B>& lds = *(BucketLds<B>*)lds_;
+    union Words {
+        PartsArgs args;
+        int word[sizeof(PartsArgs) / 4];
+        __device__ Words() {}
+    } a;
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(a.word) / 4; ++i)
+        a.word[i] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(lds.pair)[i]);
+    __syncthreads();
+    const SplitPlan& plan = a.args.plan;
+    BucketOut out = a.args.out;
+    const uint32_t* __restrict__ bases = plan.bases;
+    const uint32_t n_parts = *plan.n_parts, buckets = gridDim.x;
+    const uint32_t n_runs = (bases[buckets] + SPLIT_SIZE - 1) / SPLIT_SIZE;
+    for (uint32_t p = blockIdx.x; p < n_parts; p += buckets) {
+        uint32_t lo = 0, hi = buckets - 1;           // the bucket: the first that parts up to it exceed p
+        while (lo < hi) {
+            const uint32_t m = (lo + hi) / 2;
+            if (plan.parts[m] > p) hi = m;
+            else lo = m + 1;
+        }
+        const uint32_t first = bases[lo], before = lo ? plan.parts[lo - 1] : 0u;
+        out.bucket = lo;
+        __syncthreads();             // the LDS of what this workgroup did before
+        sort_part<B>(a.args.pairs + first, bases[lo + 1] - first, p - before, plan.parts[lo] - before,
+                     a.args.counts + lo, buckets, n_runs, first, out, lds);
+    }
+}
+
+// pairs: the split pass's output; tmp_keys: a second buffer for streamed buckets (with the
+// values' place).  plan.limit is LIMIT and plan.alone CAP, or both 0 to divide every bucket
+// (for tests).  counts: the split pass's tiles' digit counts.
+template <typename B>
+__global__ __launch_bounds__(B::THREADS, B::WAVES_SIMD) void k_bucket_sort(uint2* pairs, uint32_t* tmp_keys,
+                                                                        SplitPlan plan, const uint32_t* counts,
+                                                                        BucketOut out) {
     constexpr int THREADS = B::THREADS;
     constexpr uint32_t CAP = B::CAP;
     __shared__ __align__(16) BucketLds<B> lds;
@@ -1394,7 +1544,7 @@ __global__ __launch_bounds__(B::THREADS, B::WAVES_SIMD) void k_bucket_sort(uint2
     const uint32_t cnt = b1 > b0 ? b1 - b0 : 0u, bits = out.lk.bits;
     uint2* src = pairs + b0;
     out.bucket = blockIdx.x;
-    if (cnt > 0 && cnt <= (n_parts ? plan.alone : plan.limit)) {
+    if (cnt > 0 && cnt <= (n_parts ? plan.alone : 2 * CAP)) {
         // ---- the bucket in LDS, or in two runs: each half sorted in LDS and
         // written back in place, then the two merged ----
         const uint32_t runs = cnt <= CAP ? 1u : 2u;
@@ -1411,23 +1561,36 @@ __global__ __launch_bounds__(B::THREADS, B::WAVES_SIMD) void k_bucket_sort(uint2
             }
         }
         if (__builtin_expect(runs == 2, false)) merge_runs<B>(src, cA, cB, b0, out, lds);
+    } else if (__builtin_expect(cnt > 0 && n_parts == 0, false)) {
+        stream_bucket<B>(src, tmp_keys + b0, cnt, b0, out, lds);
     }
     if (__builtin_expect(n_parts == 0, true)) return;
-    // ---- parts of larger buckets, a workgroup's share of them ----
-    const uint32_t n_runs = (bases[gridDim.x] + SPLIT_SIZE - 1) / SPLIT_SIZE;
-    for (uint32_t p = blockIdx.x; p < n_parts; p += gridDim.x) {
-        uint32_t lo = 0, hi = gridDim.x - 1;         // the bucket: the first that parts up to it exceed p
-        while (lo < hi) {
-            const uint32_t m = (lo + hi) / 2;
-            if (plan.parts[m] > p) hi = m;
-            else lo = m + 1;
-        }
-        const uint32_t first = bases[lo], before = lo ? plan.parts[lo - 1] : 0u;
-        out.bucket = lo;
-        __syncthreads();             // the LDS of what this workgroup did before
-        sort_part<B>(pairs + first, bases[lo + 1] - first, p - before, plan.parts[lo] - before, counts + lo, gridDim.x,
-                     n_runs, first, out, lds);
+    static_assert(sizeof(PartsArgs) <= sizeof(lds.pair), "the arguments fit");
+    __syncthreads();                 // the LDS of the bucket before the arguments
+    if (tid == 0) {                  // (field by field: a temporary would live in LDS, a copy per thread)
+        PartsArgs* a = reinterpret_cast<PartsArgs*>(lds.pair);
+        a->pairs = pairs;
+        a->counts = counts;
+        a->plan.bases = plan.bases;
+        a->plan.n_parts = plan.n_parts;
+        a->plan.parts = plan.parts;
+        a->plan.limit = plan.limit;
+        a->plan.alone = plan.alone;
+        a->plan.part = plan.part;
+        a->out.vals = out.vals;
+        a->out.ranges = out.ranges;
+        a->out.keys32 = out.keys32;
+        a->out.keys64 = out.keys64;
+        a->out.order = out.order;
+        a->out.error = out.error;
+        a->out.prm = out.prm;
+        a->out.lk.bits = out.lk.bits;
+        a->out.lk.tile_bits = out.lk.tile_bits;
+        a->out.n_tiles = out.n_tiles;
+        a->out.bucket = out.bucket;
     }
+    __syncthreads();
+    bucket_parts<B>((Lds<BucketLds<B>>*)&lds);
 }
 
 template <typename KeyT, int BITS>
@@ -1455,9 +1618,9 @@ static void launch_split(hipStream_t s, const FrameDev& f, const WsDev& ws, uint
     // the unused half of the first
     static_assert(2 * SPLIT_DIGITS_MAX <= MAX_PASSES * RADIX, "the parts table fits");
     // the frame's radix tiles, the runs of a divided bucket, fit the entries' LDS
-    static_assert(((uint64_t)(ROOM + 1) << SPLIT_WIDE_BT) / SPLIT_SIZE * sizeof(PartRun) < B::CAP * sizeof(uint2) / 2,
+    static_assert(((uint64_t)(ROOM + 1) << SPLIT_WIDE_BT) / SPLIT_SIZE * sizeof(PartRun) < B::CAP * sizeof(uint2),
                   "the runs, and samples of them, fit");
-    const SplitPlan plan{ws.bases, ws.bases + SPLIT_DIGITS_MAX + 1, ws.hist + SPLIT_DIGITS_MAX, force ? 0u : 2 * B::CAP,
+    const SplitPlan plan{ws.bases, ws.bases + SPLIT_DIGITS_MAX + 1, ws.hist + SPLIT_DIGITS_MAX, force ? 0u : B::LIMIT,
                          force ? 0u : B::CAP, B::PART};
     if (key_bytes == 8) {
         if (f.split_bits == 10) launch_split_pass<uint64_t, 10>(s, f, ws, pairs, plan, force);
@@ -1466,8 +1629,8 @@ static void launch_split(hipStream_t s, const FrameDev& f, const WsDev& ws, uint
         if (f.split_bits == 10) launch_split_pass<uint32_t, 10>(s, f, ws, pairs, plan, force);
         else launch_split_pass<uint32_t, 8>(s, f, ws, pairs, plan, force);
     }
-    hipLaunchKernelGGL(k_bucket_sort<B>, dim3(1u << f.split_bits), dim3(B::THREADS), 0, s, pairs, plan, ws.sort_state,
-                       out);
+    hipLaunchKernelGGL(k_bucket_sort<B>, dim3(1u << f.split_bits), dim3(B::THREADS), 0, s, pairs,
+                       key_bytes == 8 ? ws.vals_b : reinterpret_cast<uint32_t*>(ws.keys_a), plan, ws.sort_state, out);
 }
 
 void launch_sort_split(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32_t key_bytes, bool force,
@@ -1492,10 +1655,11 @@ void launch_sort_split(hipStream_t s, const FrameDev& f, const WsDev& ws, uint32
     // while smaller workgroups start together and share a CU better.  Kernel
     // times in us with 512 x 9, 512 x 16 and 1024 x 16 entries:
     // 1280x720 28, 35, 56; 1080p (1M) 33, 42, 68 (plain 65, 63, 94); 4K (3M) 94, 73, 104.
+    // Sort with 512 x 16 and 1024 x 16: plain 4K (4M), room 14000, 299, 285 (LSD passes 569).
     const uint32_t room = f.capacity >> f.split_bits;
-    if (room <= 4608) launch_split<BucketShape<512, 9, 6>, 4608>(s, f, ws, key_bytes, pairs, out, force);
-    else if (room <= 12288) launch_split<BucketShape<512, 16, 4>, 12288>(s, f, ws, key_bytes, pairs, out, force);
-    else launch_split<BucketShape<1024, 16, 4>, SPLIT_MAX_ROOM>(s, f, ws, key_bytes, pairs, out, force);
+    if (room <= 4608) launch_split<BucketShape<512, 9, 6, 3>, 4608>(s, f, ws, key_bytes, pairs, out, force);
+    else if (room <= 12288) launch_split<BucketShape<512, 16, 4, 4>, 12288>(s, f, ws, key_bytes, pairs, out, force);
+    else launch_split<BucketShape<1024, 16, 4, 4>, SPLIT_MAX_ROOM>(s, f, ws, key_bytes, pairs, out, force);
 }
 
 // ---------------------------------------------------------------------------

@@ -60,7 +60,7 @@ struct FrameHooks {
 };
 
 // How a frame of fl seen by cam is sorted, set in fl.f and fl.w: by the split sort
-// (at least 2^SPLIT_MIN_BT tiles, and what its buckets sort fits 32 bits; for
+// (SPLIT_MIN_BT tile bits or more, and what its buckets sort fits 32 bits; for
 // 64-bit keys that depends on the camera's depth interval) or by the LSD
 // passes; and where its tile schedule comes from (debug: a debug render).
 // Returns whether the split sort applies.

@@ -78,7 +78,7 @@ struct SortTile {
 inline uint32_t sort_tile_size(uint32_t key_bytes) {
     return key_bytes == 8 ? (uint32_t)SortTile<uint64_t>::SIZE : (uint32_t)SortTile<uint32_t>::SIZE;
 }
-// The split pass (frames of at least 2^SPLIT_MIN_BT tiles): radix tiles of 9216
+// The split pass (frames of SPLIT_MIN_BT tile bits, 129 tiles, or more): radix tiles of 9216
 // keys, ranked by the tile index's top 10 bits where it has them, else 8.  1024
 // buckets spread the 2.2M entries of a 1M / 1080p frame over four times the
 // workgroups that 256 do, and its busiest bucket (about twice the average) is one
@@ -93,7 +93,10 @@ constexpr uint32_t SPLIT_SIZE = SPLIT_THREADS * SPLIT_ITEMS;
 constexpr int32_t SPLIT_MIN_BT = 8, SPLIT_WIDE_BT = 10;
 constexpr uint32_t SPLIT_DIGITS_MAX = 1024;
 constexpr uint32_t SPLIT_WIDE_CAPACITY = 1u << 18;
-constexpr uint32_t SPLIT_MAX_ROOM = 24576;       // capacity per bucket
+// What a workspace may hold per bucket: a frame has a run of a divided bucket for each
+// radix tile, and their table is to fit the largest workgroup's LDS (the LSD passes
+// are slower where it does: sort at room 39000, plain 10M Gaussians / 4K, 1267 us against 1004).
+constexpr uint32_t SPLIT_MAX_ROOM = 57344;
 // Radix tiles per look-back group: the last tile of each group publishes the
 // group's digit counts, so a tile reads at most SORT_GROUP - 1 tile states plus
 // one state per earlier group.  32 balances the two (1M / 1080p fast sort:

@@ -64,7 +64,7 @@ def far(distance, W, H, half=1.0):
 @pytest.mark.parametrize("runs", [2, 3, 9])
 def test_every_workgroup(R, path, cap, runs):
     """Buckets of just over one and two of what a workgroup holds, and of many, with long runs of equal
-    keys: merged as two runs in LDS, or divided."""
+    keys: merged as two runs in LDS, streamed, or divided."""
     cam = wl.config_camera("small", width=256, height=256)
     times = int({2: 1.5, 3: 2.6, 9: 9.0}[runs] * cap / 5)          # the busiest tile has about 5 entries a copy
     sc = copies_of(40, times)
@@ -109,7 +109,7 @@ def test_two_depths_far_apart(R, path):
 @pytest.mark.parametrize("path", ["fast", "plain"])
 def test_workspace_beyond_the_bucket_sort(R, path):
     """More entries a bucket than the split sort takes: the frame takes the LSD passes."""
-    check(R, copies_of(40, 500), wl.config_camera("small", width=256, height=256), path, (24577 << 8) + 4096)
+    check(R, copies_of(40, 500), wl.config_camera("small", width=256, height=256), path, (57345 << 8) + 4096)
 
 
 @pytest.mark.parametrize("path", ["fast", "plain"])
