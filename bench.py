@@ -219,7 +219,7 @@ def frame_counts(R, ds, cam, path):
 def bucket_sorted(n_tiles):
     """Whether the library sorts this frame's keys with the split sort (one radix pass on the
     tile index's top bits, then the rest of the key per bucket in LDS, which also writes the tile
-    ranges): frames of at least 2^8 tiles whose depth interval fits the local key, which those
+    ranges): frames of more than 2^7 tiles whose depth interval fits the local key, which those
     of every workload here do."""
     return max(1, int(np.ceil(np.log2(n_tiles)))) >= 8
 
@@ -228,8 +228,7 @@ def rooflines(path, counts, stage_ms, n, n_tiles):
     by = stage_bytes(path, n, counts["n_visible"], counts["n_entries"], n_tiles, counts["passes"])
     bucket = bucket_sorted(n_tiles)
     if bucket:
-        # the ranges stage holds only the rasterizers' schedule (read 8 B, write 4 B per tile)
-        by["ranges"] = 12 * n_tiles
+        del by["ranges"]           # the sort stage's second kernel writes them, and the rasterizers' schedule
     out = {}
     for s, b in by.items():
         ms = stage_ms.get(s, 0.0)

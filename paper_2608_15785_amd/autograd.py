@@ -13,6 +13,12 @@ device scene has been rewritten since (a forward at another size, or with
 other parameters), it renders its own frame again first.  The library checks
 the same thing on its side (the workspace records which scene state, camera
 and size its last frame came from) and refuses a mismatch.
+
+Streams: called on the context's own stream, a forward returns once the frame's
+outcome is known, before its image is finished, like any torch operation; work
+that reads the image on another stream has to wait for this one.  Called on another
+stream, forward and backward first wait for that stream (the parameters, or dL/dimg, are its
+work) and return with the image, or the gradients, finished.
 """
 from __future__ import annotations
 

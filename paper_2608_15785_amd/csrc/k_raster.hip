@@ -37,10 +37,10 @@
 // backward pass recomputes every alpha from them bit for bit.
 //
 // The lists.  A lane costs the same whether its pair passes the skip test or
-// not, so what bounds the kernel (VALU issue: 0.36 wave instructions per SIMD
-// and cycle while its CUs are busy, where eight independent FMA chains reach
-// 0.39) is how many pairs it evaluates for each one it blends: at 1M / 1080p
-// 5.1 with one list per 16x8 half-tile, 3.4 with one per 8x8, 2.4 with one per
+// not, so what bounds the kernel (VALU issue: 0.29 wave instructions per SIMD
+// and cycle over the launch at 1M / 1080p, of the 0.40 that eight waves of
+// independent FMA chains reach) is how many pairs it evaluates for each one it blends: at 1M /
+// 1080p 5.1 with one list per 16x8 half-tile, 3.4 with one per 8x8, 2.64 with one per
 // 4x4 (eight lists walked side by side, to the length of the longest of each
 // batch), 2.1 with one per 4x2, whose lists would cost twice the staging.
 // While a batch is staged, one entry per lane, each entry finds the columns
@@ -87,23 +87,23 @@ enum ExpMode : int {
     EXP_PLAIN = 3,  // min(0.99, o expf(p)), p by Eq. power from (x - u, y - v)
 };
 
-// Alpha of a pair from its folded exponent P, 0 when P is below the threshold
-// thr (the skip threshold, or NaN for a pixel that has stopped or lies outside
-// the image: no P passes).
+// Alpha of a pair that passes the skip test, from its folded exponent P.
+template <int EXPM>
+__device__ inline float kept_alpha(float P) {
+    if (EXPM == EXP_LIBM) return fminf(ALPHA_MAX, expf(P));      // the exponential's ablation
+    if (EXPM == EXP_HW2) return fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(P));
+    // min(0.99, exp_hat(P)) without the minimum, which cannot bind here: P = ln o - q/2 with
+    // ln o <= 0 and q >= 0, and for a kept pair every term of its float32 evaluation is below
+    // ~1600 in magnitude (conic entries <= 1/0.3, coordinates within a tile), so P < 1e-3 and
+    // exp_hat(P) < 0.978
+    return __int_as_float((int)fmaf(P, FEXP_A, FEXP_B));
+}
+
+// Alpha of a pair, 0 when P is below the threshold thr (the skip threshold, or NaN
+// for a pixel that has stopped or lies outside the image: no P passes).
 template <int EXPM>
 __device__ inline float alpha_of(float P, float thr) {
-    float al;
-    if (EXPM == EXP_LIBM) {             // the exponential's ablation: alpha = min(0.99, exp(P))
-        al = fminf(ALPHA_MAX, expf(P));
-    } else if (EXPM == EXP_HW2) {
-        al = fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(P));
-    } else {
-        // alpha = min(0.99, exp_hat(P)) without the minimum, which cannot bind here:
-        // P = ln o - q/2 with ln o <= 0 and q >= 0, and for a kept pair every term of
-        // its float32 evaluation is below ~1600 in magnitude (conic entries <= 1/0.3,
-        // coordinates within a tile), so P < 1e-3 and exp_hat(P) < 0.978
-        al = __int_as_float((int)fmaf(P, FEXP_A, FEXP_B));
-    }
+    const float al = kept_alpha<EXPM>(P);
     return P >= thr ? al : 0.0f;
 }
 
@@ -177,8 +177,9 @@ __device__ void export_stamp(const WsDev& ws) {
     __hip_atomic_store(&dst->seq, prm->stamp_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// The workgroup that exports the stamp: among the first that the grid starts (256
-// CUs hold 8192), but not one of the longest tiles'.
+// The workgroup that exports the stamp: among the first that the grid starts (the
+// kernels that export it run 6 to 8 waves a SIMD, so 256 CUs hold 6144 or more), but not
+// one of the longest tiles'.
 constexpr uint32_t STAMP_BLOCK = 4096;
 
 // TRAIN: a path with a backward pass (EXP_PLAIN, and its training variant:
@@ -428,8 +429,9 @@ __global__ __launch_bounds__(64) void k_raster(FrameDev f, WsDev ws, const uint3
 // pixels per lane, Eq. dual_pixel applied three times, one wave per tile).  A
 // tile's workgroup has one wave per band of 4 PIX rows: the 64 lanes of a wave
 // form four row groups of 16 columns, group j owning PIX consecutive rows and
-// each lane PIX pixels of one column.  Staging, culling and the per-pair
-// decisions are those of the dual-pixel kernel above, written for any PIX.
+// each lane PIX pixels of one column.  The per-pair decisions are those of the
+// dual-pixel kernel above, written for any PIX; a wave has one list, of the entries
+// that reach its band of rows, so against the dual pixel's eight lists it evaluates more pairs.
 template <int PIX>
 struct FastShape {
     static constexpr int ROWS = 4 * PIX;            // rows of a wave's band
@@ -438,17 +440,6 @@ struct FastShape {
     static constexpr int BATCH = THREADS;           // entries staged at once, one per thread
     static constexpr int CAP = BATCH + LIST_UNROLL;
 };
-
-template <int EXPM>
-__device__ inline float fast_alpha(float P) {
-    if (EXPM == EXP_LIBM) return fminf(ALPHA_MAX, expf(P));
-    if (EXPM == EXP_HW2) return fminf(ALPHA_MAX, __builtin_amdgcn_exp2f(P));
-    // min(0.99, exp_hat(P)) without the minimum, which cannot bind here: P = ln o - q/2 with
-    // ln o <= 0 and q >= 0, and for a kept pair every term of its float32 evaluation is below
-    // ~1600 in magnitude (conic entries <= 1/0.3, coordinates within a tile), so P < 1e-3 and
-    // exp_hat(P) < 0.978
-    return __int_as_float((int)fmaf(P, FEXP_A, FEXP_B));
-}
 
 template <bool COUNT, int EXPM, int PIX>
 __global__ __launch_bounds__(FastShape<PIX>::THREADS) void k_raster_fast_px(FrameDev f, WsDev ws,
@@ -605,7 +596,7 @@ __global__ __launch_bounds__(FastShape<PIX>::THREADS) void k_raster_fast_px(Fram
 #pragma unroll
                     for (int i = 0; i < PIX; ++i) {
                         // a skipped or finished pixel takes alpha = 0
-                        const float al = (live(i) && P[i] >= SKIP) ? fast_alpha<EXPM>(P[i]) : 0.0f;
+                        const float al = (live(i) && P[i] >= SKIP) ? kept_alpha<EXPM>(P[i]) : 0.0f;
                         const float w = al * T[i];
                         Tn[i] = T[i] - w;
                         nr[i] = fmaf(w, m.z, cr[i]);
