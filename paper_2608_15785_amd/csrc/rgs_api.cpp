@@ -601,7 +601,7 @@ static void make_layout(int64_t n, const rgs_plan& p, int32_t path, uint64_t cap
         off = align256(off + (in_vals ? lsd : std::max(lsd, split)) * 4);
     }
     L.bases = off;
-    off = align256(off + (uint64_t)(SPLIT_DIGITS_MAX + 1) * 4);
+    off = align256(off + (uint64_t)(SPLIT_DIGITS_MAX + 2) * 4);      // and the count of parts
     L.t_final = off;
     off = align256(off + (uint64_t)p.width * p.height * 4);
     L.n_proc = off;

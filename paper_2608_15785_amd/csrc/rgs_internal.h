@@ -269,7 +269,7 @@ struct WsDev {
     uint32_t* sort_state;     // look-back words: ready flag (bit 31) | digit count.  LSD passes: 2 x
                               // [sort_rows + sort_groups][RADIX], one set per pass parity; split pass:
                               // one set of rows of its digits
-    uint32_t* bases;          // split pass: first entry of each bucket, and the entry count
+    uint32_t* bases;          // split pass: first entry of each bucket, the entry count, the count of parts
     uint32_t sort_rows;       // radix tiles at capacity
     uint32_t sort_groups;     // ceil(sort_rows / SORT_GROUP)
     float* t_final;           // [H][W]
